@@ -249,6 +249,7 @@ __global__ __launch_bounds__(SPMM_PLAN_NT) void spmm_plan_kernel(uint32_t rows, 
     if (row == 0) {
         n_chunks[1] = (uint32_t)long_len;
         n_chunks[2] = (uint32_t)spmm_rows_per_wave(rows, entries);
+        n_chunks[3] = (uint32_t)min(entries / rows, (uint64_t)0xffffffffu);
     }
     int64_t len = 0;
     if (row < rows) len = min(rp_load(rowptr, rp64, (uint64_t)row + 1), (int64_t)capacity) - min(rp_load(rowptr, rp64, row), (int64_t)capacity);
@@ -263,8 +264,10 @@ __global__ __launch_bounds__(SPMM_PLAN_NT) void spmm_plan_kernel(uint32_t rows, 
     if (nch == 0) return;
     const uint32_t base = wg_base + excl;
     part_base[row] = base;
-    if (base < max_chunks) ticket[base] = 0;
-    for (uint32_t c = 0; c < nch && base + c < max_chunks; ++c) desc[base + c] = make_uint2(row, c);
+    for (uint32_t c = 0; c < nch && base + c < max_chunks; ++c) {
+        desc[base + c] = make_uint2(row, c);
+        ticket[base + c] = 0;      // the first one of a row is its ticket, the panel kernel has one per panel
+    }
 }
 
 // What happens to a finished output row: out = act(acc + bias), then (optionally) zero where the
@@ -599,8 +602,9 @@ __global__ __launch_bounds__(SPMM_NT) void spmm_main_kernel(uint32_t rows, const
                                                             unsigned n_piece_waves, const uint32_t *__restrict__ n_chunks,
                                                             uint32_t max_chunks, const uint2 *__restrict__ desc,
                                                             uint32_t *__restrict__ ticket, float *part, float *__restrict__ out,
-                                                            int64_t ldo, spmm_epi ep, int rows_per_wave)
+                                                            int64_t ldo, spmm_epi ep, int rows_per_wave, uint32_t mean_limit)
 {
+    if (mean_limit && n_chunks[3] >= mean_limit) return;        // the panel kernel's matrix
     constexpr int U = spmm_unroll<VEC, CH>::U;
     const int lane = threadIdx.x & 63;
     const uint32_t wave = blockIdx.x * (uint32_t)(SPMM_NT / 64) + (threadIdx.x >> 6);
@@ -815,10 +819,13 @@ int build_plan(sgnn_ctx *ctx, const sgnn_csr *A, void *plan, hipStream_t st)
     return SGNN_OK;
 }
 
+#include "spmm_panel.h"
+
 // XENT: the cross-entropy epilogue; loss_out / colsum_out receive the mean loss and the column sums of the gradient
 template <int VEC, int CH, typename XT, bool XENT = false>
 int launch_vc(sgnn_ctx *ctx, const sgnn_csr *A, const XT *X, int64_t ldx, const int32_t *row_index, int d, float *out,
-              int64_t ldo, const spmm_epi &ep_in, ws_alloc *ws, hipStream_t st, float *loss_out = nullptr, float *colsum_out = nullptr)
+              int64_t ldo, const spmm_epi &ep_in, ws_alloc *ws, hipStream_t st, float *loss_out = nullptr, float *colsum_out = nullptr,
+              uint32_t mean_limit = 0)
 {
     spmm_epi ep = ep_in;
     const int rows_per_wave = spmm_rows_per_wave(A->rows, A->capacity);   // lower bound of the plan's figure
@@ -853,15 +860,16 @@ int launch_vc(sgnn_ctx *ctx, const sgnn_csr *A, const XT *X, int64_t ldx, const 
                              ws->off);
         // wavefronts that take pieces: 2048, more for matrices with many entries (about 32 pieces of 64 entries
         // each if every entry sat in a long row); those that find no piece leave at once
-        const uint64_t want = std::min<uint64_t>(std::max<uint64_t>(A->capacity / 2048, SPMM_PIECE_WAVES), 65536);
+        const uint64_t want = mean_limit ? SPMM_PIECE_WAVES : std::min<uint64_t>(std::max<uint64_t>(A->capacity / 2048, SPMM_PIECE_WAVES), 65536);
         n_piece_waves = cdiv(std::min<uint64_t>(max_chunks, want), SPMM_NT / 64) * (SPMM_NT / 64);
     }
     // The host sizes the grid from the capacity (the entry count is on the device), which for a sparse mini-batch is many
     // times the true count: most of the workgroups of such a launch would find no block of rows and leave at once, and
     // dispatching a quarter of a million of them cost a third of the kernel's time.  16384 workgroups fill the machine
     // several times over; the wavefronts stride over whatever is left.
-    // (with the cross-entropy epilogue every workgroup leaves a row of partial sums for the final kernel: a quarter of that)
-    const unsigned row_blocks = std::min<unsigned>(cdiv(A->rows, rows_per_block), XENT ? 4096u : 16384u);
+    // (a quarter of that with the cross-entropy epilogue, where every workgroup leaves a row of partial sums for the final kernel,
+    // and of a launch that will most likely leave at once because the panel kernel takes the matrix)
+    const unsigned row_blocks = std::min<unsigned>(cdiv(A->rows, rows_per_block), XENT || mean_limit ? 4096u : 16384u);
     const unsigned grid = n_piece_waves / (SPMM_NT / 64) + row_blocks;
     if (XENT) {
         ep.loss_partial = ws->get<float>(grid);
@@ -874,7 +882,7 @@ int launch_vc(sgnn_ctx *ctx, const sgnn_csr *A, const XT *X, int64_t ldx, const 
     }
     SGNN_LAUNCH(ctx, st, "spmm_main_kernel", tag, (spmm_main_kernel<VEC, CH, XT, XENT>), dim3(grid),
                 dim3(SPMM_NT), 0, st, A->rows, A->rowptr, A->rowptr_is_i64, A->colidx, A->val, A->capacity, X, ldx, row_index, d,
-                n_piece_waves, pv.n_chunks, max_chunks, pv.desc, pv.ticket, part, out, ldo, ep, rows_per_wave);
+                n_piece_waves, pv.n_chunks, max_chunks, pv.desc, pv.ticket, part, out, ldo, ep, rows_per_wave, mean_limit);
     if (XENT && (loss_out || colsum_out))
         return sgnn_launch_xent_final(ctx, ep.loss_partial, (int)grid, ep.inv_rows, loss_out, ep.cs_partial, d, colsum_out, ep.fix, XENT_SLOTS,
                                       1.0 / XENT_FIX_CS, 1.0 / XENT_FIX_LOSS, st);
@@ -883,22 +891,20 @@ int launch_vc(sgnn_ctx *ctx, const sgnn_csr *A, const XT *X, int64_t ldx, const 
 
 template <int VEC, typename XT>
 int launch_v(sgnn_ctx *ctx, const sgnn_csr *A, const XT *X, int64_t ldx, const int32_t *row_index, int d, float *out,
-             int64_t ldo, const spmm_epi &ep, ws_alloc *ws, hipStream_t st)
+             int64_t ldo, const spmm_epi &ep, ws_alloc *ws, hipStream_t st, uint32_t mean_limit)
 {
     const int per = (d + VEC - 1) / VEC;   // lanes needed for one pass over the row
     const int ch = (per + 63) / 64;
     switch (ch) {
-    case 1: return launch_vc<VEC, 1, XT>(ctx, A, X, ldx, row_index, d, out, ldo, ep, ws, st);
-    case 2: return launch_vc<VEC, 2, XT>(ctx, A, X, ldx, row_index, d, out, ldo, ep, ws, st);
-    case 3: return launch_vc<VEC, 3, XT>(ctx, A, X, ldx, row_index, d, out, ldo, ep, ws, st);
-    case 4: return launch_vc<VEC, 4, XT>(ctx, A, X, ldx, row_index, d, out, ldo, ep, ws, st);
-    case 5: return launch_vc<VEC, 5, XT>(ctx, A, X, ldx, row_index, d, out, ldo, ep, ws, st);
-    case 6: return launch_vc<VEC, 6, XT>(ctx, A, X, ldx, row_index, d, out, ldo, ep, ws, st);
-    case 7: return launch_vc<VEC, 7, XT>(ctx, A, X, ldx, row_index, d, out, ldo, ep, ws, st);
-    case 8: return launch_vc<VEC, 8, XT>(ctx, A, X, ldx, row_index, d, out, ldo, ep, ws, st);
-    default: break;
+    case 1: return launch_vc<VEC, 1, XT>(ctx, A, X, ldx, row_index, d, out, ldo, ep, ws, st, nullptr, nullptr, mean_limit);
+    case 2: return launch_vc<VEC, 2, XT>(ctx, A, X, ldx, row_index, d, out, ldo, ep, ws, st, nullptr, nullptr, mean_limit);
+    case 3: return launch_vc<VEC, 3, XT>(ctx, A, X, ldx, row_index, d, out, ldo, ep, ws, st, nullptr, nullptr, mean_limit);
+    case 4: return launch_vc<VEC, 4, XT>(ctx, A, X, ldx, row_index, d, out, ldo, ep, ws, st, nullptr, nullptr, mean_limit);
+    case 5: return launch_vc<VEC, 5, XT>(ctx, A, X, ldx, row_index, d, out, ldo, ep, ws, st, nullptr, nullptr, mean_limit);
+    case 6: return launch_vc<VEC, 6, XT>(ctx, A, X, ldx, row_index, d, out, ldo, ep, ws, st, nullptr, nullptr, mean_limit);
+    case 7: return launch_vc<VEC, 7, XT>(ctx, A, X, ldx, row_index, d, out, ldo, ep, ws, st, nullptr, nullptr, mean_limit);
+    default: return launch_vc<VEC, 8, XT>(ctx, A, X, ldx, row_index, d, out, ldo, ep, ws, st, nullptr, nullptr, mean_limit);    // the caller has checked the width
     }
-    return sgnn_fail(ctx, SGNN_ERR_UNSUPPORTED, "sgnn_spmm: feature width %d is beyond %d columns", d, 64 * 8 * VEC);
 }
 
 } // namespace
@@ -931,11 +937,29 @@ static int launch_x(sgnn_ctx *ctx, const sgnn_csr *A, const XT *X, int64_t ldx, 
     const int64_t lds_ = ldx | ldo | (ep.mask ? ep.ldm : 0) | (ep.add ? ep.ldadd : 0);
     const bool ok4 = d % 4 == 0 && lds_ % 4 == 0 && (bits & 15) == 0;
     const bool ok2 = d % 2 == 0 && lds_ % 2 == 0 && (bits & 7) == 0;
-    if (d <= 64) return launch_v<1, XT>(ctx, A, X, ldx, row_index, (int)d, out, ldo, ep, ws, st);
-    if (d <= 128 && ok2) return launch_v<2, XT>(ctx, A, X, ldx, row_index, (int)d, out, ldo, ep, ws, st);
-    if (ok4) return launch_v<4, XT>(ctx, A, X, ldx, row_index, (int)d, out, ldo, ep, ws, st);
-    if (ok2) return launch_v<2, XT>(ctx, A, X, ldx, row_index, (int)d, out, ldo, ep, ws, st);
-    return launch_v<1, XT>(ctx, A, X, ldx, row_index, (int)d, out, ldo, ep, ws, st);
+    const int vec = d <= 64 ? 1 : ((d <= 128 && ok2) ? 2 : (ok4 ? 4 : (ok2 ? 2 : 1)));
+    if (d > 64 * 8 * vec) return sgnn_fail(ctx, SGNN_ERR_UNSUPPORTED, "sgnn_spmm: feature width %d is beyond %d columns", (int)d, 64 * 8 * vec);
+    // A matrix with room for many entries a row: whether it has them is known on the device only, so both kernels are
+    // launched and the one whose matrix it is not leaves at once (about 3 us of the 100 or more that such a product takes).
+    sgnn_csr planned = *A;
+    uint32_t mean_limit = 0;
+    if (spmm_panel_wanted<XT>(A, d)) {
+        if (!A->plan) {     // no plan attached to the matrix: one for this call
+            planned.plan = ws->get<uint8_t>(sgnn_csr_plan_bytes(A->rows, A->capacity));
+            if (!ws->ok)
+                return sgnn_fail(ctx, SGNN_ERR_CAPACITY, "sgnn_spmm: scratch too small (%zu bytes needed): call sgnn_ctx_reserve", ws->off);
+            const int rc = build_plan(ctx, A, planned.plan, st);
+            if (rc) return rc;
+        }
+        A = &planned;
+        ws_alloc w2 = *ws;      // the two kernels share the scratch of the partial rows
+        const int rc = launch_panel<XT>(ctx, A, X, ldx, row_index, (int)d, out, ldo, ep, &w2, st);
+        if (rc) return rc;
+        mean_limit = SPMM_PANEL_MEAN;
+    }
+    if (vec == 4) return launch_v<4, XT>(ctx, A, X, ldx, row_index, (int)d, out, ldo, ep, ws, st, mean_limit);
+    if (vec == 2) return launch_v<2, XT>(ctx, A, X, ldx, row_index, (int)d, out, ldo, ep, ws, st, mean_limit);
+    return launch_v<1, XT>(ctx, A, X, ldx, row_index, (int)d, out, ldo, ep, ws, st, mean_limit);
 }
 
 // O = A X + bias with the softmax cross-entropy of O's rows in the epilogue (see spmm_row_xent).  Returns

@@ -1,0 +1,364 @@
+// The sparse product for matrices with many entries a row: several entries per gather instruction, columns in panels.
+// Included by spmm.hip, inside its anonymous namespace.
+//
+// What bounds the product there is the gathers: every entry reads a row of X, nnz * d elements in all, many times the
+// size of X itself, out of L2 and the Infinity Cache.  Two things make them cheaper than one row per wavefront-wide
+// instruction:
+//  - G lanes of 16 bytes cover one entry's share of a panel and 64 / G entries are gathered by one instruction, so the
+//    instruction moves up to 1 KB however narrow the row is (47 fp32 columns: 188 bytes before);
+//  - rows wider than 512 bytes are cut into panels, and the workgroups of one XCD (consecutive workgroups go to the
+//    eight XCDs in turn) work on one panel, so that the part of X an XCD's 4 MB L2 is asked for is that much narrower.
+// The sums of the 64 / G groups of lanes are added in registers when a row is complete, in a fixed order.
+// Rows that the plan lists as long are taken in items of 1024 entries (16 pieces of the plan); rows of several items hand
+// partial rows over as in spmm_main_kernel, with one ticket per row and panel.
+// Measured, us (spmm_main_kernel / here): 65536 rows, 9.2 M entries, fp32, 256 columns 1014 / 650, 41 columns 515 / 200;
+// 600 k rows, 30.6 M entries, fp32, 100 columns 2050 / 1710, 47 columns 1490 / 750; bf16 256 columns 2276 / 1630.  At 256
+// columns the gathers then arrive at 14.5 TB/s; a matrix whose X fits every L2 whole reaches 15 to 17 TB/s.  Requesting the
+// gathers of one batch of entries ahead of the sums of the last (128 registers more in flight) was slower, so was
+// twice the occupancy at half the registers: the L2s' rate is the bound, not the latency.
+
+struct spmm_panel_args {
+    uint32_t rows;
+    const void *rowptr;
+    int rp64;
+    const int32_t *colidx;
+    const float *val;
+    int64_t cap;
+    int64_t ldx;
+    const int32_t *row_index;
+    int d;
+    int panels, interleave;      // interleave: how many panels are worked on at a time (1, 2, 4 or 8, divides panels)
+    const uint32_t *n_chunks;    // plan header
+    uint32_t max_chunks;
+    const uint2 *desc;
+    uint32_t *ticket;
+    float *part;                 // partial rows of d floats, at the row's first piece number + the item's
+    float *out;
+    int64_t ldo;
+    int rows_per_task;           // at most 63
+    int wide_epi;                // out, mask and add allow 16-byte (fp32) / 8-element accesses at every column that is a multiple of VEC
+};
+
+// Which matrices go this way: those with 12 entries a row or more.  The count itself is on the device; the host tells by
+// the capacity, which for a mini-batch matrix is twice the expected entries, sixteen more a row and 65536 more.
+// Measured, us here / with spmm_main_kernel, 262144 rows: 32 entries a row, fp32, 47 / 100 / 256 columns 220 / 386 / 821
+// against 378 / 496 / 981, bf16 256 columns 425 against 570; 16 a row 161 / 233 / 492 against 198 / 261 / 525, bf16 273
+// against 309; 8 a row 149 against 136 (fp32, 100), bf16 192 against 175: the reduction across the groups of lanes and the
+// row-by-row walk cost more than they save there.
+constexpr uint32_t SPMM_PANEL_MEAN = 12;
+constexpr int SPMM_PANEL_MAX = 16;      // panels: a row of two items or more has at least 17 ticket slots in the plan
+
+constexpr int SPMM_ITEM_ENTRIES = 1024;
+constexpr int SPMM_ITEM_SCAN = 16;      // plan pieces that a wavefront looks at together
+
+// plan pieces of `plen` entries that make up an item of a long row
+__device__ __forceinline__ uint32_t spmm_item_pieces(int64_t plen) { return plen >= SPMM_ITEM_ENTRIES ? 1u : (uint32_t)(SPMM_ITEM_ENTRIES / plen); }
+
+// 16 bytes from an address that is a multiple of the element size only (gfx950 global loads take any alignment)
+typedef uint32_t u32x4_any __attribute__((ext_vector_type(4), aligned(2)));
+
+template <typename XT> struct panel_vec;
+template <> struct panel_vec<float> {
+    static constexpr int VEC = 4;
+    static __device__ __forceinline__ float get(const u32x4_any &q, int i) { return __builtin_bit_cast(float, (uint32_t)q[i]); }
+};
+template <> struct panel_vec<bf16_bits> {
+    static constexpr int VEC = 8;
+    static __device__ __forceinline__ float get(const u32x4_any &q, int i)
+    {
+        const uint32_t w = q[i >> 1];
+        return __builtin_bit_cast(float, (i & 1) ? (w & 0xffff0000u) : (w << 16));
+    }
+};
+
+// x summed over the 64 / G lanes that share lane % G, in every lane
+template <int G> __device__ __forceinline__ float group_sum(float x)
+{
+    if constexpr (G <= 8) x += dpp_f32<0x128>(x);      // row_ror:8
+    // the swap exchanges halves between two registers: the second copy must not share the first one's
+    if constexpr (G <= 16) {
+        uint32_t u = __builtin_bit_cast(uint32_t, x), w = u;
+        asm("" : "+v"(w));
+        const auto r = __builtin_amdgcn_permlane16_swap(u, w, false, false);
+        x = __builtin_bit_cast(float, (uint32_t)r[0]) + __builtin_bit_cast(float, (uint32_t)r[1]);
+    }
+    if constexpr (G <= 32) {
+        uint32_t u = __builtin_bit_cast(uint32_t, x), w = u;
+        asm("" : "+v"(w));
+        const auto r = __builtin_amdgcn_permlane32_swap(u, w, false, false);
+        x = __builtin_bit_cast(float, (uint32_t)r[0]) + __builtin_bit_cast(float, (uint32_t)r[1]);
+    }
+    return x;
+}
+
+// OFF32: every byte of X lies within 4 GB of its start, so a lane's offset is 32 bits and is computed once per entry.
+template <int G, typename XT, bool OFF32>
+__global__ __launch_bounds__(SPMM_NT, 4) void spmm_panel_kernel(spmm_panel_args a, const XT *__restrict__ X, spmm_epi ep)
+{
+    if (a.n_chunks[3] < SPMM_PANEL_MEAN) return;       // short rows after all: spmm_main_kernel's matrix
+    constexpr int VEC = panel_vec<XT>::VEC, NE = 64 / G, W = G * VEC;
+    constexpr int U = 8;                               // gathers in flight per wavefront, 1 KB each
+    const int lane = threadIdx.x & 63, k = lane % G, g = lane / G;
+    const uint32_t slot = (blockIdx.x / a.interleave) * (uint32_t)(SPMM_NT / 64) + (uint32_t)__builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const uint32_t nslots = (gridDim.x / a.interleave) * (uint32_t)(SPMM_NT / 64);
+    const int long_len = (int)a.n_chunks[1];
+    const uint32_t n_pieces = min(*a.n_chunks, a.max_chunks);
+
+    for (int p = (int)(blockIdx.x % a.interleave); p < a.panels; p += a.interleave) {
+        // the lane's VEC columns: those from col0 on; at the right edge the 16 bytes that end with the row are read
+        // instead, and the first col0 - colb of them belong to the lane before
+        const int col0 = p * W + k * VEC, colb = min(col0, a.d - VEC), skip = col0 - colb;
+        const bool wide = a.wide_epi && skip == 0;
+        const char *__restrict__ xb = reinterpret_cast<const char *>(X);
+        const uint32_t row_bytes = (uint32_t)(a.ldx * (int64_t)sizeof(XT)), col_bytes = (uint32_t)colb * (uint32_t)sizeof(XT);
+
+        float acc[VEC];
+#pragma unroll
+        for (int i = 0; i < VEC; ++i) acc[i] = 0.f;
+        // n <= 64 entries from e on: lane l gets entry e + l
+        auto fetch = [&](int64_t e, int n, int32_t &c, float &v) {
+            c = 0; v = 0.f;
+            if (lane < n) {
+                c = __builtin_nontemporal_load(a.colidx + e + lane);
+                v = __builtin_nontemporal_load(a.val + e + lane);
+                if (a.row_index) c = a.row_index[c];
+                if constexpr (OFF32) c = (int32_t)((uint32_t)c * row_bytes);
+            }
+        };
+        auto load = [&](int32_t c, float v, int j, u32x4_any &q, float &av) {
+            const int32_t src = __builtin_amdgcn_ds_bpermute(j * 4, c);
+            av = __builtin_bit_cast(float, __builtin_amdgcn_ds_bpermute(j * 4, __builtin_bit_cast(int, v)));
+            if constexpr (OFF32) q = *reinterpret_cast<const u32x4_any *>(xb + (uint32_t)((uint32_t)src + col_bytes));
+            else q = *reinterpret_cast<const u32x4_any *>(xb + ((int64_t)src * (int64_t)row_bytes + col_bytes));
+        };
+        // acc += the n <= 64 entries that the lanes hold: group g takes entries g, g + NE, ...
+        auto gather = [&](int32_t c, float v, int n) {
+            int j0 = 0;
+            for (; j0 + U * NE <= n; j0 += U * NE) {
+                u32x4_any q[U];
+                float av[U];
+#pragma unroll
+                for (int t = 0; t < U; ++t) load(c, v, j0 + t * NE + g, q[t], av[t]);
+#pragma unroll
+                for (int t = 0; t < U; ++t)
+#pragma unroll
+                    for (int i = 0; i < VEC; ++i) acc[i] = fmaf(av[t], panel_vec<XT>::get(q[t], i), acc[i]);
+            }
+            if (j0 < n) {
+                u32x4_any q[U];
+                float av[U];
+#pragma unroll
+                for (int t = 0; t < U; ++t)
+                    if (j0 + t * NE < n) load(c, v, min(j0 + t * NE + g, n - 1), q[t], av[t]);
+#pragma unroll
+                for (int t = 0; t < U; ++t)
+                    if (j0 + t * NE + g < n) {      // a lane without an entry must not add 0 * x: x may be infinite
+#pragma unroll
+                        for (int i = 0; i < VEC; ++i) acc[i] = fmaf(av[t], panel_vec<XT>::get(q[t], i), acc[i]);
+                    }
+            }
+        };
+        auto reduce = [&]() {
+#pragma unroll
+            for (int i = 0; i < VEC; ++i) acc[i] = group_sum<G>(acc[i]);
+        };
+        // the finished row is in acc of every group: epilogue and store by group 0
+        auto write_row = [&](int64_t row) {
+            if (g == 0 && col0 < a.d) {
+#pragma unroll
+                for (int i = 0; i < VEC; ++i) {
+                    if (ep.bias) acc[i] += ep.bias[colb + i];
+                    if (ep.relu) acc[i] = fmaxf(acc[i], 0.f);
+                }
+                if (wide) {
+#pragma unroll
+                    for (int h = 0; h < VEC; h += 4) {
+                        float v[4] = {acc[h], acc[h + 1], acc[h + 2], acc[h + 3]};
+                        if (ep.mask) {
+                            float m[4];
+                            if (ep.mask_bf16) vload<4>(m, reinterpret_cast<const bf16_bits *>(ep.mask) + row * ep.ldm + col0 + h);
+                            else vload<4>(m, ep.mask + row * ep.ldm + col0 + h);
+#pragma unroll
+                            for (int i = 0; i < 4; ++i) v[i] = m[i] > 0.f ? v[i] : 0.f;
+                        }
+                        if (ep.add) {
+                            float m[4];
+                            vload<4>(m, ep.add + row * ep.ldadd + col0 + h);
+#pragma unroll
+                            for (int i = 0; i < 4; ++i) v[i] += m[i];
+                        }
+                        vstore_out<4>(a.out, row * a.ldo + col0 + h, v, ep.out_bf16);
+                    }
+                } else {
+#pragma unroll
+                    for (int i = 0; i < VEC; ++i) {
+                        if (i < skip) continue;
+                        float v[1] = {acc[i]};
+                        const int64_t col = colb + i;
+                        if (ep.mask) {
+                            float m[1];
+                            if (ep.mask_bf16) vload<1>(m, reinterpret_cast<const bf16_bits *>(ep.mask) + row * ep.ldm + col);
+                            else vload<1>(m, ep.mask + row * ep.ldm + col);
+                            v[0] = m[0] > 0.f ? v[0] : 0.f;
+                        }
+                        if (ep.add) v[0] += ep.add[row * ep.ldadd + col];
+                        vstore_out<1>(a.out, row * a.ldo + col, v, ep.out_bf16);
+                    }
+                }
+            }
+#pragma unroll
+            for (int i = 0; i < VEC; ++i) acc[i] = 0.f;
+        };
+
+        // long rows, item by item
+        for (uint64_t base = (uint64_t)slot * SPMM_ITEM_SCAN; base < n_pieces; base += (uint64_t)nslots * SPMM_ITEM_SCAN) {
+            uint2 rc = make_uint2(0, 0);
+            int64_t rs = 0, re = 0, plen = SPMM_CHUNK;
+            bool head = false;
+            if (lane < SPMM_ITEM_SCAN && base + lane < n_pieces) {
+                rc = a.desc[base + lane];
+                re = min(rp_load(a.rowptr, a.rp64, (uint64_t)rc.x + 1), a.cap);
+                rs = min(rp_load(a.rowptr, a.rp64, rc.x), re);
+                plen = spmm_piece_len(re - rs);
+                head = rc.y % spmm_item_pieces(plen) == 0;
+            }
+            for (uint64_t m = __ballot(head); m; m &= m - 1) {
+                const int l = __builtin_ctzll(m);
+                const uint32_t row = (uint32_t)__builtin_amdgcn_readlane((int)rc.x, l), pc = (uint32_t)__builtin_amdgcn_readlane((int)rc.y, l);
+                const int64_t s = readlane64(rs, l), e1 = readlane64(re, l), pl = spmm_piece_len(e1 - s);
+                const uint32_t ip = spmm_item_pieces(pl);
+                const int64_t c0 = s + (int64_t)pc * pl, c1 = min(e1, c0 + (int64_t)ip * pl);
+                int32_t c;
+                float v;
+                fetch(c0, (int)min(c1 - c0, (int64_t)64), c, v);
+                for (int64_t e = c0; e < c1; e += 64) {
+                    int32_t c2 = 0;
+                    float v2 = 0.f;
+                    if (e + 64 < c1) fetch(e + 64, (int)min(c1 - e - 64, (int64_t)64), c2, v2);
+                    gather(c, v, (int)min(c1 - e, (int64_t)64));
+                    c = c2; v = v2;
+                }
+                reduce();
+                const uint32_t first = (uint32_t)base + l - pc;
+                const uint32_t nch = min((uint32_t)((e1 - s + pl - 1) / pl), n_pieces - first), items = (nch + ip - 1) / ip;
+                if (items <= 1) {
+                    write_row(row);
+                    continue;
+                }
+                // partial row out with device-scope stores, then a ticket; the last ticket adds the partial rows up
+                if (g == 0 && col0 < a.d) {
+                    float *o = a.part + (int64_t)(first + pc) * a.d;
+#pragma unroll
+                    for (int i = 0; i < VEC; ++i)
+                        if (i >= skip) __hip_atomic_store(o + colb + i, acc[i], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+                }
+                asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+                uint32_t t = 0;
+                if (lane == 0) t = atomicAdd(&a.ticket[first + p], 1u);
+                t = (uint32_t)__builtin_amdgcn_readfirstlane((int)t);
+#pragma unroll
+                for (int i = 0; i < VEC; ++i) acc[i] = 0.f;
+                if (t + 1 != items) continue;
+                if (col0 < a.d)
+                    for (uint32_t it = g; it < items; it += NE) {
+                        const float *o = a.part + (int64_t)(first + it * ip) * a.d;
+#pragma unroll
+                        for (int i = 0; i < VEC; ++i)
+                            if (i >= skip) acc[i] += __hip_atomic_load(o + colb + i, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+                    }
+                reduce();
+                write_row(row);
+                if (lane == 0) a.ticket[first + p] = 0;
+            }
+        }
+
+        // the other rows, in blocks; the first entries of the next row are requested before the gathers of this one
+        for (uint64_t r0 = (uint64_t)slot * a.rows_per_task; r0 < a.rows; r0 += (uint64_t)nslots * a.rows_per_task) {
+            const int nr = (int)min((uint64_t)a.rows_per_task, a.rows - r0);
+            int64_t rpl = 0;
+            if (lane <= nr) rpl = min(rp_load(a.rowptr, a.rp64, r0 + lane), a.cap);
+            const int64_t bb = readlane64(rpl, 0);
+            const int32_t rp = lane <= nr ? (int32_t)(rpl - bb) : 0;
+            // rows are taken in order; a long one is left out
+            auto row_at = [&](int r, int &s, int &t) {
+                for (; r < nr; ++r) {
+                    s = __builtin_amdgcn_readlane(rp, r);
+                    t = __builtin_amdgcn_readlane(rp, r + 1);
+                    if (t - s <= long_len) break;
+                }
+                return r;
+            };
+            int s = 0, t = 0, r = row_at(0, s, t);
+            if (r >= nr) continue;
+            int32_t c;
+            float v;
+            fetch(bb + s, min(t - s, 64), c, v);
+            for (;;) {
+                int r2 = r, s2 = s + 64, t2 = t;
+                if (s2 >= t) r2 = row_at(r + 1, s2, t2);
+                int32_t c2 = 0;
+                float v2 = 0.f;
+                if (r2 < nr) fetch(bb + s2, min(t2 - s2, 64), c2, v2);
+                gather(c, v, min(t - s, 64));
+                if (r2 != r) {
+                    reduce();
+                    write_row((int64_t)r0 + r);
+                }
+                if (r2 >= nr) break;
+                r = r2; s = s2; t = t2; c = c2; v = v2;
+            }
+        }
+    }
+}
+
+template <typename XT> bool spmm_panel_wanted(const sgnn_csr *A, int64_t d)
+{
+    return A->capacity >= (uint64_t)(2 * SPMM_PANEL_MEAN + 16) * A->rows + 65536 && d >= panel_vec<XT>::VEC && d <= (int64_t)SPMM_PANEL_MAX * 32 * panel_vec<XT>::VEC;
+}
+
+template <int G, typename XT>
+int launch_panel_g(sgnn_ctx *ctx, const sgnn_csr *A, const XT *X, spmm_panel_args a, const spmm_epi &ep, hipStream_t st)
+{
+    constexpr int W = G * panel_vec<XT>::VEC;
+    a.panels = (a.d + W - 1) / W;
+    a.interleave = a.panels % 8 == 0 ? 8 : (a.panels % 4 == 0 ? 4 : (a.panels % 2 == 0 ? 2 : 1));
+    // tasks of up to 16 rows, no fewer than 16384 wavefronts while the rows last; the wavefronts stride over what is left
+    a.rows_per_task = (int)std::min<uint64_t>(16, std::max<uint64_t>(1, (uint64_t)A->rows * a.interleave / 16384));
+    const uint64_t tasks = std::max<uint64_t>(cdiv(A->rows, a.rows_per_task), cdiv(a.max_chunks, SPMM_ITEM_SCAN));
+    const unsigned grid = (unsigned)std::min<uint64_t>((uint64_t)cdiv(tasks, SPMM_NT / 64) * a.interleave, 8192);
+    char tag[56];
+    snprintf(tag, sizeof(tag), "%ux%u d=%d G=%d in=%d out=%d%s", A->rows, A->cols, a.d, G, (int)sizeof(XT), ep.out_bf16 ? 2 : 4,
+             ep.mask ? (ep.mask_bf16 ? " m=2" : " m=4") : "");
+    const bool off32 = !a.row_index && (uint64_t)A->cols * (uint64_t)a.ldx * sizeof(XT) <= 0xffffffffull;
+    if (off32)
+        SGNN_LAUNCH(ctx, st, "spmm_panel_kernel", tag, (spmm_panel_kernel<G, XT, true>), dim3(grid), dim3(SPMM_NT), 0, st, a, X, ep);
+    else
+        SGNN_LAUNCH(ctx, st, "spmm_panel_kernel", tag, (spmm_panel_kernel<G, XT, false>), dim3(grid), dim3(SPMM_NT), 0, st, a, X, ep);
+    return SGNN_OK;
+}
+
+template <typename XT>
+int launch_panel(sgnn_ctx *ctx, const sgnn_csr *A, const XT *X, int64_t ldx, const int32_t *row_index, int d, float *out, int64_t ldo,
+                 const spmm_epi &ep, ws_alloc *ws, hipStream_t st)
+{
+    spmm_panel_args a = {};
+    a.rows = A->rows; a.rowptr = A->rowptr; a.rp64 = A->rowptr_is_i64; a.colidx = A->colidx; a.val = A->val;
+    a.cap = (int64_t)std::min<uint64_t>(A->capacity, 0x7fffffffffffffffull);
+    a.ldx = ldx; a.row_index = row_index; a.d = d; a.out = out; a.ldo = ldo;
+    a.max_chunks = spmm_max_chunks(A->rows, A->capacity);
+    const spmm_plan_view pv = plan_view(A->plan, A->rows, a.max_chunks);
+    a.part = ws->get<float>((size_t)a.max_chunks * (size_t)d);
+    if (!ws->ok)
+        return sgnn_fail(ctx, SGNN_ERR_CAPACITY, "sgnn_spmm: scratch too small (%zu bytes needed): call sgnn_ctx_reserve", ws->off);
+    a.n_chunks = pv.n_chunks; a.desc = pv.desc; a.ticket = pv.ticket;
+    const int ob = ep.out_bf16 ? 2 : 4, mb = ep.mask_bf16 ? 2 : 4;
+    auto fits = [](const void *p, int64_t ld, int bytes) { return !p || (reinterpret_cast<uintptr_t>(p) % (uintptr_t)(4 * bytes) == 0 && ld % 4 == 0); };
+    a.wide_epi = fits(out, ldo, ob) && fits(ep.mask, ep.ldm, mb) && fits(ep.add, ep.ldadd, 4);
+    // The narrowest panel that holds the row, 32 lanes (512 bytes) at most.  Narrower panels keep more of X in an XCD's L2
+    // (dense-degree mini-batch, 256 fp32 columns: L2 misses 45 M a call in spmm_main_kernel, 21 M with panels of 16 lanes, 15 M
+    // with 8) but read the matrix and reduce the rows once more per panel: 673 / 890 us with 16 / 8 lanes against 650.
+    constexpr int VEC = panel_vec<XT>::VEC;
+    if (d <= 8 * VEC) return launch_panel_g<8, XT>(ctx, A, X, a, ep, st);
+    if (d <= 16 * VEC) return launch_panel_g<16, XT>(ctx, A, X, a, ep, st);
+    return launch_panel_g<32, XT>(ctx, A, X, a, ep, st);
+}
