@@ -9,8 +9,8 @@
 //  - rows wider than 512 bytes are cut into panels, and the workgroups of one XCD (consecutive workgroups go to the
 //    eight XCDs in turn) work on one panel, so that the part of X an XCD's 4 MB L2 is asked for is that much narrower.
 // The sums of the 64 / G groups of lanes are added in registers when a row is complete, in a fixed order.
-// Rows that the plan lists as long are taken in items of 1024 entries (16 pieces of the plan); rows of several items hand
-// partial rows over as in spmm_main_kernel, with one ticket per row and panel.
+// Rows that the plan lists as long are taken in items of up to 1024 entries (16 pieces of the plan); rows of several items
+// hand partial rows over as in spmm_main_kernel, with one ticket per row and panel.
 // Measured, us (spmm_main_kernel / here): 65536 rows, 9.2 M entries, fp32, 256 columns 1014 / 650, 41 columns 515 / 200;
 // 600 k rows, 30.6 M entries, fp32, 100 columns 2050 / 1710, 47 columns 1490 / 750; bf16 256 columns 2276 / 1630.  At 256
 // columns the gathers then arrive at 14.5 TB/s; a matrix whose X fits every L2 whole reaches 15 to 17 TB/s.  Requesting the
@@ -46,13 +46,19 @@ struct spmm_panel_args {
 // against 309; 8 a row 149 against 136 (fp32, 100), bf16 192 against 175: the reduction across the groups of lanes and the
 // row-by-row walk cost more than they save there.
 constexpr uint32_t SPMM_PANEL_MEAN = 12;
-constexpr int SPMM_PANEL_MAX = 16;      // panels: a row of two items or more has at least 17 ticket slots in the plan
+constexpr int SPMM_PANEL_MAX = 16;
 
-constexpr int SPMM_ITEM_ENTRIES = 1024;
-constexpr int SPMM_ITEM_SCAN = 16;      // plan pieces that a wavefront looks at together
 
-// plan pieces of `plen` entries that make up an item of a long row
-__device__ __forceinline__ uint32_t spmm_item_pieces(int64_t plen) { return plen >= SPMM_ITEM_ENTRIES ? 1u : (uint32_t)(SPMM_ITEM_ENTRIES / plen); }
+// Plan pieces that make up an item of a long row of `nch` pieces of `plen` entries: up to 1024 entries, fewer on a matrix with so few
+// pieces that they would not give every wavefront of the machine one.  A row with fewer pieces than there are panels is one
+// item (it has as many ticket slots as pieces).  A lone wavefront takes about a microsecond for 32 entries: with items of
+// 1024 whatever the matrix, a layer on 1057 rows with 24.6 k entries took 171 us instead of 110.
+__device__ __forceinline__ uint32_t spmm_item_pieces(int64_t plen, uint32_t nch, uint32_t n_pieces, int panels)
+{
+    if (nch <= (uint32_t)panels) return nch;
+    const uint32_t want = min(n_pieces / 8192u, 16u) * SPMM_CHUNK / (uint32_t)plen;
+    return want ? want : 1u;
+}
 
 // 16 bytes from an address that is a multiple of the element size only (gfx950 global loads take any alignment)
 typedef uint32_t u32x4_any __attribute__((ext_vector_type(4), aligned(2)));
@@ -210,23 +216,24 @@ __global__ __launch_bounds__(SPMM_NT, 4) void spmm_panel_kernel(spmm_panel_args 
             for (int i = 0; i < VEC; ++i) acc[i] = 0.f;
         };
 
-        // long rows, item by item
-        for (uint64_t base = (uint64_t)slot * SPMM_ITEM_SCAN; base < n_pieces; base += (uint64_t)nslots * SPMM_ITEM_SCAN) {
+        // long rows, item by item; a wavefront looks at its share of the pieces at a time, at most 16
+        const uint32_t scan = min(max((n_pieces + nslots - 1) / nslots, 1u), 16u);
+        for (uint64_t base = (uint64_t)slot * scan; base < n_pieces; base += (uint64_t)nslots * scan) {
             uint2 rc = make_uint2(0, 0);
             int64_t rs = 0, re = 0, plen = SPMM_CHUNK;
             bool head = false;
-            if (lane < SPMM_ITEM_SCAN && base + lane < n_pieces) {
+            if (lane < (int)scan && base + lane < n_pieces) {
                 rc = a.desc[base + lane];
                 re = min(rp_load(a.rowptr, a.rp64, (uint64_t)rc.x + 1), a.cap);
                 rs = min(rp_load(a.rowptr, a.rp64, rc.x), re);
                 plen = spmm_piece_len(re - rs);
-                head = rc.y % spmm_item_pieces(plen) == 0;
+                head = rc.y % spmm_item_pieces(plen, (uint32_t)((re - rs + plen - 1) / plen), n_pieces, a.panels) == 0;
             }
             for (uint64_t m = __ballot(head); m; m &= m - 1) {
                 const int l = __builtin_ctzll(m);
                 const uint32_t row = (uint32_t)__builtin_amdgcn_readlane((int)rc.x, l), pc = (uint32_t)__builtin_amdgcn_readlane((int)rc.y, l);
                 const int64_t s = readlane64(rs, l), e1 = readlane64(re, l), pl = spmm_piece_len(e1 - s);
-                const uint32_t ip = spmm_item_pieces(pl);
+                const uint32_t all = (uint32_t)((e1 - s + pl - 1) / pl), ip = spmm_item_pieces(pl, all, n_pieces, a.panels);
                 const int64_t c0 = s + (int64_t)pc * pl, c1 = min(e1, c0 + (int64_t)ip * pl);
                 int32_t c;
                 float v;
@@ -240,7 +247,7 @@ __global__ __launch_bounds__(SPMM_NT, 4) void spmm_panel_kernel(spmm_panel_args 
                 }
                 reduce();
                 const uint32_t first = (uint32_t)base + l - pc;
-                const uint32_t nch = min((uint32_t)((e1 - s + pl - 1) / pl), n_pieces - first), items = (nch + ip - 1) / ip;
+                const uint32_t nch = min(all, n_pieces - first), items = (nch + ip - 1) / ip;
                 if (items <= 1) {
                     write_row(row);
                     continue;
@@ -324,7 +331,7 @@ int launch_panel_g(sgnn_ctx *ctx, const sgnn_csr *A, const XT *X, spmm_panel_arg
     a.interleave = a.panels % 8 == 0 ? 8 : (a.panels % 4 == 0 ? 4 : (a.panels % 2 == 0 ? 2 : 1));
     // tasks of up to 16 rows, no fewer than 16384 wavefronts while the rows last; the wavefronts stride over what is left
     a.rows_per_task = (int)std::min<uint64_t>(16, std::max<uint64_t>(1, (uint64_t)A->rows * a.interleave / 16384));
-    const uint64_t tasks = std::max<uint64_t>(cdiv(A->rows, a.rows_per_task), cdiv(a.max_chunks, SPMM_ITEM_SCAN));
+    const uint64_t tasks = std::max<uint64_t>(cdiv(A->rows, a.rows_per_task), a.max_chunks);
     const unsigned grid = (unsigned)std::min<uint64_t>((uint64_t)cdiv(tasks, SPMM_NT / 64) * a.interleave, 8192);
     char tag[56];
     snprintf(tag, sizeof(tag), "%ux%u d=%d G=%d in=%d out=%d%s", A->rows, A->cols, a.d, G, (int)sizeof(XT), ep.out_bf16 ? 2 : 4,
