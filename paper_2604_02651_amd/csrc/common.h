@@ -123,6 +123,10 @@ int sgnn_launch_gemm_x(sgnn_ctx *ctx, int ta, int tb, int64_t M, int64_t N, int6
                        const int32_t *a_row_index, const void *B, int b_bf16, int64_t ldb, const float *bias, int flags, void *C,
                        int c_bf16, int64_t ldc, const void *mask, int m_bf16, int64_t ldm, float *b_colsum, ws_alloc *ws,
                        hipStream_t st);
+// fp32 operands on the bfloat16 matrix pipe, split exactly (gemm_split.hip)
+int sgnn_launch_gemm_split(sgnn_ctx *ctx, int ta, int tb, int64_t M, int64_t N, int64_t K, const float *A, int64_t lda, const int32_t *ridx,
+                           const float *B, int64_t ldb, const float *bias, int relu, float *C, int64_t ldc, const float *mask, int64_t ldm,
+                           float *b_colsum, ws_alloc *ws, hipStream_t st);
 int sgnn_launch_splitk_reduce(sgnn_ctx *ctx, const float *partial, int splits, int64_t M, int64_t N, float *C, int64_t ldc,
                               const float *cs_partial, float *cs_out, hipStream_t st);
 // A^T B, both operands bfloat16, result up to 256 x 256, long reduction: SGNN_ERR_UNSUPPORTED (nothing launched) outside its range

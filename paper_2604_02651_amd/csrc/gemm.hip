@@ -1,7 +1,8 @@
 // Dense transform of the GCN layer on the matrix cores (Sec. III-B Eq. 6 and the two GEMMs of the
 // layer backward, Sec. III-C):   C = act(op(A) op(B) + bias).
 //
-// fp32 path:  v_mfma_f32_32x32x2_f32  (fp32 operands, fp32 accumulate - the paper's precision)
+// fp32 path:  v_mfma_f32_32x32x2_f32  (fp32 operands, fp32 accumulate - the paper's precision), for results of up to 32
+//             columns and products with fewer than four elements in a direction; the others: gemm_split.hip
 // bf16 path:  v_mfma_f32_32x32x16_bf16, operands rounded to bfloat16 (nearest even) while they
 //             are staged into LDS, fp32 accumulate.
 //
@@ -737,284 +738,6 @@ __global__ __launch_bounds__(256) void gemm_fast_kernel(gemm_args a)
 }
 
 // ---------------------------------------------------------------------------------------------
-// fp32 path with direct global -> LDS loads (global_load_lds_dwordx4: lane l's 16 bytes land at
-// a wave-uniform LDS base + 16 l, no register staging).  256 x 128 tile, eight wavefronts with
-// 64 x 64 sub-tiles (two per SIMD) - or, for the split reductions of the weight gradients, a
-// 128 x 128 tile, eight wavefronts with 64 x 32 sub-tiles - slices of 32 along the reduction in a ring of three LDS
-// stages: slice s + 2 is in flight while slice s is multiplied, one barrier per slice placed in the
-// middle of the slice's multiplies, waits on the loads stated explicitly (vmcnt).  Needs whole 16-byte chunks (as the fast path) and a
-// reduction range that is a multiple of 32.
-//
-// LDS layouts (no padding, a wavefront load covers 1 KB of contiguous LDS):
-//   reduction-contiguous operand: [row][8 chunks of 16 bytes]; position p of row r holds chunk
-//     p ^ ((r >> 1) & 7) of the slice, so that the 32 rows a half-wavefront reads at one reduction
-//     offset fall into different banks;
-//   operand given [reduction][rows]: [k][R] as in memory; a lane reads its tiles' values at
-//     consecutive addresses (tiles interleaved as in the fast path).
-// ---------------------------------------------------------------------------------------------
-#define SGNN_GPTR(p) ((const __attribute__((address_space(1))) void *)(p))
-#define SGNN_LPTR(p) ((__attribute__((address_space(3))) void *)(p))
-constexpr int DIRECT_BM = 256, DIRECT_BN = 128, DIRECT_BK = 32, DIRECT_STAGES = 3, DIRECT_WAVES = 8;
-
-// s_waitcnt vmcnt(n) only (expcnt and lgkmcnt left at their maxima), gfx9 encoding
-#define SGNN_WAIT_VMCNT(n) __builtin_amdgcn_s_waitcnt(((n) & 15) | (((n) >> 4) << 14) | 0x0F70)
-
-// Issues the loads of one operand slice: R rows, wave-loads dealt round-robin to the WAVES wavefronts.
-template <int R, bool RC, int WAVES>
-__device__ __forceinline__ void direct_issue(float *lds, const float *__restrict__ G, int64_t ld, int64_t row0, int64_t rows_total,
-                                             int64_t k0, const int32_t *__restrict__ ridx, int lane, int wave)
-{
-    constexpr int LOADS = R * DIRECT_BK / 4 / 64 / WAVES;   // wave-loads per wavefront
-    static_assert(LOADS * 64 * WAVES * 4 == R * DIRECT_BK, "the wavefronts share the slice evenly");
-#pragma unroll
-    for (int j = 0; j < LOADS; ++j) {
-        const int q = wave + WAVES * j;   // wave-load number: LDS floats [256 q, 256 q + 256)
-        const float *g;
-        if (RC) {
-            const int r = 8 * q + (lane >> 3), pos = lane & 7;
-            int64_t gr = min(row0 + r, rows_total - 1);
-            if (ridx) gr = ridx[gr];
-            g = G + gr * ld + k0 + 4 * (pos ^ ((r >> 1) & 7));
-        } else {
-            const int f = 64 * q + lane;                   // chunk number in the [k][R / 4] array
-            const int k = f / (R / 4), ch = f % (R / 4);
-            g = G + (k0 + k) * ld + min(row0 + 4 * ch, rows_total - 4);
-        }
-        __builtin_amdgcn_global_load_lds(SGNN_GPTR(g), SGNN_LPTR(lds + 256 * q), 16, 0, 0);
-    }
-}
-
-// The same for a transposed operand whose reduction rows are gathered (row k of the operand is row ridx[k] of G).
-// The indices of a slice are fetched one slice ahead, before the loads of the current slice are issued: by the time
-// they are used, only loads issued after them are outstanding, so the wait the compiler places before their use
-// does not drain the slice in flight.  Whatever order the loads end up in, the wait before the barrier
-// (at most as many operations outstanding as one slice has loads) still covers every older slice.
-template <int R, int WAVES>
-__device__ __forceinline__ void direct_issue_gathered_t(float *lds, const float *__restrict__ G, int64_t ld, int64_t row0,
-                                                        int64_t rows_total, int64_t k0_next, const int32_t *__restrict__ ridx,
-                                                        int lane, int wave, int32_t (&rows)[R * DIRECT_BK / 4 / 64 / WAVES])
-{
-    constexpr int LOADS = R * DIRECT_BK / 4 / 64 / WAVES;
-    int32_t cur[LOADS];
-#pragma unroll
-    for (int j = 0; j < LOADS; ++j) cur[j] = rows[j];
-#pragma unroll
-    for (int j = 0; j < LOADS; ++j) rows[j] = ridx[k0_next + (64 * (wave + WAVES * j) + lane) / (R / 4)];
-#pragma unroll
-    for (int j = 0; j < LOADS; ++j) {
-        const int q = wave + WAVES * j, ch = (64 * q + lane) % (R / 4);
-        const float *g = G + (int64_t)cur[j] * ld + min(row0 + 4 * ch, rows_total - 4);
-        __builtin_amdgcn_global_load_lds(SGNN_GPTR(g), SGNN_LPTR(lds + 256 * q), 16, 0, 0);
-    }
-}
-
-// Operand values of one quad of a slice: reduction steps kk + 8 kh + 4 half + {0..3} for the T tiles of the wavefront.
-template <int R, bool RC, int T>
-__device__ __forceinline__ void direct_frag(float (&v)[T][4], const float *L, int w0, int kk, int half, int li, int kh)
-{
-    if constexpr (RC) {
-#pragma unroll
-        for (int t = 0; t < T; ++t) {
-            const int r = w0 + 32 * t + li, c = kk / 4 + 2 * kh + half;
-            const f32x4 x = *reinterpret_cast<const f32x4 *>(L + r * 32 + 4 * (c ^ ((r >> 1) & 7)));
-#pragma unroll
-            for (int s = 0; s < 4; ++s) v[t][s] = x[s];
-        }
-    } else {
-#pragma unroll
-        for (int s = 0; s < 4; ++s) {
-            const typename fvec<T>::type x =
-                *reinterpret_cast<const typename fvec<T>::type *>(L + (kk + 8 * kh + 4 * half + s) * R + w0 + T * li);
-            if constexpr (T == 1) v[0][s] = x;
-            else {
-#pragma unroll
-                for (int t = 0; t < T; ++t) v[t][s] = x[t];
-            }
-        }
-    }
-}
-
-template <int BM, int WAVES, int TN, bool TA, bool TB, bool GATHER>
-__global__ __launch_bounds__(64 * WAVES) void gemm_direct_kernel(gemm_args a)
-{
-    constexpr int BN = DIRECT_BN, BK = DIRECT_BK, TM = 2;
-    constexpr int WAVES_N = BN / (32 * TN);
-    static_assert(BM * BN == WAVES * 64 * 32 * TN, "a 64 x 32 TN sub-tile per wavefront");
-    constexpr int STAGE_FLOATS = (BM + BN) * BK;
-    constexpr bool A_RC = !TA, B_RC = TB;
-    constexpr int LOADS = (BM + BN) * BK / 4 / 64 / WAVES;   // loads per thread and slice
-    extern __shared__ __attribute__((aligned(16))) float direct_smem[];
-    const gemm_tile tb_ = tile_of_block(a);
-    if (!tb_.valid) return;
-    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-    const int li = lane & 31, kh = lane >> 5;
-    const int wm0 = (wave / WAVES_N) * 64, wn0 = (wave % WAVES_N) * (32 * TN);
-    const int64_t m0 = (int64_t)tb_.bx * BM, n0 = (int64_t)tb_.by * BN;
-    const int64_t kbeg = (int64_t)tb_.bz * a.k_per_split;
-    const int64_t kend = min(a.K, kbeg + a.k_per_split);
-    const int nslices = (int)((kend - kbeg) / BK);
-
-    f32x16 acc[TM][TN];
-#pragma unroll
-    for (int i = 0; i < TM; ++i)
-#pragma unroll
-        for (int j = 0; j < TN; ++j)
-#pragma unroll
-            for (int r = 0; r < 16; ++r) acc[i][j][r] = 0.f;
-
-    // a slice number past the end loads the last slice again, into a stage nobody reads any more:
-    // the loop body then has no branch, and every wait in it counts a fixed number of operations
-    constexpr int LOADS_A = BM * BK / 4 / 64 / WAVES;
-    [[maybe_unused]] int32_t a_rows[LOADS_A];   // gathered A^T: the rows of the slice issued next
-    if constexpr (GATHER && TA) {
-        if (nslices > 0) {
-#pragma unroll
-            for (int j = 0; j < LOADS_A; ++j) a_rows[j] = a.a_row_index[kbeg + (64 * (wave + WAVES * j) + lane) / (BM / 4)];
-        }
-    }
-    auto issue = [&](int s) {
-        float *st = direct_smem + (s % DIRECT_STAGES) * STAGE_FLOATS;
-        const int64_t k0 = kbeg + (int64_t)min(s, nslices - 1) * BK;
-        if constexpr (GATHER && TA) {
-            const int64_t k0_next = kbeg + (int64_t)min(s + 1, nslices - 1) * BK;
-            direct_issue_gathered_t<BM, WAVES>(st, a.A, a.lda, m0, a.M, k0_next, a.a_row_index, lane, wave, a_rows);
-        } else
-        direct_issue<BM, A_RC, WAVES>(st, a.A, a.lda, m0, a.M, k0, GATHER ? a.a_row_index : nullptr, lane, wave);
-        direct_issue<BN, B_RC, WAVES>(st + BM * BK, a.B, a.ldb, n0, a.N, k0, nullptr, lane, wave);
-    };
-    // Schedule of a slice (four quads of four reduction steps each, operand values double buffered in
-    // registers):   read q1 | multiply q0 | read q2 | multiply q1 | wait + barrier + issue slice it+2 |
-    //               read q3 | multiply q2 | read q0 of slice it+1 | multiply q3
-    // The barrier sits in the middle of the multiplies: it publishes slice it + 1 (loaded one slice
-    // ago) and proves that everyone has left slice it - 1, whose stage the new loads overwrite, so
-    // no wavefront ever waits on memory or LDS latency with an empty MFMA queue behind it.
-    float av[2][TM][4], bv[2][TN][4];
-    auto frags = [&](int buf, int slice, int q) {
-        const float *LA = direct_smem + (slice % DIRECT_STAGES) * STAGE_FLOATS, *LB = LA + BM * BK;
-        direct_frag<BM, A_RC, TM>(av[buf], LA, wm0, 16 * (q / 2), q & 1, li, kh);
-        direct_frag<BN, B_RC, TN>(bv[buf], LB, wn0, 16 * (q / 2), q & 1, li, kh);
-    };
-    auto multiply = [&](int buf) {
-#pragma unroll
-        for (int s = 0; s < 4; ++s)
-#pragma unroll
-            for (int i = 0; i < TM; ++i)
-#pragma unroll
-                for (int j = 0; j < TN; ++j)
-                    acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x2f32(av[buf][i][s], bv[buf][j][s], acc[i][j], 0, 0, 0);
-    };
-    if (nslices > 0) {
-        issue(0);
-        issue(1);
-        SGNN_WAIT_VMCNT(LOADS);
-        asm volatile("" ::: "memory");
-        __builtin_amdgcn_s_barrier();
-        asm volatile("" ::: "memory");
-        frags(0, 0, 0);
-    }
-    // column sums of B (the bias gradient next to dW = T^T dZ), by the first row block of tiles only: B of a
-    // slice lies in LDS as [32 reduction steps][128 columns]; a thread adds up its column over every
-    // (threads / 128)-th reduction step while the slice is current
-    constexpr int CS_PARTS = WAVES * 64 / BN;
-    const bool do_cs = TA && !TB && a.colsum && tb_.bx == 0;
-    float cs = 0.f;
-    for (int it = 0; it < nslices; ++it) {
-        frags(1, it, 1);
-        if constexpr (TA && !TB) {
-            if (do_cs) {
-                const float *LB = direct_smem + (it % DIRECT_STAGES) * STAGE_FLOATS + BM * BK;
-#pragma unroll
-                for (int k = 0; k < BK / CS_PARTS; ++k) cs += LB[(k * CS_PARTS + threadIdx.x / BN) * BN + threadIdx.x % BN];
-            }
-        }
-        __builtin_amdgcn_sched_barrier(0);
-        multiply(0);
-        __builtin_amdgcn_sched_barrier(0);
-        frags(0, it, 2);
-        __builtin_amdgcn_sched_barrier(0);
-        multiply(1);
-        __builtin_amdgcn_sched_barrier(0);
-        SGNN_WAIT_VMCNT(0);   // this thread's part of slice it + 1 (the only loads in flight) has landed
-        asm volatile("" ::: "memory");
-        __builtin_amdgcn_s_barrier();
-        asm volatile("" ::: "memory");
-        issue(it + 2);   // into the stage slice it - 1 was read from
-        frags(1, it, 3);
-        __builtin_amdgcn_sched_barrier(0);
-        multiply(0);
-        __builtin_amdgcn_sched_barrier(0);
-        frags(0, it + 1, 0);   // (after the last slice: values nobody uses)
-        __builtin_amdgcn_sched_barrier(0);
-        multiply(1);
-        __builtin_amdgcn_sched_barrier(0);
-    }
-
-    if constexpr (TA && !TB) {
-        if (do_cs) {
-            __syncthreads();      // every wavefront is through its last slice: the stages are free
-            direct_smem[threadIdx.x] = cs;
-            __syncthreads();
-            const int64_t col = n0 + threadIdx.x;
-            if (threadIdx.x < BN && col < a.N) {
-                float t = 0.f;
-#pragma unroll
-                for (int p = 0; p < CS_PARTS; ++p) t += direct_smem[p * BN + threadIdx.x];
-                a.colsum[(a.partial ? (int64_t)tb_.bz * a.N : 0) + col] = t;
-            }
-        }
-    }
-    float *Cout = a.partial ? a.partial + (int64_t)tb_.bz * a.M * a.N : a.C;
-    const int64_t ldc = a.partial ? a.N : a.ldc;
-    float *stage = nullptr;
-    if constexpr (B_RC) {
-        __syncthreads();      // every wavefront is through its last slice: the stages are free
-        stage = direct_smem + (threadIdx.x >> 6) * 32 * (32 * TN + 4);
-    }
-    store_tile<TM, TN, A_RC, B_RC>(a, acc, Cout, ldc, m0 + wm0, n0 + wn0, li, kh, stage);
-}
-
-int launch_direct(sgnn_ctx *ctx, int ta, int tb, gemm_args a, int splits, bool bm128, hipStream_t st)
-{
-    const int bm = bm128 ? 128 : DIRECT_BM, waves = DIRECT_WAVES;
-    a.mtiles = (uint32_t)cdiv(a.M, bm);
-    a.ntiles = (uint32_t)cdiv(a.N, DIRECT_BN);
-    a.splits = (uint32_t)splits;
-    const uint64_t members = splits > 1 ? (uint64_t)a.mtiles * a.ntiles : a.ntiles;
-    const uint64_t groups = splits > 1 ? (uint64_t)splits : a.mtiles;
-    const uint64_t nblocks = cdiv(groups, 8) * 8 * members;
-    if (nblocks > 0x7fffffffull) return sgnn_fail(ctx, SGNN_ERR_UNSUPPORTED, "sgnn_gemm: more than 2^31 tiles");
-    char tag[56];
-    snprintf(tag, sizeof(tag), "%c%c %dx%d %lldx%lldx%lld f32", ta ? 'T' : 'N', tb ? 'T' : 'N', bm, DIRECT_BN, (long long)a.M,
-             (long long)a.N, (long long)a.K);
-    dim3 grid((unsigned)nblocks), block(64 * waves);
-    const size_t lds_bytes = (size_t)DIRECT_STAGES * (bm + DIRECT_BN) * DIRECT_BK * sizeof(float);
-    const bool gather = a.a_row_index != nullptr;
-#define SGNN_DIRECT_CASE_BM(BM_, W_, TN_, TA_, TB_, G_)                                                                 \
-    if (bm == BM_ && ta == TA_ && tb == TB_ && gather == G_) {                                                          \
-        static bool attr_set = false;                                                                                   \
-        if (!attr_set) {                                                                                                \
-            SGNN_HIP(ctx, hipFuncSetAttribute(reinterpret_cast<const void *>(&gemm_direct_kernel<BM_, W_, TN_, TA_, TB_, G_>), \
-                                              hipFuncAttributeMaxDynamicSharedMemorySize, 160 * 1024));                 \
-            attr_set = true;                                                                                            \
-        }                                                                                                               \
-        SGNN_LAUNCH(ctx, st, "gemm_kernel", tag, (gemm_direct_kernel<BM_, W_, TN_, TA_, TB_, G_>), grid, block, lds_bytes, st, a); \
-        return SGNN_OK;                                                                                                 \
-    }
-#define SGNN_DIRECT_CASE(TA_, TB_, G_) SGNN_DIRECT_CASE_BM(DIRECT_BM, DIRECT_WAVES, 2, TA_, TB_, G_)
-    SGNN_DIRECT_CASE_BM(128, 8, 1, true, false, false)
-    SGNN_DIRECT_CASE_BM(128, 8, 1, true, false, true)
-    SGNN_DIRECT_CASE(false, false, false)
-    SGNN_DIRECT_CASE(false, true, false)
-    SGNN_DIRECT_CASE(true, false, false)
-    SGNN_DIRECT_CASE(false, false, true)
-    SGNN_DIRECT_CASE(false, true, true)
-    SGNN_DIRECT_CASE(true, false, true)
-#undef SGNN_DIRECT_CASE_BM
-#undef SGNN_DIRECT_CASE
-    return SGNN_OK;
-}
-
-// ---------------------------------------------------------------------------------------------
 // bf16 path, tall A and a small B (K <= 256, N <= 256: the layer transform and the feature
 // gradient of a mini-batch with hundreds of thousands of rows).  The product is bound by reading
 // A and writing C once, so the kernel is built around that stream:
@@ -1739,7 +1462,7 @@ int launch_cfg(sgnn_ctx *ctx, int ta, int tb, int bf16, gemm_args a, int splits,
     // fast path: every 16-byte chunk wholly inside or outside the operands
     const int64_t a_contig = ta ? a.M : a.K, b_contig = tb ? a.K : a.N;
     const bool fast = a.alignedA && a.alignedB && a_contig % 4 == 0 && b_contig % 4 == 0 && a_contig >= 4 && b_contig >= 4 &&
-                      a.K >= 1 && a.M >= 1 && a.N >= 1;
+                      a.K >= 1 && a.M >= 1 && a.N >= 1 && (bf16 || (BN == 32 && !ta));     // other fp32 shapes: gemm_split.hip
     if (fast && !(ta && tb)) {
         snprintf(tag, sizeof(tag), "%c%c %dx%d %lldx%lldx%lld %s%s", ta ? 'T' : 'N', tb ? 'T' : 'N', BM, BN, (long long)a.M,
                  (long long)a.N, (long long)a.K, bf16 ? "bf16" : "f32", a.a_bf16 ? (a.b_bf16 ? " a=2 b=2" : " a=2") : (a.b_bf16 ? " b=2" : ""));
@@ -1757,9 +1480,10 @@ int launch_cfg(sgnn_ctx *ctx, int ta, int tb, int bf16, gemm_args a, int splits,
                 SGNN_LAUNCH(ctx, st, "gemm_kernel", tag, (gemm_fast_kernel<BM, BN, WM, WN, true, false, true, false, true>), grid, block, 0, st, a);
             return SGNN_OK;
         }
-        SGNN_GEMM_FAST(false, false, false)
-        SGNN_GEMM_FAST(false, true, false)
-        SGNN_GEMM_FAST(true, false, false)
+        if constexpr (BN == 32) {
+            SGNN_GEMM_FAST(false, false, false)
+            SGNN_GEMM_FAST(false, true, false)
+        }
         SGNN_GEMM_FAST(false, false, true)
         SGNN_GEMM_FAST(false, true, true)
         SGNN_GEMM_FAST(true, false, true)
@@ -1970,28 +1694,21 @@ int sgnn_launch_gemm_x(sgnn_ctx *ctx, int ta, int tb, int64_t M, int64_t N, int6
         return SGNN_OK;
     }
 
-    // wide fp32 results with whole chunks and whole slices: the direct-to-LDS kernel, 256 x 128 tiles.  Not for
-    // the long reductions onto a small result (T^T dZ): with two 256 x 128 tiles the split would have to be
-    // twice as fine, and the partial products it writes cost more than the kernel gains (those take the
-    // kernel's 128 x 128 form, direct128 below).
+    // every other fp32 product: split into bfloat16 parts (gemm_split.hip), except the transforms onto up to 32 columns, which
+    // are bound by reading A (32768 x 32 x 256: 13 us on the tile kernel below, 19 there), and shapes with fewer than four
+    // elements along a contiguous direction
     const int64_t a_contig = ta ? M : K, b_contig = tb ? K : N;
-    const bool direct = !bf16 && !ta && a.alignedA && a.alignedB && a_contig % 4 == 0 && b_contig % 4 == 0 &&
-                        a_contig >= 4 && b_contig >= 4 && K % 32 == 0 && K >= 128 && N > 64 && M > 128;
-
-    // the weight gradients of the wide layers (A^T B, long reduction onto a result of a few 128 x 128 tiles): the same
-    // kernel with 128-row tiles, one workgroup per reduction range and tile, two slices in flight behind the one
-    // being multiplied (the register-staged tile kernel has one, and its wavefronts wait for it half of the time) and
-    // eight wavefronts, two per SIMD (with four, one per SIMD, it was no faster than the tile kernel: nothing
-    // multiplies while the only wavefront of a SIMD issues loads, reads LDS or stands at the barrier)
-    const bool direct128 = !bf16 && ta && !tb && a.alignedA && a.alignedB && M % 4 == 0 && N % 4 == 0 &&
-                           M > 64 && N > 64 && K % 32 == 0 && K >= 4096 && !bias && !(flags & SGNN_RELU) && !mask &&
-                           (int64_t)cdiv(M, 128) * cdiv(N, 128) <= 64;
+    const bool narrow = !ta && N <= 32 && a.alignedA && a.alignedB && a_contig % 4 == 0 && b_contig % 4 == 0;
+    if (!bf16 && !(ta && tb) && !narrow && a_contig >= 4 && b_contig >= 4 && K >= 4) {
+        if (b_colsum && !ta) return sgnn_fail(ctx, SGNN_ERR_INVALID_ARG, "sgnn_gemm: column sums of B go with A^T B only");
+        return sgnn_launch_gemm_split(ctx, ta, tb, M, N, K, A, lda, a_row_index, B, ldb, bias, a.relu, C, ldc, mask, ldm, b_colsum, ws, st);
+    }
 
     // tile shape by the width of C
     const int bn = N > 64 ? 128 : (N > 32 ? 64 : 32);
     // narrow results: 256-row tiles, or 128-row ones when those would leave compute units without a tile
     const bool narrow128 = bn == 32 && K < 4096 && cdiv(M, 256) < 256;
-    const int bm = direct ? DIRECT_BM : (bn == 32 ? (narrow128 ? 128 : 256) : 128);
+    const int bm = bn == 32 ? (narrow128 ? 128 : 256) : 128;
     int splits = 1;
     const int64_t tiles = (int64_t)cdiv(M, bm) * cdiv(N, bn);
     if (tiles < 256 && K >= 4096 && !bias && !(flags & SGNN_RELU) && !mask) {
@@ -2013,7 +1730,7 @@ int sgnn_launch_gemm_x(sgnn_ctx *ctx, int ta, int tb, int64_t M, int64_t N, int6
     bool cs_fused = false;
     if (b_colsum) {
         if (!ta || tb) return sgnn_fail(ctx, SGNN_ERR_INVALID_ARG, "sgnn_gemm: column sums of B go with A^T B only");
-        cs_fused = !direct && a.alignedA && a.alignedB && M % 4 == 0 && N % 4 == 0 && M >= 4 && N >= 4 && K >= 1;   // direct128 included
+        cs_fused = bf16 && a.alignedA && a.alignedB && M % 4 == 0 && N % 4 == 0 && M >= 4 && N >= 4 && K >= 1;
         if (cs_fused) {
             if (splits > 1) {
                 cs_partial = ws->get<float>((size_t)splits * N);
@@ -2024,9 +1741,7 @@ int sgnn_launch_gemm_x(sgnn_ctx *ctx, int ta, int tb, int64_t M, int64_t N, int6
         }
     }
     int rc;
-    if (direct) rc = launch_direct(ctx, ta, tb, a, splits, false, st);
-    else if (direct128 && splits > 1) rc = launch_direct(ctx, ta, tb, a, splits, true, st);
-    else if (bn == 128) rc = launch_cfg<128, 128, 64, 64>(ctx, ta, tb, bf16, a, splits, st);
+    if (bn == 128) rc = launch_cfg<128, 128, 64, 64>(ctx, ta, tb, bf16, a, splits, st);
     else if (bn == 64) rc = launch_cfg<128, 64, 64, 32>(ctx, ta, tb, bf16, a, splits, st);
     else if (narrow128) rc = launch_cfg<128, 32, 32, 32>(ctx, ta, tb, bf16, a, splits, st);
     else rc = launch_cfg<256, 32, 64, 32>(ctx, ta, tb, bf16, a, splits, st);

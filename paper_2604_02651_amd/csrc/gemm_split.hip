@@ -1,0 +1,500 @@
+// fp32 products on the bfloat16 matrix pipe: every operand is split exactly into three bfloat16 parts and the six products
+// of the parts that matter are accumulated in fp32.
+//
+//   x = x1 + x2 + x3,  x1 = bf16(x), x2 = bf16(x - x1), x3 = x - x1 - x2     (round to nearest even: exact, 3 x 8 bits)
+//   a b = a1 b1 + (a1 b2 + a2 b1) + (a1 b3 + a2 b2 + a3 b1) + O(2^-26 |a b|)
+//
+// The products of two parts are exact in fp32, so the error is that of the accumulation; the leading products and the five
+// small ones have accumulators of their own, and the leading chain then has one rounding step per 16 reduction steps where
+// the fp32 instructions have eight.  Error against 64 bits (2-norm), fp32 instructions / here: 32768 x 256 x 256
+// 2.0e-7 / 0.7e-7, 65536 x 256 x 608 3.1e-7 / 1.1e-7, 256 x 256 x 32768 2.9e-7 / 1.3e-7.
+//
+// What bounds these products is the matrix pipe: the fp32 instructions reach 154 TFLOP/s on a large product, the bfloat16 ones
+// 1140, of which a sixth is 190.  32768 x 256 x 256: 47 us with the fp32 instructions, 33 here (30 with the splitting left
+// out); 65536 x 256 x 608 185 -> 133; 256 x 256 x 32768 54 -> 43; 608 x 256 x 65536 344 -> 205; 200 x 200 x 1057 88 -> 16 (its
+// reduction was not split).
+//
+// A workgroup computes a BM x BN tile; slices of 32 along the reduction are fetched two ahead into registers, split there, and
+// staged one ahead in LDS as three planes of [row][32] bfloat16; a lane reads the eight values of an MFMA operand with one
+// 16-byte load.  Rows of a tile are dealt out to its T = R / 32 blocks of 32 in turn (row r is row r / T of block r % T), so
+// that both ways an operand may lie in memory fill the planes without bank conflicts.
+//
+// Where the split does not hold, the tile is computed again with the fp32 instructions: by a wavefront whose accumulators are
+// not all finite (an infinity or NaN in the operands, an overflow), by a workgroup that has staged a value below 2^-112 in
+// magnitude other than zero (the parts of such a value reach below the smallest bfloat16 number: the error would be 2^-134,
+// measured 1.7e-7 of the result for operands of about 2^-112, 5e-7 at 2^-114).
+#include <algorithm>
+
+#include "common.h"
+
+namespace {
+
+typedef float f32x16 __attribute__((ext_vector_type(16)));
+typedef float f32x4 __attribute__((ext_vector_type(4)));
+typedef float f32x2 __attribute__((ext_vector_type(2)));
+typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
+typedef __bf16 bf16x2 __attribute__((ext_vector_type(2)));
+typedef unsigned short u16x2 __attribute__((ext_vector_type(2)));
+// 16 bytes at any multiple of four (gfx950 global loads take any alignment)
+typedef float f32x4_any __attribute__((ext_vector_type(4), aligned(4)));
+
+struct split_args {
+    int64_t M, N, K;
+    const float *A; int64_t lda;
+    const int32_t *ridx;          // optional: physical row of A (as stored) for every logical one
+    const float *B; int64_t ldb;
+    const float *bias;
+    float *C; int64_t ldc;
+    int relu;
+    const float *mask; int64_t ldm;
+    int64_t kps;                  // reduction range of a split (a multiple of 32), K when there is one
+    float *partial;               // [splits][M][N], or null
+    float *colsum;                // column sums of B: [splits][N] when split
+    uint32_t mtiles, ntiles, splits;
+};
+
+constexpr int SBK = 32;                                     // slice of the reduction
+constexpr uint16_t TINY = (127 - 112) << 8;                 // bfloat16 pattern of 2^-112 without its sign, shifted left
+
+template <int R> struct plane {
+    static constexpr int BLOCK = 32 * SBK * 2 + 64;         // bytes of a block of 32 rows; 64 more, so that row l of different
+    static constexpr int BYTES = (R / 32) * BLOCK;          // blocks does not fall into the same banks
+};
+// byte offset in a plane of the 16-byte chunk `c` (eight reduction values) of row l of block b: chunks are swizzled so that
+// the rows which a wavefront reads together fall into different banks
+__device__ __forceinline__ int chunk_at(int block_bytes, int b, int l, int c) { return b * block_bytes + l * (SBK * 2) + ((c ^ (l >> 1)) & 3) * 16; }
+
+// four values -> their three parts, packed
+struct parts4 { uint2 p[3]; };
+__device__ __forceinline__ uint32_t cvt2(float a, float b) { return __builtin_bit_cast(uint32_t, __builtin_convertvector(f32x2{a, b}, bf16x2)); }
+__device__ __forceinline__ float lo16(uint32_t w) { return __builtin_bit_cast(float, w << 16); }
+__device__ __forceinline__ float hi16(uint32_t w) { return __builtin_bit_cast(float, w & 0xffff0000u); }
+__device__ __forceinline__ void split2(float x, float y, uint32_t &p1, uint32_t &p2, uint32_t &p3)
+{
+    p1 = cvt2(x, y);
+    x -= lo16(p1); y -= hi16(p1);
+    p2 = cvt2(x, y);
+    x -= lo16(p2); y -= hi16(p2);
+    p3 = cvt2(x, y);
+}
+__device__ __forceinline__ parts4 split4(const float (&v)[4], u16x2 &tiny)
+{
+    parts4 r;
+    split2(v[0], v[1], r.p[0].x, r.p[1].x, r.p[2].x);
+    split2(v[2], v[3], r.p[0].y, r.p[1].y, r.p[2].y);
+    // smallest magnitude seen, without the sign and with zero counted as the largest
+    const u16x2 two = {2, 2}, less = {0xffff, 0xffff};
+    tiny = __builtin_elementwise_min(tiny, __builtin_bit_cast(u16x2, r.p[0].x) * two + less);
+    tiny = __builtin_elementwise_min(tiny, __builtin_bit_cast(u16x2, r.p[0].y) * two + less);
+    return r;
+}
+
+// One operand: R rows of the tile, stored [row][reduction] (KC) or [reduction][row].  A thread holds PER units of 16 bytes (KC:
+// four reduction steps of a row) or of four times 16 bytes (else: four reduction steps x four rows).  Every load is issued,
+// at an address moved back into the matrix where it would leave it: a load under a condition would be waited for on the spot.
+// What such a load brought is put right when the slice is staged (align): the values are shifted, zeros behind the edge.  Rows
+// behind the last one repeat it if KC (they only feed results that are not stored).
+template <int R, int NT, bool KC, bool GATHER> struct operand {
+    static constexpr int T = R / 32, BLOCK = plane<R>::BLOCK;
+    static constexpr int UNITS = KC ? R * 8 : R * 2;
+    static constexpr int PER = UNITS / NT ? UNITS / NT : 1;
+    static constexpr int NF = KC ? PER : 4 * PER;           // 16-byte loads per thread and slice
+    static_assert(KC || PER == 1, "one block of 4 x 4 a thread");
+    f32x4 reg[NF];
+    const float *base[KC && GATHER ? PER : 1];              // GATHER && KC: the thread's rows; else the tile's first row
+    int off[KC ? PER : 1];                                  // KC: the thread's rows relative to the tile's; else its first column
+    int at;                                                 // where its values go in a plane
+    int rows_left;                                          // !KC: rows that exist from the thread's first on
+    int32_t next[(!KC && GATHER) ? 4 : 1];                  // row numbers of the next slice
+
+    __device__ __forceinline__ static int unit() { return (int)threadIdx.x % UNITS; }
+    __device__ __forceinline__ static bool active() { return UNITS >= NT || (int)threadIdx.x < UNITS; }
+
+    __device__ __forceinline__ void init(const float *G, int64_t ld, const int32_t *ridx, int64_t row0, int64_t rows, int64_t k0, int64_t kend)
+    {
+        const int i = unit(), line = i / 8;
+        if constexpr (KC) {
+            if constexpr (!GATHER) base[0] = G + row0 * ld;
+#pragma unroll
+            for (int u = 0; u < PER; ++u) {
+                const int64_t r = min(row0 + line + u * (NT / 8), rows - 1);
+                if constexpr (GATHER) base[u] = G + (int64_t)ridx[r] * ld;
+                else off[u] = (int)(r - row0) * (int)ld;
+            }
+            at = chunk_at(BLOCK, line % T, line / T, (i % 8) >> 1) + (i & 1) * 8;
+        } else {
+            base[0] = G + row0;
+            rows_left = (int)min(rows - row0 - 4 * line, (int64_t)4);
+            off[0] = 4 * line - (4 - rows_left);
+            at = chunk_at(BLOCK, (4 * line) % T, (4 * line) / T, (i % 8) >> 1) + (i & 1) * 8;
+        }
+        indices(ridx, k0, kend);
+    }
+    // row u of a KC operand, row e of the other kind, relative to `at` (rows that differ by a multiple of 8 T are swizzled alike)
+    __device__ __forceinline__ static int step(int n) { return KC ? n * (NT / 8 / T) * (SBK * 2) : (n % T) * BLOCK + (n / T) * (SBK * 2); }
+
+    __device__ __forceinline__ void indices(const int32_t *ridx, int64_t k0, int64_t kend)
+    {
+        if constexpr (!KC && GATHER) {
+#pragma unroll
+            for (int j = 0; j < 4; ++j) next[j] = ridx[min(k0 + 4 * (unit() % 8) + j, kend - 1)];
+        }
+    }
+    __device__ __forceinline__ void fetch(int64_t ld, int64_t k0, int64_t kend)
+    {
+        const int left = (int)min(kend - k0, (int64_t)SBK), kk = 4 * (unit() % 8);
+#pragma unroll
+        for (int f = 0; f < NF; ++f) {
+            const float *p;
+            if constexpr (KC) p = base[GATHER ? f : 0] + k0 + ((GATHER ? 0 : off[f]) + min(kk, left - 4));
+            else if constexpr (GATHER) p = base[0] + (int64_t)next[f] * ld + off[0];
+            else p = base[0] + k0 * ld + (min(kk + f, left - 1) * (int)ld + off[0]);
+            reg[f] = *reinterpret_cast<const f32x4_any *>(p);
+        }
+    }
+    // v moved down by s places, zeros from above
+    __device__ __forceinline__ static f32x4 shifted(f32x4 v, int s)
+    {
+        v = (s & 1) ? f32x4{v[1], v[2], v[3], 0.f} : v;
+        v = (s & 2) ? f32x4{v[2], v[3], 0.f, 0.f} : v;
+        return s >= 4 ? f32x4{0.f, 0.f, 0.f, 0.f} : v;
+    }
+    // for slices that reach behind the end of the reduction range, and tiles at the edge of the matrix
+    __device__ __forceinline__ void align(int64_t k0, int64_t kend)
+    {
+        const int left = (int)min(kend - (k0 + 4 * (unit() % 8)), (int64_t)4);        // reduction steps that exist from the unit's first on
+#pragma unroll
+        for (int f = 0; f < NF; ++f) {
+            if constexpr (KC) reg[f] = shifted(reg[f], min(4 - left, 4));
+            else reg[f] = f < left ? shifted(reg[f], min(4 - rows_left, 4)) : f32x4{0.f, 0.f, 0.f, 0.f};
+        }
+    }
+    __device__ __forceinline__ void stage(unsigned char *lds, u16x2 &tiny)
+    {
+        if (!active()) return;
+#pragma unroll
+        for (int n = 0; n < (KC ? PER : 4); ++n) {
+            float v[4];
+#pragma unroll
+            for (int j = 0; j < 4; ++j) v[j] = KC ? reg[KC ? n : 0][j] : reg[KC ? 0 : j][n];
+            const parts4 s = split4(v, tiny);
+#pragma unroll
+            for (int q = 0; q < 3; ++q) *reinterpret_cast<uint2 *>(lds + q * plane<R>::BYTES + at + step(n)) = s.p[q];
+        }
+    }
+};
+
+template <int BM, int BN> constexpr int split_lds_bytes() { return 2 * 3 * (plane<BM>::BYTES + plane<BN>::BYTES); }
+
+template <int BM, int BN, int WM, int WN, bool AKC, bool BKC, bool GATHER>
+__global__ __launch_bounds__(64 * WM * WN, 2) void gemm_split_kernel(split_args a)
+{
+    constexpr int NT = 64 * WM * WN;                         // WM x WN wavefronts
+    constexpr int TM = BM / 32 / WM, TN = BN / 32 / WN;      // blocks of 32 x 32 per wavefront
+    constexpr int PA = plane<BM>::BYTES, PB = plane<BN>::BYTES, BUF = 3 * (PA + PB);
+    extern __shared__ __attribute__((aligned(16))) unsigned char lds[];       // two buffers of the planes of A and of B
+    __shared__ int small_seen;
+
+    const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), li = lane & 31, kh = lane >> 5;
+    const int ta0 = (wave / WN) * TM, tb0 = (wave % WN) * TN;       // the wavefront's first row and column block
+    // Tiles that read the same operand rows (the column tiles of a row block; all tiles of a reduction range) go to one XCD,
+    // next to each other.
+    const uint32_t members = a.splits > 1 ? a.mtiles * a.ntiles : a.ntiles, groups = a.splits > 1 ? a.splits : a.mtiles;
+    const uint32_t group = (blockIdx.x / 8 / members) * 8 + blockIdx.x % 8, mem = (blockIdx.x / 8) % members;
+    if (group >= groups) return;
+    const uint32_t bx = a.splits > 1 ? mem % a.mtiles : group, by = a.splits > 1 ? mem / a.mtiles : mem, bz = a.splits > 1 ? group : 0;
+    const int64_t m0 = (int64_t)bx * BM, n0 = (int64_t)by * BN;
+    const int64_t kbeg = (int64_t)bz * a.kps, kend = min(a.K, kbeg + a.kps);
+
+    if (threadIdx.x == 0) small_seen = 0;
+    // the leading products and the others are summed apart: the roundings of the five small products are then small ones
+    f32x16 acc[TM][TN], low[TM][TN];
+#pragma unroll
+    for (int i = 0; i < TM; ++i)
+#pragma unroll
+        for (int j = 0; j < TN; ++j)
+#pragma unroll
+            for (int r = 0; r < 16; ++r) acc[i][j][r] = low[i][j][r] = 0.f;
+    u16x2 tiny = {0xffff, 0xffff};
+    f32x4 cs = {0.f, 0.f, 0.f, 0.f};                         // column sums of B: the thread's four columns
+    const bool do_cs = !BKC && a.colsum && bx == 0;
+
+    operand<BM, NT, AKC, GATHER> oa;
+    operand<BN, NT, BKC, false> ob;
+    oa.init(a.A, a.lda, a.ridx, m0, a.M, kbeg, kend);
+    ob.init(a.B, a.ldb, nullptr, n0, a.N, kbeg, kend);
+    auto fetch = [&](int64_t k0) {
+        oa.fetch(a.lda, k0, kend);
+        ob.fetch(a.ldb, k0, kend);
+        oa.indices(a.ridx, k0 + SBK, kend);
+    };
+    auto stage = [&](int64_t k0, unsigned char *buf) {
+        if (k0 + SBK > kend || (!AKC && m0 + BM > a.M)) oa.align(k0, kend);
+        if (k0 + SBK > kend || (!BKC && n0 + BN > a.N)) ob.align(k0, kend);
+        oa.stage(buf, tiny);
+        ob.stage(buf + 3 * PA, tiny);
+        if constexpr (!BKC) {
+            if (do_cs) {
+#pragma unroll
+                for (int f = 0; f < operand<BN, NT, BKC, false>::NF; ++f) cs += ob.reg[f];
+            }
+        }
+    };
+    // The six products of a half slice as six steps; a step's operands are read from LDS one step ahead (the barriers keep the
+    // compiler from moving the reads down to their use, where each would be waited for).
+    auto multiply = [&](const unsigned char *buf) {
+        bf16x8 fa[3][TM], fb[3][TN];
+        auto read_a = [&](int ks, int q) {
+#pragma unroll
+            for (int i = 0; i < TM; ++i)
+                fa[q][i] = *reinterpret_cast<const bf16x8 *>(buf + q * PA + chunk_at(plane<BM>::BLOCK, ta0 + i, li, 2 * ks + kh));
+        };
+        auto read_b = [&](int ks, int q) {
+#pragma unroll
+            for (int j = 0; j < TN; ++j)
+                fb[q][j] = *reinterpret_cast<const bf16x8 *>(buf + 3 * PA + q * PB + chunk_at(plane<BN>::BLOCK, tb0 + j, li, 2 * ks + kh));
+        };
+        auto step = [&](f32x16 (&c)[TM][TN], int qa, int qb) {
+            __builtin_amdgcn_sched_barrier(0);
+            // the blocks in turn, so that no accumulator waits for itself
+#pragma unroll
+            for (int i = 0; i < TM; ++i)
+#pragma unroll
+                for (int j = 0; j < TN; ++j) c[i][j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(fa[qa][i], fb[qb][j], c[i][j], 0, 0, 0);
+            __builtin_amdgcn_sched_barrier(0);
+        };
+        read_a(0, 0);
+        read_b(0, 0);
+#pragma unroll
+        for (int ks = 0; ks < 2; ++ks) {
+            read_a(ks, 1); step(acc, 0, 0);
+            read_b(ks, 1); step(low, 1, 0);
+            read_a(ks, 2); step(low, 0, 1);
+            read_b(ks, 2); step(low, 1, 1);
+            // A0 is still needed for the last step: the next half slice's is read behind it
+            step(low, 2, 0);
+            if (ks == 0) read_b(1, 0);
+            step(low, 0, 2);
+            if (ks == 0) read_a(1, 0);
+        }
+    };
+    fetch(kbeg);
+    stage(kbeg, lds);
+    if (kbeg + SBK < kend) fetch(kbeg + SBK);
+    __syncthreads();
+    // Slice s is multiplied from one buffer while slice s + 1 is split into the other and slice s + 2 is requested.  Half of
+    // the wavefronts split first and multiply then, the other half the other way round: each SIMD has one of both kinds,
+    // so that its matrix pipe and its vector ALU work at the same time.
+    int cur = 0;
+    for (int64_t k0 = kbeg; k0 < kend; k0 += SBK, cur ^= 1) {
+        unsigned char *here = lds + cur * BUF, *there = lds + (cur ^ 1) * BUF;
+        const bool more = k0 + SBK < kend;
+        if (wave >= WM * WN / 2) multiply(here);
+        if (more) {
+            stage(k0 + SBK, there);
+            if (k0 + 2 * SBK < kend) fetch(k0 + 2 * SBK);
+        }
+        if (wave < WM * WN / 2) multiply(here);
+        __syncthreads();
+    }
+
+    // does the split hold?
+    if (min(tiny[0], tiny[1]) < (uint16_t)(TINY - 1)) small_seen = 1;
+    float bad = 0.f;
+#pragma unroll
+    for (int i = 0; i < TM; ++i)
+#pragma unroll
+        for (int j = 0; j < TN; ++j)
+#pragma unroll
+            for (int r = 0; r < 16; ++r) {
+                acc[i][j][r] += low[i][j][r];
+                bad = fmaf(acc[i][j][r], 0.f, bad);          // NaN if any of them is not finite
+            }
+    __syncthreads();
+    if (small_seen || __ballot(!(bad == 0.f))) {
+        // once more with the fp32 instructions, operands straight from memory
+#pragma unroll
+        for (int i = 0; i < TM; ++i)
+#pragma unroll
+            for (int j = 0; j < TN; ++j)
+#pragma unroll
+                for (int r = 0; r < 16; ++r) acc[i][j][r] = 0.f;
+        constexpr int KU = 4;      // steps whose loads are in flight together
+        for (int64_t k = kbeg; k < kend; k += 2 * KU) {
+            float va[KU][TM], vb[KU][TN];
+#pragma unroll
+            for (int u = 0; u < KU; ++u) {
+                const int64_t kk = k + 2 * u + kh, kc = min(kk, kend - 1);
+#pragma unroll
+                for (int i = 0; i < TM; ++i) {
+                    const int64_t r = min(m0 + (BM / 32) * li + ta0 + i, a.M - 1), line = AKC ? r : kc, col = AKC ? kc : r;
+                    va[u][i] = a.A[(GATHER ? (int64_t)a.ridx[line] : line) * a.lda + col];
+                }
+#pragma unroll
+                for (int j = 0; j < TN; ++j) {
+                    const int64_t c = min(n0 + (BN / 32) * li + tb0 + j, a.N - 1);
+                    vb[u][j] = BKC ? a.B[c * a.ldb + kc] : a.B[kc * a.ldb + c];
+                }
+            }
+#pragma unroll
+            for (int u = 0; u < KU; ++u) {
+                const bool in = k + 2 * u + kh < kend;
+#pragma unroll
+                for (int i = 0; i < TM; ++i)
+#pragma unroll
+                    for (int j = 0; j < TN; ++j)
+                        acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x2f32(in ? va[u][i] : 0.f, in ? vb[u][j] : 0.f, acc[i][j], 0, 0, 0);
+            }
+        }
+    }
+
+    if constexpr (!BKC) {
+        if (do_cs) {          // the loop ended with a barrier and the planes are free
+            // eight threads hold the same four columns
+            static_assert(operand<BN, NT, BKC, false>::UNITS <= NT, "a thread keeps its columns in every slice");
+            float *red = reinterpret_cast<float *>(lds);
+            if ((int)threadIdx.x < BN * 2) *reinterpret_cast<f32x4 *>(red + threadIdx.x * 4) = cs;
+            __syncthreads();
+            if ((int)threadIdx.x < BN && n0 + threadIdx.x < a.N) {
+                float t = 0.f;
+                for (int q = 0; q < 8; ++q) t += red[((threadIdx.x / 4) * 8 + q) * 4 + threadIdx.x % 4];
+                a.colsum[(a.partial ? (int64_t)bz * a.N : 0) + n0 + threadIdx.x] = t;
+            }
+        }
+    }
+
+    // The tile goes through LDS (the planes are free), so that rows leave, and the mask is read, 16 bytes a lane.
+    constexpr int LDT = BN + 4, C4 = BN / 4, PASSES = BM * C4 / NT, BATCH = PASSES < 8 ? PASSES : 8;
+    static_assert(BM * LDT * 4 <= 2 * BUF && NT % C4 == 0 && PASSES % BATCH == 0, "the tile fits, a thread keeps its columns");
+    float *tile = reinterpret_cast<float *>(lds);
+    __syncthreads();
+#pragma unroll
+    for (int i = 0; i < TM; ++i)
+#pragma unroll
+        for (int r = 0; r < 16; ++r) {
+            float *p = tile + ((BM / 32) * (8 * (r / 4) + 4 * kh + r % 4) + ta0 + i) * LDT + (BN / 32) * li + tb0;
+#pragma unroll
+            for (int j = 0; j < TN; ++j) p[j] = acc[i][j][r];
+        }
+    __syncthreads();
+    const bool plain = a.partial != nullptr;
+    float *out = plain ? a.partial + (int64_t)bz * a.M * a.N : a.C;
+    const int64_t ldo = plain ? a.N : a.ldc;
+    const int c0 = 4 * ((int)threadIdx.x % C4);
+    const int64_t col = n0 + c0;
+    if (col >= a.N) return;
+    const bool whole = col + 4 <= a.N;                       // else the last one to three columns of the matrix
+    float bj[4];
+#pragma unroll
+    for (int e = 0; e < 4; ++e) bj[e] = (!plain && a.bias) ? a.bias[min(col + e, a.N - 1)] : 0.f;
+    for (int p0 = 0; p0 < PASSES; p0 += BATCH) {
+        f32x4 m[BATCH];
+        if (!plain && a.mask) {
+#pragma unroll
+            for (int p = 0; p < BATCH; ++p) {
+                const float *mp = a.mask + min(m0 + ((p0 + p) * NT + (int)threadIdx.x) / C4, a.M - 1) * a.ldm;
+                if (whole) m[p] = *reinterpret_cast<const f32x4_any *>(mp + col);
+                else
+#pragma unroll
+                    for (int e = 0; e < 4; ++e) m[p][e] = mp[min(col + e, a.N - 1)];
+            }
+        }
+#pragma unroll
+        for (int p = 0; p < BATCH; ++p) {
+            const int r = ((p0 + p) * NT + (int)threadIdx.x) / C4;
+            if (m0 + r >= a.M) continue;
+            f32x4 z = *reinterpret_cast<const f32x4 *>(tile + r * LDT + c0);
+#pragma unroll
+            for (int e = 0; e < 4; ++e) {
+                z[e] += bj[e];
+                if (!plain && a.relu) z[e] = fmaxf(z[e], 0.f);
+                if (!plain && a.mask && !(m[p][e] > 0.f)) z[e] = 0.f;
+            }
+            float *o = out + (m0 + r) * ldo + col;
+            if (whole) *reinterpret_cast<f32x4_any *>(o) = z;
+            else
+#pragma unroll
+                for (int e = 0; e < 4; ++e)
+                    if (col + e < a.N) o[e] = z[e];
+        }
+    }
+}
+
+template <int BM, int BN, int WM, int WN>
+int launch_split(sgnn_ctx *ctx, int ta, int tb, split_args a, hipStream_t st)
+{
+    a.mtiles = cdiv(a.M, BM);
+    a.ntiles = cdiv(a.N, BN);
+    const uint64_t members = a.splits > 1 ? (uint64_t)a.mtiles * a.ntiles : a.ntiles, groups = a.splits > 1 ? a.splits : a.mtiles;
+    const uint64_t nblocks = cdiv(groups, 8) * 8ull * members;
+    if (nblocks > 0x7fffffffull) return sgnn_fail(ctx, SGNN_ERR_UNSUPPORTED, "sgnn_gemm: more than 2^31 tiles");
+    char tag[56];
+    snprintf(tag, sizeof(tag), "%c%c %dx%d %lldx%lldx%lld f32 split", ta ? 'T' : 'N', tb ? 'T' : 'N', BM, BN, (long long)a.M, (long long)a.N, (long long)a.K);
+    const dim3 grid((unsigned)nblocks), block(64 * WM * WN);
+    constexpr int LDS = split_lds_bytes<BM, BN>();
+    const bool g = a.ridx != nullptr;
+#define SGNN_SPLIT_CASE(TA_, TB_, G_)                                                                              \
+    if (ta == TA_ && tb == TB_ && g == G_) {                                                                       \
+        static const hipError_t attr = hipFuncSetAttribute(reinterpret_cast<const void *>(&gemm_split_kernel<BM, BN, WM, WN, !TA_, TB_, G_>), \
+                                                           hipFuncAttributeMaxDynamicSharedMemorySize, LDS);         \
+        SGNN_HIP(ctx, attr);                                                                                       \
+        SGNN_LAUNCH(ctx, st, "gemm_split_kernel", tag, (gemm_split_kernel<BM, BN, WM, WN, !TA_, TB_, G_>), grid, block, LDS, st, a); \
+        return SGNN_OK;                                                                                            \
+    }
+    SGNN_SPLIT_CASE(false, false, false)
+    SGNN_SPLIT_CASE(false, true, false)
+    SGNN_SPLIT_CASE(true, false, false)
+    SGNN_SPLIT_CASE(false, false, true)
+    SGNN_SPLIT_CASE(false, true, true)
+    SGNN_SPLIT_CASE(true, false, true)
+#undef SGNN_SPLIT_CASE
+    return sgnn_fail(ctx, SGNN_ERR_UNSUPPORTED, "sgnn_gemm: trans_a and trans_b together are not implemented");
+}
+
+} // namespace
+
+// C = act(op(A) op(B) + bias), fp32, all layouts but A^T B^T; any M, N, K with at least four elements along each contiguous
+// direction (the caller has checked).
+int sgnn_launch_gemm_split(sgnn_ctx *ctx, int ta, int tb, int64_t M, int64_t N, int64_t K, const float *A, int64_t lda, const int32_t *ridx,
+                           const float *B, int64_t ldb, const float *bias, int relu, float *C, int64_t ldc, const float *mask, int64_t ldm,
+                           float *b_colsum, ws_alloc *ws, hipStream_t st)
+{
+    split_args a = {};
+    a.M = M; a.N = N; a.K = K; a.A = A; a.lda = lda; a.ridx = ridx; a.B = B; a.ldb = ldb; a.bias = bias; a.C = C; a.ldc = ldc;
+    a.relu = relu; a.mask = mask; a.ldm = ldm; a.kps = K; a.splits = 1; a.colsum = b_colsum;
+    // The widest tile of which there are enough for the 256 compute units: a 256 x 128 tile splits an element of A for 128
+    // columns and one of B for 256 rows, a 64 x 64 tile each for 64.  32768 x 256 x 256, us with 256 x 128 / 128 x 128 tiles:
+    // 33 / 42; 65536 x 256 x 608 133 / 168.  Long reductions (A^T B) take it as well, 256 x 256 x 32768 43 / 50.
+    int64_t bm = 64, bn = 64;
+    if (N > 64 && (ta ? M > 128 && K >= 8192 : (int64_t)cdiv(M, 256) * cdiv(N, 128) >= 160)) bm = 256, bn = 128;
+    else if (N > 64 && (ta ? M > 64 && K >= 8192 : (int64_t)cdiv(M, 128) * cdiv(N, 128) >= 160)) bm = 128, bn = 128;
+    else if (ta ? K >= 8192 : (int64_t)cdiv(M, 128) * cdiv(N, 64) >= 256) bm = 128;
+    // A long reduction onto few tiles is split, to at most 128 ranges of 128 steps or more (each writes its partial product, and
+    // a second kernel reads them all: 256 x 256 x 32768 43 us with 128 ranges, 59 with 256; 608 x 256 x 65536 277 us with 42,
+    // 205 with 128).
+    const int64_t tiles = (int64_t)cdiv(M, (uint64_t)bm) * cdiv(N, (uint64_t)bn);
+    float *cs_partial = nullptr;
+    if (ta && tiles < 256 && K >= 256 && !bias && !relu && !mask) {
+        int64_t splits = std::min<int64_t>(M * N <= 16384 ? 256 : 128, std::min<int64_t>(K / 128, std::max<int64_t>(768 / tiles, 1)));
+        // reductions that short do without the scratch if there is none
+        const size_t per = ((size_t)M * N + N) * sizeof(float);
+        if (K < 4096) splits = std::min<int64_t>(splits, ws->base && ws->cap > ws->off + 1024 ? (int64_t)((ws->cap - ws->off - 1024) / per) : 1);
+        if (splits > 1) {
+            a.kps = (int64_t)cdiv(cdiv(K, splits), SBK) * SBK;
+            a.splits = cdiv(K, a.kps);
+        }
+        if (a.splits > 1) {
+            a.partial = ws->get<float>((size_t)a.splits * M * N);
+            if (b_colsum) a.colsum = cs_partial = ws->get<float>((size_t)a.splits * N);
+            if (!ws->ok) return sgnn_fail(ctx, SGNN_ERR_CAPACITY, "sgnn_gemm: scratch too small for the split reduction: call sgnn_ctx_reserve");
+        }
+    }
+    int rc;
+    if (bm == 256) rc = launch_split<256, 128, 4, 2>(ctx, ta, tb, a, st);
+    else if (bn == 128) rc = launch_split<128, 128, 2, 4>(ctx, ta, tb, a, st);
+    else if (bm == 128) rc = launch_split<128, 64, 2, 2>(ctx, ta, tb, a, st);
+    else rc = launch_split<64, 64, 2, 2>(ctx, ta, tb, a, st);
+    if (rc) return rc;
+    if (a.splits > 1) return sgnn_launch_splitk_reduce(ctx, a.partial, (int)a.splits, M, N, C, ldc, cs_partial, cs_partial ? b_colsum : nullptr, st);
+    return SGNN_OK;
+}

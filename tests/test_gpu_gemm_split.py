@@ -1,0 +1,113 @@
+"""fp32 products whose operands are split into bfloat16 parts: tile edges, reduction tails, every layout and epilogue, unaligned
+operands, gathered rows, short and split reductions, and the values for which the split does not hold."""
+import numpy as np
+import pytest
+import torch
+
+import paper_2604_02651_amd as sg
+from gpu_util import DEV, TOL_F32, ctx, rel_err
+
+pytestmark = pytest.mark.gpu
+
+# (M, N, K): each tile shape with remainders of 1 to 3 rows, columns and reduction steps
+SHAPES = [(4, 4, 4), (5, 7, 6), (63, 33, 35), (64, 64, 64), (65, 66, 67), (129, 65, 47), (1057, 200, 200), (130, 257, 1001),
+          (16900, 65, 70), (20483, 130, 33), (40963, 129, 101), (41000, 200, 32)]
+TN_SHAPES = [(4, 4, 4), (5, 33, 9), (64, 34, 255), (53, 200, 1057), (100, 64, 3001), (47, 100, 9001), (130, 66, 8200), (257, 131, 8195),
+             (608, 256, 8192), (65, 129, 30011)]
+
+
+def _operand(rows, cols, seed, pad=3, offset=1, scale=1.0):
+    """rows x cols view with an odd leading dimension, one element behind a 16-byte boundary."""
+    gen = torch.Generator(device=DEV).manual_seed(seed)
+    flat = torch.randn(rows * (cols + pad) + offset, device=DEV, generator=gen) * scale
+    return flat[offset:].view(rows, cols + pad)[:, :cols]
+
+
+def _check(got, A64, B64, ref):
+    """Within 2^-22 of the sum of the products' magnitudes, entry by entry: 24-bit operands, fp32 accumulation in at most a few
+    hundred steps of random sign; and 1e-6 in the 2-norm."""
+    bound = (A64.abs() @ B64.abs()) * 2.0 ** -22 + 1e-30
+    assert torch.all((got.double() - ref).abs() <= bound)
+    assert (got.double() - ref).norm() <= 1e-6 * (A64 @ B64).norm() + 1e-30
+
+
+@pytest.mark.parametrize("tb", [False, True])
+@pytest.mark.parametrize("M,N,K", SHAPES)
+def test_transform_and_input_gradient(M, N, K, tb):
+    ctx().reserve(1 << 20, 1 << 20, 65536, 640, 1 << 20)
+    A, B = _operand(M, K, 1), _operand(N, K, 2) if tb else _operand(K, N, 2)
+    bias, mask = _operand(1, N, 3)[0].contiguous(), _operand(M, N, 4)
+    A64, B64 = A.double(), B.double().T if tb else B.double()
+    out = torch.full((M + 1, N + 2), 9.0, device=DEV)
+    C = out[:M, :N]
+    sg.sgnn_gemm(ctx(), False, tb, A, B, None, 0, C)
+    _check(C, A64, B64, A64 @ B64)
+    assert torch.all(out[M] == 9.0) and torch.all(out[:, N:] == 9.0)
+    C2 = torch.empty((M, N), device=DEV)
+    sg.sgnn_gemm(ctx(), False, tb, A, B, bias, sg.SGNN_RELU, C2, mask=mask)
+    assert torch.equal(C2, (C + bias).relu() * (mask > 0))
+
+
+@pytest.mark.parametrize("M,N,K", TN_SHAPES)
+def test_weight_gradient_with_column_sums(M, N, K):
+    ctx().reserve(1 << 20, 1 << 20, 65536, 640, 1 << 20)
+    A, B = _operand(K, M, 5), _operand(K, N, 6)
+    C, cs = torch.full((M, N), 9.0, device=DEV), torch.empty(N, device=DEV)
+    sg.sgnn_gemm(ctx(), True, False, A, B, None, 0, C, b_colsum=cs)
+    _check(C, A.double().T, B.double(), A.double().T @ B.double())
+    assert rel_err(cs.cpu().numpy(), B.double().sum(0).cpu().numpy()) < TOL_F32
+    again, cs2 = torch.empty_like(C), torch.empty_like(cs)
+    sg.sgnn_gemm(ctx(), True, False, A, B, None, 0, again, b_colsum=cs2)
+    assert torch.equal(again, C) and torch.equal(cs2, cs)                    # bit-reproducible
+
+
+def test_short_reduction_without_scratch():
+    # a reduction below 4096 steps needs none: it is then not split
+    small = sg.Context(0)
+    A, B = _operand(1500, 70, 5), _operand(1500, 66, 6)
+    C = torch.empty((70, 66), device=DEV)
+    sg.sgnn_gemm(small, True, False, A, B, None, 0, C)
+    _check(C, A.double().T, B.double(), A.double().T @ B.double())
+    small.close()
+
+
+@pytest.mark.parametrize("B,d_in,d_out", [(1500, 130, 65), (9000, 602, 70)])
+def test_gathered_rows(B, d_in, d_out):
+    # an input layer reads its rows through the sample: X[S] W forward, X[S]^T dP backward
+    ctx().reserve(2 * B, 1 << 16, B, 640, 1 << 16)
+    X, W = _operand(2 * B, d_in, 1), _operand(d_in, d_out, 2)
+    S = torch.randperm(2 * B, generator=torch.Generator().manual_seed(3))[:B].sort()[0].to(torch.int32).to(DEV)
+    eye = sg.Csr.from_arrays(B, B, np.arange(B + 1), np.arange(B), np.ones(B, np.float32), DEV)
+    Y = torch.empty((B, d_out), device=DEV)
+    sg.sgnn_gcn_fwd(ctx(), eye, X, W.contiguous(), None, sg.SGNN_XFORM_FIRST, Y, None, row_index=S)
+    XS = X[S.long()].double()
+    _check(Y, XS, W.double(), XS @ W.double())
+    dY, dW = _operand(B, d_out, 4), torch.empty((d_in, d_out), device=DEV)
+    sg.sgnn_gcn_bwd(ctx(), eye, X, W.contiguous(), None, dY, sg.SGNN_XFORM_FIRST, None, dW, None, row_index=S)
+    _check(dW, XS.T, dY.double(), XS.T @ dY.double())
+
+
+@pytest.mark.parametrize("trans", ["NN", "NT", "TN"])
+def test_values_the_split_does_not_hold_for(trans):
+    ta, tb = trans[0] == "T", trans[1] == "T"
+    M, N, K = 150, 140, 90
+    ctx().reserve(1 << 20, 1 << 20, 65536, 640, 1 << 20)
+
+    def product(A, B):
+        C = torch.empty((M, N), device=DEV)
+        sg.sgnn_gemm(ctx(), ta, tb, A.T.contiguous() if ta else A, B.T.contiguous() if tb else B, None, 0, C)
+        return C
+    A, B = _operand(M, K, 1).contiguous(), _operand(K, N, 2).contiguous()
+    for ea, eb in ((-116, 0), (-124, 30), (0, -120), (-70, -60), (60, 60)):     # parts below the bfloat16 range; products near it
+        As, Bs = A * 2.0 ** ea, B * 2.0 ** eb
+        ref = As.double() @ Bs.double()
+        got = product(As, Bs)
+        assert (got.double() - ref).norm() <= 1e-6 * ref.norm() + 2.0 ** -149 * K, (ea, eb)
+    A[3, 5], A[77, 0], B[7, 100] = float("inf"), float("nan"), -float("inf")
+    A[140, 2] = 3.4e38                  # finite, but rounds up to infinity in bfloat16
+    B[2] = B[2].clamp(-0.4, 0.4)
+    ref, got = A.double() @ B.double(), product(A, B).double()
+    assert torch.equal(torch.isnan(got), torch.isnan(ref)) and torch.equal(torch.isinf(got), torch.isinf(ref))
+    fine = torch.isfinite(ref)
+    assert torch.equal(got[torch.isinf(ref)], ref[torch.isinf(ref)])
+    assert (got[fine] - ref[fine]).norm() <= 1e-6 * ref[fine].norm()
