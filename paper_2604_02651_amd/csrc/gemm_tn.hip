@@ -1,22 +1,27 @@
-// Weight gradient of a wide mini-batch (Sec. III-C: dW = H_agg^T dZ) with both operands stored as bfloat16:
-//   C [M x N] = A^T B,   A given [K x M], B given [K x N], M, N <= 256, K = the number of sampled vertices (10^5 .. 10^6).
+// Weight gradient of a mini-batch (Sec. III-C: dW = H_agg^T dZ) with both operands stored as bfloat16:
+//   C [M x N] = A^T B,   A given [K x M], B given [K x N], M, N <= 256, K = the number of sampled vertices (10^3 .. 10^6).
 //
 // The product reads 2 K (M + N) bytes and computes 2 K M N flop: with M = N = 256 that is 128 flop per byte, far below
 // the machine's bf16 ridge, so the kernel is built as a stream over K and nothing else:
-//  - a workgroup owns a range of K and the WHOLE M x N result (accumulators in registers: 8 wavefronts, each a
-//    128 x 64 part as 4 x 2 MFMA tiles of 32 x 32), so every row of A and of B is fetched from HBM once, by one workgroup;
-//  - 32 consecutive rows of A (and of B) are one contiguous block of memory, copied as it is into LDS with direct
-//    global -> LDS loads (16 bytes a lane, no registers in between), four slices deep: three slices are in flight
-//    behind the one being multiplied, one barrier per slice;
-//  - v_mfma_f32_32x32x16_bf16 wants, per lane, eight consecutive reduction steps of ONE column of A, which in this
-//    storage are eight rows apart.  A lane reads four adjacent columns of one row at a time (8 bytes; two for B) and
-//    the wavefront's tiles are interleaved - tile i takes columns 4 l + i - so the eight reads of a 16-step block serve
-//    all four tiles, and a v_perm puts two reduction steps into one operand register;
+//  - a workgroup takes slices of 32 rows and holds the WHOLE M x N result in registers (eight wavefronts), so every row of A
+//    and of B is fetched from HBM once, by one workgroup;
+//  - a slice goes into LDS with direct global -> LDS loads (16 bytes a lane, no registers in between), four slices deep: three
+//    are in flight behind the one being multiplied, one barrier per slice;
+//  - v_mfma_f32_32x32x16_bf16 wants, per lane, eight consecutive reduction steps of one column, which in this storage are eight
+//    rows apart: the transposing LDS reads (ds_read_b64_tr_b16: sixteen lanes read 4 rows x 16 columns and each gets the four
+//    values of one column) deliver them two registers at a time.  With ordinary reads, two thirds of the instructions
+//    of the loop were reads and byte permutes, and those, not memory, set its pace;
+//  - a row of a slice takes a frame of FA (FB) elements in LDS whatever the leading dimension is, and its 16-byte chunks are
+//    swizzled by the row, so that the four rows which such a read takes together lie in different banks.  The direct loads write
+//    LDS in lane order, so the swizzle is in the global address a lane loads from;
 //  - the column sums of B (the bias gradient that rides along) come from the matrix pipe too: one more MFMA per B
 //    tile with an A operand that is 1 in result row 0 and 0 elsewhere;
 //  - every workgroup writes one partial product; they are added in a fixed order by the split reduction of gemm.hip.
-// Columns of the 256 x 256 frame beyond M or N read whatever follows in LDS (finite or not): they only feed result
-// rows and columns that are never stored.
+// Rows behind the last one of a ragged K repeat it in LDS and are zeroed in registers.  Columns of the frame beyond M or N repeat
+// the row's last chunk: they only feed result rows and columns that are never stored.
+// Measured with the reduction of the partial products (us, ordinary reads and permutes / here): 256 x 256 x 2^20 313 / 289, of which
+// the stream is 272 = 3.95 TB/s, what a plain read of 1 GiB reaches on the card; 256 x 47 x 2^18 62 / 46; and where the K or the
+// width was outside the earlier form: 200 x 193 x 56399 183 / 40, 256 x 256 x 999 37 / 14, 30 x 256 x 300007 565 / 47.
 #include <algorithm>
 
 #include "common.h"
@@ -25,14 +30,12 @@ namespace {
 
 typedef float f32x16 __attribute__((ext_vector_type(16)));
 typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
+typedef short i16x4 __attribute__((ext_vector_type(4)));
 typedef unsigned short u16;
 
 constexpr int TNS_BK = 32;          // rows of a slice
 constexpr int TNS_STAGES = 4;
 constexpr int TNS_WAVES = 8;
-constexpr int TNS_LOADS = 4;        // wave-loads (1 KB each) a wavefront issues per slice: 8 x 4 KB = 32 KB >= 32 x (256 + 256) x 2
-constexpr int TNS_STAGE_BYTES = TNS_BK * 512 * 2;                 // room for 32 rows of up to 256 + 256 elements
-constexpr int TNS_SLACK = 4096;     // head-room behind the last stage (reads of the frame's unused columns end exactly at a stage's end when ld = 256)
 
 #define TNS_GPTR(p) ((const __attribute__((address_space(1))) void *)(p))
 #define TNS_LPTR(p) ((__attribute__((address_space(3))) void *)(p))
@@ -43,150 +46,171 @@ struct tns_args {
     const u16 *A; int64_t lda;      // [K x M] bfloat16, lda a multiple of 8
     const u16 *B; int64_t ldb;      // [K x N] bfloat16, ldb a multiple of 8
     int M, N;
-    int64_t K, k_per_split;         // multiples of 32
+    int64_t K;
     float *partial;                 // [splits][M][N]
     float *cs_partial;              // [splits][N] or NULL
-    int interleave;
 };
 
+// frame of an operand: F elements a row, F / 8 chunks of 16 bytes.  Chunks are swizzled in groups of four (the 32 columns of a
+// tile) by the row: rows 0 to 3 of any four take different 64 bytes of the 256 that the banks span.
+template <int F> struct frame {
+    static constexpr int CHUNKS = F / 8, BYTES = TNS_BK * F * 2;
+    static __device__ __forceinline__ int swizzle(int row) { return F >= 128 ? 4 * (row & 3) : 4 * ((row >> 1) & 1); }
+};
+
+template <int FA, int FB> constexpr int tns_stage_bytes() { return frame<FA>::BYTES + frame<FB>::BYTES; }
+
+// the four values along the reduction of the lane's column (see above); p: where the lane reads its 8 bytes
+__device__ __forceinline__ uint2 read_tr(const unsigned char *p)
+{
+    return __builtin_bit_cast(uint2, __builtin_amdgcn_ds_read_tr16_b64_v4i16((__attribute__((address_space(3))) i16x4 *)(p)));
+}
+
+// WM x WN wavefronts share the frame's FA x FB result
+template <int FA, int FB, int WM, int WN>
 __global__ __launch_bounds__(64 * TNS_WAVES) void gemm_tn_stream_kernel(tns_args a)
 {
+    constexpr int TM = FA / 32 / WM, TN = FB / 32 / WN;
+    constexpr int STAGE = tns_stage_bytes<FA, FB>(), LOADS = (STAGE / 1024 + TNS_WAVES - 1) / TNS_WAVES;
+    constexpr int CA = frame<FA>::CHUNKS, CB = frame<FB>::CHUNKS;
     extern __shared__ __attribute__((aligned(16))) unsigned char tns_smem[];
-    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+    const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const int li = lane & 31, kh = lane >> 5;
-    const int wm0 = (wave >> 2) * 128, wn0 = (wave & 3) * 64;
-    // interleave: workgroup w takes slices w, w + splits, ... (the workgroups read one region together, as a copy kernel
-    // does); else a contiguous range of k_per_split rows
-    const int64_t kbeg = a.interleave ? (int64_t)blockIdx.x * TNS_BK : (int64_t)blockIdx.x * a.k_per_split;
-    const int64_t kend = min(a.K, kbeg + a.k_per_split);
-    const int64_t kstep = a.interleave ? (int64_t)gridDim.x * TNS_BK : TNS_BK;
-    const int64_t total_slices = a.K / TNS_BK;
-    const int nslices = a.interleave ? (int)((total_slices - blockIdx.x + gridDim.x - 1) / gridDim.x) : (int)((kend - kbeg) / TNS_BK);
-    // one slice in LDS: the 32 rows of A as in memory (32 lda elements), then the 32 rows of B
-    const int a_bytes = (int)(64 * a.lda), b_bytes = (int)(64 * a.ldb);     // 32 rows x ld x 2 bytes
-    const int a_chunks = a_bytes / 16, chunks = (a_bytes + b_bytes) / 16;
-    // the last row of a matrix need not be allocated beyond its last element: chunks of a block that hold nothing but the
-    // padding behind the block's last row are not fetched (the chunk with the row's last element is fetched in their place)
-    const int a_valid = (int)((2 * (31 * a.lda + a.M) + 15) / 16), b_valid = (int)((2 * (31 * a.ldb + a.N) + 15) / 16);
+    // workgroup w takes slices w, w + grid, ...: the workgroups read one region together, as a copy kernel does
+    const int64_t total = (a.K + TNS_BK - 1) / TNS_BK;
+    const int nslices = (int)((total - blockIdx.x + gridDim.x - 1) / gridDim.x);
 
-    // the wavefront's TNS_LOADS wave-loads of a slice: chunk (wave + 8 j) 64 + lane of [A block | B block]; a chunk past
-    // the end repeats the last one (the same bytes to the same place), so that every wavefront has the same number of
-    // loads in flight and the waits below count exactly
+    // the wavefront's wave-loads of a slice: load j fills KB wave + 8 j of the stage.  A lane's row and byte offset from the
+    // slice's first row; a wavefront without a load repeats the last one (same bytes, same place), so that every wavefront has the
+    // same number in flight and the waits below count exactly
+    int row[LOADS], off[LOADS];
+    bool of_b[LOADS];
+#pragma unroll
+    for (int j = 0; j < LOADS; ++j) {
+        const int pos = min(wave + TNS_WAVES * j, STAGE / 1024 - 1) * 64 + lane;
+        of_b[j] = pos >= TNS_BK * CA;
+        const int p = of_b[j] ? pos - TNS_BK * CA : pos, ch = of_b[j] ? CB : CA;
+        row[j] = p / ch;
+        const int c = (p % ch) ^ (of_b[j] ? frame<FB>::swizzle(row[j]) : frame<FA>::swizzle(row[j]));
+        off[j] = 16 * min(c, ((of_b[j] ? a.N : a.M) - 1) / 8);
+    }
     auto issue = [&](int s) {
         const int sl = min(s, nslices - 1);          // past the end: the last slice again, into a stage nobody reads
-        unsigned char *stage = tns_smem + (s % TNS_STAGES) * TNS_STAGE_BYTES;
-        const unsigned char *ga = reinterpret_cast<const unsigned char *>(a.A + (kbeg + (int64_t)sl * kstep) * a.lda);
-        const unsigned char *gb = reinterpret_cast<const unsigned char *>(a.B + (kbeg + (int64_t)sl * kstep) * a.ldb);
+        unsigned char *stage = tns_smem + (s % TNS_STAGES) * STAGE;
+        const int64_t k0 = ((int64_t)sl * gridDim.x + blockIdx.x) * TNS_BK;
+        const int last = (int)min(a.K - k0, (int64_t)TNS_BK) - 1;
 #pragma unroll
-        for (int j = 0; j < TNS_LOADS; ++j) {
-            const int q = wave + TNS_WAVES * j;
-            const int c = min(64 * q + lane, chunks - 1);
-            const unsigned char *g = c < a_chunks ? ga + 16 * min(c, a_valid - 1) : gb + 16 * min(c - a_chunks, b_valid - 1);
-            // the LDS address of a direct load is wave-uniform base + 16 lane: chunk 64 q + lane lands at 16 (64 q + lane),
-            // the clamped lanes' copies of the last chunk behind the slice's data, still inside the 32 KB of the stage
-            __builtin_amdgcn_global_load_lds(TNS_GPTR(g), TNS_LPTR(stage + 1024 * q), 16, 0, 0);
+        for (int j = 0; j < LOADS; ++j) {
+            const int64_t r = k0 + min(row[j], last);
+            const unsigned char *g = (of_b[j] ? reinterpret_cast<const unsigned char *>(a.B + r * a.ldb) : reinterpret_cast<const unsigned char *>(a.A + r * a.lda)) + off[j];
+            __builtin_amdgcn_global_load_lds(TNS_GPTR(g), TNS_LPTR(stage + 1024 * min(wave + TNS_WAVES * j, STAGE / 1024 - 1)), 16, 0, 0);
         }
     };
 
-    f32x16 acc[4][2], cs[2];
+    const int wm = wave / WN, wn = wave % WN;
+    f32x16 acc[TM][TN], cs[TN];
 #pragma unroll
-    for (int r = 0; r < 16; ++r) {
+    for (int r = 0; r < 16; ++r)
 #pragma unroll
-        for (int i = 0; i < 4; ++i) { acc[i][0][r] = 0.f; acc[i][1][r] = 0.f; }
-        cs[0][r] = 0.f; cs[1][r] = 0.f;
-    }
+        for (int j = 0; j < TN; ++j) {
+#pragma unroll
+            for (int i = 0; i < TM; ++i) acc[i][j][r] = 0.f;
+            cs[j][r] = 0.f;
+        }
     // A operand of the column sums: 1.0 for result row 0 (lanes with li == 0), 0 elsewhere
     bf16x8 ones;
 #pragma unroll
     for (int t = 0; t < 8; ++t) ones[t] = (__bf16)(li == 0 ? 1.0f : 0.0f);
-    const bool wave_live = wm0 < a.M && wn0 < a.N;       // its part of the frame holds something of the result
-    const bool do_cs = a.cs_partial && wm0 == 0 && wn0 < a.N;
+    const bool live = wm < WM && wm * TM * 32 < a.M && wn * TN * 32 < a.N;       // its part of the frame holds something of the result
+    const bool do_cs = a.cs_partial && wm == 0 && wn * TN * 32 < a.N;
+
+    // where a lane reads: of the sixteen lanes that read together, lane x takes columns 4 (x % 4) .. of row x / 4
+    const int x = lane & 15, r3 = x >> 2, half = (lane >> 4) & 1;
+    int at_a[TM], at_b[TN];
+#pragma unroll
+    for (int i = 0; i < TM; ++i)
+        at_a[i] = (8 * kh + r3) * FA * 2 + (((wm * TM + i) * 4 + 2 * half + ((x & 3) >> 1)) ^ frame<FA>::swizzle(r3)) * 16 + (x & 1) * 8;
+#pragma unroll
+    for (int j = 0; j < TN; ++j)
+        at_b[j] = frame<FA>::BYTES + (8 * kh + r3) * FB * 2 + (((wn * TN + j) * 4 + 2 * half + ((x & 3) >> 1)) ^ frame<FB>::swizzle(r3)) * 16 + (x & 1) * 8;
 
     issue(0);
     issue(1);
     issue(2);
     for (int s = 0; s < nslices; ++s) {
-        TNS_WAIT_VMCNT(2 * TNS_LOADS);           // slice s has landed (this wavefront's part); s + 1 and s + 2 may be in flight
+        TNS_WAIT_VMCNT(2 * LOADS);               // slice s has landed (this wavefront's part); s + 1 and s + 2 may be in flight
         asm volatile("" ::: "memory");
         __builtin_amdgcn_s_barrier();            // everybody's part has; and everybody is through slice s - 1
         asm volatile("" ::: "memory");
         issue(s + 3);                            // into the stage slice s - 1 was read from
-        if (wave_live) {
-            const unsigned char *stage = tns_smem + (s % TNS_STAGES) * TNS_STAGE_BYTES;
-            const unsigned char *LA = stage + 2 * (wm0 + 4 * li);
-            const unsigned char *LB = stage + a_bytes + 2 * (wn0 + 2 * li);
-            const int rowA = (int)(2 * a.lda), rowB = (int)(2 * a.ldb);
+        if (live) {
+            const unsigned char *stage = tns_smem + (s % TNS_STAGES) * STAGE;
+            const int rows = (int)min(a.K - ((int64_t)s * gridDim.x + blockIdx.x) * TNS_BK, (int64_t)TNS_BK);
 #pragma unroll
             for (int h = 0; h < 2; ++h) {          // the two 16-step blocks of the slice
-                uint2 ra[8];
-                uint32_t rb[8];
+                uint2 fa[TM][2], fb[TN][2];
 #pragma unroll
-                for (int t = 0; t < 8; ++t) {
-                    const int k = 16 * h + 8 * kh + t;
-                    ra[t] = *reinterpret_cast<const uint2 *>(LA + k * rowA);
-                    rb[t] = *reinterpret_cast<const uint32_t *>(LB + k * rowB);
+                for (int t = 0; t < 2; ++t) {
+#pragma unroll
+                    for (int j = 0; j < TN; ++j) fb[j][t] = read_tr(stage + at_b[j] + (16 * h + 4 * t) * FB * 2);
+#pragma unroll
+                    for (int i = 0; i < TM; ++i) fa[i][t] = read_tr(stage + at_a[i] + (16 * h + 4 * t) * FA * 2);
                 }
-                // tile i of A: column 4 li + i = half (i & 1) of word (i >> 1) of every read; two steps a register
-                bf16x8 fa[4], fb[2];
+                if (rows < TNS_BK) {               // the last slice of a ragged K: steps behind the last row count as zeros
 #pragma unroll
-                for (int i = 0; i < 4; ++i) {
-                    uint32_t w[4];
+                    for (int t = 0; t < 2; ++t) {
+                        const int left = rows - (16 * h + 8 * kh + 4 * t);
+                        const uint32_t m0 = left >= 2 ? 0xffffffffu : (left == 1 ? 0xffffu : 0u), m1 = left >= 4 ? 0xffffffffu : (left == 3 ? 0xffffu : 0u);
 #pragma unroll
-                    for (int p = 0; p < 4; ++p) {
-                        const uint32_t x0 = (i >> 1) ? ra[2 * p].y : ra[2 * p].x, x1 = (i >> 1) ? ra[2 * p + 1].y : ra[2 * p + 1].x;
-                        // bytes of the result, low to high: the chosen half of x0, then the chosen half of x1
-                        w[p] = (i & 1) ? __builtin_amdgcn_perm(x1, x0, 0x07060302u) : __builtin_amdgcn_perm(x1, x0, 0x05040100u);
+                        for (int j = 0; j < TN; ++j) { fb[j][t].x &= m0; fb[j][t].y &= m1; }
+#pragma unroll
+                        for (int i = 0; i < TM; ++i) { fa[i][t].x &= m0; fa[i][t].y &= m1; }
                     }
-                    fa[i] = __builtin_bit_cast(bf16x8, *reinterpret_cast<const uint4 *>(w));
                 }
+                auto operand = [](const uint2 (&f)[2]) { return __builtin_bit_cast(bf16x8, make_uint4(f[0].x, f[0].y, f[1].x, f[1].y)); };
 #pragma unroll
-                for (int j = 0; j < 2; ++j) {
-                    uint32_t w[4];
+                for (int i = 0; i < TM; ++i)
 #pragma unroll
-                    for (int p = 0; p < 4; ++p)
-                        w[p] = j ? __builtin_amdgcn_perm(rb[2 * p + 1], rb[2 * p], 0x07060302u)
-                                 : __builtin_amdgcn_perm(rb[2 * p + 1], rb[2 * p], 0x05040100u);
-                    fb[j] = __builtin_bit_cast(bf16x8, *reinterpret_cast<const uint4 *>(w));
-                }
-#pragma unroll
-                for (int i = 0; i < 4; ++i)
-#pragma unroll
-                    for (int j = 0; j < 2; ++j) acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(fa[i], fb[j], acc[i][j], 0, 0, 0);
+                    for (int j = 0; j < TN; ++j)
+                        acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(operand(fa[i]), operand(fb[j]), acc[i][j], 0, 0, 0);
                 if (do_cs) {
 #pragma unroll
-                    for (int j = 0; j < 2; ++j) cs[j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(ones, fb[j], cs[j], 0, 0, 0);
+                    for (int j = 0; j < TN; ++j) cs[j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(ones, operand(fb[j]), cs[j], 0, 0, 0);
                 }
             }
         }
     }
     TNS_WAIT_VMCNT(0);       // the repeated loads past the end are still in flight: nothing may leave before they land
 
-    // result: register r of lane (li, kh) of tile (i, j) is row wm0 + 4 rho + i, rho = 8 (r / 4) + 4 kh + r % 4,
-    // column wn0 + 2 li + j: the lane's two tiles j are adjacent columns, one 8-byte store
-    if (wave_live) {
+    // register r of lane (li, kh) of tile (i, j) is row 32 i + 8 (r / 4) + 4 kh + r % 4, column 32 j + li of the wavefront's part
+    if (live) {
         float *P = a.partial + (int64_t)blockIdx.x * a.M * a.N;
-        const int n = wn0 + 2 * li;
-        const bool n_even = (a.N & 1) == 0;   // odd N: rows of the partial result start on odd words, one store per value
 #pragma unroll
-        for (int i = 0; i < 4; ++i)
+        for (int j = 0; j < TN; ++j) {
+            const int n = (wn * TN + j) * 32 + li;
+            if (n >= a.N) continue;
 #pragma unroll
-            for (int r = 0; r < 16; ++r) {
-                const int m = wm0 + 4 * (8 * (r / 4) + 4 * kh + (r % 4)) + i;
-                if (m < a.M && n < a.N) {
-                    float *p = P + (int64_t)m * a.N + n;
-                    if (n_even) *reinterpret_cast<float2 *>(p) = make_float2(acc[i][0][r], acc[i][1][r]);   // wholly inside
-                    else {
-                        p[0] = acc[i][0][r];
-                        if (n + 1 < a.N) p[1] = acc[i][1][r];
-                    }
+            for (int i = 0; i < TM; ++i)
+#pragma unroll
+                for (int r = 0; r < 16; ++r) {
+                    const int m = (wm * TM + i) * 32 + 8 * (r / 4) + 4 * kh + r % 4;
+                    if (m < a.M) P[(int64_t)m * a.N + n] = acc[i][j][r];
                 }
-            }
-        if (do_cs && kh == 0 && n < a.N) {           // result row 0: register 0 of the lanes with kh == 0
-            float *p = a.cs_partial + (int64_t)blockIdx.x * a.N + n;
-            p[0] = cs[0][0];
-            if (n + 1 < a.N) p[1] = cs[1][0];
+            if (do_cs && kh == 0) a.cs_partial[(int64_t)blockIdx.x * a.N + n] = cs[j][0];      // result row 0
         }
     }
+}
+
+template <int FA, int FB, int WM, int WN> int launch_tns(sgnn_ctx *ctx, const tns_args &a, unsigned grid, hipStream_t st)
+{
+    constexpr int lds = TNS_STAGES * tns_stage_bytes<FA, FB>();
+    static const hipError_t attr = hipFuncSetAttribute(reinterpret_cast<const void *>(&gemm_tn_stream_kernel<FA, FB, WM, WN>),
+                                                       hipFuncAttributeMaxDynamicSharedMemorySize, lds);
+    SGNN_HIP(ctx, attr);
+    char tag[56];
+    snprintf(tag, sizeof(tag), "TN stream %dx%dx%lld bf16 a=2 b=2", a.M, a.N, (long long)a.K);
+    SGNN_LAUNCH(ctx, st, "gemm_tn_stream_kernel", tag, (gemm_tn_stream_kernel<FA, FB, WM, WN>), dim3(grid), dim3(64 * TNS_WAVES), lds, st, a);
+    return SGNN_OK;
 }
 
 } // namespace
@@ -196,31 +220,33 @@ __global__ __launch_bounds__(64 * TNS_WAVES) void gemm_tn_stream_kernel(tns_args
 int sgnn_launch_gemm_tn_stream(sgnn_ctx *ctx, int64_t M, int64_t N, int64_t K, const void *A, int64_t lda, const void *B, int64_t ldb,
                                float *C, int64_t ldc, float *b_colsum, ws_alloc *ws, hipStream_t st)
 {
-    if (M < 1 || N < 2 || M > 256 || N > 256 || K < 8192 || K % TNS_BK || lda % 8 || ldb % 8 || lda > 256 || ldb > 256 ||
-        lda < M || ldb < N || (reinterpret_cast<uintptr_t>(A) & 15) || (reinterpret_cast<uintptr_t>(B) & 15))
+    if (M < 1 || N < 1 || M > 256 || N > 256 || K < 64 || lda % 8 || ldb % 8 || lda < M || ldb < N ||
+        (reinterpret_cast<uintptr_t>(A) & 15) || (reinterpret_cast<uintptr_t>(B) & 15))
         return SGNN_ERR_UNSUPPORTED;
-    // one workgroup a compute unit; every workgroup at least 16 slices
-    int64_t splits = std::min<int64_t>(256, K / (16 * TNS_BK));
-    int64_t kps = (K / splits + TNS_BK - 1) / TNS_BK * TNS_BK;
-    splits = (K + kps - 1) / kps;
-    tns_args a;
-    a.A = static_cast<const u16 *>(A); a.lda = lda; a.B = static_cast<const u16 *>(B); a.ldb = ldb;
-    a.M = (int)M; a.N = (int)N; a.K = K; a.k_per_split = kps;
-    a.interleave = 1;       // measured 4-6 % faster at K = 2^20 than contiguous ranges (256 separate streams through memory)
+    // As many workgroups as make the partial products (written and read: 8 M N bytes each) about as much traffic as the operands,
+    // no fewer than one for every four slices up to 64, at most one a compute unit.
+    const int64_t slices = cdiv(K, TNS_BK);
+    int64_t splits = std::max<int64_t>(K * (M + N) / (4 * M * N), std::min<int64_t>(slices / 4, 64));
+    splits = std::max<int64_t>(1, std::min<int64_t>(splits, std::min<int64_t>(slices, 256)));
     // not enough scratch for one partial product per workgroup: the tile kernel needs less
     const size_t need = (((size_t)splits * M * N * 4 + 255) & ~size_t(255)) + (((size_t)splits * N * 4 + 255) & ~size_t(255));
     if (!ws->base || ws->off + need > ws->cap) return SGNN_ERR_UNSUPPORTED;
+    tns_args a;
+    a.A = static_cast<const u16 *>(A); a.lda = lda; a.B = static_cast<const u16 *>(B); a.ldb = ldb;
+    a.M = (int)M; a.N = (int)N; a.K = K;
     a.partial = ws->get<float>((size_t)splits * M * N);
     a.cs_partial = b_colsum ? ws->get<float>((size_t)splits * N) : nullptr;
-    const size_t lds = (size_t)TNS_STAGES * TNS_STAGE_BYTES + TNS_SLACK;
-    static bool attr_set = false;
-    if (!attr_set) {
-        SGNN_HIP(ctx, hipFuncSetAttribute(reinterpret_cast<const void *>(&gemm_tn_stream_kernel),
-                                          hipFuncAttributeMaxDynamicSharedMemorySize, 160 * 1024));
-        attr_set = true;
-    }
-    char tag[56];
-    snprintf(tag, sizeof(tag), "TN stream %lldx%lldx%lld bf16 a=2 b=2", (long long)M, (long long)N, (long long)K);
-    SGNN_LAUNCH(ctx, st, "gemm_tn_stream_kernel", tag, gemm_tn_stream_kernel, dim3((unsigned)splits), dim3(64 * TNS_WAVES), lds, st, a);
+    const int fa = M > 128 ? 256 : (M > 64 ? 128 : 64), fb = N > 128 ? 256 : (N > 64 ? 128 : 64);
+    int rc = SGNN_ERR_UNSUPPORTED;
+    if (fa == 256 && fb == 256) rc = launch_tns<256, 256, 2, 4>(ctx, a, (unsigned)splits, st);
+    else if (fa == 256 && fb == 128) rc = launch_tns<256, 128, 4, 2>(ctx, a, (unsigned)splits, st);
+    else if (fa == 256) rc = launch_tns<256, 64, 4, 2>(ctx, a, (unsigned)splits, st);
+    else if (fa == 128 && fb == 256) rc = launch_tns<128, 256, 2, 4>(ctx, a, (unsigned)splits, st);
+    else if (fa == 128 && fb == 128) rc = launch_tns<128, 128, 2, 4>(ctx, a, (unsigned)splits, st);
+    else if (fa == 128) rc = launch_tns<128, 64, 4, 2>(ctx, a, (unsigned)splits, st);
+    else if (fb == 256) rc = launch_tns<64, 256, 2, 4>(ctx, a, (unsigned)splits, st);
+    else if (fb == 128) rc = launch_tns<64, 128, 2, 4>(ctx, a, (unsigned)splits, st);
+    else rc = launch_tns<64, 64, 2, 2>(ctx, a, (unsigned)splits, st);
+    if (rc) return rc;
     return sgnn_launch_splitk_reduce(ctx, a.partial, (int)splits, M, N, C, ldc, a.cs_partial, b_colsum, st);
 }
