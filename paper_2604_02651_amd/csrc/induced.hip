@@ -15,8 +15,8 @@
 //   4. prefix sum              survivors in earlier tiles, for every tile
 //   5. induced_fill_kernel     survivors only (keep words of pass 3): ordered compaction, colidx, val, rowptr
 //   6. induced_renorm_kernel   only for norm_mode 1: weights from the degrees of the induced graph
-// A tile stages the starts of the rows it touches in LDS, so finding the row of an edge is a
-// binary search in LDS, and the whole tile needs one barrier for its ordered compaction.
+// A tile marks the starts of the rows it touches in a bit mask of its 2048 edges in LDS, so finding the row of an
+// edge is a count of bits (tile_table).
 #include <algorithm>
 
 #include "block_prims.h"
@@ -28,10 +28,12 @@ constexpr int IND_NT = 256;
 constexpr int IND_ITEMS = 8;
 constexpr int IND_TILE = IND_NT * IND_ITEMS;      // 2048 flat edges per workgroup (4096 and 8192 with 512 threads measured slower)
 constexpr int IND_WORDS = IND_ITEMS * (IND_NT / 64);   // 64-bit keep words of a tile: one per slab and wavefront
-constexpr int IND_ROWS = 512;                     // rows a tile's LDS table holds (more only when rows average under 4 edges): 6 KB, so LDS does not limit occupancy
-#ifndef IND_FILL_SLOTS
-#define IND_FILL_SLOTS 2                          // survivors a thread of the fill pass works on at a time
-#endif
+// Rows a tile's LDS table holds, less one (more only when rows average under two edges).  9 KB in the count pass, 19 KB in
+// the fill pass: LDS does not limit occupancy.  With 512 about half of the tiles of a graph with six edges a row, most of
+// them far fewer, went to the searches in global memory: 10^6 rows of 4 10^7, count pass 91 us against 53, fill pass 44
+// against 36; with 2048 the fill pass loses occupancy and nothing is gained.
+constexpr int IND_ROWS = 1024;
+constexpr int IND_FILL_SLOTS = 2;                 // survivors a thread of the fill pass works on at a time (4 spill: 35 -> 62 us)
 constexpr unsigned IND_MAX_GRID = 8192;
 constexpr int DEG_TILE = 2048;                    // sampled rows per workgroup in the offset kernels
 
@@ -47,16 +49,22 @@ __global__ __launch_bounds__(256) void induced_deg_kernel(const RP *__restrict__
     __shared__ uint64_t lds[256 / 64];
     if (blockIdx.x == 0 && threadIdx.x == 0) *total64 = 0ull;     // survivors of the whole mini-batch, summed by the count pass
     uint64_t s = 0;
+    // every load unconditional (a thread behind the last row repeats it), so that a thread's eight pairs of gathers are in
+    // flight together: 2^18 rows of 2.4 M vertices 9 -> 7 us (10^6 rows of 4 10^7 stay at 27: a memory line for every row)
+    int32_t v[DEG_TILE / 256];
+    int64_t rs[DEG_TILE / 256], re[DEG_TILE / 256];
+#pragma unroll
+    for (int k = 0; k < DEG_TILE / 256; ++k) v[k] = S[min(blockIdx.x * DEG_TILE + k * 256 + threadIdx.x, B - 1)];
+#pragma unroll
+    for (int k = 0; k < DEG_TILE / 256; ++k) { rs[k] = (int64_t)rowptr[v[k]]; re[k] = (int64_t)rowptr[(int64_t)v[k] + 1]; }
 #pragma unroll
     for (int k = 0; k < DEG_TILE / 256; ++k) {
         const uint32_t i = blockIdx.x * DEG_TILE + k * 256 + threadIdx.x;
+        // a sampled row outside the shard's row range contributes no edge: it comes out as an empty row
+        const uint32_t dgr = (v[k] >= rg.r0 && v[k] < rg.r1) ? (uint32_t)(re[k] - rs[k]) : 0u;
         if (i < B) {
-            const int64_t v = S[i];
-            // a sampled row outside the shard's row range contributes no edge: it comes out as an empty row
-            const int64_t rs = (int64_t)rowptr[v];
-            const uint32_t dgr = (v >= rg.r0 && v < rg.r1) ? (uint32_t)((int64_t)rowptr[v + 1] - rs) : 0u;
             deg[i] = dgr;
-            rowstart[i] = rs;      // kept for the tile kernels: no second gather through S
+            rowstart[i] = rs[k];   // kept for the tile kernels: no second gather through S
             s += dgr;
         }
     }
@@ -123,13 +131,21 @@ __device__ __forceinline__ uint32_t find_row(const uint64_t *__restrict__ P, uin
     return lo;
 }
 
-// Per-tile row table in LDS.  Rows r_lo .. r_lo+nr-1 intersect the tile [f0, f1).
-//   relP[k]  = P[r_lo+k] - f0, clamped to -1 when the row starts before the tile
-//   ebase[k] = rowptr[S[r]] - P[r]: the position in colidx of flat edge f of that row is ebase + f
-// staged == false (more rows than the table holds: rows averaging under four edges, or the run of empty
+// Per-tile row table in LDS.  Rows r_lo .. r_lo+nr-1 intersect the tile [f0, f1); those with entries in it are numbered
+// in order, and
+//   start[w]  bit b is set iff such a row starts at offset 64 w + b of the tile (one that starts in front of it: offset 0)
+//   ebase[j]  = rowptr[S[r]] - P[r] for the j-th of them: the position in colidx of flat edge f of that row is ebase + f
+// The row of an edge is the number of start bits at or below its offset, minus one.  A wavefront's 64 edges of a slab lie
+// in one word of `start`, so that is a count under a lane mask of a word and a prefix that are the same for the whole
+// wavefront: no search.  (A binary search of the row starts was ten dependent rounds of LDS reads for each of the eight
+// edges of a thread.)  What bounds the count pass then is the bit test of every edge, 13 M gathers of words that
+// only an L2 holds, at about 250 a nanosecond: 2^18 rows of 2.4 M vertices, 66 -> 53 us (52 MB of column ids);
+// 2^15 rows of 2^18 vertices, 12 -> 8 us.
+// Two copies of `start`, used in turn: one is cleared for the next tile while the other is read.
+// staged == false (more rows than the table holds: rows averaging under two edges, or the run of empty
 // rows behind the last tile of a shard) falls back to searching P in global memory.
 struct tile_table {
-    int32_t relP[IND_ROWS + 1];
+    unsigned long long start[2][IND_WORDS];
     int64_t ebase[IND_ROWS + 1];
 };
 
@@ -144,73 +160,96 @@ __device__ __forceinline__ void tile_rows(const uint32_t *__restrict__ tile_row,
     nr = r_hi - r_lo + 1;
 }
 
-// Staging of a tile's row table.  The first IND_NT rows arrive in registers: (p, rs) of row r_lo + threadIdx.x, requested
-// while the tile before this one was being worked on (tile_prefetch), so that the two round trips that fetch a
-// tile's rows - tile_row, then P / row starts - are off its critical path.
+// Staging of a tile's row table.  The first IND_NT rows arrive in registers: flat offset, first entry and length of row
+// r_lo + threadIdx.x, requested while the tile before this one was being worked on (tile_prefetch), so that the two
+// round trips that fetch a tile's rows - tile_row, then P / row starts / lengths - are off its critical path.
 struct tile_pref {
     uint64_t p;
     int64_t rs;
+    uint32_t d;
 };
 
 __device__ __forceinline__ tile_pref tile_prefetch(const int64_t *__restrict__ rowstart, const uint64_t *__restrict__ P,
-                                                   bool valid, uint32_t r_lo, uint32_t nr)
+                                                   const uint32_t *__restrict__ deg, bool valid, uint32_t r_lo, uint32_t nr)
 {
-    tile_pref t = {0, 0};
+    tile_pref t = {0, 0, 0};
     if (valid && threadIdx.x < nr && nr <= (uint32_t)IND_ROWS + 1) {
         t.p = P[r_lo + threadIdx.x];
         t.rs = rowstart[r_lo + threadIdx.x];
+        t.d = deg[r_lo + threadIdx.x];
     }
     return t;
 }
 
-__device__ __forceinline__ bool stage_tile_prefetched(tile_table &tt, const tile_pref &pf, const int64_t *__restrict__ rowstart,
-                                                      const uint64_t *__restrict__ P, uint64_t f0, uint32_t r_lo, uint32_t nr)
+// Row starts of the tile as seen by a wavefront: lane w < IND_WORDS holds word w of `start` and the number of bits in
+// the words before it.
+struct tile_starts {
+    uint64_t word;
+    uint32_t pre;
+};
+
+// number of the row (among those with entries in the tile) of offset 64 wd + lane; wd is the same for the whole wavefront
+__device__ __forceinline__ uint32_t row_of_lane(const tile_starts &ts, unsigned wd, unsigned lane)
+{
+    const uint32_t w0 = (uint32_t)__builtin_amdgcn_readlane((int)(uint32_t)ts.word, (int)wd);
+    const uint32_t w1 = (uint32_t)__builtin_amdgcn_readlane((int)(uint32_t)(ts.word >> 32), (int)wd);
+    const uint32_t pre = (uint32_t)__builtin_amdgcn_readlane((int)ts.pre, (int)wd);
+    const uint64_t w = (uint64_t)w1 << 32 | w0;
+    // the tile's first bit is always set, so the count is at least one
+    return pre + __builtin_amdgcn_mbcnt_hi(w1, __builtin_amdgcn_mbcnt_lo(w0, 0u)) + (uint32_t)((w >> lane) & 1ull) - 1u;
+}
+
+// Two barriers; afterwards ebase (and row_no, if given: the row's index behind r_lo) can be read.  All of start[buf] is
+// zero on entry; start[buf ^ 1] is on return.
+template <bool ROW_NO>
+__device__ __forceinline__ bool stage_tile(tile_table &tt, uint16_t *row_no, int buf, const tile_pref &pf,
+                                           const int64_t *__restrict__ rowstart, const uint64_t *__restrict__ P,
+                                           const uint32_t *__restrict__ deg, uint64_t f0, uint32_t tile_len, uint32_t r_lo,
+                                           uint32_t nr, tile_starts &ts)
 {
     const bool staged = nr <= (uint32_t)IND_ROWS + 1;
+    // offset in the tile at which row k's entries start, -1 if it has none here
+    auto offset = [&](uint32_t k, uint64_t p, uint32_t d) -> int32_t {
+        const int64_t rel = (int64_t)p - (int64_t)f0;      // signed on purpose: the row may start in front of the tile
+        return (k < nr && d != 0 && rel < (int64_t)tile_len) ? (int32_t)max(rel, (int64_t)0) : -1;
+    };
     if (staged) {
         for (uint32_t k = threadIdx.x; k < nr; k += IND_NT) {
-            const uint64_t p = k < IND_NT ? pf.p : P[r_lo + k];
-            const int64_t rs = k < IND_NT ? pf.rs : rowstart[r_lo + k];
-            const int64_t rel = (int64_t)p - (int64_t)f0;      // signed on purpose: the row may start in front of the tile
-            tt.relP[k] = rel < 0 ? -1 : (rel > IND_TILE ? IND_TILE : (int32_t)rel);
-            tt.ebase[k] = rs - (int64_t)p;
+            const int32_t x = k < IND_NT ? offset(k, pf.p, pf.d) : offset(k, P[r_lo + k], deg[r_lo + k]);
+            if (x >= 0) atomicOr(&tt.start[buf][x >> 6], 1ull << (x & 63));
+        }
+    }
+    __syncthreads();
+    const unsigned lane = lane_id();
+    ts.word = lane < IND_WORDS ? tt.start[buf][lane] : 0ull;
+    const uint32_t pc = (uint32_t)__popcll(ts.word);
+    ts.pre = wave_incl_scan(pc) - pc;
+    if (threadIdx.x < IND_WORDS) tt.start[buf ^ 1][threadIdx.x] = 0ull;
+    if (staged) {
+        for (uint32_t k0 = 0; k0 < nr; k0 += IND_NT) {         // every lane stays in the loop: the prefix is read across lanes
+            const uint32_t k = k0 + threadIdx.x;
+            uint64_t p = pf.p;
+            int64_t rs = pf.rs;
+            uint32_t d = pf.d;
+            if (k0) {
+                const uint32_t r = r_lo + min(k, nr - 1);
+                p = P[r]; rs = rowstart[r]; d = deg[r];
+            }
+            const int32_t x = offset(k, p, d);
+            const uint32_t pre = (uint32_t)__shfl((int)ts.pre, max(x, 0) >> 6);
+            if (x >= 0) {
+                const uint32_t j = pre + (uint32_t)__popcll(tt.start[buf][x >> 6] & ((1ull << (x & 63)) - 1ull));
+                tt.ebase[j] = rs - (int64_t)p;
+                if constexpr (ROW_NO) row_no[j] = (uint16_t)k;
+            }
         }
     }
     __syncthreads();
     return staged;
 }
 
-// index k of the row of flat offset x = f - f0 >= 0: largest k < nr with relP[k] <= x
-__device__ __forceinline__ uint32_t find_row_lds(const tile_table &tt, uint32_t nr, int32_t x)
-{
-    uint32_t lo = 0, hi = nr - 1;
-    while (lo < hi) {
-        const uint32_t mid = lo + (hi - lo + 1) / 2;
-        if (tt.relP[mid] <= x) lo = mid; else hi = mid - 1;
-    }
-    return lo;
-}
-
-// The same search for the edges of a thread at once, in lock step with a fixed number of rounds,
-// so that the LDS reads of the slabs are in flight together (x[k] < 0: no edge, the result is unused).
-template <int ITEMS>
-__device__ __forceinline__ void find_rows_lds(const tile_table &tt, uint32_t nr, const int32_t (&x)[ITEMS], uint32_t (&rk)[ITEMS])
-{
-#pragma unroll
-    for (int k = 0; k < ITEMS; ++k) rk[k] = 0;
-    for (uint32_t step = 1u << (31 - __clz((int)nr)); step; step >>= 1) {
-#pragma unroll
-        for (int k = 0; k < ITEMS; ++k) {
-            // the read is unconditional (of the last row where t is beyond it), so that the compiler issues the reads
-            // of a round together instead of branching round each one and waiting for it
-            const uint32_t t = rk[k] + step;
-            const int32_t start = tt.relP[min(t, nr - 1)];
-            rk[k] = (t < nr && start <= x[k]) ? t : rk[k];
-        }
-    }
-}
-
 __global__ __launch_bounds__(IND_NT) void induced_count_kernel(const int64_t *__restrict__ rowstart,
+                                                               const uint32_t *__restrict__ deg,
                                                                const int32_t *__restrict__ colidx, uint32_t B,
                                                                const uint64_t *__restrict__ bitmap,
                                                                const uint8_t *__restrict__ coarse, shard_range rg,
@@ -222,8 +261,13 @@ __global__ __launch_bounds__(IND_NT) void induced_count_kernel(const int64_t *__
                                                                unsigned long long *__restrict__ total64)
 {
     __shared__ tile_table tt;
-    __shared__ uint32_t lds[IND_NT / 64];
-    const unsigned lane = lane_id(), wave = threadIdx.x >> 6;
+    __shared__ uint32_t wave_cnt[2][IND_NT / 64];
+    const unsigned lane = lane_id(), wave = (unsigned)__builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
+    if (threadIdx.x < 2 * IND_WORDS) tt.start[threadIdx.x / IND_WORDS][threadIdx.x % IND_WORDS] = 0ull;
+    __syncthreads();
+    // column range of the shard in 32 bits: column ids are below 2^31
+    const uint32_t c_lo = (uint32_t)min(max(rg.c0, (int64_t)0), (int64_t)1 << 31);
+    const uint32_t c_n = (uint32_t)min(max(rg.c1, (int64_t)c_lo), (int64_t)1 << 31) - c_lo;
     const uint64_t F = P[B];
     const uint64_t n_tiles = (F + IND_TILE - 1) / IND_TILE;
     if (blockIdx.x == 0 && threadIdx.x == 0) *n_tiles_out = n_tiles;
@@ -234,70 +278,83 @@ __global__ __launch_bounds__(IND_NT) void induced_count_kernel(const int64_t *__
     uint32_t r_lo = 0, nr = 0, r_lo1 = 0, nr1 = 0;
     if (blockIdx.x < n_tiles) tile_rows(tile_row, blockIdx.x, n_tiles, B, r_lo, nr);
     if (blockIdx.x + g < n_tiles) tile_rows(tile_row, blockIdx.x + g, n_tiles, B, r_lo1, nr1);
-    tile_pref pf = tile_prefetch(rowstart, P, blockIdx.x < n_tiles, r_lo, nr);
-    for (uint64_t c = blockIdx.x; c < n_tiles; c += g) {
-        const uint64_t f0 = c * IND_TILE, f1 = min(F, f0 + IND_TILE);
-        const bool staged = stage_tile_prefetched(tt, pf, rowstart, P, f0, r_lo, nr);
+    tile_pref pf = tile_prefetch(rowstart, P, deg, blockIdx.x < n_tiles, r_lo, nr);
+    int buf = 0;
+    for (uint64_t c = blockIdx.x; c < n_tiles; c += g, buf ^= 1) {
+        const uint64_t f0 = c * IND_TILE;
+        const uint32_t tile_len = (uint32_t)(min(F, f0 + IND_TILE) - f0);
+        tile_starts ts;
+        const bool staged = stage_tile<false>(tt, nullptr, buf, pf, rowstart, P, deg, f0, tile_len, r_lo, nr, ts);
         uint32_t r_lo2 = 0, nr2 = 0;
         if (c + 2 * g < n_tiles) tile_rows(tile_row, c + 2 * g, n_tiles, B, r_lo2, nr2);
-        pf = tile_prefetch(rowstart, P, c + g < n_tiles, r_lo1, nr1);
-        int32_t x[IND_ITEMS], u[IND_ITEMS];
-        uint32_t rk[IND_ITEMS];
-#pragma unroll
-        for (int k = 0; k < IND_ITEMS; ++k) {
-            const uint64_t f = f0 + (uint64_t)k * IND_NT + threadIdx.x;
-            x[k] = f < f1 ? (int32_t)(f - f0) : -1;
-        }
+        pf = tile_prefetch(rowstart, P, deg, c + g < n_tiles, r_lo1, nr1);
+        // Branch-free, one step for all eight edges at a time, and every load unconditional (an edge that does not need
+        // it reads an address that some other one reads): the gathers of a step are then in flight together.  A
+        // load that only some lanes want is compiled to a branch and a wait for the load before it.
+        int32_t u[IND_ITEMS];
         if (staged) {
-            // Branch-free, one step for all eight edges at a time: the eight gathers of colidx are then in flight together
-            // (with a branch round each edge the compiler waits for every load before it issues the next: eight round
-            // trips per tile instead of one).  An offset behind the end of the last tile reads the tile's first edge.
-            find_rows_lds(tt, nr, x, rk);
             int64_t e[IND_ITEMS];
 #pragma unroll
-            for (int k = 0; k < IND_ITEMS; ++k) e[k] = tt.ebase[rk[k]] + (int64_t)(f0 + (uint64_t)max(x[k], 0));
+            for (int k = 0; k < IND_ITEMS; ++k) {
+                const uint32_t x = k * IND_NT + threadIdx.x;
+                const bool in = x < tile_len;                   // an offset behind the end of the last tile reads the tile's first edge
+                const uint32_t j = row_of_lane(ts, k * (IND_NT / 64) + wave, lane);
+                e[k] = tt.ebase[in ? j : 0u] + (int64_t)(f0 + (in ? x : 0u));
+            }
 #pragma unroll
             for (int k = 0; k < IND_ITEMS; ++k) u[k] = colidx[e[k]];
-#pragma unroll
-            for (int k = 0; k < IND_ITEMS; ++k)
-                if (x[k] < 0 || u[k] < rg.c0 || u[k] >= rg.c1) u[k] = -1;   // no edge, or a column outside the shard
         } else {
+#pragma unroll 1
+            for (int k = 0; k < IND_ITEMS; ++k) {
+                const uint32_t x = k * IND_NT + threadIdx.x;
+                const uint64_t f = f0 + (x < tile_len ? x : 0u);
+                const uint32_t r = find_row(P, r_lo, r_lo + nr - 1, f);
+                const int32_t q = colidx[rowstart[r] + (int64_t)(f - P[r])];
+#pragma unroll
+                for (int kk = 0; kk < IND_ITEMS; ++kk) u[kk] = kk == k ? q : u[kk];
+            }
+        }
+        // no edge, or a column outside the shard: its column reads as vertex 0 and its keep bit is taken back below
+        bool in[IND_ITEMS];
+#pragma unroll
+        for (int k = 0; k < IND_ITEMS; ++k) {
+            in[k] = (k * IND_NT + threadIdx.x < tile_len) & ((uint32_t)u[k] - c_lo < c_n);
+            u[k] = in[k] ? u[k] : 0;
+        }
+        if (coarse) {
+            // the filter first (all eight probes in flight), the bitmap only for the edges it lets through (the others
+            // share the first word)
+            uint32_t cf[IND_ITEMS];
+#pragma unroll
+            for (int k = 0; k < IND_ITEMS; ++k) cf[k] = coarse[(uint32_t)u[k] >> 6];
 #pragma unroll
             for (int k = 0; k < IND_ITEMS; ++k) {
-                u[k] = -1;
-                if (x[k] >= 0) {
-                    const uint64_t f = f0 + (uint64_t)x[k];
-                    const uint32_t r = find_row(P, r_lo, r_lo + nr - 1, f);
-                    u[k] = colidx[rowstart[r] + (int64_t)(f - P[r])];
-                    if (u[k] < rg.c0 || u[k] >= rg.c1) u[k] = -1;   // a column outside the shard
-                }
+                in[k] = in[k] & (((cf[k] >> (((uint32_t)u[k] >> 3) & 7)) & 1u) != 0u);
+                u[k] = in[k] ? u[k] : 0;
             }
         }
         uint64_t word[IND_ITEMS];
-        if (coarse) {
-            // the filter first (all eight probes in flight), the bitmap only for the edges it lets through
-            uint8_t cf[IND_ITEMS];
 #pragma unroll
-            for (int k = 0; k < IND_ITEMS; ++k) cf[k] = u[k] >= 0 ? coarse[(uint32_t)u[k] >> 6] : (uint8_t)0;
-#pragma unroll
-            for (int k = 0; k < IND_ITEMS; ++k)
-                word[k] = ((cf[k] >> (((uint32_t)u[k] >> 3) & 7)) & 1) ? bitmap[(uint32_t)u[k] >> 6] : 0ull;
-        } else {
-#pragma unroll
-            for (int k = 0; k < IND_ITEMS; ++k) word[k] = u[k] >= 0 ? bitmap[(uint32_t)u[k] >> 6] : 0ull;
-        }
+        for (int k = 0; k < IND_ITEMS; ++k) word[k] = bitmap[(uint32_t)u[k] >> 6];
         // one keep word per slab and wavefront, kept for the fill pass; the count is their popcount
         uint32_t cnt = 0;
+        uint64_t mine = 0;
 #pragma unroll
         for (int k = 0; k < IND_ITEMS; ++k) {
-            const uint64_t bal = __ballot(u[k] >= 0 && ((word[k] >> (u[k] & 63)) & 1ull));
-            if (lane == 0) {
-                keepbits[c * IND_WORDS + k * (IND_NT / 64) + wave] = bal;
-                cnt += (uint32_t)__popcll(bal);
-            }
+            const uint64_t bal = __ballot(in[k] & (((word[k] >> (u[k] & 63)) & 1ull) != 0ull));
+            cnt += (uint32_t)__popcll(bal);
+            mine = lane == (unsigned)k ? bal : mine;
         }
-        const uint32_t t = block_sum<uint32_t, IND_NT>(cnt, lds);   // ends with a barrier: tt may be reused
-        if (threadIdx.x == 0) { tile_total[c] = t; wg_total += t; }
+        if (lane < IND_ITEMS) keepbits[c * IND_WORDS + lane * (IND_NT / 64) + wave] = mine;
+        if (lane == 0) wave_cnt[buf][wave] = cnt;
+        __syncthreads();       // also: the row table may be reused
+        if (threadIdx.x == 0) {
+            uint32_t t = 0;
+#pragma unroll
+            for (int w = 0; w < IND_NT / 64; ++w) t += wave_cnt[buf][w];
+            tile_total[c] = t;
+            wg_total += t;
+        }
         r_lo = r_lo1; nr = nr1; r_lo1 = r_lo2; nr1 = nr2;
     }
     if (threadIdx.x == 0 && wg_total) atomicAdd(total64, wg_total);     // integer: the sum does not depend on the order
@@ -318,12 +375,15 @@ __global__ __launch_bounds__(IND_NT) __attribute__((amdgpu_waves_per_eu(8, 8))) 
     int sticky_capacity, int deg_by_rank)
 {
     __shared__ tile_table tt;
+    __shared__ uint16_t row_no[IND_ROWS + 1];
     __shared__ uint64_t balw[IND_WORDS];
     __shared__ uint32_t pre[IND_WORDS + 1];
-    __shared__ uint16_t xs[IND_TILE];
+    __shared__ uint32_t xs[IND_TILE];
     const uint64_t F = P[B];
     const uint64_t n_tiles = *n_tiles_p;
-    const unsigned lane = lane_id(), wave = threadIdx.x >> 6;
+    const unsigned lane = lane_id(), wave = (unsigned)__builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
+    if (threadIdx.x < 2 * IND_WORDS) tt.start[threadIdx.x / IND_WORDS][threadIdx.x % IND_WORDS] = 0ull;
+    __syncthreads();
     if (blockIdx.x == 0) {
         const uint32_t total = tile_off_all[n_tiles];
         if (threadIdx.x == 0) {
@@ -344,16 +404,17 @@ __global__ __launch_bounds__(IND_NT) __attribute__((amdgpu_waves_per_eu(8, 8))) 
     uint32_t r_lo = 0, nr = 0, r_lo1 = 0, nr1 = 0;
     if (blockIdx.x < n_tiles) tile_rows(tile_row, blockIdx.x, n_tiles, B, r_lo, nr);
     if (blockIdx.x + g < n_tiles) tile_rows(tile_row, blockIdx.x + g, n_tiles, B, r_lo1, nr1);
-    tile_pref pf = tile_prefetch(rowstart, P, blockIdx.x < n_tiles, r_lo, nr);
+    tile_pref pf = tile_prefetch(rowstart, P, deg, blockIdx.x < n_tiles, r_lo, nr);
     uint64_t kw = 0;               // wavefront 0: keep word `lane` of the tile
     uint32_t tile_off = 0;         // survivors in earlier tiles (exclusive prefix of the tile counts)
     if (blockIdx.x < n_tiles) {
         if (wave == 0 && lane < IND_WORDS) kw = keepbits[(uint64_t)blockIdx.x * IND_WORDS + lane];
         tile_off = tile_off_all[blockIdx.x];
     }
-    for (uint64_t c = blockIdx.x; c < n_tiles; c += g) {
-        const uint64_t f0 = c * IND_TILE, f1 = min(F, f0 + IND_TILE);
-        const uint32_t tile_len = (uint32_t)(f1 - f0);
+    int buf = 0;
+    for (uint64_t c = blockIdx.x; c < n_tiles; c += g, buf ^= 1) {
+        const uint64_t f0 = c * IND_TILE;
+        const uint32_t tile_len = (uint32_t)(min(F, f0 + IND_TILE) - f0);
         const bool last = c + 1 == n_tiles;
         if (wave == 0) {
             const uint64_t w = lane < IND_WORDS ? kw : 0ull;
@@ -363,111 +424,106 @@ __global__ __launch_bounds__(IND_NT) __attribute__((amdgpu_waves_per_eu(8, 8))) 
             if (lane < IND_WORDS) pre[lane] = inc - pc;
             if (lane == IND_WORDS - 1) pre[IND_WORDS] = inc;
         }
-        const bool staged = stage_tile_prefetched(tt, pf, rowstart, P, f0, r_lo, nr);     // ends with a barrier
+        tile_starts ts;
+        const bool staged = stage_tile<true>(tt, row_no, buf, pf, rowstart, P, deg, f0, tile_len, r_lo, nr, ts);     // ends with a barrier
         const uint32_t tile_off_cur = tile_off;
+        const uint64_t p_cur = pf.p;
         uint32_t r_lo2 = 0, nr2 = 0;
         if (c + 2 * g < n_tiles) tile_rows(tile_row, c + 2 * g, n_tiles, B, r_lo2, nr2);
-        pf = tile_prefetch(rowstart, P, c + g < n_tiles, r_lo1, nr1);
+        pf = tile_prefetch(rowstart, P, deg, c + g < n_tiles, r_lo1, nr1);
         if (c + g < n_tiles) {
             if (wave == 0 && lane < IND_WORDS) kw = keepbits[(c + g) * IND_WORDS + lane];
             tile_off = tile_off_all[c + g];
         }
 
-        // row offsets.  A row that starts right at the end of the tile is empty if it is not the row the next
-        // tile begins with (that tile writes that one); behind the last tile every such row is empty.
-        for (uint32_t k = threadIdx.x; k < nr; k += IND_NT) {
-            int64_t x;
-            if (staged) x = tt.relP[k];
-            else {
-                const int64_t rel = (int64_t)P[r_lo + k] - (int64_t)f0;
-                x = rel < 0 ? -1 : (rel > IND_TILE ? IND_TILE : rel);
-            }
-            if (x < 0) continue;
-            if (x < (int64_t)tile_len) {
-                const uint32_t wd = ((uint32_t)x / IND_NT) * (IND_NT / 64) + (((uint32_t)x % IND_NT) >> 6);
-                rowptr_S[r_lo + k] = (int32_t)(tile_off_cur + pre[wd] + (uint32_t)__popcll(balw[wd] & ((1ull << (x & 63)) - 1ull)));
-            } else if (x == (int64_t)tile_len && (last || k + 1 < nr)) rowptr_S[r_lo + k] = (int32_t)(tile_off_cur + pre[IND_WORDS]);
-        }
-
-        // Survivors, in their order: the flat offsets of the set bits of the keep words are written to a list in LDS, and
-        // thread i takes survivor i, i + 256, ... (IND_FILL_SLOTS of them at a time).  A thread then holds the state of a few
-        // survivors instead of one slot for each of its eight edges, of which one in eight survives on a typical
-        // mini-batch: half the registers, twice the tiles in flight on a compute unit.
-        const uint64_t below = (1ull << lane) - 1ull;
+        // Survivors, in their order: the flat offsets of the set bits of the keep words are written to a list in LDS, each
+        // with the number of its row, and thread i takes survivor i, i + 256, ... (IND_FILL_SLOTS of them at a time).
+        // A thread then holds the state of a few survivors instead of one slot for each of its eight edges, of which one
+        // in eight survives on a typical mini-batch: half the registers, twice the tiles in flight on a compute unit.
 #pragma unroll
         for (int k = 0; k < IND_ITEMS; ++k) {
             const uint32_t wd = k * (IND_NT / 64) + wave;
             const uint64_t w = balw[wd];
-            if ((w >> lane) & 1ull) xs[pre[wd] + (uint32_t)__popcll(w & below)] = (uint16_t)(k * IND_NT + threadIdx.x);
+            const uint32_t at = pre[wd] + __builtin_amdgcn_mbcnt_hi((uint32_t)(w >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)w, 0u));
+            const uint32_t j = row_of_lane(ts, wd, lane);       // no meaning in a tile that is not staged, and not used there
+            if ((w >> lane) & 1ull) xs[at] = (k * IND_NT + threadIdx.x) | j << 16;
+        }
+
+        // row offsets.  A row that starts right at the end of the tile is empty if it is not the row the next
+        // tile begins with (that tile writes that one); behind the last tile every such row is empty.
+        for (uint32_t k = threadIdx.x; k < nr; k += IND_NT) {
+            const int64_t x = (int64_t)(staged && k < IND_NT ? p_cur : P[r_lo + k]) - (int64_t)f0;
+            if (x < 0) continue;
+            if (x < (int64_t)tile_len) {
+                const uint32_t wd = (uint32_t)x >> 6;
+                rowptr_S[r_lo + k] = (int32_t)(tile_off_cur + pre[wd] + (uint32_t)__popcll(balw[wd] & ((1ull << (x & 63)) - 1ull)));
+            } else if (x == (int64_t)tile_len && (last || k + 1 < nr)) rowptr_S[r_lo + k] = (int32_t)(tile_off_cur + pre[IND_WORDS]);
         }
         __syncthreads();
         const uint32_t n_surv = pre[IND_WORDS];
         for (uint32_t i0 = 0; i0 < n_surv; i0 += IND_FILL_SLOTS * IND_NT) {
-            int32_t x[IND_FILL_SLOTS], u[IND_FILL_SLOTS];
-            uint32_t rk[IND_FILL_SLOTS];
+            // Every load is unconditional: a slot behind the last survivor repeats it, and only the stores are guarded.
+            uint32_t r[IND_FILL_SLOTS];
+            int64_t e[IND_FILL_SLOTS];
 #pragma unroll
             for (int k = 0; k < IND_FILL_SLOTS; ++k) {
-                const uint32_t i = i0 + k * IND_NT + threadIdx.x;
-                x[k] = i < n_surv ? (int32_t)xs[i] : -1;
-            }
-            if (staged) find_rows_lds(tt, nr, x, rk);
-            int64_t eidx[IND_FILL_SLOTS];
-#pragma unroll
-            for (int k = 0; k < IND_FILL_SLOTS; ++k) {
-                u[k] = -1; eidx[k] = 0;
-                if (x[k] >= 0) {
-                    const uint64_t f = f0 + (uint64_t)x[k];
-                    if (staged) eidx[k] = tt.ebase[rk[k]] + (int64_t)f;
-                    else {
-                        const uint32_t r = find_row(P, r_lo, r_lo + nr - 1, f);
-                        rk[k] = r - r_lo;
-                        eidx[k] = rowstart[r] + (int64_t)(f - P[r]);
-                    }
-                    u[k] = colidx[eidx[k]];
+                const uint32_t q = xs[min(i0 + k * IND_NT + threadIdx.x, n_surv - 1)];
+                const uint64_t f = f0 + (q & 0xffffu);
+                if (staged) {
+                    e[k] = tt.ebase[q >> 16] + (int64_t)f;
+                    r[k] = r_lo + row_no[q >> 16];
+                } else {
+                    r[k] = find_row(P, r_lo, r_lo + nr - 1, f);
+                    e[k] = rowstart[r[k]] + (int64_t)(f - P[r[k]]);
                 }
             }
-            uint64_t word[IND_FILL_SLOTS];
-            uint32_t rnk[IND_FILL_SLOTS];
-            int64_t du[IND_FILL_SLOTS];
+            int32_t u[IND_FILL_SLOTS], v[IND_FILL_SLOTS];
+            uint32_t dr[IND_FILL_SLOTS];
+            float gv[IND_FILL_SLOTS];
 #pragma unroll
-            for (int k = 0; k < IND_FILL_SLOTS; ++k) {
-                word[k] = 0; rnk[k] = 0; du[k] = 1;
-                if (u[k] >= 0) {
-                    word[k] = bitmap[(uint32_t)u[k] >> 6];
-                    rnk[k] = rank[(uint32_t)u[k] >> 6];
-                    if (write_val && !gval && !deg_by_rank) du[k] = (int64_t)rowptr[(int64_t)u[k] + 1] - (int64_t)rowptr[u[k]];
-                }
+            for (int k = 0; k < IND_FILL_SLOTS; ++k) { u[k] = colidx[e[k]]; v[k] = S[r[k]]; dr[k] = deg[r[k]]; }
+            if (write_val && gval) {
+#pragma unroll
+                for (int k = 0; k < IND_FILL_SLOTS; ++k) gv[k] = gval[e[k]];
             }
             // compact column ids; a surviving column is itself a sampled vertex, so with every sampled row inside the row
             // range its degree is already in deg[] (B entries, cache resident) and need not be gathered from rowptr
+            uint64_t word[IND_FILL_SLOTS];
             uint32_t cid[IND_FILL_SLOTS];
 #pragma unroll
-            for (int k = 0; k < IND_FILL_SLOTS; ++k) {
-                cid[k] = rnk[k] + (uint32_t)__popcll(word[k] & ((1ull << (u[k] & 63)) - 1ull));
-                if (u[k] >= 0 && write_val && !gval && deg_by_rank) du[k] = (int64_t)deg[min(cid[k], B - 1)];
+            for (int k = 0; k < IND_FILL_SLOTS; ++k) { word[k] = bitmap[(uint32_t)u[k] >> 6]; cid[k] = rank[(uint32_t)u[k] >> 6]; }
+#pragma unroll
+            for (int k = 0; k < IND_FILL_SLOTS; ++k) cid[k] += (uint32_t)__popcll(word[k] & ((1ull << (u[k] & 63)) - 1ull));
+            int64_t du[IND_FILL_SLOTS];
+            if (write_val && !gval) {
+                if (deg_by_rank) {
+#pragma unroll
+                    for (int k = 0; k < IND_FILL_SLOTS; ++k) du[k] = (int64_t)deg[min(cid[k], B - 1)];
+                } else {
+#pragma unroll
+                    for (int k = 0; k < IND_FILL_SLOTS; ++k) du[k] = (int64_t)rowptr[(int64_t)u[k] + 1] - (int64_t)rowptr[u[k]];
+                }
             }
 #pragma unroll
             for (int k = 0; k < IND_FILL_SLOTS; ++k) {
-                if (u[k] < 0) continue;
-                const uint32_t pos = tile_off_cur + i0 + k * IND_NT + threadIdx.x;
-                if (pos >= capacity) continue;
+                const uint32_t i = i0 + k * IND_NT + threadIdx.x;
+                const uint32_t pos = tile_off_cur + i;
+                if (i >= n_surv || pos >= capacity) continue;
                 colidx_S[pos] = (int32_t)cid[k];
                 if (write_val) {
-                    const uint32_t r = r_lo + rk[k];
-                    const int64_t v = S[r];
                     float a;
-                    if (gval) a = gval[eidx[k]];
+                    if (gval) a = gv[k];
                     else {
                         // 1 / sqrt(deg(v) deg(u)) in single precision: product, reciprocal square root, one Newton step.
                         // Against the double-precision formula rounded once: a few 1e-7 relative (two roundings of
                         // 2^-24 here, one for 1/p, the Newton step leaves under one more), inside the 1e-6 the weights are held to.
                         // A row that holds an edge lies inside the row range: deg is its full length.
-                        const float xx = (float)deg[r] * (float)du[k];
+                        const float xx = (float)dr[k] * (float)du[k];
                         float y = __frsqrt_rn(xx);
                         const float err = fmaf(-xx * y, y, 1.0f);
                         a = fmaf(0.5f * y, err, y);
                     }
-                    if ((int64_t)u[k] != v) a *= inv_p;
+                    if (u[k] != v[k]) a *= inv_p;
                     val_S[pos] = a;
                 }
             }
@@ -539,7 +595,7 @@ int launch_typed(sgnn_ctx *ctx, const sgnn_graph *g, const int32_t *S, uint32_t 
     if (use_coarse)
         SGNN_LAUNCH(ctx, st, "induced_coarse_kernel", SGNN_TAG, induced_coarse_kernel, dim3((unsigned)std::min<uint64_t>(cdiv(W, 256), 4096)),
                     dim3(256), 0, st, bitmap, W, coarse);
-    SGNN_LAUNCH(ctx, st, "induced_count_kernel", SGNN_TAG, induced_count_kernel, dim3(grid), dim3(IND_NT), 0, st, rowstart,
+    SGNN_LAUNCH(ctx, st, "induced_count_kernel", SGNN_TAG, induced_count_kernel, dim3(grid), dim3(IND_NT), 0, st, rowstart, deg,
                 g->colidx, B, bitmap, coarse, rg, P, tile_row, tile_total, keepbits, n_tiles, total64);
     int rc = sgnn_scan_u32_devn(ctx, tile_total, tile_off, n_tiles, max_tiles, scan_tmp, st);
     if (rc) return rc;
