@@ -254,7 +254,7 @@ static int induced_impl(sgnn_ctx *ctx, const sgnn_graph *g, const int32_t *S, ui
     // with a host read-back the overflow is reported right here; without one through the sticky status word
     rc = sgnn_launch_induced(ctx, g, S, B, bitmap, rank, norm_mode, rescale, R0, R1, C0, C1, &o, nnz_host ? 0 : 1, st);
     if (rc) return rc;
-    rc = sgnn_launch_spmm_plan(ctx, &o, st);
+    rc = sgnn_launch_spmm_plan(ctx, &o, true, st);
     if (rc) return rc;
     out->rows = out->cols = B;
     if (nnz_host) {
@@ -303,7 +303,7 @@ int sgnn_csr_transpose(sgnn_ctx *ctx, const sgnn_csr *A, sgnn_csr *out, sgnn_str
     ws_alloc ws(ctx);
     rc = sgnn_launch_csr_transpose(ctx, A, out, &ws, static_cast<hipStream_t>(stream));
     if (rc) return rc;
-    return sgnn_launch_spmm_plan(ctx, out, static_cast<hipStream_t>(stream));
+    return sgnn_launch_spmm_plan(ctx, out, false, static_cast<hipStream_t>(stream));
 }
 
 int sgnn_csr_plan(sgnn_ctx *ctx, const sgnn_csr *A, sgnn_stream stream)
@@ -312,7 +312,7 @@ int sgnn_csr_plan(sgnn_ctx *ctx, const sgnn_csr *A, sgnn_stream stream)
     if (!A || !A->rowptr || !A->plan) return sgnn_fail(ctx, SGNN_ERR_INVALID_ARG, "sgnn_csr_plan: null pointer");
     int rc = bind_device(ctx);
     if (rc) return rc;
-    return sgnn_launch_spmm_plan(ctx, A, static_cast<hipStream_t>(stream));
+    return sgnn_launch_spmm_plan(ctx, A, false, static_cast<hipStream_t>(stream));
 }
 
 int sgnn_gather_rows(sgnn_ctx *ctx, const float *X, int64_t d, int64_t ldx, const int32_t *S, uint32_t B, float *out,

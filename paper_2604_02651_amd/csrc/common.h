@@ -89,6 +89,7 @@ static inline unsigned cdiv(uint64_t a, uint64_t b) { return (unsigned)((a + b -
 // ---- scan.hip ---------------------------------------------------------------------------------
 // Exclusive prefix sum of n uint32 (n known on the host), 64-bit result: out[i] = sum_{k<i} in[k]
 // for i <= n (out has n+1 entries).  tmp: ceil(n/2048)+1 uint64.
+constexpr uint64_t SGNN_SCAN_SINGLE_MAX = 65536;      // lengths up to which a prefix sum is one launch
 size_t sgnn_scan_tmp_elems(uint64_t n);
 int sgnn_scan_u32_to_u64(sgnn_ctx *ctx, const uint32_t *in, uint64_t *out, uint64_t n, uint64_t *tmp,
                          hipStream_t st);
@@ -110,7 +111,9 @@ int sgnn_launch_spmm(sgnn_ctx *ctx, const sgnn_csr *A, const void *X, int x_bf16
 int sgnn_launch_spmm_x(sgnn_ctx *ctx, const sgnn_csr *A, const void *X, int x_bf16, int64_t ldx, const int32_t *row_index, int64_t d,
                        void *out, int out_bf16, int64_t ldo, const float *bias, int relu, const void *mask, int mask_bf16,
                        int64_t ldm, const float *add, int64_t ldadd, ws_alloc *ws, hipStream_t st);
-int sgnn_launch_spmm_plan(sgnn_ctx *ctx, const sgnn_csr *A, hipStream_t st);   // fills A->plan when it is attached
+// fills A->plan when it is attached; cleared: an earlier launch of the same call has zeroed its counter already
+int sgnn_launch_spmm_plan(sgnn_ctx *ctx, const sgnn_csr *A, bool cleared, hipStream_t st);
+uint32_t *sgnn_spmm_plan_counter(const sgnn_csr *A);
 // a_row_index (may be NULL): physical row of A for every logical row (M x K operand: rows of the
 // result; K x M operand used transposed: reduction index)
 int sgnn_launch_gemm(sgnn_ctx *ctx, int ta, int tb, int64_t M, int64_t N, int64_t K, const float *A,

@@ -12,7 +12,8 @@
 //   1. induced_deg_kernel      row length of every sampled row and per-workgroup sums
 //   2. induced_offsets_kernel  flat offsets P[B+1] (exclusive prefix of the row lengths)
 //   3. induced_count_kernel    survivors per tile (wave ballots / popcounts)
-//   4. prefix sum              survivors in earlier tiles, for every tile
+//   4. prefix sum              survivors in earlier tiles, for every tile; only where many tiles are expected, otherwise
+//                              each workgroup of pass 5 adds up the counts of the tiles before its own
 //   5. induced_fill_kernel     survivors only (keep words of pass 3): ordered compaction, colidx, val, rowptr
 //   6. induced_renorm_kernel   only for norm_mode 1: weights from the degrees of the induced graph
 // A tile marks the starts of the rows it touches in a bit mask of its 2048 edges in LDS, so finding the row of an
@@ -35,17 +36,49 @@ constexpr int IND_WORDS = IND_ITEMS * (IND_NT / 64);   // 64-bit keep words of a
 constexpr int IND_ROWS = 1024;
 constexpr int IND_FILL_SLOTS = 2;                 // survivors a thread of the fill pass works on at a time (4 spill: 35 -> 62 us)
 constexpr unsigned IND_MAX_GRID = 8192;
+// Expected tiles up to which a workgroup of the fill pass adds up the survivors of the tiles before its own, instead of
+// reading a prefix sum that launches of their own have written.  271 tiles: fill pass 7.6 -> 7.7 us and a launch of 3.5 us
+// less; 6570 tiles: 34 -> 46 us for 6.5 us less, so that is no gain.  Where the prefix sum takes three launches
+// (room for more than 65536 tiles, which are those of the whole graph), 2930 tiles: 37 -> 40 us for 14 us less.
+constexpr uint64_t IND_OWN_PREFIX = 1024, IND_OWN_PREFIX_3 = 4096;
 constexpr int DEG_TILE = 2048;                    // sampled rows per workgroup in the offset kernels
 
 // Row and column range of a shard (Algorithm 2: [R0, R1) x [C0, C1) in global vertex ids); the whole graph by default.
 struct shard_range { int64_t r0, r1, c0, c1; };
 
+// Coarse membership filter for sparse samples of large graphs: one byte per bitmap word, bit b set iff byte b of the
+// word holds a sampled vertex (1 bit per 8 vertices).  With a sample of 1 % of 10^8 vertices the 14 MB bitmap does not
+// stay in a 4 MB L2 and every edge's probe is a cache-line fetch from further away; the filter (N / 64 bytes) does stay,
+// and turns away the 93 % of the edges whose eight-vertex group holds no sampled vertex at all.
+// Workgroups wg of n_wg, 256 threads each.
+__device__ __forceinline__ void coarse_filter(const uint64_t *__restrict__ bitmap, uint64_t W, uint8_t *__restrict__ coarse,
+                                              unsigned wg, unsigned n_wg)
+{
+    for (uint64_t w = (uint64_t)wg * 256 + threadIdx.x; w < W; w += (uint64_t)n_wg * 256) {
+        const uint64_t x = bitmap[w];
+        uint32_t c = 0;
+#pragma unroll
+        for (int b = 0; b < 8; ++b) c |= ((x >> (8 * b)) & 0xffull) ? (1u << b) : 0u;
+        coarse[w] = (uint8_t)c;
+    }
+}
+
+// The first n_deg_wg workgroups take the rows; those behind them build the coarse filter meanwhile, which no row needs
+// (a launch of its own was 5 us; these hide behind the gathers of the row lengths).
+// plan_count: piece counter of the plan that will be attached to the result, cleared here instead of in a launch of its own (or null).
 template <class RP>
 __global__ __launch_bounds__(256) void induced_deg_kernel(const RP *__restrict__ rowptr, const int32_t *__restrict__ S,
                                                           uint32_t B, shard_range rg, uint32_t *__restrict__ deg,
                                                           int64_t *__restrict__ rowstart, uint64_t *__restrict__ wg_sum,
-                                                          unsigned long long *__restrict__ total64)
+                                                          unsigned long long *__restrict__ total64, uint32_t *__restrict__ plan_count,
+                                                          unsigned n_deg_wg, const uint64_t *__restrict__ bitmap, uint64_t W,
+                                                          uint8_t *__restrict__ coarse)
 {
+    if (blockIdx.x >= n_deg_wg) {
+        coarse_filter(bitmap, W, coarse, blockIdx.x - n_deg_wg, gridDim.x - n_deg_wg);
+        return;
+    }
+    if (plan_count && blockIdx.x == 0 && threadIdx.x == 0) *plan_count = 0u;
     __shared__ uint64_t lds[256 / 64];
     if (blockIdx.x == 0 && threadIdx.x == 0) *total64 = 0ull;     // survivors of the whole mini-batch, summed by the count pass
     uint64_t s = 0;
@@ -103,22 +136,6 @@ __global__ __launch_bounds__(256) void induced_offsets_kernel(const uint32_t *__
         ex += d[k];
     }
     if (blockIdx.x == gridDim.x - 1 && threadIdx.x == 0) P[B] = base + total;
-}
-
-// Coarse membership filter for sparse samples of large graphs: one byte per bitmap word, bit b set iff byte b of the
-// word holds a sampled vertex (1 bit per 8 vertices).  With a sample of 1 % of 10^8 vertices the 14 MB bitmap does not
-// stay in a 4 MB L2 and every edge's probe is a cache-line fetch from further away; the filter (N / 64 bytes) does stay,
-// and turns away the 93 % of the edges whose eight-vertex group holds no sampled vertex at all.
-__global__ __launch_bounds__(256) void induced_coarse_kernel(const uint64_t *__restrict__ bitmap, uint64_t W,
-                                                             uint8_t *__restrict__ coarse)
-{
-    for (uint64_t w = (uint64_t)blockIdx.x * 256 + threadIdx.x; w < W; w += (uint64_t)gridDim.x * 256) {
-        const uint64_t x = bitmap[w];
-        uint32_t c = 0;
-#pragma unroll
-        for (int b = 0; b < 8; ++b) c |= ((x >> (8 * b)) & 0xffull) ? (1u << b) : 0u;
-        coarse[w] = (uint8_t)c;
-    }
 }
 
 // largest r in [lo, hi] with P[r] <= f   (P[lo] <= f is guaranteed by the caller)
@@ -364,8 +381,9 @@ __global__ __launch_bounds__(IND_NT) void induced_count_kernel(const int64_t *__
 // position = survivors in earlier tiles + survivors before the edge in the tile (prefix over the popcounts of
 // the tile's keep words).  Row offsets come from the row side: every row that starts inside the tile gets the
 // position of the first survivor at or behind its start, which also covers rows without any stored entry.
-template <class RP>
-__global__ __launch_bounds__(IND_NT) __attribute__((amdgpu_waves_per_eu(8, 8))) void induced_fill_kernel(
+// OWN_PREFIX: tile_off_all holds the counts of the tiles themselves, and the workgroup adds up those before its tile.
+template <class RP, bool OWN_PREFIX>
+__global__ __launch_bounds__(IND_NT) __attribute__((amdgpu_waves_per_eu(7, 7))) void induced_fill_kernel(
     const RP *__restrict__ rowptr, const int32_t *__restrict__ colidx, const float *__restrict__ gval,
     const int32_t *__restrict__ S, const int64_t *__restrict__ rowstart, const uint32_t *__restrict__ deg, uint32_t B,
     const uint64_t *__restrict__ bitmap, const uint32_t *__restrict__ rank, const uint64_t *__restrict__ P,
@@ -379,15 +397,16 @@ __global__ __launch_bounds__(IND_NT) __attribute__((amdgpu_waves_per_eu(8, 8))) 
     __shared__ uint64_t balw[IND_WORDS];
     __shared__ uint32_t pre[IND_WORDS + 1];
     __shared__ uint32_t xs[IND_TILE];
+    __shared__ uint32_t sum_lds[IND_NT / 64];
     const uint64_t F = P[B];
     const uint64_t n_tiles = *n_tiles_p;
     const unsigned lane = lane_id(), wave = (unsigned)__builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
     if (threadIdx.x < 2 * IND_WORDS) tt.start[threadIdx.x / IND_WORDS][threadIdx.x % IND_WORDS] = 0ull;
     __syncthreads();
     if (blockIdx.x == 0) {
-        const uint32_t total = tile_off_all[n_tiles];
         if (threadIdx.x == 0) {
             const unsigned long long t64 = *total64;
+            const uint32_t total = (uint32_t)t64;
             if (t64 > 0x7fffffffull) atomicOr(status, SGNN_ST_NNZ_OVERFLOW);
             // entries beyond the capacity are dropped below: without a host read-back of the count the caller learns
             // of it through the sticky status word (sgnn_ctx_status)
@@ -407,9 +426,16 @@ __global__ __launch_bounds__(IND_NT) __attribute__((amdgpu_waves_per_eu(8, 8))) 
     tile_pref pf = tile_prefetch(rowstart, P, deg, blockIdx.x < n_tiles, r_lo, nr);
     uint64_t kw = 0;               // wavefront 0: keep word `lane` of the tile
     uint32_t tile_off = 0;         // survivors in earlier tiles (exclusive prefix of the tile counts)
+    // OWN_PREFIX: survivors of tiles [a, b), every thread; wrapping 32-bit sums, as the prefix sum's
+    auto sum_tiles = [&](uint64_t a, uint64_t b) -> uint32_t {
+        uint32_t t = 0;
+#pragma unroll 1
+        for (uint64_t i = a + threadIdx.x; i < b; i += IND_NT) t += tile_off_all[i];
+        return block_sum<uint32_t, IND_NT>(t, sum_lds);
+    };
     if (blockIdx.x < n_tiles) {
         if (wave == 0 && lane < IND_WORDS) kw = keepbits[(uint64_t)blockIdx.x * IND_WORDS + lane];
-        tile_off = tile_off_all[blockIdx.x];
+        tile_off = OWN_PREFIX ? sum_tiles(0, blockIdx.x) : tile_off_all[blockIdx.x];
     }
     int buf = 0;
     for (uint64_t c = blockIdx.x; c < n_tiles; c += g, buf ^= 1) {
@@ -433,7 +459,7 @@ __global__ __launch_bounds__(IND_NT) __attribute__((amdgpu_waves_per_eu(8, 8))) 
         pf = tile_prefetch(rowstart, P, deg, c + g < n_tiles, r_lo1, nr1);
         if (c + g < n_tiles) {
             if (wave == 0 && lane < IND_WORDS) kw = keepbits[(c + g) * IND_WORDS + lane];
-            tile_off = tile_off_all[c + g];
+            tile_off = OWN_PREFIX ? tile_off_cur + sum_tiles(c, c + g) : tile_off_all[c + g];
         }
 
         // Survivors, in their order: the flat offsets of the set bits of the keep words are written to a list in LDS, each
@@ -581,8 +607,9 @@ int launch_typed(sgnn_ctx *ctx, const sgnn_graph *g, const int32_t *S, uint32_t 
         return sgnn_fail(ctx, SGNN_ERR_CAPACITY, "sgnn_induced_csr: scratch too small (%zu bytes needed): call sgnn_ctx_reserve",
                          ws.off);
 
-    SGNN_LAUNCH(ctx, st, "induced_deg_kernel", SGNN_TAG, induced_deg_kernel<RP>, dim3(n_deg_wg), dim3(256), 0, st, rowptr, S, B,
-                rg, deg, rowstart, deg_sum, total64);
+    const unsigned n_coarse_wg = use_coarse ? (unsigned)std::min<uint64_t>(cdiv(W, 1024), 1024) : 0u;
+    SGNN_LAUNCH(ctx, st, "induced_deg_kernel", SGNN_TAG, induced_deg_kernel<RP>, dim3(n_deg_wg + n_coarse_wg), dim3(256), 0, st, rowptr, S, B,
+                rg, deg, rowstart, deg_sum, total64, sgnn_spmm_plan_counter(out), n_deg_wg, bitmap, W, coarse);
     SGNN_LAUNCH(ctx, st, "induced_offsets_kernel", SGNN_TAG, induced_offsets_kernel, dim3(n_deg_wg), dim3(256), 0, st, deg, B,
                 deg_sum, P, tile_row);
     // Workgroups walk their tiles in a software pipeline (the next tile's row table is requested while the current
@@ -592,17 +619,17 @@ int launch_typed(sgnn_ctx *ctx, const sgnn_graph *g, const int32_t *S, uint32_t 
     const uint64_t expected_tiles = (uint64_t)((double)g->E * (double)B / (double)std::max<uint64_t>(g->N, 1) / IND_TILE);
     const unsigned grid_fill = (unsigned)std::min<uint64_t>(max_tiles, IND_MAX_GRID);
     const unsigned grid = (expected_tiles >= 2048 && expected_tiles < IND_MAX_GRID) ? 2048u : grid_fill;
-    if (use_coarse)
-        SGNN_LAUNCH(ctx, st, "induced_coarse_kernel", SGNN_TAG, induced_coarse_kernel, dim3((unsigned)std::min<uint64_t>(cdiv(W, 256), 4096)),
-                    dim3(256), 0, st, bitmap, W, coarse);
     SGNN_LAUNCH(ctx, st, "induced_count_kernel", SGNN_TAG, induced_count_kernel, dim3(grid), dim3(IND_NT), 0, st, rowstart, deg,
                 g->colidx, B, bitmap, coarse, rg, P, tile_row, tile_total, keepbits, n_tiles, total64);
-    int rc = sgnn_scan_u32_devn(ctx, tile_total, tile_off, n_tiles, max_tiles, scan_tmp, st);
-    if (rc) return rc;
+    const bool own_prefix = expected_tiles <= (max_tiles > SGNN_SCAN_SINGLE_MAX ? IND_OWN_PREFIX_3 : IND_OWN_PREFIX);
+    if (!own_prefix) {
+        const int rc = sgnn_scan_u32_devn(ctx, tile_total, tile_off, n_tiles, max_tiles, scan_tmp, st);
+        if (rc) return rc;
+    }
     double p = 1.0;
     if (rescale && B > 1) p = ((double)B - 1.0) / ((double)g->N - 1.0);
-    SGNN_LAUNCH(ctx, st, "induced_fill_kernel", SGNN_TAG, induced_fill_kernel<RP>, dim3(grid_fill), dim3(IND_NT), 0, st, rowptr,
-                g->colidx, norm_mode == 0 ? g->val : nullptr, S, rowstart, deg, B, bitmap, rank, P, tile_row, tile_off,
+    SGNN_LAUNCH(ctx, st, "induced_fill_kernel", SGNN_TAG, (own_prefix ? induced_fill_kernel<RP, true> : induced_fill_kernel<RP, false>), dim3(grid_fill), dim3(IND_NT), 0, st, rowptr,
+                g->colidx, norm_mode == 0 ? g->val : nullptr, S, rowstart, deg, B, bitmap, rank, P, tile_row, own_prefix ? tile_total : tile_off,
                 n_tiles, keepbits, (float)(1.0 / p), norm_mode == 0 ? 1 : 0, out->rowptr, out->colidx, out->val,
                 out->capacity, out->nnz_dev, ctx->status, total64, sticky_capacity,
                 (rg.r0 <= 0 && rg.r1 >= (int64_t)g->N) ? 1 : 0);

@@ -8,15 +8,15 @@
 // later passes read those instead: they decide all but 2^-11 (candidates) and 2^-16 (ties with the
 // threshold's prefix) of the vertices, and only for these is the key computed again.
 //
-// Sparse samples of large graphs take passes 1, 2, 4 and 6 only, pass 1 in the form of sampler_hist_window_kernel
-// (which also appends the candidates and sets the bits of the vertices that are in for certain).
+// Sparse samples of large graphs take pass 1 in the form of sampler_hist_window_kernel (which also appends the candidates
+// and sets the bits of the vertices that are in for certain); pass 2 then only finds the bin and pass 4 only counts.
 //
 //   1. sampler_hist_kernel     histogram of the top 11 key bits (LDS histograms, one merge)
-//   2. sampler_pick_bin_kernel the bin b* that holds the B-th smallest key and the rank r inside
-//   3. sampler_collect_kernel  (key, v) of every vertex in bin b* -> candidate list (about N/2048)
-//   4. sampler_threshold_kernel exact r-th smallest (key, v) of the candidates, by radix select
-//   5. sampler_emit_kernel     bitmap word per 64 vertices from wave ballots + per-workgroup counts
-//   6. sampler_rank_kernel     rank prefix per bitmap word and the ascending list S
+//   2. sampler_collect_kernel  the bin b* that holds the B-th smallest key and the rank r inside (every workgroup for
+//                              itself), and (key, v) of every vertex in bin b* -> candidate list (about N/2048)
+//   3. sampler_threshold_kernel exact r-th smallest (key, v) of the candidates
+//   4. sampler_emit_kernel     bitmap word per 64 vertices from wave ballots + per-workgroup counts
+//   5. sampler_rank_kernel     rank prefix per bitmap word and the ascending list S
 #include "block_prims.h"
 #include <algorithm>
 #include <cmath>
@@ -42,6 +42,7 @@ struct sampler_state {
     uint64_t thr_key;   // threshold key
     uint32_t fallback;  // windowed call whose threshold bin fell outside the window: the recomputing passes run instead
     uint32_t nmark;     // candidates the threshold pass looked at (ncand is zero again when it ends)
+    uint32_t ncand_fb;  // candidates appended by the collect pass of a windowed call that fell back
 };
 
 // keys of vertices 2j (even) and 2j+1 (odd)
@@ -69,9 +70,11 @@ __device__ __forceinline__ uint64_t spread_even(uint32_t x32)
 // times as long as the keys.  Hence at most a few hundred workgroups of 1024 threads.
 // prefix (may be NULL): word j receives the top 16 bits of the keys of vertices 2j (low half) and 2j+1.
 __global__ __launch_bounds__(SCAN_NT) void sampler_hist_kernel(uint64_t N, uint64_t seed, uint64_t step,
-                                                               uint32_t *__restrict__ hist, uint32_t *__restrict__ prefix)
+                                                               uint32_t *__restrict__ hist, uint32_t *__restrict__ prefix,
+                                                               sampler_state *__restrict__ state)
 {
     __shared__ uint32_t lh[HIST_BINS];
+    if (blockIdx.x == 0 && threadIdx.x == 0) state->ncand = 0;
     for (int i = threadIdx.x; i < HIST_BINS; i += SCAN_NT) lh[i] = 0;
     __syncthreads();
     const uint64_t J = (N + 1) >> 1;
@@ -99,7 +102,7 @@ template <uint32_t LCAP> struct cand_lds {
 
 template <uint32_t LCAP>
 __device__ __forceinline__ void cand_append(cand_lds<LCAP> &l, bool me, bool mo, uint64_t ke, uint64_t ko, uint64_t j,
-                                            sampler_state *__restrict__ state, uint64_t *__restrict__ cand_key,
+                                            uint32_t *__restrict__ ncand, uint64_t *__restrict__ cand_key,
                                             uint32_t *__restrict__ cand_v, uint32_t cap, uint32_t *__restrict__ status)
 {
     if (!(me || mo)) return;
@@ -113,7 +116,7 @@ __device__ __forceinline__ void cand_append(cand_lds<LCAP> &l, bool me, bool mo,
         // Reservations only grow, so every one before the first that failed fitted, and they
         // fill [0, first failing offset) without holes.
         atomicMin(&l.fail, p);
-        uint32_t q = atomicAdd(&state->ncand, cnt);
+        uint32_t q = atomicAdd(ncand, cnt);
         if (me) { if (q < cap) { cand_key[q] = ke; cand_v[q] = (uint32_t)(2 * j); } else atomicOr(status, SGNN_ST_CAND_OVERFLOW); ++q; }
         if (mo) { if (q < cap) { cand_key[q] = ko; cand_v[q] = (uint32_t)(2 * j + 1); } else atomicOr(status, SGNN_ST_CAND_OVERFLOW); }
     }
@@ -121,12 +124,12 @@ __device__ __forceinline__ void cand_append(cand_lds<LCAP> &l, bool me, bool mo,
 
 // every thread of the workgroup; NT threads
 template <uint32_t LCAP, int NT>
-__device__ __forceinline__ void cand_flush(cand_lds<LCAP> &l, sampler_state *__restrict__ state, uint64_t *__restrict__ cand_key,
+__device__ __forceinline__ void cand_flush(cand_lds<LCAP> &l, uint32_t *__restrict__ ncand, uint64_t *__restrict__ cand_key,
                                            uint32_t *__restrict__ cand_v, uint32_t cap, uint32_t *__restrict__ status)
 {
     __syncthreads();
     const uint32_t n_local = min(l.n, l.fail);
-    if (threadIdx.x == 0) l.base = n_local ? atomicAdd(&state->ncand, n_local) : 0u;
+    if (threadIdx.x == 0) l.base = n_local ? atomicAdd(ncand, n_local) : 0u;
     __syncthreads();
     const uint32_t base = l.base;
     for (uint32_t i = threadIdx.x; i < n_local; i += NT) {
@@ -144,7 +147,7 @@ __device__ __forceinline__ void cand_flush(cand_lds<LCAP> &l, sampler_state *__r
 // Nothing per vertex is stored for later passes - no key prefixes - and no later pass touches a key again: the
 // threshold comes from the candidates, the candidates at or below it get their bits set (sampler_mark_kernel), and
 // the bitmap is complete.  If the threshold's bin is outside the window after all
-// (sampler_pick_bin_kernel checks), the recomputing passes run instead and overwrite everything.
+// (pick_bin, at the head of the collect pass, checks), the recomputing passes run instead and overwrite everything.
 constexpr uint32_t WIN_LCAP = 2048;
 __global__ __launch_bounds__(SCAN_NT) void sampler_hist_window_kernel(uint64_t N, uint64_t seed, uint64_t step,
                                                                       uint32_t *__restrict__ hist, uint32_t b_lo, uint32_t b_hi,
@@ -158,6 +161,7 @@ __global__ __launch_bounds__(SCAN_NT) void sampler_hist_window_kernel(uint64_t N
     __shared__ __attribute__((aligned(8))) uint8_t strip[SCAN_NT / 64][64];
     for (int i = threadIdx.x; i < HIST_BINS; i += SCAN_NT) lh[i] = 0;
     if (threadIdx.x == 0) { cl.n = 0; cl.fail = 0xffffffffu; }
+    if (blockIdx.x == 0 && threadIdx.x == 0) state->ncand_fb = 0;
     __syncthreads();
     const unsigned wave = threadIdx.x >> 6, lane = lane_id();
     // A wavefront takes eight bitmap words (512 vertices) per round: lane l computes the keys of vertices 8l .. 8l+7 of
@@ -186,7 +190,7 @@ __global__ __launch_bounds__(SCAN_NT) void sampler_hist_window_kernel(uint64_t N
                     mo = bo_ >= b_lo && bo_ <= b_hi;
                     byte |= (bo_ < b_lo ? 1u : 0u) << (2 * q + 1);
                 }
-                cand_append(cl, me, mo, ke, ko, ve >> 1, state, cand_key, cand_v, cap, status);
+                cand_append(cl, me, mo, ke, ko, ve >> 1, &state->ncand, cand_key, cand_v, cap, status);
             }
         }
         my_bytes[lane] = (uint8_t)byte;          // volatile: written and read in program order; LDS serves a wavefront in order
@@ -195,58 +199,63 @@ __global__ __launch_bounds__(SCAN_NT) void sampler_hist_window_kernel(uint64_t N
             if (wb + lane < W) bitmap[wb + lane] = word;
         }
     }
-    cand_flush<WIN_LCAP, SCAN_NT>(cl, state, cand_key, cand_v, cap, status);
+    cand_flush<WIN_LCAP, SCAN_NT>(cl, &state->ncand, cand_key, cand_v, cap, status);
     for (int i = threadIdx.x; i < HIST_BINS; i += SCAN_NT) {
         uint32_t c = lh[i];
         if (c) atomicAdd(&hist[i], c);
     }
 }
 
-// One workgroup of 1024 threads, two bins a thread.  Leaves the histogram zeroed for the next call.
-// windowed: the candidates of bins b_lo .. b_hi are in the list already; they stay if the threshold's bin is one of
-// those, otherwise the list is emptied and the call falls back to the recomputing passes.
-__global__ __launch_bounds__(1024) void sampler_pick_bin_kernel(uint32_t B, uint32_t *__restrict__ hist,
-                                                                sampler_state *__restrict__ state, int windowed, uint32_t b_lo,
-                                                                uint32_t b_hi)
+// Bin of the B-th smallest key and its rank in there, from the histogram: 1024 threads, two bins a thread.  Every workgroup
+// of the collect pass does this for itself (8 KB from an L2 and a scan, under two microseconds side by side): a
+// launch of its own for one workgroup cost 2.4 us on a small graph and 4.8 behind a long pass.
+__device__ __forceinline__ void pick_bin(uint32_t B, const uint32_t *__restrict__ hist, uint32_t &bin_out, uint32_t &r_out)
 {
-    __shared__ uint32_t lds[1024 / 64 + 1];
-    const uint32_t h0 = hist[2 * threadIdx.x], h1 = hist[2 * threadIdx.x + 1];
-    hist[2 * threadIdx.x] = 0;
-    hist[2 * threadIdx.x + 1] = 0;
+    __shared__ uint32_t lds[SCAN_NT / 64 + 1];
+    __shared__ uint32_t sel[2];
+    const uint2 h = reinterpret_cast<const uint2 *>(hist)[threadIdx.x];
     uint32_t total;
-    const uint32_t ex = block_excl_scan<uint32_t, 1024>(h0 + h1, &total, lds);
+    const uint32_t ex = block_excl_scan<uint32_t, SCAN_NT>(h.x + h.y, &total, lds);
     // exactly one thread owns the bin of the B-th smallest key (1 <= B <= N)
-    uint32_t bin = 0xffffffffu, r = 0;
-    if (ex < B && B <= ex + h0) { bin = 2 * threadIdx.x; r = B - ex; }
-    else if (ex + h0 < B && B <= ex + h0 + h1) { bin = 2 * threadIdx.x + 1; r = B - ex - h0; }
-    if (bin != 0xffffffffu) {
-        // with a window, r counts inside the threshold's bin as always: the threshold pass looks only at the candidates of that bin
-        const bool miss = windowed && (bin < b_lo || bin > b_hi);
-        state->bin = bin;
-        state->r = r;
-        state->fallback = miss ? 1u : 0u;
-        if (!windowed || miss) state->ncand = 0;
-    }
+    if (ex < B && B <= ex + h.x) { sel[0] = 2 * threadIdx.x; sel[1] = B - ex; }
+    else if (ex + h.x < B && B <= ex + h.x + h.y) { sel[0] = 2 * threadIdx.x + 1; sel[1] = B - ex - h.x; }
+    __syncthreads();
+    bin_out = sel[0];
+    r_out = sel[1];
 }
+static_assert(HIST_BINS == 2 * SCAN_NT, "two bins a thread");
 
+// windowed: the candidates of bins b_lo .. b_hi are in the list already; they stay if the threshold's bin is one of
+// those (r counts inside the threshold's bin as always: the threshold pass looks only at the candidates of that bin), otherwise
+// the call falls back to this pass, which writes the list anew with a counter of its own.
 template <bool PREFIX>
-__global__ __launch_bounds__(SCAN_NT) void sampler_collect_kernel(uint64_t N, uint64_t seed, uint64_t step,
+__global__ __launch_bounds__(SCAN_NT) void sampler_collect_kernel(uint64_t N, uint32_t B, uint64_t seed, uint64_t step,
+                                                                  const uint32_t *__restrict__ hist,
                                                                   sampler_state *__restrict__ state,
                                                                   uint64_t *__restrict__ cand_key,
                                                                   uint32_t *__restrict__ cand_v, uint32_t cap,
                                                                   uint32_t *__restrict__ status,
-                                                                  const uint32_t *__restrict__ prefix, int only_on_fallback)
+                                                                  const uint32_t *__restrict__ prefix, int windowed, uint32_t b_lo,
+                                                                  uint32_t b_hi)
 {
     // Matches are rare (one vertex in 2048): gathered per workgroup (cand_lds).
     constexpr uint32_t LCAP = 1024;
     __shared__ cand_lds<LCAP> cl;
-    if (only_on_fallback && !state->fallback) return;      // a windowed call that found its threshold bin in the window
-    const uint32_t bin = state->bin;
+    uint32_t bin, r;
+    pick_bin(B, hist, bin, r);
+    const bool miss = windowed && (bin < b_lo || bin > b_hi);
+    if (blockIdx.x == 0 && threadIdx.x == 0) {
+        state->bin = bin;
+        state->r = r;
+        state->fallback = miss ? 1u : 0u;
+    }
+    if (windowed && !miss) return;                         // a windowed call that found its threshold bin in the window
+    uint32_t *ncand = windowed ? &state->ncand_fb : &state->ncand;
     const uint64_t J = (N + 1) >> 1;
     if (threadIdx.x == 0) { cl.n = 0; cl.fail = 0xffffffffu; }
     __syncthreads();
     auto append = [&](bool me, bool mo, uint64_t ke, uint64_t ko, uint64_t j) {
-        cand_append(cl, me, mo, ke, ko, j, state, cand_key, cand_v, cap, status);
+        cand_append(cl, me, mo, ke, ko, j, ncand, cand_key, cand_v, cap, status);
     };
     const uint64_t J_rounds = PREFIX ? (J + 3) / 4 : J;      // loop items: quads of prefix words, or Philox blocks
     for (uint64_t j = (uint64_t)blockIdx.x * SCAN_NT + threadIdx.x; j < J_rounds; j += (uint64_t)gridDim.x * SCAN_NT) {
@@ -272,60 +281,63 @@ __global__ __launch_bounds__(SCAN_NT) void sampler_collect_kernel(uint64_t N, ui
             append((uint32_t)(ke >> (64 - HIST_BITS)) == bin, (2 * j + 1 < N) && (uint32_t)(ko >> (64 - HIST_BITS)) == bin, ke, ko, j);
         }
     }
-    cand_flush<LCAP, SCAN_NT>(cl, state, cand_key, cand_v, cap, status);
+    cand_flush<LCAP, SCAN_NT>(cl, ncand, cand_key, cand_v, cap, status);
 }
 
-// Exact r-th smallest (key, v) among the candidates: most-significant-digit radix select over the
-// 96-bit composite, 8 bits a pass, starting below the 11 bits that all candidates share.  One
-// workgroup; a thread keeps its first THR_R candidates in registers, so that a pass costs no memory
-// traffic, and the passes stop as soon as the chosen digit holds a single candidate (after three or
-// four of them for keys that differ, instead of eleven).
-constexpr int THR_R = 12;
+// Exact r-th smallest (key, v) among the candidates of the threshold's bin.  One workgroup, and what it costs is the
+// trips to memory, the barriers in a row and, at a few hundred candidates, the fetching of its own code.  So: one radix
+// pass over the 8 bits below the 11 that the bin has decided (none if the list is short to begin with), then the
+// candidates that still agree - one in 256 of those in the bin - move to a list in LDS, and the ones below each are counted
+// by as many threads as there are for it.  A thread requests THR_BATCH keys at a time.  Where more than THR_LIST remain
+// (vertex counts beyond 2^29) another eight bits are decided first.
+// 4 10^7 vertices (39 thousand candidates): 33 -> 16.5 us, what is left is one compute unit's rate of reads and
+// LDS atomics; 2.4 10^6 vertices and fewer: 5 to 7 us before and after.  With 32 keys a thread in registers it spilled (24 us).
+// Leaves the histogram zeroed for the next call.
+constexpr int THR_BATCH = 16;
+constexpr uint32_t THR_LIST = 1024;
 
-__global__ __launch_bounds__(1024) void sampler_threshold_kernel(sampler_state *__restrict__ state,
+__global__ __launch_bounds__(1024) void sampler_threshold_kernel(sampler_state *__restrict__ state, uint32_t *__restrict__ bin_hist,
                                                                  const uint64_t *__restrict__ cand_key,
                                                                  const uint32_t *__restrict__ cand_v, uint32_t cap)
 {
     __shared__ uint32_t hist[256];
-    __shared__ uint32_t sel_digit, sel_r, sel_cnt;
+    __shared__ uint32_t sel_digit, sel_r;
     __shared__ uint64_t found_key;
     __shared__ uint32_t found_v;
-    const uint32_t n = min(state->ncand, cap);
+    __shared__ uint64_t list_key[THR_LIST];
+    __shared__ uint32_t list_v[THR_LIST], list_below[THR_LIST];
+    __shared__ uint32_t n_list;
+    const uint32_t n = min(state->fallback ? state->ncand_fb : state->ncand, cap);
     uint32_t r = state->r;
-    uint64_t rk[THR_R];
-    uint32_t rv[THR_R];
-#pragma unroll
-    for (int q = 0; q < THR_R; ++q) {
-        const uint32_t i = q * 1024 + threadIdx.x;
-        rk[q] = i < n ? cand_key[i] : 0ull;
-        rv[q] = i < n ? cand_v[i] : 0u;
-    }
     uint64_t pk = (uint64_t)state->bin << (64 - HIST_BITS);   // decided high bits of the key
     uint32_t pv = 0;                                          // decided high bits of the vertex
-    int kd = HIST_BITS, vd = 0;                               // how many of each are decided
-    if (threadIdx.x == 0) sel_cnt = 0;
+    int kd = HIST_BITS;                                       // how many of them are decided
+    reinterpret_cast<uint2 *>(bin_hist)[threadIdx.x] = make_uint2(0u, 0u);
+    list_below[threadIdx.x] = 0;
+    if (threadIdx.x < 256) hist[threadIdx.x] = 0;
+    if (threadIdx.x == 0) { sel_digit = 0; sel_r = 1; n_list = 0; found_key = 0; found_v = 0; }
+    __syncthreads();
 
-    // does (k, v) agree with every decided bit?
-    auto agrees = [&](uint64_t k, uint32_t v) {
-        if ((k >> (64 - kd)) != (pk >> (64 - kd))) return false;
-        return vd == 0 || (v >> (32 - vd)) == (pv >> (32 - vd));
-    };
-    bool single = false;
-    while (kd < 64 || vd < 32) {
-        const bool in_key = kd < 64;
-        const int width = in_key ? min(8, 64 - kd) : 8;
-        const int lo = in_key ? 64 - kd - width : 32 - vd - 8;
-        const uint32_t dmask = (1u << width) - 1u;
-        if (threadIdx.x < 256) hist[threadIdx.x] = 0;
-        __syncthreads();
-        auto count = [&](uint64_t k, uint32_t v) {
-            if (agrees(k, v)) atomicAdd(&hist[(in_key ? (uint32_t)(k >> lo) : (v >> lo)) & dmask], 1u);
-        };
+    // f(key, index) for every candidate whose key agrees with the decided bits; a thread's first batch stays in registers
+    auto fetch = [&](uint32_t i0, uint64_t (&k)[THR_BATCH]) {
 #pragma unroll
-        for (int q = 0; q < THR_R; ++q)
-            if (q * 1024 + threadIdx.x < n) count(rk[q], rv[q]);
-        for (uint32_t i = THR_R * 1024 + threadIdx.x; i < n; i += 1024) count(cand_key[i], cand_v[i]);
-        __syncthreads();
+        for (int q = 0; q < THR_BATCH; ++q) k[q] = cand_key[min(i0 + q * 1024 + threadIdx.x, n - 1)];
+    };
+    uint64_t first[THR_BATCH];
+    if (n) fetch(0, first);
+    auto for_agreeing = [&](auto f) {
+        for (uint32_t i0 = 0; i0 < n; i0 += THR_BATCH * 1024) {
+            uint64_t k[THR_BATCH];
+            if (i0) fetch(i0, k);
+#pragma unroll
+            for (int q = 0; q < THR_BATCH; ++q) {
+                k[q] = i0 ? k[q] : first[q];
+                if (i0 + q * 1024 + threadIdx.x < n && (k[q] >> (64 - kd)) == (pk >> (64 - kd))) f(k[q], i0 + q * 1024 + threadIdx.x);
+            }
+        }
+    };
+    // the digit of the r-th smallest from the histogram of digits, and its rank among the candidates with that digit
+    auto select = [&]() {
         if (threadIdx.x < 64) {
             // lane l owns digits 4l .. 4l+3
             const uint32_t a0 = hist[4 * threadIdx.x], a1 = hist[4 * threadIdx.x + 1], a2 = hist[4 * threadIdx.x + 2],
@@ -333,34 +345,70 @@ __global__ __launch_bounds__(1024) void sampler_threshold_kernel(sampler_state *
             const uint32_t s = a0 + a1 + a2 + a3;
             const uint32_t ex = wave_incl_scan(s) - s;
             if (ex < r && r <= ex + s) {
-                uint32_t d = 4 * threadIdx.x, e = ex, c = a0;
-                if (r > e + a0) { e += a0; ++d; c = a1; if (r > e + a1) { e += a1; ++d; c = a2; if (r > e + a2) { e += a2; ++d; c = a3; } } }
+                uint32_t d = 4 * threadIdx.x, e = ex;
+                if (r > e + a0) { e += a0; ++d; if (r > e + a1) { e += a1; ++d; if (r > e + a2) { e += a2; ++d; } } }
                 sel_digit = d;
                 sel_r = r - e;
-                sel_cnt = c;
             }
         }
         __syncthreads();
-        const uint32_t d = sel_digit;
         r = sel_r;
-        single = sel_cnt == 1;
-        if (in_key) { pk |= (uint64_t)d << lo; kd += width; }
-        else { pv |= d << lo; vd += 8; }
+    };
+    bool found = false;
+    for (bool radix = n > THR_LIST; !found && !(radix && kd == 64); radix = true) {
+        if (radix) {
+            const int width = min(8, 64 - kd), lo = 64 - kd - width;
+            for_agreeing([&](uint64_t k, uint32_t) { atomicAdd(&hist[(uint32_t)(k >> lo) & ((1u << width) - 1u)], 1u); });
+            __syncthreads();
+            select();
+            pk |= (uint64_t)sel_digit << lo;
+            kd += width;
+        }
+        for_agreeing([&](uint64_t k, uint32_t i) {
+            const uint32_t at = atomicAdd(&n_list, 1u);
+            if (at < THR_LIST) { list_key[at] = k; list_v[at] = cand_v[i]; }
+        });
         __syncthreads();
-        if (single) break;
+        const uint32_t m = n_list;
+        found = m <= THR_LIST;
+        if (found) {
+            // the vertices differ, so exactly one candidate has r - 1 others below it; the candidates an entry is
+            // compared with are shared out among 1024 / m2 threads
+            uint32_t m2 = 64;
+            while (m2 < m) m2 *= 2;
+            const uint32_t t = threadIdx.x & (m2 - 1), part = threadIdx.x / m2, parts = 1024 / m2;
+            if (t < m) {
+                const uint64_t k = list_key[t];
+                const uint32_t v = list_v[t];
+                uint32_t below = 0;
+#pragma unroll 4
+                for (uint32_t i = part; i < m; i += parts) below += (list_key[i] < k) | ((list_key[i] == k) & (list_v[i] < v));
+                if (below) atomicAdd(&list_below[t], below);
+            }
+            __syncthreads();
+            if (threadIdx.x < m && list_below[threadIdx.x] == r - 1) { found_key = list_key[threadIdx.x]; found_v = list_v[threadIdx.x]; }
+            __syncthreads();
+            pk = found_key;
+            pv = found_v;
+        } else {
+            __syncthreads();                               // every thread has read the count
+            if (threadIdx.x < 256) hist[threadIdx.x] = 0;
+            if (threadIdx.x == 0) n_list = 0;
+            __syncthreads();
+        }
     }
-    if (single) {
-        // exactly one candidate agrees with the decided bits: it is the threshold
-        auto take = [&](uint64_t k, uint32_t v) {
-            if (agrees(k, v)) { found_key = k; found_v = v; }
-        };
-#pragma unroll
-        for (int q = 0; q < THR_R; ++q)
-            if (q * 1024 + threadIdx.x < n) take(rk[q], rv[q]);
-        for (uint32_t i = THR_R * 1024 + threadIdx.x; i < n; i += 1024) take(cand_key[i], cand_v[i]);
+    // more candidates of one key than the list holds: the vertex decides
+    for (int vd = 0; !found && vd < 32; vd += 8) {
+        for_agreeing([&](uint64_t, uint32_t i) {
+            const uint32_t v = cand_v[i];
+            if (vd == 0 || (v >> (32 - vd)) == (pv >> (32 - vd))) atomicAdd(&hist[(v >> (24 - vd)) & 255u], 1u);
+        });
         __syncthreads();
-        pk = found_key;
-        pv = found_v;
+        select();
+        pv |= sel_digit << (24 - vd);
+        __syncthreads();
+        if (threadIdx.x < 256) hist[threadIdx.x] = 0;
+        __syncthreads();
     }
     if (threadIdx.x == 0) {
         state->thr_key = pk;
@@ -371,7 +419,7 @@ __global__ __launch_bounds__(1024) void sampler_threshold_kernel(sampler_state *
 }
 
 // Windowed calls: the candidates at or below the threshold get their bits (the vertices of the bins below the window
-// have theirs from the key pass), then the workgroup counts the rank pass wants.
+// have theirs from the key pass).
 __global__ __launch_bounds__(SAMP_NT) void sampler_mark_kernel(const sampler_state *__restrict__ state,
                                                                const uint64_t *__restrict__ cand_key,
                                                                const uint32_t *__restrict__ cand_v, uint64_t *__restrict__ bitmap)
@@ -386,39 +434,30 @@ __global__ __launch_bounds__(SAMP_NT) void sampler_mark_kernel(const sampler_sta
     }
 }
 
-__global__ __launch_bounds__(SAMP_NT) void sampler_count_kernel(const sampler_state *__restrict__ state,
-                                                                const uint64_t *__restrict__ bitmap, uint64_t W, uint64_t wpw,
-                                                                uint32_t *__restrict__ wg_count)
-{
-    __shared__ uint32_t lds[SAMP_NT / 64];
-    if (state->fallback) return;       // the recomputing emit pass has written bitmap and counts
-    const uint64_t wbeg = (uint64_t)blockIdx.x * wpw;
-    const uint64_t wend = min(W, wbeg + wpw);
-    uint32_t cnt = 0;
-    for (uint64_t w = wbeg + threadIdx.x; w < wend; w += SAMP_NT) cnt += (uint32_t)__popcll(bitmap[w]);
-    cnt = block_sum<uint32_t, SAMP_NT>(cnt, lds);
-    if (threadIdx.x == 0) wg_count[blockIdx.x] = cnt;
-}
-
-
 // Workgroup g owns bitmap words [g*wpw, (g+1)*wpw), wpw a multiple of 8.  A wavefront takes 64 words
 // at a time and builds two of them per iteration: lane l evaluates vertices 2j and 2j+1 of Philox block
 // j = 32*w0 + l.  Lane l keeps word l of the 64, so that the wave writes them with one 512-byte store:
 // an 8-byte store by a single lane per word reached memory as a partial write of its own, a quarter of a
 // million of them at a rate of about one per nanosecond.
+// windowed: the bitmap is complete unless the call fell back, and only the workgroup's count is left to take.
 __global__ __launch_bounds__(SAMP_NT) void sampler_emit_kernel(uint64_t N, uint64_t seed, uint64_t step,
                                                                const sampler_state *__restrict__ state,
                                                                uint64_t *__restrict__ bitmap, uint64_t W, uint64_t wpw,
-                                                               uint32_t *__restrict__ wg_count, int only_on_fallback)
+                                                               uint32_t *__restrict__ wg_count, int windowed)
 {
     __shared__ uint32_t lds[SAMP_NT / 64];
-    if (only_on_fallback && !state->fallback) return;
     const uint64_t tk = state->thr_key;
     const uint32_t tv = state->thr_v;
     const uint64_t wbeg = (uint64_t)blockIdx.x * wpw;
     const uint64_t wend = min(W, wbeg + wpw);
     const unsigned wave = threadIdx.x >> 6, lane = lane_id();
     uint32_t cnt = 0;
+    if (windowed && !state->fallback) {
+        for (uint64_t w = wbeg + threadIdx.x; w < wend; w += SAMP_NT) cnt += (uint32_t)__popcll(bitmap[w]);
+        cnt = block_sum<uint32_t, SAMP_NT>(cnt, lds);
+        if (threadIdx.x == 0) wg_count[blockIdx.x] = cnt;
+        return;
+    }
     for (uint64_t chunk = wbeg + 64 * wave; chunk < wend; chunk += 64 * (SAMP_NT / 64)) {
         uint64_t mine = 0;
         for (unsigned it = 0; it < 32; ++it) {
@@ -565,7 +604,7 @@ size_t sgnn_sampler_ws_bytes(uint64_t N)
     return cap * 12 + EMIT_MAX_WG * 4 + 4 * 256 + prefix_bytes(N) + 256;
 }
 
-// The six launches.  ctx may be NULL (no profiling, errors through sgnn_fail(NULL, ...)); every buffer
+// The launches.  ctx may be NULL (no profiling, errors through sgnn_fail(NULL, ...)); every buffer
 // comes from the caller of this function: hist (HIST_BINS words, zero on entry, left zero), state,
 // the candidate list of `cap` entries, EMIT_MAX_WG workgroup counts and the sticky status word.
 #define SAMP_LAUNCH(name, kernel, grid, block, ...)                                                        \
@@ -607,33 +646,31 @@ static int sampler_launches(sgnn_ctx *ctx, uint64_t N, uint32_t B, uint64_t seed
     const unsigned egrid = (unsigned)std::min<uint64_t>(cdiv(W, 8), EMIT_MAX_WG);
     const uint64_t wpw = (uint64_t)cdiv(cdiv(W, egrid), 8) * 8;
     if (win.on) {
-        // one pass over the keys; the passes marked "fallback" leave at once unless the threshold's bin missed the window
+        // one pass over the keys; the collect pass leaves at once and the emit pass only counts unless the threshold's
+        // bin missed the window
         SAMP_LAUNCH("sampler_hist_window_kernel", sampler_hist_window_kernel, dim3(grid), dim3(SCAN_NT), N, seed, step, hist, win.b_lo, win.b_hi,
                     state, cand_key, cand_v, cap, status, bitmap, W);
-        SAMP_LAUNCH("sampler_pick_bin_kernel", sampler_pick_bin_kernel, dim3(1), dim3(1024), B, hist, state, 1, win.b_lo, win.b_hi);
-        SAMP_LAUNCH("sampler_collect_kernel", sampler_collect_kernel<false>, dim3(grid), dim3(SCAN_NT), N, seed, step, state, cand_key,
-                    cand_v, cap, status, (const uint32_t *)nullptr, 1);      // fallback
-        SAMP_LAUNCH("sampler_threshold_kernel", sampler_threshold_kernel, dim3(1), dim3(1024), state, cand_key, cand_v, cap);
+        SAMP_LAUNCH("sampler_collect_kernel", sampler_collect_kernel<false>, dim3(grid), dim3(SCAN_NT), N, B, seed, step,
+                    (const uint32_t *)hist, state, cand_key, cand_v, cap, status, (const uint32_t *)nullptr, 1, win.b_lo, win.b_hi);
+        SAMP_LAUNCH("sampler_threshold_kernel", sampler_threshold_kernel, dim3(1), dim3(1024), state, hist, (const uint64_t *)cand_key,
+                    (const uint32_t *)cand_v, cap);
         SAMP_LAUNCH("sampler_mark_kernel", sampler_mark_kernel, dim3(64), dim3(SAMP_NT), (const sampler_state *)state,
                     (const uint64_t *)cand_key, (const uint32_t *)cand_v, bitmap);
         SAMP_LAUNCH("sampler_emit_kernel", sampler_emit_kernel, dim3(egrid), dim3(SAMP_NT), N, seed, step, state, bitmap, W, wpw,
-                    wg_count, 1);                                            // fallback
-        SAMP_LAUNCH("sampler_count_kernel", sampler_count_kernel, dim3(egrid), dim3(SAMP_NT), (const sampler_state *)state,
-                    (const uint64_t *)bitmap, W, wpw, wg_count);
+                    wg_count, 1);
         SAMP_LAUNCH("sampler_rank_kernel", sampler_rank_kernel, dim3(egrid), dim3(SAMP_NT), bitmap, W, wpw, wg_count, B, rank, S,
                     status);
         return SGNN_OK;
     }
-    SAMP_LAUNCH("sampler_hist_kernel", sampler_hist_kernel, dim3(grid), dim3(SCAN_NT), N, seed, step, hist, prefix);
-    SAMP_LAUNCH("sampler_pick_bin_kernel", sampler_pick_bin_kernel, dim3(1), dim3(1024), B, hist, state, 0, 0u, 0u);
+    SAMP_LAUNCH("sampler_hist_kernel", sampler_hist_kernel, dim3(grid), dim3(SCAN_NT), N, seed, step, hist, prefix, state);
     if (prefix)
-        SAMP_LAUNCH("sampler_collect_kernel", sampler_collect_kernel<true>, dim3(grid), dim3(SCAN_NT), N, seed, step, state, cand_key,
-                    cand_v, cap, status, (const uint32_t *)prefix, 0);
+        SAMP_LAUNCH("sampler_collect_kernel", sampler_collect_kernel<true>, dim3(grid), dim3(SCAN_NT), N, B, seed, step,
+                    (const uint32_t *)hist, state, cand_key, cand_v, cap, status, (const uint32_t *)prefix, 0, 0u, 0u);
     else
-        SAMP_LAUNCH("sampler_collect_kernel", sampler_collect_kernel<false>, dim3(grid), dim3(SCAN_NT), N, seed, step, state, cand_key,
-                    cand_v, cap, status, (const uint32_t *)nullptr, 0);
-    SAMP_LAUNCH("sampler_threshold_kernel", sampler_threshold_kernel, dim3(1), dim3(1024), state, cand_key, cand_v, cap);
-
+        SAMP_LAUNCH("sampler_collect_kernel", sampler_collect_kernel<false>, dim3(grid), dim3(SCAN_NT), N, B, seed, step,
+                    (const uint32_t *)hist, state, cand_key, cand_v, cap, status, (const uint32_t *)nullptr, 0, 0u, 0u);
+    SAMP_LAUNCH("sampler_threshold_kernel", sampler_threshold_kernel, dim3(1), dim3(1024), state, hist, (const uint64_t *)cand_key,
+                (const uint32_t *)cand_v, cap);
     if (prefix)
         SAMP_LAUNCH("sampler_emit_kernel", sampler_emit_prefix_kernel, dim3(egrid), dim3(SAMP_NT), N, seed, step, state, bitmap, W,
                     wpw, wg_count, (const uint32_t *)prefix);

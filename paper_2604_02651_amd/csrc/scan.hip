@@ -8,7 +8,7 @@ namespace {
 constexpr int SCAN_NT = 256;
 constexpr int SCAN_ITEMS = 8;
 constexpr int SCAN_TILE = SCAN_NT * SCAN_ITEMS;   // 2048
-constexpr uint64_t SCAN_SINGLE_MAX = 65536;
+constexpr uint64_t SCAN_SINGLE_MAX = SGNN_SCAN_SINGLE_MAX;
 
 // One workgroup scans everything: 1024 threads, chunks of 1024*16 with a running carry; the loads of the
 // next chunk are issued before the current one is scanned.

@@ -244,7 +244,10 @@ __global__ __launch_bounds__(SPMM_PLAN_NT) void spmm_plan_kernel(uint32_t rows, 
     __shared__ uint32_t scan_lds[SPMM_PLAN_NT / 64 + 1];
     __shared__ uint32_t wg_base;
     const uint32_t row = blockIdx.x * SPMM_PLAN_NT + threadIdx.x;
-    const uint64_t entries = min((uint64_t)rp_load(rowptr, rp64, rows), capacity);
+    // the row's offsets are requested together with the count of entries, which the length of a long row depends on
+    const uint64_t r0 = min(row, rows - 1);
+    const int64_t end = rp_load(rowptr, rp64, rows), e0 = rp_load(rowptr, rp64, r0), e1 = rp_load(rowptr, rp64, r0 + 1);
+    const uint64_t entries = min((uint64_t)end, capacity);
     const int long_len = spmm_long_len(rows, entries);
     if (row == 0) {
         n_chunks[1] = (uint32_t)long_len;
@@ -252,9 +255,9 @@ __global__ __launch_bounds__(SPMM_PLAN_NT) void spmm_plan_kernel(uint32_t rows, 
         n_chunks[3] = (uint32_t)min(entries / rows, (uint64_t)0xffffffffu);
     }
     int64_t len = 0;
-    if (row < rows) len = min(rp_load(rowptr, rp64, (uint64_t)row + 1), (int64_t)capacity) - min(rp_load(rowptr, rp64, row), (int64_t)capacity);
+    if (row < rows) len = min(e1, (int64_t)capacity) - min(e0, (int64_t)capacity);
     const int64_t plen = spmm_piece_len(len);
-    const uint32_t nch = len > long_len ? (uint32_t)((len + plen - 1) / plen) : 0u;
+    const uint32_t nch = len > long_len ? (uint32_t)((len + plen - 1) >> (63 - __clzll(plen))) : 0u;   // plen is a power of two
     // one atomic per workgroup of 1024 rows (atomics on one address cost about 10 ns each, whoever issues
     // them): the long rows of the workgroup take consecutive piece numbers
     uint32_t wg_total;
@@ -809,11 +812,12 @@ __global__ __launch_bounds__(256) void spmm_xent_clear_kernel(unsigned long long
     if (i < n) p[i] = 0ull;
 }
 
-int build_plan(sgnn_ctx *ctx, const sgnn_csr *A, void *plan, hipStream_t st)
+int build_plan(sgnn_ctx *ctx, const sgnn_csr *A, void *plan, bool cleared, hipStream_t st)
 {
     const uint32_t max_chunks = spmm_max_chunks(A->rows, A->capacity);
     const spmm_plan_view pv = plan_view(plan, A->rows, max_chunks);
-    SGNN_LAUNCH(ctx, st, "spmm_plan_clear_kernel", SGNN_TAG, spmm_plan_clear_kernel, dim3(1), dim3(1), 0, st, pv.n_chunks);
+    if (!cleared)
+        SGNN_LAUNCH(ctx, st, "spmm_plan_clear_kernel", SGNN_TAG, spmm_plan_clear_kernel, dim3(1), dim3(1), 0, st, pv.n_chunks);
     SGNN_LAUNCH(ctx, st, "spmm_plan_kernel", SGNN_TAG, spmm_plan_kernel, dim3(cdiv(A->rows, SPMM_PLAN_NT)), dim3(SPMM_PLAN_NT), 0, st, A->rows,
                 A->rowptr, A->rowptr_is_i64, A->capacity, pv.n_chunks, max_chunks, pv.part_base, pv.desc, pv.ticket);
     return SGNN_OK;
@@ -850,7 +854,7 @@ int launch_vc(sgnn_ctx *ctx, const sgnn_csr *A, const XT *X, int64_t ldx, const 
             if (!ws->ok)
                 return sgnn_fail(ctx, SGNN_ERR_CAPACITY, "sgnn_spmm: scratch too small (%zu bytes needed): call sgnn_ctx_reserve",
                                  ws->off);
-            int rc = build_plan(ctx, A, plan, st);
+            int rc = build_plan(ctx, A, plan, false, st);
             if (rc) return rc;
         }
         pv = plan_view(plan, A->rows, max_chunks);
@@ -921,10 +925,16 @@ extern "C" uint64_t sgnn_csr_plan_bytes(uint32_t rows, uint64_t capacity)
     return 256 + (((uint64_t)rows * 4 + 255) & ~uint64_t(255)) + (uint64_t)spmm_max_chunks(rows, capacity) * 12 + 512;
 }
 
-int sgnn_launch_spmm_plan(sgnn_ctx *ctx, const sgnn_csr *A, hipStream_t st)
+// the plan's piece counter, which has to be zero when the plan is built (null without a plan)
+uint32_t *sgnn_spmm_plan_counter(const sgnn_csr *A)
+{
+    return A->plan && A->rows ? plan_view(A->plan, A->rows, 0).n_chunks : nullptr;
+}
+
+int sgnn_launch_spmm_plan(sgnn_ctx *ctx, const sgnn_csr *A, bool cleared, hipStream_t st)
 {
     if (!A->plan || A->rows == 0) return SGNN_OK;
-    return build_plan(ctx, A, A->plan, st);
+    return build_plan(ctx, A, A->plan, cleared, st);
 }
 
 template <typename XT>
@@ -948,7 +958,7 @@ static int launch_x(sgnn_ctx *ctx, const sgnn_csr *A, const XT *X, int64_t ldx, 
             planned.plan = ws->get<uint8_t>(sgnn_csr_plan_bytes(A->rows, A->capacity));
             if (!ws->ok)
                 return sgnn_fail(ctx, SGNN_ERR_CAPACITY, "sgnn_spmm: scratch too small (%zu bytes needed): call sgnn_ctx_reserve", ws->off);
-            const int rc = build_plan(ctx, A, planned.plan, st);
+            const int rc = build_plan(ctx, A, planned.plan, false, st);
             if (rc) return rc;
         }
         A = &planned;

@@ -6,7 +6,7 @@ import torch
 
 import oracle
 import paper_2604_02651_amd as sg
-from gpu_util import DEV, TOL_VAL, ctx, gpu_sample
+from gpu_util import DEV, TOL_VAL, bitmap_rank_from_sample, ctx, gpu_sample
 
 pytestmark = pytest.mark.gpu
 
@@ -63,3 +63,86 @@ def test_tiles_against_oracle(kind, rp32):
             got = out.val.cpu().numpy()[:nnz].astype(np.float64)
             assert np.all(np.abs(got - v) <= TOL_VAL * np.abs(v)), (kind, B, rg)
     ctx().status()
+
+
+def _induced(N, rowptr, colidx, S, out, want=True):
+    words, ranks = bitmap_rank_from_sample(N, S)
+    to = lambda a, t: torch.as_tensor(np.asarray(a).astype(t)).to(DEV)
+    return sg.sgnn_induced_csr(ctx(), N, to(rowptr, np.int64), to(colidx, np.int32), None, to(S, np.int32), len(S),
+                               torch.as_tensor(words.view(np.int64)).to(DEV), to(ranks, np.int32), out, want_nnz=want)
+
+
+def test_many_expected_tiles():
+    # 1220 tiles are expected: the survivors of earlier tiles come from the prefix sum
+    N, d = 5000, 500
+    rng = np.random.default_rng(5)
+    rowptr = np.arange(N + 1) * d
+    colidx = np.sort(np.argpartition(rng.random((N, N), np.float32), d, axis=1)[:, :d], axis=1).ravel()
+    ctx().reserve(N, N * d, N, 8, N * d)
+    for B in (N, N - 3, 2000):
+        S = np.sort(rng.choice(N, B, replace=False))
+        out = sg.Csr(B, B, N * d, DEV)
+        nnz = _induced(N, rowptr, colidx, S, out)
+        rp, ci, v = oracle.induced_csr(N, rowptr, colidx, S)
+        assert nnz == len(ci) and np.array_equal(out.rowptr.cpu().numpy(), rp) and np.array_equal(out.colidx.cpu().numpy()[:nnz], ci)
+        assert np.all(np.abs(out.val.cpu().numpy()[:nnz] - v) <= TOL_VAL * np.abs(v))
+
+
+def test_far_more_tiles_than_expected():
+    # eight rows hold nearly all entries and all eight are sampled: 17 tiles expected, 8600 there, more than workgroups
+    N, big, d = 4000, np.array([0, 7, 8, 1000, 1001, 2500, 3998, 3999]), 2200007
+    rng = np.random.default_rng(6)
+    deg = np.ones(N, np.int64)
+    deg[big] = d
+    rowptr = np.concatenate([[0], np.cumsum(deg)])
+    colidx = rng.integers(0, N, rowptr[-1]).astype(np.int32)
+    keep = np.isin(colidx, big)
+    row = np.repeat(np.arange(N), deg)
+    sel = keep & np.isin(row, big)
+    rp = np.concatenate([[0], np.cumsum(np.bincount(np.searchsorted(big, row[sel]), minlength=8))])
+    ci = np.searchsorted(big, colidx[sel])
+    ctx().reserve(N, len(colidx), 8, 8, len(ci))
+    out = sg.Csr(8, 8, len(ci), DEV)
+    assert _induced(N, rowptr, colidx, big, out) == len(ci)
+    assert np.array_equal(out.rowptr.cpu().numpy(), rp) and np.array_equal(out.colidx.cpu().numpy(), ci)
+    ctx().status()
+
+
+def test_plan_of_a_matrix_that_is_filled_again():
+    # the plan's counter starts at zero in every call: hub rows, two samples into one matrix, products with and without
+    N = 6000
+    rng = np.random.default_rng(8)
+    deg = np.where(rng.random(N) < 0.05, 3000, 2)
+    rowptr = np.concatenate([[0], np.cumsum(deg)])
+    colidx = np.concatenate([np.sort(rng.choice(N, d, replace=False)) for d in deg])
+    B, E = 3000, len(colidx)
+    ctx().reserve(N, E, B, 64, E)
+    out = sg.Csr(B, B, E, DEV)
+    X = torch.randn(B, 64, device=DEV, generator=torch.Generator(DEV).manual_seed(1))
+    for seed in (1, 2, 3):
+        S = np.sort(np.random.default_rng(seed).choice(N, B, replace=False))
+        nnz = _induced(N, rowptr, colidx, S, out)
+        rp, ci, v = oracle.induced_csr(N, rowptr, colidx, S)
+        assert nnz == len(ci) and np.array_equal(out.rowptr.cpu().numpy(), rp)
+        Y = torch.empty(B, 64, device=DEV)
+        sg.sgnn_spmm(ctx(), out, X, Y)
+        H = X.cpu().numpy()
+        # one rounding for every product and addition, and the weights to TOL_VAL
+        bound = (np.diff(rp).max() + 2) * 2.0**-24 + TOL_VAL
+        assert np.all(np.abs(Y.cpu().numpy() - oracle.spmm(rp, ci, v, H)) <= bound * oracle.spmm(rp, ci, np.abs(v), np.abs(H)) + 1e-12)
+
+
+@pytest.mark.parametrize("N,B", [(1200000011, 400000000), (1200000011, 1001), (600000000, 200000001)])
+def test_sample_of_a_graph_with_more_candidates_than_the_list_holds(N, B):
+    # Exactly B vertices with keys up to one threshold is the whole definition of the sample: the count is taken from the
+    # bitmap, and of some vertices the keys.
+    S, bitmap, rank = gpu_sample(N, B, 5, 3)
+    ctx().status()
+    got = S.cpu().numpy()
+    assert np.all(np.diff(got) > 0) and got[0] >= 0 and got[-1] < N
+    words = bitmap.cpu().numpy().view(np.uint64)
+    assert int(np.bitwise_count(words).sum()) == B
+    v = np.r_[np.random.default_rng(1).integers(0, N, 3000), got[np.random.default_rng(2).integers(0, B, 1000)]]
+    inside = (words[v >> 6] >> (v & 63).astype(np.uint64)) & np.uint64(1) == 1
+    keys = np.array([oracle.vertex_key(5, 3, int(x)) for x in v], np.uint64)
+    assert inside[-1000:].all() and keys[inside].max() < keys[~inside].min()
