@@ -1,5 +1,5 @@
 // Weight gradient of a mini-batch (Sec. III-C: dW = H_agg^T dZ) with both operands stored as bfloat16:
-//   C [M x N] = A^T B,   A given [K x M], B given [K x N], M, N <= 256, K = the number of sampled vertices (10^3 .. 10^6).
+//   C [M x N] = A^T B,   A given [K x M], B given [K x N], M, N <= 256, K = the number of sampled vertices (8192 .. 10^6).
 //
 // The product reads 2 K (M + N) bytes and computes 2 K M N flop: with M = N = 256 that is 128 flop per byte, far below
 // the machine's bf16 ridge, so the kernel is built as a stream over K and nothing else:
@@ -21,7 +21,7 @@
 // the row's last chunk: they only feed result rows and columns that are never stored.
 // Measured with the reduction of the partial products (us, ordinary reads and permutes / here): 256 x 256 x 2^20 313 / 289, of which
 // the stream is 272 = 3.95 TB/s, what a plain read of 1 GiB reaches on the card; 256 x 47 x 2^18 62 / 46; and where the K or the
-// width was outside the earlier form: 200 x 193 x 56399 183 / 40, 256 x 256 x 999 37 / 14, 30 x 256 x 300007 565 / 47.
+// width was outside the earlier form: 200 x 193 x 56399 183 / 40, 30 x 256 x 300007 565 / 47.
 #include <algorithm>
 
 #include "common.h"
@@ -220,7 +220,10 @@ template <int FA, int FB, int WM, int WN> int launch_tns(sgnn_ctx *ctx, const tn
 int sgnn_launch_gemm_tn_stream(sgnn_ctx *ctx, int64_t M, int64_t N, int64_t K, const void *A, int64_t lda, const void *B, int64_t ldb,
                                float *C, int64_t ldc, float *b_colsum, ws_alloc *ws, hipStream_t st)
 {
-    if (M < 1 || N < 1 || M > 256 || N > 256 || K < 64 || lda % 8 || ldb % 8 || lda < M || ldb < N ||
+    // Reductions of fewer than 8192 rows stay with the tile kernel: there the product of operands stored as bfloat16 is, bit for
+    // bit, that of the same values stored as fp32 (which the tile kernel rounds), and callers may mix the two.  It costs at
+    // most some 20 us a product: 256 x 256 x 999 37 us there, 14 here.
+    if (M < 1 || N < 1 || M > 256 || N > 256 || K < 8192 || lda % 8 || ldb % 8 || lda < M || ldb < N ||
         (reinterpret_cast<uintptr_t>(A) & 15) || (reinterpret_cast<uintptr_t>(B) & 15))
         return SGNN_ERR_UNSUPPORTED;
     // As many workgroups as make the partial products (written and read: 8 M N bytes each) about as much traffic as the operands,
