@@ -136,12 +136,19 @@ def test_plan_of_a_matrix_that_is_filled_again():
 def test_sample_of_a_graph_with_more_candidates_than_the_list_holds(N, B):
     # Exactly B vertices with keys up to one threshold is the whole definition of the sample: the count is taken from the
     # bitmap, and of some vertices the keys.
-    S, bitmap, rank = gpu_sample(N, B, 5, 3)
-    ctx().status()
+    c = sg.Context(0)                                    # not the shared one, which would keep room for this size
+    c.reserve(N, 1, 1, 1)
+    S, W = torch.full((B,), -1, dtype=torch.int32, device=DEV), (N + 63) // 64
+    bitmap, rank = torch.full((W,), -1, dtype=torch.int64, device=DEV), torch.empty(W, dtype=torch.int32, device=DEV)
+    sg.sgnn_sample_uniform(c, N, B, 5, 3, S, bitmap, rank)
+    c.status()
     got = S.cpu().numpy()
     assert np.all(np.diff(got) > 0) and got[0] >= 0 and got[-1] < N
     words = bitmap.cpu().numpy().view(np.uint64)
     assert int(np.bitwise_count(words).sum()) == B
+    del S, bitmap, rank
+    c.close()
+    torch.cuda.empty_cache()
     v = np.r_[np.random.default_rng(1).integers(0, N, 3000), got[np.random.default_rng(2).integers(0, B, 1000)]]
     inside = (words[v >> 6] >> (v & 63).astype(np.uint64)) & np.uint64(1) == 1
     keys = np.array([oracle.vertex_key(5, 3, int(x)) for x in v], np.uint64)
