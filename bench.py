@@ -206,18 +206,24 @@ def measure(args, sg, si, torch, cfg, g, X, labels, weights, use_graph_req: str,
         nnz_total += st.A.nnz()
     nnz_avg = nnz_total / nprof
     groups = {}
+    # widths whose products are launched for the panel kernel too; of the two kernels the one runs that the mean row
+    # length names (12 entries), the other leaves at once
+    panel_widths = {tag.split("d=")[1].split()[0] for name, tag, _, _ in recs if name == "spmm_panel_kernel"}
+    panels_run = nnz_avg >= 12 * cfg.B
     for name, tag, calls, ms in recs:
         key = name   # one group per kernel symbol, as rocprofv3 lists them
         if name == "gemm_kernel":
             p = tag.split()
             key = "gemm_kernel<%s,%s,%s>" % (p[1], p[0], p[3])
+        elif name == "gemm_split_kernel":
+            key = "gemm_split_kernel<%s,%s>" % (tag.split()[1], tag.split()[0])
         elif name == "spmm_main_kernel":
             # the instantiation with the loss in its epilogue (tag: "... dO=<bytes>") is a kernel symbol of its own
             key = name + (tag.split()[2][:-1] + ",xent>" if " dO=" in tag else tag.split()[2])
         gq = groups.setdefault(key, {"calls": 0, "ms": 0.0, "flops": 0.0, "bytes": 0.0})
         gq["calls"] += calls
         gq["ms"] += ms
-        if name in ("gemm_kernel", "gemm_direct_kernel"):
+        if name in ("gemm_kernel", "gemm_split_kernel"):
             gq["flops"] += gemm_flops(tag) * calls
         elif name == "gemm_skinny_bf16_kernel":
             # tall operand streamed once, small operand resident: bound by reading A and writing C.
@@ -237,17 +243,18 @@ def measure(args, sg, si, torch, cfg, g, X, labels, weights, use_graph_req: str,
             eb = next((float(w[2:]) for w in p if w.startswith("b=")), 2.0)
             gq["bytes"] += calls * k_ * (ea * m_ + eb * n_)
             gq["flops"] += calls * 2.0 * m_ * n_ * k_
-        elif name == "spmm_main_kernel":
+        elif name in ("spmm_main_kernel", "spmm_panel_kernel"):
             d = int(tag.split("d=")[1].split()[0])
             w = tag.split()
             ein = next((float(x[3:]) for x in w if x.startswith("in=")), 2.0 if "bf16 in" in tag else 4.0)
             eout = next((float(x[4:]) for x in w if x.startswith("out=")), 4.0)
             edo = next((float(x[3:]) for x in w if x.startswith("dO=")), 0.0)      # the loss epilogue also writes the gradient rows
             # compulsory traffic: CSR once, every input row once, the output once
-            gq["bytes"] += calls * (8.0 * nnz_avg + 4.0 * (cfg.B + 1) + cfg.B * d * (ein + eout + edo))
+            runs = panels_run if name == "spmm_panel_kernel" else not (panels_run and " dO=" not in tag and str(d) in panel_widths)
+            gq["bytes"] += runs * calls * (8.0 * nnz_avg + 4.0 * (cfg.B + 1) + cfg.B * d * (ein + eout + edo))
     total_ms = sum(v["ms"] for v in groups.values())
     dom_name, dom = max(groups.items(), key=lambda kv: kv[1]["ms"])
-    sp = [v for k, v in groups.items() if k.startswith("spmm_main_kernel")]
+    sp = [v for k, v in groups.items() if k.startswith(("spmm_main_kernel", "spmm_panel_kernel"))]
     sparse_ms, sparse_bytes = sum(v["ms"] for v in sp), sum(v["bytes"] for v in sp)
     if args.breakdown:
         for name, tag, calls, ms in recs:

@@ -138,7 +138,7 @@ def bench_eval(cfg, args):
     torch.cuda.synchronize()
     wall_ms = 1e3 * (time.perf_counter() - t0) / reps
     ks = _kernels(recs, reps)
-    sp_ms = sum(ms for n, t, c, ms in recs if n == "spmm_main_kernel") / reps
+    sp_ms = sum(ms for n, t, c, ms in recs if n in ("spmm_main_kernel", "spmm_panel_kernel")) / reps
     sp_bytes = sp_gather = 0.0
     for n, t, c, ms in recs:
         if n == "spmm_main_kernel":
@@ -154,7 +154,7 @@ def bench_eval(cfg, args):
                                                          "not fit one GPU)" % cfg.d_in) if first_only
                                     else "GCN " + "-".join(map(str, cfg.dims))),
                        "normalised_matrix_and_plan_ms": build_ms},
-            "roofline": {"bound": "hbm", "kernel": "spmm_main_kernel (all widths)", "achieved": sp_bytes / (sp_ms * 1e-3) / 1e9,
+            "roofline": {"bound": "hbm", "kernel": "sparse products (all widths)", "achieved": sp_bytes / (sp_ms * 1e-3) / 1e9,
                          "peak": PEAK_HBM_GBS, "unit": "GB/s", "frac": sp_bytes / (sp_ms * 1e-3) / 1e9 / PEAK_HBM_GBS,
                          "ms_per_pass": sp_ms, "traffic": None,
                          "gather_GBps": sp_gather / (sp_ms * 1e-3) / 1e9},
@@ -243,7 +243,7 @@ def bench_gemm(cfg, args):
         mask = torch.randn((M, N), device=dev, generator=gen) if masked else None
         recs = _timed(ctx, lambda: sg.sgnn_gemm(ctx, ta, tb, A, Bm, None, flags, Cm, mask=mask), reps)
         us = sum(ms for _, _, _, ms in recs) * 1e3 / reps
-        main_us = sum(ms for n, _, _, ms in recs if n == "gemm_kernel") * 1e3 / reps
+        main_us = sum(ms for n, _, _, ms in recs if n in ("gemm_kernel", "gemm_split_kernel")) * 1e3 / reps
         fl = 2.0 * M * N * K
         byt = 4.0 * (M * K + K * N + M * N * (2 if masked else 1))
         out.append({"product": name, "M": M, "N": N, "K": K, "us": us, "gemm_kernel_us": main_us,
