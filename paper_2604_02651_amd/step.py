@@ -53,7 +53,7 @@ class GcnStep:
             raise ValueError("bfloat16 features are read by the first layer's sparse product only: they need fuse_slice "
                              "and a first layer that aggregates first")
         # A transform-first first layer multiplies X[S] by W_1 and X[S]^T by dP: with fp32 operands both go through
-        # the direct-to-LDS kernels, which copy whole 32-column slices of 16-byte aligned rows.  A feature width that is
+        # kernels that take whole 32-column slices of 16-byte aligned rows fastest.  A feature width that is
         # not a multiple of 32 (602) is therefore padded with zero columns, in a copy of X made once here, and W_1 / dW_1
         # live in buffers with as many zero rows; weights[0][0] and dW[0] are views of their first d_in rows.
         self.d_in_padded = dims[0]
