@@ -101,8 +101,8 @@ template <int R, int NT, bool KC, bool GATHER> struct operand {
     static constexpr int NF = KC ? PER : 4 * PER;           // 16-byte loads per thread and slice
     static_assert(KC || PER == 1, "one block of 4 x 4 a thread");
     f32x4 reg[NF];
-    const float *base[KC && GATHER ? PER : 1];              // GATHER && KC: the thread's rows; else the tile's first row
-    int off[KC ? PER : 1];                                  // KC: the thread's rows relative to the tile's; else its first column
+    const float *base[KC ? PER : 1];                        // KC: the thread's rows; else its first element (addresses are 64 bits
+                                                            // throughout: a leading dimension may be as long as a graph has vertices)
     int at;                                                 // where its values go in a plane
     int rows_left;                                          // !KC: rows that exist from the thread's first on
     int32_t next[(!KC && GATHER) ? 4 : 1];                  // row numbers of the next slice
@@ -114,18 +114,15 @@ template <int R, int NT, bool KC, bool GATHER> struct operand {
     {
         const int i = unit(), line = i / 8;
         if constexpr (KC) {
-            if constexpr (!GATHER) base[0] = G + row0 * ld;
 #pragma unroll
             for (int u = 0; u < PER; ++u) {
                 const int64_t r = min(row0 + line + u * (NT / 8), rows - 1);
-                if constexpr (GATHER) base[u] = G + (int64_t)ridx[r] * ld;
-                else off[u] = (int)(r - row0) * (int)ld;
+                base[u] = G + (GATHER ? (int64_t)ridx[r] : r) * ld;
             }
             at = chunk_at(BLOCK, line % T, line / T, (i % 8) >> 1) + (i & 1) * 8;
         } else {
-            base[0] = G + row0;
             rows_left = (int)min(rows - row0 - 4 * line, (int64_t)4);
-            off[0] = 4 * line - (4 - rows_left);
+            base[0] = G + row0 + (4 * line - (4 - rows_left)) + (GATHER ? 0 : 4 * (i % 8) * ld);
             at = chunk_at(BLOCK, (4 * line) % T, (4 * line) / T, (i % 8) >> 1) + (i & 1) * 8;
         }
         indices(ridx, k0, kend);
@@ -146,9 +143,9 @@ template <int R, int NT, bool KC, bool GATHER> struct operand {
 #pragma unroll
         for (int f = 0; f < NF; ++f) {
             const float *p;
-            if constexpr (KC) p = base[GATHER ? f : 0] + k0 + ((GATHER ? 0 : off[f]) + min(kk, left - 4));
-            else if constexpr (GATHER) p = base[0] + (int64_t)next[f] * ld + off[0];
-            else p = base[0] + k0 * ld + (min(kk + f, left - 1) * (int)ld + off[0]);
+            if constexpr (KC) p = base[f] + k0 + min(kk, left - 4);
+            else if constexpr (GATHER) p = base[0] + (int64_t)next[f] * ld;
+            else p = base[0] + k0 * ld + (left == SBK ? f * ld : (min(kk + f, left - 1) - kk) * ld);
             reg[f] = *reinterpret_cast<const f32x4_any *>(p);
         }
     }

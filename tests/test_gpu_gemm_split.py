@@ -71,6 +71,27 @@ def test_short_reduction_without_scratch():
     small.close()
 
 
+@pytest.mark.parametrize("trans", ["NN", "NT", "TN"])
+def test_long_leading_dimensions(trans):
+    # rows of a tile that lie more than 2^31 elements apart (features kept feature-major on a graph of tens of millions of
+    # vertices): 63 steps of 35 M between the rows of a tile, 31 of 70 M between the reduction steps of a slice
+    ta, tb = trans[0] == "T", trans[1] == "T"
+    M, N, K, ld = 64, 60, 32, 35_000_000
+    flat = torch.empty(64 * ld, device=DEV)
+    narrow, wide = flat.view(64, ld), flat.view(32, 2 * ld)
+    A = wide[:, :M] if ta else narrow[:, :K]
+    B = narrow[:N, 1000:1000 + K] if tb else wide[:, 1000:1000 + N]
+    gen = torch.Generator(device=DEV).manual_seed(8)
+    for t in (A, B):
+        t.copy_(torch.randn(t.shape, device=DEV, generator=gen))
+    C = torch.empty((M, N), device=DEV)
+    sg.sgnn_gemm(ctx(), ta, tb, A, B, None, 0, C)
+    A64, B64 = (A.T if ta else A).double(), (B.T if tb else B).double()
+    _check(C, A64, B64, A64 @ B64)
+    del flat, narrow, wide, A, B
+    torch.cuda.empty_cache()
+
+
 @pytest.mark.parametrize("B,d_in,d_out", [(1500, 130, 65), (9000, 602, 70)])
 def test_gathered_rows(B, d_in, d_out):
     # an input layer reads its rows through the sample: X[S] W forward, X[S]^T dP backward
