@@ -34,7 +34,6 @@ typedef float f32x4 __attribute__((ext_vector_type(4)));
 typedef float f32x2 __attribute__((ext_vector_type(2)));
 typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
 typedef __bf16 bf16x2 __attribute__((ext_vector_type(2)));
-typedef unsigned short u16x2 __attribute__((ext_vector_type(2)));
 // 16 bytes at any multiple of four (gfx950 global loads take any alignment)
 typedef float f32x4_any __attribute__((ext_vector_type(4), aligned(4)));
 
@@ -54,7 +53,7 @@ struct split_args {
 };
 
 constexpr int SBK = 32;                                     // slice of the reduction
-constexpr uint16_t TINY = (127 - 112) << 8;                 // bfloat16 pattern of 2^-112 without its sign, shifted left
+constexpr uint32_t TINY = 2u * ((127u - 112u) << 23) - 1u;   // tiny_key() of 2^-112
 
 template <int R> struct plane {
     static constexpr int BLOCK = 32 * SBK * 2 + 64;         // bytes of a block of 32 rows; 64 more, so that row l of different
@@ -77,15 +76,16 @@ __device__ __forceinline__ void split2(float x, float y, uint32_t &p1, uint32_t 
     x -= lo16(p2); y -= hi16(p2);
     p3 = cvt2(x, y);
 }
-__device__ __forceinline__ parts4 split4(const float (&v)[4], u16x2 &tiny)
+// a value's bits without the sign, shifted left, less one: in the order of the magnitudes, but zero is the largest
+__device__ __forceinline__ uint32_t tiny_key(float x) { return 2u * __builtin_bit_cast(uint32_t, x) - 1u; }
+__device__ __forceinline__ parts4 split4(const float (&v)[4], uint32_t &tiny)
 {
     parts4 r;
     split2(v[0], v[1], r.p[0].x, r.p[1].x, r.p[2].x);
     split2(v[2], v[3], r.p[0].y, r.p[1].y, r.p[2].y);
-    // smallest magnitude seen, without the sign and with zero counted as the largest
-    const u16x2 two = {2, 2}, less = {0xffff, 0xffff};
-    tiny = __builtin_elementwise_min(tiny, __builtin_bit_cast(u16x2, r.p[0].x) * two + less);
-    tiny = __builtin_elementwise_min(tiny, __builtin_bit_cast(u16x2, r.p[0].y) * two + less);
+    // smallest key seen: of the values themselves, because a value of up to 2^-134 has a zero for its first part
+    tiny = min(tiny, min(tiny_key(v[0]), tiny_key(v[1])));
+    tiny = min(tiny, min(tiny_key(v[2]), tiny_key(v[3])));
     return r;
 }
 
@@ -166,7 +166,7 @@ template <int R, int NT, bool KC, bool GATHER> struct operand {
             else reg[f] = f < left ? shifted(reg[f], min(4 - rows_left, 4)) : f32x4{0.f, 0.f, 0.f, 0.f};
         }
     }
-    __device__ __forceinline__ void stage(unsigned char *lds, u16x2 &tiny)
+    __device__ __forceinline__ void stage(unsigned char *lds, uint32_t &tiny)
     {
         if (!active()) return;
 #pragma unroll
@@ -212,7 +212,7 @@ __global__ __launch_bounds__(64 * WM * WN, 2) void gemm_split_kernel(split_args 
         for (int j = 0; j < TN; ++j)
 #pragma unroll
             for (int r = 0; r < 16; ++r) acc[i][j][r] = low[i][j][r] = 0.f;
-    u16x2 tiny = {0xffff, 0xffff};
+    uint32_t tiny = 0xffffffffu;
     f32x4 cs = {0.f, 0.f, 0.f, 0.f};                         // column sums of B: the thread's four columns
     const bool do_cs = !BKC && a.colsum && bx == 0;
 
@@ -296,7 +296,7 @@ __global__ __launch_bounds__(64 * WM * WN, 2) void gemm_split_kernel(split_args 
     }
 
     // does the split hold?
-    if (min(tiny[0], tiny[1]) < (uint16_t)(TINY - 1)) small_seen = 1;
+    if (tiny < TINY) small_seen = 1;
     float bad = 0.f;
 #pragma unroll
     for (int i = 0; i < TM; ++i)

@@ -124,6 +124,12 @@ def test_values_the_split_does_not_hold_for(trans):
         ref = As.double() @ Bs.double()
         got = product(As, Bs)
         assert (got.double() - ref).norm() <= 1e-6 * ref.norm() + 2.0 ** -149 * K, (ea, eb)
+    # every value of one operand so small that its first part is zero (up to 2^-134), down to the smallest number there is
+    for e in (-136, -149):
+        small = torch.full_like(A, 2.0 ** e) * torch.where(A > 0, 1.0, -1.0)
+        for As, Bs in ((small, B * 2.0 ** 30), (torch.full_like(A, 2.0 ** 30), torch.full_like(B, 2.0 ** e))):
+            ref = As.double() @ Bs.double()
+            assert (product(As, Bs).double() - ref).norm() <= 1e-6 * ref.norm() and ref.norm() > 0, e
     A[3, 5], A[77, 0], B[7, 100] = float("inf"), float("nan"), -float("inf")
     A[140, 2] = 3.4e38                  # finite, but rounds up to infinity in bfloat16
     B[2] = B[2].clamp(-0.4, 0.4)
