@@ -116,7 +116,8 @@ __global__ __launch_bounds__(SPMM_NT, 4) void spmm_panel_kernel(spmm_panel_args 
         const int col0 = p * W + k * VEC, colb = min(col0, a.d - VEC), skip = col0 - colb;
         const bool wide = a.wide_epi && skip == 0;
         const char *__restrict__ xb = reinterpret_cast<const char *>(X);
-        const uint32_t row_bytes = (uint32_t)(a.ldx * (int64_t)sizeof(XT)), col_bytes = (uint32_t)colb * (uint32_t)sizeof(XT);
+        const int64_t row_bytes = a.ldx * (int64_t)sizeof(XT);          // below 2^32 if OFF32
+        const uint32_t col_bytes = (uint32_t)colb * (uint32_t)sizeof(XT);
 
         float acc[VEC];
 #pragma unroll
@@ -128,14 +129,14 @@ __global__ __launch_bounds__(SPMM_NT, 4) void spmm_panel_kernel(spmm_panel_args 
                 c = __builtin_nontemporal_load(a.colidx + e + lane);
                 v = __builtin_nontemporal_load(a.val + e + lane);
                 if (a.row_index) c = a.row_index[c];
-                if constexpr (OFF32) c = (int32_t)((uint32_t)c * row_bytes);
+                if constexpr (OFF32) c = (int32_t)((uint32_t)c * (uint32_t)row_bytes);
             }
         };
         auto load = [&](int32_t c, float v, int j, u32x4_any &q, float &av) {
             const int32_t src = __builtin_amdgcn_ds_bpermute(j * 4, c);
             av = __builtin_bit_cast(float, __builtin_amdgcn_ds_bpermute(j * 4, __builtin_bit_cast(int, v)));
             if constexpr (OFF32) q = *reinterpret_cast<const u32x4_any *>(xb + (uint32_t)((uint32_t)src + col_bytes));
-            else q = *reinterpret_cast<const u32x4_any *>(xb + ((int64_t)src * (int64_t)row_bytes + col_bytes));
+            else q = *reinterpret_cast<const u32x4_any *>(xb + ((int64_t)src * row_bytes + col_bytes));
         };
         // acc += the n <= 64 entries that the lanes hold: group g takes entries g, g + NE, ...
         auto gather = [&](int32_t c, float v, int n) {

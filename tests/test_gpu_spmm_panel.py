@@ -127,3 +127,19 @@ def test_infinities_stay_in_their_rows(matrix, x_dtype):
     assert np.array_equal(np.isnan(got), np.isnan(ref)) and np.array_equal(np.isinf(got), np.isinf(ref))
     fine = np.isfinite(ref)
     assert rel_err(got[fine], ref[fine]) < TOL_F32
+
+
+def test_rows_of_more_than_4_gb():
+    rows, cols, d, ld = 900, 3, 40, (1 << 30) + 8
+    rng = np.random.default_rng(11)
+    rp = np.arange(rows + 1) * 120
+    ci = rng.integers(0, cols, rp[-1]).astype(np.int32)
+    v = rng.standard_normal(len(ci)).astype(np.float32)
+    A = sg.Csr.from_arrays(rows, cols, rp, ci, v, DEV)
+    X = torch.empty(cols * ld, device=DEV).view(cols, ld)[:, :d]
+    X.copy_(torch.randn((cols, d), generator=torch.Generator().manual_seed(12)))
+    out = torch.empty((rows, d), device=DEV)
+    sg.sgnn_spmm(ctx(), A, X, out)
+    assert rel_err(out.cpu().numpy(), oracle.spmm(rp, ci, v, _np(X))) < TOL_F32
+    del X
+    torch.cuda.empty_cache()
