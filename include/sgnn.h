@@ -284,7 +284,8 @@ int sgnn_gcn_fwd(sgnn_ctx *ctx, const sgnn_csr *A, const sgnn_mat *H, const sgnn
  *         T^T dZ itself, e.g. on another stream: with SGNN_DY_MASKED or without SGNN_RELU dZ is dY);
  *         dbias out fp32[d_out] or NULL
  * The reduction over the B rows in dW and dbias uses a fixed split and a fixed summation order:
- * results are bit-reproducible from run to run.
+ * results are bit-reproducible from run to run.  The split follows from the shape alone in every context
+ * reserved for it; with less scratch an fp32 product takes a smaller number of ranges, which also follows from the shape.
  */
 int sgnn_gcn_bwd(sgnn_ctx *ctx, const sgnn_csr *A_T, const sgnn_mat *T, const sgnn_mat *W,
                  const sgnn_mat *Y, const sgnn_mat *dY, int flags, sgnn_mat *dH, const sgnn_mat *H_in,

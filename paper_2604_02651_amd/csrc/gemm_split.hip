@@ -468,23 +468,34 @@ int sgnn_launch_gemm_split(sgnn_ctx *ctx, int ta, int tb, int64_t M, int64_t N, 
     else if (ta ? K >= 8192 : (int64_t)cdiv(M, 128) * cdiv(N, 64) >= 256) bm = 128;
     // A long reduction onto few tiles is split, to at most 128 ranges of 128 steps or more (each writes its partial product, and
     // a second kernel reads them all: 256 x 256 x 32768 43 us with 128 ranges, 59 with 256; 608 x 256 x 65536 277 us with 42,
-    // 205 with 128).
+    // 205 with 128).  The number of ranges, and with it the order of the sums, depends on the shape alone wherever there is
+    // scratch for them.  Where there is not, it is the number that gives each compute unit one 128-row tile, for which 4096 steps and
+    // more need scratch, or one range for shorter reductions: never what the scratch happens to hold.
     const int64_t tiles = (int64_t)cdiv(M, (uint64_t)bm) * cdiv(N, (uint64_t)bn);
     float *cs_partial = nullptr;
+    const size_t ws_off = ws->off;
     if (ta && tiles < 256 && K >= 256 && !bias && !relu && !mask) {
-        int64_t splits = std::min<int64_t>(M * N <= 16384 ? 256 : 128, std::min<int64_t>(K / 128, std::max<int64_t>(768 / tiles, 1)));
-        // reductions that short do without the scratch if there is none
-        const size_t per = ((size_t)M * N + N) * sizeof(float);
-        if (K < 4096) splits = std::min<int64_t>(splits, ws->base && ws->cap > ws->off + 1024 ? (int64_t)((ws->cap - ws->off - 1024) / per) : 1);
-        if (splits > 1) {
-            a.kps = (int64_t)cdiv(cdiv(K, splits), SBK) * SBK;
+        const int64_t tiles128 = (int64_t)cdiv(M, 128) * cdiv(N, N > 64 ? 128 : 64);
+        const int64_t full = std::min<int64_t>(M * N <= 16384 ? 256 : 128, std::min<int64_t>(K / 128, std::max<int64_t>(768 / tiles, 1)));
+        const int64_t few = K >= 4096 ? std::min<int64_t>(full, cdiv(256, (uint64_t)tiles128)) : 1;
+        for (int64_t want : {full, few}) {
+            ws->off = ws_off;
+            ws->ok = true;
+            a.kps = (int64_t)cdiv(cdiv(K, want), SBK) * SBK;
             a.splits = cdiv(K, a.kps);
-        }
-        if (a.splits > 1) {
+            if (a.splits <= 1) break;
             a.partial = ws->get<float>((size_t)a.splits * M * N);
             if (b_colsum) a.colsum = cs_partial = ws->get<float>((size_t)a.splits * N);
-            if (!ws->ok) return sgnn_fail(ctx, SGNN_ERR_CAPACITY, "sgnn_gemm: scratch too small for the split reduction: call sgnn_ctx_reserve");
+            if (ws->ok) break;
         }
+        if (a.splits <= 1) {
+            a.kps = K;
+            a.splits = 1;
+            a.partial = nullptr;
+            a.colsum = b_colsum;
+            cs_partial = nullptr;
+        } else if (!ws->ok)
+            return sgnn_fail(ctx, SGNN_ERR_CAPACITY, "sgnn_gemm: scratch too small for the split reduction: call sgnn_ctx_reserve");
     }
     int rc;
     if (bm == 256) rc = launch_split<256, 128, 4, 2>(ctx, ta, tb, a, st);
@@ -492,6 +503,9 @@ int sgnn_launch_gemm_split(sgnn_ctx *ctx, int ta, int tb, int64_t M, int64_t N, 
     else if (bm == 128) rc = launch_split<128, 64, 2, 2>(ctx, ta, tb, a, st);
     else rc = launch_split<64, 64, 2, 2>(ctx, ta, tb, a, st);
     if (rc) return rc;
-    if (a.splits > 1) return sgnn_launch_splitk_reduce(ctx, a.partial, (int)a.splits, M, N, C, ldc, cs_partial, cs_partial ? b_colsum : nullptr, st);
-    return SGNN_OK;
+    if (a.splits > 1) {
+        rc = sgnn_launch_splitk_reduce(ctx, a.partial, (int)a.splits, M, N, C, ldc, cs_partial, cs_partial ? b_colsum : nullptr, st);
+        ws->off = ws_off;      // what the caller launches next on this stream may have the scratch
+    }
+    return rc;
 }

@@ -71,6 +71,50 @@ def test_short_reduction_without_scratch():
     small.close()
 
 
+def _context(scratch_bytes):
+    """A context whose scratch is that and less than 1 MB more (reserve() takes 1 KB for every square of the width)."""
+    c = sg.Context(0)
+    c.reserve(1, 1, 1, max(1, int((scratch_bytes / 1024) ** 0.5)))
+    return c
+
+
+def _tn(c, A, B):
+    C = torch.empty((A.shape[1], B.shape[1]), device=DEV)
+    sg.sgnn_gemm(c, True, False, A, B, None, 0, C)
+    return C
+
+
+def test_scratch_limits():
+    big = _context(1 << 28)
+    # 256 tiles of 128 x 128 fill the chip without ranges, and 169 need two of them (20.5 MB): neither call needs more scratch
+    for n, scratch in ((2048, 0), (1600, 22 << 20)):
+        A, B = _operand(8192, n, 5), _operand(8192, n, 6)
+        c = _context(scratch)
+        _check(_tn(c, A, B), A.double().T, B.double(), A.double().T @ B.double())
+        c.close()
+    # 4096 steps and more onto few tiles are refused without scratch
+    A, B = _operand(8192, 256, 5), _operand(8192, 256, 6)
+    c = _context(0)
+    with pytest.raises(sg.SgnnError):
+        _tn(c, A, B)
+    c.close()
+    # the order of the sums does not follow the scratch: the same bits in every context that holds the ranges (300 x 300 x 3000:
+    # 8.3 MB), and those of a single range in every context that does not
+    for n, K, ample, scarce in ((300, 3000, 9 << 20, (0, 1 << 20, 4 << 20)), (257, 8195, 40 << 20, ())):
+        A, B = _operand(K, n, 5), _operand(K, n, 6)
+        c = _context(ample)
+        assert torch.equal(_tn(c, A, B), _tn(big, A, B))
+        c.close()
+        single = None
+        for scratch in scarce:
+            c = _context(scratch)
+            got = _tn(c, A, B)
+            single = got if single is None else single
+            assert torch.equal(got, single)
+            c.close()
+    big.close()
+
+
 @pytest.mark.parametrize("trans", ["NN", "NT", "TN"])
 def test_long_leading_dimensions(trans):
     # rows of a tile that lie more than 2^31 elements apart (features kept feature-major on a graph of tens of millions of
