@@ -462,23 +462,31 @@ int sgnn_launch_gemm_split(sgnn_ctx *ctx, int ta, int tb, int64_t M, int64_t N, 
     // The widest tile of which there are enough for the 256 compute units: a 256 x 128 tile splits an element of A for 128
     // columns and one of B for 256 rows, a 64 x 64 tile each for 64.  32768 x 256 x 256, us with 256 x 128 / 128 x 128 tiles:
     // 33 / 42; 65536 x 256 x 608 133 / 168.  Long reductions (A^T B) take it as well, 256 x 256 x 32768 43 / 50.
+    const bool plain = !bias && !relu && !mask;
+    const bool long_ab = !ta && plain && K >= 4096;      // A B and A B^T too, where the tiles alone do not fill the chip
     int64_t bm = 64, bn = 64;
     if (N > 64 && (ta ? M > 128 && K >= 8192 : (int64_t)cdiv(M, 256) * cdiv(N, 128) >= 160)) bm = 256, bn = 128;
     else if (N > 64 && (ta ? M > 64 && K >= 8192 : (int64_t)cdiv(M, 128) * cdiv(N, 128) >= 160)) bm = 128, bn = 128;
-    else if (ta ? K >= 8192 : (int64_t)cdiv(M, 128) * cdiv(N, 64) >= 256) bm = 128;
+    else if (long_ab && M > 128) bm = N > 64 ? 256 : 128, bn = N > 64 ? 128 : 64;
+    else if (!long_ab && (ta ? K >= 8192 : (int64_t)cdiv(M, 128) * cdiv(N, 64) >= 256)) bm = 128;
     // A long reduction onto few tiles is split, to at most 128 ranges of 128 steps or more (each writes its partial product, and
     // a second kernel reads them all: 256 x 256 x 32768 43 us with 128 ranges, 59 with 256; 608 x 256 x 65536 277 us with 42,
-    // 205 with 128).  The number of ranges, and with it the order of the sums, depends on the shape alone wherever there is
-    // scratch for them.  Where there is not, it is the number that gives each compute unit one 128-row tile, for which 4096 steps and
-    // more need scratch, or one range for shorter reductions: never what the scratch happens to hold.
+    // 205 with 128).  A B and A B^T take as many as give every compute unit a tile, a multiple of eight (the ranges are dealt to
+    // the eight XCDs): 256 x 256 x 65536 67 us, 2010 unsplit; 1024 x 256 x 8416 46 with 32 ranges, 58 with 64 and 16, 263 unsplit;
+    // 8192 x 256 x 8192 251 with 8, 297 with 12; 100 x 40 x 30000 24 with 128 ranges of 64 x 64 tiles, 28 with 234 of 128 x 64.
+    // The number of ranges, and with it the order of the sums, depends on the shape alone wherever there is
+    // scratch for them.  Where there is not, it is the number that gives each compute unit one 128-row tile, for which an A^T B of 4096
+    // steps and more needs scratch, or one range otherwise: never what the scratch happens to hold.
     const int64_t tiles = (int64_t)cdiv(M, (uint64_t)bm) * cdiv(N, (uint64_t)bn);
     float *cs_partial = nullptr;
     const size_t ws_off = ws->off;
-    if (ta && tiles < 256 && K >= 256 && !bias && !relu && !mask) {
+    if (plain && tiles < 256 && (ta ? K >= 256 : long_ab)) {
         const int64_t tiles128 = (int64_t)cdiv(M, 128) * cdiv(N, N > 64 ? 128 : 64);
-        const int64_t full = std::min<int64_t>(M * N <= 16384 ? 256 : 128, std::min<int64_t>(K / 128, std::max<int64_t>(768 / tiles, 1)));
+        const int64_t wanted = ta ? std::max<int64_t>(768 / tiles, 1) : (int64_t)cdiv(cdiv(256, (uint64_t)tiles), 8) * 8;
+        const int64_t full = std::min<int64_t>(M * N <= 16384 ? 256 : 128, std::min<int64_t>(K / 128, wanted));
         const int64_t few = K >= 4096 ? std::min<int64_t>(full, cdiv(256, (uint64_t)tiles128)) : 1;
-        for (int64_t want : {full, few}) {
+        const int64_t least = ta ? few : 1;
+        for (int64_t want : {full, few, least}) {
             ws->off = ws_off;
             ws->ok = true;
             a.kps = (int64_t)cdiv(cdiv(K, want), SBK) * SBK;

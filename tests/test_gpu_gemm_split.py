@@ -71,6 +71,30 @@ def test_short_reduction_without_scratch():
     small.close()
 
 
+@pytest.mark.parametrize("tb", [False, True])
+@pytest.mark.parametrize("M,N,K", [(256, 256, 65536), (257, 129, 4097), (1024, 256, 8416), (1000, 66, 5003), (300, 64, 9001), (128, 200, 4099),
+                                   (64, 64, 60000), (33, 40, 8195), (5000, 200, 4160)])
+def test_long_reductions_onto_few_tiles(M, N, K, tb):
+    ctx().reserve(1 << 20, 1 << 20, 65536, 640, 1 << 20)
+    A, B = _operand(M, K, 1), _operand(N, K, 2) if tb else _operand(K, N, 2)
+    C, again = torch.full((M + 1, N + 2), 9.0, device=DEV), torch.empty((M, N), device=DEV)
+    ctx().profile(True)
+    sg.sgnn_gemm(ctx(), False, tb, A, B, None, 0, C[:M, :N])
+    kernels = [k[0] for k in ctx().profile_read()]
+    ctx().profile(False)
+    assert kernels == ["gemm_split_kernel", "splitk_reduce_kernel"]          # one workgroup would walk all of K otherwise
+    B64 = B.double().T if tb else B.double()
+    _check(C[:M, :N], A.double(), B64, A.double() @ B64)
+    assert torch.all(C[M] == 9.0) and torch.all(C[:, N:] == 9.0)
+    sg.sgnn_gemm(ctx(), False, tb, A, B, None, 0, again)
+    assert torch.equal(again, C[:M, :N])
+    if K <= 5003:                # without scratch it is not split: one chain of K / 16 sums, to which the bounds of _check() still apply
+        none = sg.Context(0)
+        sg.sgnn_gemm(none, False, tb, A, B, None, 0, again)
+        _check(again, A.double(), B64, A.double() @ B64)
+        none.close()
+
+
 def _context(scratch_bytes):
     """A context whose scratch is that and less than 1 MB more (reserve() takes 1 KB for every square of the width)."""
     c = sg.Context(0)
