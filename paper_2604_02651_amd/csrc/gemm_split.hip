@@ -84,8 +84,8 @@ __device__ __forceinline__ parts4 split4(const float (&v)[4], uint32_t &tiny)
     split2(v[0], v[1], r.p[0].x, r.p[1].x, r.p[2].x);
     split2(v[2], v[3], r.p[0].y, r.p[1].y, r.p[2].y);
     // smallest key seen: of the values themselves, because a value of up to 2^-134 has a zero for its first part
-    tiny = min(tiny, min(tiny_key(v[0]), tiny_key(v[1])));
-    tiny = min(tiny, min(tiny_key(v[2]), tiny_key(v[3])));
+    asm("v_min3_u32 %0, %0, %1, %2" : "+v"(tiny) : "v"(tiny_key(v[0])), "v"(tiny_key(v[1])));
+    asm("v_min3_u32 %0, %0, %1, %2" : "+v"(tiny) : "v"(tiny_key(v[2])), "v"(tiny_key(v[3])));
     return r;
 }
 
