@@ -101,7 +101,7 @@ template <int R, int NT, bool KC, bool GATHER> struct operand {
     static constexpr int NF = KC ? PER : 4 * PER;           // 16-byte loads per thread and slice
     static_assert(KC || PER == 1, "one block of 4 x 4 a thread");
     f32x4 reg[NF];
-    const float *base[KC ? PER : 1];                        // KC: the thread's rows; else its first element (addresses are 64 bits
+    const float *base[KC ? PER : 1];                        // KC: the thread's rows; else its first column (addresses are 64 bits
                                                             // throughout: a leading dimension may be as long as a graph has vertices)
     int at;                                                 // where its values go in a plane
     int rows_left;                                          // !KC: rows that exist from the thread's first on
@@ -122,7 +122,7 @@ template <int R, int NT, bool KC, bool GATHER> struct operand {
             at = chunk_at(BLOCK, line % T, line / T, (i % 8) >> 1) + (i & 1) * 8;
         } else {
             rows_left = (int)min(rows - row0 - 4 * line, (int64_t)4);
-            base[0] = G + row0 + (4 * line - (4 - rows_left)) + (GATHER ? 0 : 4 * (i % 8) * ld);
+            base[0] = G + row0 + (4 * line - (4 - rows_left));
             at = chunk_at(BLOCK, (4 * line) % T, (4 * line) / T, (i % 8) >> 1) + (i & 1) * 8;
         }
         indices(ridx, k0, kend);
@@ -145,7 +145,8 @@ template <int R, int NT, bool KC, bool GATHER> struct operand {
             const float *p;
             if constexpr (KC) p = base[f] + k0 + min(kk, left - 4);
             else if constexpr (GATHER) p = base[0] + (int64_t)next[f] * ld;
-            else p = base[0] + k0 * ld + (left == SBK ? f * ld : (min(kk + f, left - 1) - kk) * ld);
+            else p = reinterpret_cast<const float *>(reinterpret_cast<const char *>(base[0] + k0 * ld) +
+                                                     (uint64_t)(uint32_t)min(kk + f, left - 1) * (uint64_t)(4 * ld));
             reg[f] = *reinterpret_cast<const f32x4_any *>(p);
         }
     }
