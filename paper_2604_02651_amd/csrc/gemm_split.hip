@@ -462,14 +462,19 @@ int sgnn_launch_gemm_split(sgnn_ctx *ctx, int ta, int tb, int64_t M, int64_t N, 
     a.relu = relu; a.mask = mask; a.ldm = ldm; a.kps = K; a.splits = 1; a.colsum = b_colsum;
     // The widest tile of which there are enough for the 256 compute units: a 256 x 128 tile splits an element of A for 128
     // columns and one of B for 256 rows, a 64 x 64 tile each for 64.  32768 x 256 x 256, us with 256 x 128 / 128 x 128 tiles:
-    // 33 / 42; 65536 x 256 x 608 133 / 168.  Long reductions (A^T B) take it as well, 256 x 256 x 32768 43 / 50.
+    // 33 / 42; 65536 x 256 x 608 133 / 168.  A^T B, whose operands both lie [reduction][rows], from 128 tiles on: 4096 x 4096 x 4096
+    // 862 / 1098 (64 x 64 tiles 1805), 20000 x 200 x 300 44 / 61 (61); with 128 tiles, 2048 x 2048 x 2048, 156 / 138 (285).
+    // Long reductions make up for few tiles with ranges, so A^T B takes the wide tile there as well, 256 x 256 x 32768 43 / 50, and
+    // 128 x 64 from half that length on: 608 x 256 x 8000 50 us, 67 with 64 x 64, which is only better where it holds all
+    // of M (40 x 256 x 50000 43 us, 52).
     const bool plain = !bias && !relu && !mask;
     const bool long_ab = !ta && plain && K >= 4096;      // A B and A B^T too, where the tiles alone do not fill the chip
+    const int64_t t256 = (int64_t)cdiv(M, 256) * cdiv(N, 128), t128 = (int64_t)cdiv(M, 128) * cdiv(N, 128);
     int64_t bm = 64, bn = 64;
-    if (N > 64 && (ta ? M > 128 && K >= 8192 : (int64_t)cdiv(M, 256) * cdiv(N, 128) >= 160)) bm = 256, bn = 128;
-    else if (N > 64 && (ta ? M > 64 && K >= 8192 : (int64_t)cdiv(M, 128) * cdiv(N, 128) >= 160)) bm = 128, bn = 128;
+    if (N > 64 && (ta ? M > 128 && (K >= 8192 || t256 > 128) : t256 >= 160)) bm = 256, bn = 128;
+    else if (N > 64 && (ta ? M > 64 && (K >= 8192 || t128 >= 160) : t128 >= 160)) bm = 128, bn = 128;
     else if (long_ab && M > 128) bm = N > 64 ? 256 : 128, bn = N > 64 ? 128 : 64;
-    else if (!long_ab && (ta ? K >= 8192 : (int64_t)cdiv(M, 128) * cdiv(N, 64) >= 256)) bm = 128;
+    else if (!long_ab && ((int64_t)cdiv(M, 128) * cdiv(N, 64) >= 256 || (ta && M > 64 && K >= 4096))) bm = 128;
     // A long reduction onto few tiles is split, to at most 128 ranges of 128 steps or more (each writes its partial product, and
     // a second kernel reads them all: 256 x 256 x 32768 43 us with 128 ranges, 59 with 256; 608 x 256 x 65536 277 us with 42,
     // 205 with 128).  A B and A B^T take as many as give every compute unit a tile, a multiple of eight (the ranges are dealt to
@@ -481,7 +486,8 @@ int sgnn_launch_gemm_split(sgnn_ctx *ctx, int ta, int tb, int64_t M, int64_t N, 
     const int64_t tiles = (int64_t)cdiv(M, (uint64_t)bm) * cdiv(N, (uint64_t)bn);
     float *cs_partial = nullptr;
     const size_t ws_off = ws->off;
-    if (plain && tiles < 256 && (ta ? K >= 256 : long_ab)) {
+    const bool filled = ta && bn == 128 && K < 8192;     // wide tiles that were taken for their number: 20000 x 200 x 300 124 us in two ranges
+    if (plain && tiles < 256 && !filled && (ta ? K >= 256 : long_ab)) {
         const int64_t tiles128 = (int64_t)cdiv(M, 128) * cdiv(N, N > 64 ? 128 : 64);
         const int64_t wanted = ta ? std::max<int64_t>(768 / tiles, 1) : (int64_t)cdiv(cdiv(256, (uint64_t)tiles), 8) * 8;
         const int64_t full = std::min<int64_t>(M * N <= 16384 ? 256 : 128, std::min<int64_t>(K / 128, wanted));

@@ -61,6 +61,23 @@ def test_weight_gradient_with_column_sums(M, N, K):
     assert torch.equal(again, C) and torch.equal(cs2, cs)                    # bit-reproducible
 
 
+@pytest.mark.parametrize("M,N,K,tile", [(33025, 129, 70, "256x128"), (20000, 200, 300, "256x128"), (2040, 1930, 35, "128x128"), (21001, 65, 33, "128x128"), (36000, 64, 65, "128x64"),
+                                        (300, 200, 5003, "128x64"), (65, 66, 4097, "128x64"), (40, 256, 9001, "64x64")])
+def test_weight_gradient_tiles(M, N, K, tile):
+    # short reductions onto many tiles, middling ones onto few, results of up to 64 rows
+    ctx().reserve(1 << 20, 1 << 20, 65536, 640, 1 << 20)
+    A, B = _operand(K, M, 5), _operand(K, N, 6)
+    C, cs = torch.full((M + 1, N + 2), 9.0, device=DEV), torch.empty(N, device=DEV)
+    ctx().profile(True)
+    sg.sgnn_gemm(ctx(), True, False, A, B, None, 0, C[:M, :N], b_colsum=cs)
+    kernels = ctx().profile_read()
+    ctx().profile(False)
+    assert kernels[0][1].split()[1] == tile and (len(kernels) == 2) == (M < 2000)          # ranges for the small results only
+    _check(C[:M, :N], A.double().T, B.double(), A.double().T @ B.double())
+    assert rel_err(cs.cpu().numpy(), B.double().sum(0).cpu().numpy()) < TOL_F32
+    assert torch.all(C[M] == 9.0) and torch.all(C[:, N:] == 9.0)
+
+
 def test_short_reduction_without_scratch():
     # a reduction below 4096 steps needs none: it is then not split
     small = sg.Context(0)
