@@ -1418,18 +1418,17 @@ __global__ __launch_bounds__(256) void splitk_reduce_kernel(const float *__restr
         // the threads behind the matrix add up the column sums of B, split by split
         const int64_t col = i - MN;
         if (cs_partial && col < N) {
-            // eight loads in flight, the same fixed order of additions every time
-            float t = 0.f;
-            int z = 0;
-            for (; z + 8 <= splits; z += 8) {
+            // eight chains, combined in a fixed order: one chain over the 128 ranges of a layer of 32768 rows had a
+            // larger error than the 64 ranges that such layers were cut into before
+            float t[8] = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
+            for (int z = 0; z < splits; z += 8) {
                 float x[8];
 #pragma unroll
-                for (int u = 0; u < 8; ++u) x[u] = cs_partial[(int64_t)(z + u) * N + col];
+                for (int u = 0; u < 8; ++u) x[u] = cs_partial[(int64_t)min(z + u, splits - 1) * N + col];
 #pragma unroll
-                for (int u = 0; u < 8; ++u) t += x[u];
+                for (int u = 0; u < 8; ++u) t[u] += z + u < splits ? x[u] : 0.f;
             }
-            for (; z < splits; ++z) t += cs_partial[(int64_t)z * N + col];
-            cs_out[col] = t;
+            cs_out[col] = ((t[0] + t[1]) + (t[2] + t[3])) + ((t[4] + t[5]) + (t[6] + t[7]));
         }
         return;
     }

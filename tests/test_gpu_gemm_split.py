@@ -78,6 +78,18 @@ def test_weight_gradient_tiles(M, N, K, tile):
     assert torch.all(C[M] == 9.0) and torch.all(C[:, N:] == 9.0)
 
 
+def test_column_sums_over_many_ranges():
+    # 128 ranges of 256 steps, each with one and the same sum: added one after the other they are off by 32 units of 2^-24, because
+    # the roundings go the same way for long.  Eight chains of 16 and three sums of those: at most 18 roundings of half a unit
+    p = 1.0499153137207031
+    A, B = _operand(32768, 256, 5), torch.zeros((32768, 256), device=DEV)
+    B[::256] = p
+    C, cs = torch.empty((256, 256), device=DEV), torch.empty(256, device=DEV)
+    ctx().reserve(1 << 20, 1 << 20, 65536, 640, 1 << 20)
+    sg.sgnn_gemm(ctx(), True, False, A, B, None, 0, C, b_colsum=cs)
+    assert torch.all((cs.double() - 128 * p).abs() <= 18 * 2.0 ** -24 * 128 * p)
+
+
 def test_short_reduction_without_scratch():
     # a reduction below 4096 steps needs none: it is then not split
     small = sg.Context(0)
