@@ -864,16 +864,15 @@ int launch_vc(sgnn_ctx *ctx, const sgnn_csr *A, const XT *X, int64_t ldx, const 
                              ws->off);
         // wavefronts that take pieces: 2048, more for matrices with many entries (about 32 pieces of 64 entries
         // each if every entry sat in a long row); those that find no piece leave at once
-        const uint64_t want = mean_limit ? SPMM_PIECE_WAVES : std::min<uint64_t>(std::max<uint64_t>(A->capacity / 2048, SPMM_PIECE_WAVES), 65536);
+        const uint64_t want = std::min<uint64_t>(std::max<uint64_t>(A->capacity / 2048, SPMM_PIECE_WAVES), 65536);
         n_piece_waves = cdiv(std::min<uint64_t>(max_chunks, want), SPMM_NT / 64) * (SPMM_NT / 64);
     }
     // The host sizes the grid from the capacity (the entry count is on the device), which for a sparse mini-batch is many
     // times the true count: most of the workgroups of such a launch would find no block of rows and leave at once, and
     // dispatching a quarter of a million of them cost a third of the kernel's time.  16384 workgroups fill the machine
     // several times over; the wavefronts stride over whatever is left.
-    // (a quarter of that with the cross-entropy epilogue, where every workgroup leaves a row of partial sums for the final kernel,
-    // and of a launch that will most likely leave at once because the panel kernel takes the matrix)
-    const unsigned row_blocks = std::min<unsigned>(cdiv(A->rows, rows_per_block), XENT || mean_limit ? 4096u : 16384u);
+    // (with the cross-entropy epilogue every workgroup leaves a row of partial sums for the final kernel: a quarter of that)
+    const unsigned row_blocks = std::min<unsigned>(cdiv(A->rows, rows_per_block), XENT ? 4096u : 16384u);
     const unsigned grid = n_piece_waves / (SPMM_NT / 64) + row_blocks;
     if (XENT) {
         ep.loss_partial = ws->get<float>(grid);
