@@ -964,7 +964,7 @@ static int launch_x(sgnn_ctx *ctx, const sgnn_csr *A, const XT *X, int64_t ldx, 
         ws_alloc w2 = *ws;      // the two kernels share the scratch of the partial rows
         const int rc = launch_panel<XT>(ctx, A, X, ldx, row_index, (int)d, out, ldo, ep, &w2, st);
         if (rc) return rc;
-        mean_limit = SPMM_PANEL_MEAN;
+        mean_limit = spmm_panel_mean<XT>(A, d);
     }
     if (vec == 4) return launch_v<4, XT>(ctx, A, X, ldx, row_index, (int)d, out, ldo, ep, ws, st, mean_limit);
     if (vec == 2) return launch_v<2, XT>(ctx, A, X, ldx, row_index, (int)d, out, ldo, ep, ws, st, mean_limit);

@@ -29,6 +29,7 @@ struct spmm_panel_args {
     int d;
     int panels, interleave;      // interleave: how many panels are worked on at a time (1, 2, 4 or 8, divides panels)
     const uint32_t *n_chunks;    // plan header
+    uint32_t mean_limit;         // entries a row from which on the matrix is this kernel's
     uint32_t max_chunks;
     const uint2 *desc;
     uint32_t *ticket;
@@ -39,15 +40,33 @@ struct spmm_panel_args {
     int wide_epi;                // out, mask and add allow 16-byte (fp32) / 8-element accesses at every column that is a multiple of VEC
 };
 
-// Which matrices go this way: those with 12 entries a row or more.  The count itself is on the device; the host tells by
-// the capacity, which for a mini-batch matrix is twice the expected entries, sixteen more a row and 65536 more.
-// Measured, us here / with spmm_main_kernel, 262144 rows: 32 entries a row, fp32, 47 / 100 / 256 columns 220 / 386 / 821
-// against 378 / 496 / 981, bf16 256 columns 425 against 570; 16 a row 161 / 233 / 492 against 198 / 261 / 525, bf16 273
-// against 309; 8 a row 149 against 136 (fp32, 100), bf16 192 against 175: the reduction across the groups of lanes and the
-// row-by-row walk cost more than they save there.
-constexpr uint32_t SPMM_PANEL_MEAN = 12;
+// Which matrices go this way: those with 13 entries a row or more, 32 or more where rows of X are 512 bytes and longer, there are
+// 32768 of them and X is under 96 MB.  The count itself is on the device; the host launches both kernels if the capacity is
+// 40 entries a row and 65536 more, which the capacity of a mini-batch matrix (twice the expected entries, sixteen more a
+// row and 65536 more) is from a mean of 12 on, or 60 a row (a mean of 22) under 8192 rows, where the second launch is a fifth of
+// the product: 1024 x 16 and 4096 x 20 19 us with both launches, whichever kernel works, 15 with one.  So a
+// matrix whose capacity is its entries takes the kernel from a mean of 40 (60) on.
+// Measured on R-MAT matrices, us here / with spmm_main_kernel:
+//   rows x mean     fp32 256 cols   bf16 256      fp32 100      fp32 47       bf16 64
+//   4096 x 80       39 / 56         44 / 56       28 / 50       21 / 48       21 / 49
+//   16384 x 40      78 / 102        85 / 98       52 / 83       34 / 76       35 / 76
+//   16384 x 13      40 / 43         43 / 39       27 / 35       23 / 32       24 / 33
+//   65536 x 24      186 / 166       168 / 135     107 / 111     84 / 87       88 / 91
+//   65536 x 12.5    127 / 101       118 / 82      73 / 70       62 / 63       65 / 63
+//   262144 x 24     630 / 742       347 / 417     304 / 361     225 / 281     213 / 283
+//   262144 x 16     483 / 517       275 / 297     236 / 252     197 / 198     195 / 199
+//   262144 x 12.5   428 / 415       257 / 243     210 / 203     187 / 164     186 / 166
+// Most rows of such a matrix are much shorter than the mean: the reduction across the groups of lanes and the row-by-row walk cost
+// more than they save there, most of all with one group or two (long rows of X), unless main's gathers miss the caches.
+// A wavefront alone adds up the partial rows of a hub row, one after the other.  65536 rows of 8 and 3000 of 180 more,
+// 47 fp32 columns: 65 / 55, the largest loss that is left.
+constexpr uint32_t spmm_panel_room(uint32_t rows) { return rows < 8192 ? 60 : 40; }
 constexpr int SPMM_PANEL_MAX = 16;
-
+template <typename XT> uint32_t spmm_panel_mean(const sgnn_csr *A, int64_t d)
+{
+    const uint64_t row = (uint64_t)d * sizeof(XT);
+    return row >= 512 && A->rows >= 32768 && row * A->cols < (96ull << 20) ? 32u : 13u;
+}
 
 // Plan pieces that make up an item of a long row of `nch` pieces of `plen` entries: up to 1024 entries, fewer on a matrix with so few
 // pieces that they would not give every wavefront of the machine one.  A row with fewer pieces than there are panels is one
@@ -101,7 +120,7 @@ template <int G> __device__ __forceinline__ float group_sum(float x)
 template <int G, typename XT, bool OFF32>
 __global__ __launch_bounds__(SPMM_NT, 4) void spmm_panel_kernel(spmm_panel_args a, const XT *__restrict__ X, spmm_epi ep)
 {
-    if (a.n_chunks[3] < SPMM_PANEL_MEAN) return;       // short rows after all: spmm_main_kernel's matrix
+    if (a.n_chunks[3] < a.mean_limit) return;          // short rows after all: spmm_main_kernel's matrix
     constexpr int VEC = panel_vec<XT>::VEC, NE = 64 / G, W = G * VEC;
     constexpr int U = 8;                               // gathers in flight per wavefront, 1 KB each
     const int lane = threadIdx.x & 63, k = lane % G, g = lane / G;
@@ -321,7 +340,7 @@ __global__ __launch_bounds__(SPMM_NT, 4) void spmm_panel_kernel(spmm_panel_args 
 
 template <typename XT> bool spmm_panel_wanted(const sgnn_csr *A, int64_t d)
 {
-    return A->capacity >= (uint64_t)(2 * SPMM_PANEL_MEAN + 16) * A->rows + 65536 && d >= panel_vec<XT>::VEC && d <= (int64_t)SPMM_PANEL_MAX * 32 * panel_vec<XT>::VEC;
+    return A->capacity >= (uint64_t)spmm_panel_room(A->rows) * A->rows + 65536 && d >= panel_vec<XT>::VEC && d <= (int64_t)SPMM_PANEL_MAX * 32 * panel_vec<XT>::VEC;
 }
 
 template <int G, typename XT>
@@ -358,7 +377,7 @@ int launch_panel(sgnn_ctx *ctx, const sgnn_csr *A, const XT *X, int64_t ldx, con
     a.part = ws->get<float>((size_t)a.max_chunks * (size_t)d);
     if (!ws->ok)
         return sgnn_fail(ctx, SGNN_ERR_CAPACITY, "sgnn_spmm: scratch too small (%zu bytes needed): call sgnn_ctx_reserve", ws->off);
-    a.n_chunks = pv.n_chunks; a.desc = pv.desc; a.ticket = pv.ticket;
+    a.n_chunks = pv.n_chunks; a.mean_limit = spmm_panel_mean<XT>(A, d); a.desc = pv.desc; a.ticket = pv.ticket;
     const int ob = ep.out_bf16 ? 2 : 4, mb = ep.mask_bf16 ? 2 : 4;
     auto fits = [](const void *p, int64_t ld, int bytes) { return !p || (reinterpret_cast<uintptr_t>(p) % (uintptr_t)(4 * bytes) == 0 && ld % 4 == 0); };
     a.wide_epi = fits(out, ldo, ob) && fits(ep.mask, ep.ldm, mb) && fits(ep.add, ep.ldadd, 4);

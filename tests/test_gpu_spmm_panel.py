@@ -110,6 +110,26 @@ def test_room_for_more_entries_than_there_are(mean):
     assert rel_err(out.cpu().numpy(), oracle.spmm(rp, ci, v, _np(X))) < TOL_F32
 
 
+@pytest.mark.parametrize("rows,d,mean", [(32768, 47, 12), (32768, 47, 13), (32768, 127, 13), (32767, 128, 13), (32768, 128, 13), (32768, 128, 31), (32768, 128, 32)])
+def test_either_side_of_the_limit(rows, d, mean):
+    # room for 40 entries a row and 65536 more: the device decides by the mean, at a limit that goes with rows and width
+    rng = np.random.default_rng(mean)
+    lens = np.full(rows, mean)
+    lens[5], lens[10:10 + 900] = lens[5] + 900, lens[10:10 + 900] - 1
+    rp = np.concatenate([[0], np.cumsum(lens)]).astype(np.int32)
+    ci = rng.integers(0, rows, rp[-1]).astype(np.int32)
+    v = rng.standard_normal(len(ci)).astype(np.float32)
+    A = sg.Csr(rows, rows, 40 * rows + 65536, DEV)
+    A.rowptr.copy_(torch.as_tensor(rp))
+    A.colidx[:len(ci)] = dev(ci)
+    A.val[:len(ci)] = dev(v)
+    sg.sgnn_csr_plan(ctx(), A)
+    X = _operand(rows, d, torch.float32, d, mean)
+    out = torch.full((rows, d), 7.0, device=DEV)
+    sg.sgnn_spmm(ctx(), A, X, out)
+    assert rel_err(out.cpu().numpy(), oracle.spmm(rp, ci, v, _np(X))) < TOL_F32
+
+
 @pytest.mark.parametrize("x_dtype", [torch.float32, torch.bfloat16])
 def test_infinities_stay_in_their_rows(matrix, x_dtype):
     # lanes without an entry of their own must not add 0 * x of somebody else's
@@ -132,7 +152,7 @@ def test_infinities_stay_in_their_rows(matrix, x_dtype):
 def test_rows_of_more_than_4_gb():
     rows, cols, d, ld = 900, 3, 40, (1 << 30) + 8
     rng = np.random.default_rng(11)
-    rp = np.arange(rows + 1) * 120
+    rp = np.arange(rows + 1) * 150
     ci = rng.integers(0, cols, rp[-1]).astype(np.int32)
     v = rng.standard_normal(len(ci)).astype(np.float32)
     A = sg.Csr.from_arrays(rows, cols, rp, ci, v, DEV)
