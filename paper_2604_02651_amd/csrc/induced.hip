@@ -39,8 +39,16 @@ constexpr unsigned IND_MAX_GRID = 8192;
 // Expected tiles up to which a workgroup of the fill pass adds up the survivors of the tiles before its own, instead of
 // reading a prefix sum that launches of their own have written.  271 tiles: fill pass 7.6 -> 7.7 us and a launch of 3.5 us
 // less; 6570 tiles: 34 -> 46 us for 6.5 us less, so that is no gain.  Where the prefix sum takes three launches
-// (room for more than 65536 tiles, which are those of the whole graph), 2930 tiles: 37 -> 40 us for 14 us less.
+// (room for more than 65536 tiles, which are those of the whole graph), 2930 tiles: 37 -> 40 us for 14 us less.  Between and beyond,
+// all launches together: 976 tiles 43 us, 52 with the prefix sum's launch; 1952 tiles 66 and 66; 4052 tiles 86, 98 with three;
+// 5859 tiles 114, 111 with three.
 constexpr uint64_t IND_OWN_PREFIX = 1024, IND_OWN_PREFIX_3 = 4096;
+// The number of tiles is known on the device only, and a sample of the highest degrees has many times the expected ones.  Where there
+// are more than IND_MANY the count pass therefore sums them up in groups of 256 as well, so that a workgroup reads at most its own
+// group's tiles and one count for each group before it: 40000 rows of 4 10^6 vertices, 966 tiles expected, 23662 there, fill pass
+// 128 -> 78 us.  Below, the atomic additions of the groups cost more than they save (4052 tiles: count pass 44 -> 61 us, fill pass 26 -> 24).
+constexpr unsigned IND_GROUP = IND_NT;
+constexpr uint64_t IND_MANY = 8192;
 constexpr int DEG_TILE = 2048;                    // sampled rows per workgroup in the offset kernels
 
 // Row and column range of a shard (Algorithm 2: [R0, R1) x [C0, C1) in global vertex ids); the whole graph by default.
@@ -65,13 +73,14 @@ __device__ __forceinline__ void coarse_filter(const uint64_t *__restrict__ bitma
 
 // The first n_deg_wg workgroups take the rows; those behind them build the coarse filter meanwhile, which no row needs
 // (a launch of its own was 5 us; these hide behind the gathers of the row lengths).
-// plan_count: piece counter of the plan that will be attached to the result, cleared here instead of in a launch of its own (or null).
+// plan_count: piece counter of the plan that will be attached to the result, cleared here instead of in a launch of its own (or null);
+// so are the n_groups survivor counts of the tile groups.
 template <class RP>
 __global__ __launch_bounds__(256) void induced_deg_kernel(const RP *__restrict__ rowptr, const int32_t *__restrict__ S,
                                                           uint32_t B, shard_range rg, uint32_t *__restrict__ deg,
                                                           int64_t *__restrict__ rowstart, uint64_t *__restrict__ wg_sum,
                                                           unsigned long long *__restrict__ total64, uint32_t *__restrict__ plan_count,
-                                                          unsigned n_deg_wg, const uint64_t *__restrict__ bitmap, uint64_t W,
+                                                          uint32_t *__restrict__ group_total, unsigned n_groups, unsigned n_deg_wg, const uint64_t *__restrict__ bitmap, uint64_t W,
                                                           uint8_t *__restrict__ coarse)
 {
     if (blockIdx.x >= n_deg_wg) {
@@ -79,6 +88,7 @@ __global__ __launch_bounds__(256) void induced_deg_kernel(const RP *__restrict__
         return;
     }
     if (plan_count && blockIdx.x == 0 && threadIdx.x == 0) *plan_count = 0u;
+    for (unsigned i = blockIdx.x * 256 + threadIdx.x; i < n_groups; i += n_deg_wg * 256) group_total[i] = 0u;
     __shared__ uint64_t lds[256 / 64];
     if (blockIdx.x == 0 && threadIdx.x == 0) *total64 = 0ull;     // survivors of the whole mini-batch, summed by the count pass
     uint64_t s = 0;
@@ -273,6 +283,7 @@ __global__ __launch_bounds__(IND_NT) void induced_count_kernel(const int64_t *__
                                                                const uint64_t *__restrict__ P,
                                                                const uint32_t *__restrict__ tile_row,
                                                                uint32_t *__restrict__ tile_total,
+                                                               uint32_t *group_total,                   // or null
                                                                uint64_t *__restrict__ keepbits,
                                                                uint64_t *__restrict__ n_tiles_out,
                                                                unsigned long long *__restrict__ total64)
@@ -288,6 +299,7 @@ __global__ __launch_bounds__(IND_NT) void induced_count_kernel(const int64_t *__
     const uint64_t F = P[B];
     const uint64_t n_tiles = (F + IND_TILE - 1) / IND_TILE;
     if (blockIdx.x == 0 && threadIdx.x == 0) *n_tiles_out = n_tiles;
+    if (n_tiles <= IND_MANY) group_total = nullptr;
     unsigned long long wg_total = 0;      // 64 bits: the 32-bit prefix over the tile counts wraps beyond 2^32 survivors
     // software pipeline over the workgroup's tiles: the rows of the tile after next and the table of the next tile are
     // requested before the current tile's edges are gathered
@@ -370,6 +382,7 @@ __global__ __launch_bounds__(IND_NT) void induced_count_kernel(const int64_t *__
 #pragma unroll
             for (int w = 0; w < IND_NT / 64; ++w) t += wave_cnt[buf][w];
             tile_total[c] = t;
+            if (group_total && t) atomicAdd(&group_total[c / IND_GROUP], t);
             wg_total += t;
         }
         r_lo = r_lo1; nr = nr1; r_lo1 = r_lo2; nr1 = nr2;
@@ -381,13 +394,14 @@ __global__ __launch_bounds__(IND_NT) void induced_count_kernel(const int64_t *__
 // position = survivors in earlier tiles + survivors before the edge in the tile (prefix over the popcounts of
 // the tile's keep words).  Row offsets come from the row side: every row that starts inside the tile gets the
 // position of the first survivor at or behind its start, which also covers rows without any stored entry.
-// OWN_PREFIX: tile_off_all holds the counts of the tiles themselves, and the workgroup adds up those before its tile.
+// OWN_PREFIX: tile_off_all holds the counts of the tiles themselves, group_total those of the groups of tiles, and the workgroup
+// adds up those before its tile.
 template <class RP, bool OWN_PREFIX>
 __global__ __launch_bounds__(IND_NT) __attribute__((amdgpu_waves_per_eu(7, 7))) void induced_fill_kernel(
     const RP *__restrict__ rowptr, const int32_t *__restrict__ colidx, const float *__restrict__ gval,
     const int32_t *__restrict__ S, const int64_t *__restrict__ rowstart, const uint32_t *__restrict__ deg, uint32_t B,
     const uint64_t *__restrict__ bitmap, const uint32_t *__restrict__ rank, const uint64_t *__restrict__ P,
-    const uint32_t *__restrict__ tile_row, const uint32_t *__restrict__ tile_off_all, const uint64_t *__restrict__ n_tiles_p, const uint64_t *__restrict__ keepbits, float inv_p, int write_val,
+    const uint32_t *__restrict__ tile_row, const uint32_t *__restrict__ tile_off_all, const uint32_t *__restrict__ group_total, const uint64_t *__restrict__ n_tiles_p, const uint64_t *__restrict__ keepbits, float inv_p, int write_val,
     int32_t *__restrict__ rowptr_S, int32_t *__restrict__ colidx_S, float *__restrict__ val_S, uint64_t capacity,
     uint32_t *__restrict__ nnz_dev, uint32_t *__restrict__ status, const unsigned long long *__restrict__ total64,
     int sticky_capacity, int deg_by_rank)
@@ -426,16 +440,25 @@ __global__ __launch_bounds__(IND_NT) __attribute__((amdgpu_waves_per_eu(7, 7))) 
     tile_pref pf = tile_prefetch(rowstart, P, deg, blockIdx.x < n_tiles, r_lo, nr);
     uint64_t kw = 0;               // wavefront 0: keep word `lane` of the tile
     uint32_t tile_off = 0;         // survivors in earlier tiles (exclusive prefix of the tile counts)
-    // OWN_PREFIX: survivors of tiles [a, b), every thread; wrapping 32-bit sums, as the prefix sum's
-    auto sum_tiles = [&](uint64_t a, uint64_t b) -> uint32_t {
+    // OWN_PREFIX: survivors of the tiles before tile c, every thread; `off` are those of the tiles before tile a.  Wrapping 32-bit
+    // sums, as the prefix sum's.
+    auto before_tile = [&](uint64_t c, uint64_t a, uint32_t off) -> uint32_t {
+        uint64_t n_groups = 0;
+        if (n_tiles > IND_MANY) {
+            n_groups = c / IND_GROUP;
+            a = n_groups * IND_GROUP;
+            off = 0;
+        }
         uint32_t t = 0;
 #pragma unroll 1
-        for (uint64_t i = a + threadIdx.x; i < b; i += IND_NT) t += tile_off_all[i];
-        return block_sum<uint32_t, IND_NT>(t, sum_lds);
+        for (uint64_t i = a + threadIdx.x; i < c; i += IND_NT) t += tile_off_all[i];
+#pragma unroll 1
+        for (uint64_t i = threadIdx.x; i < n_groups; i += IND_NT) t += group_total[i];
+        return off + block_sum<uint32_t, IND_NT>(t, sum_lds);
     };
     if (blockIdx.x < n_tiles) {
         if (wave == 0 && lane < IND_WORDS) kw = keepbits[(uint64_t)blockIdx.x * IND_WORDS + lane];
-        tile_off = OWN_PREFIX ? sum_tiles(0, blockIdx.x) : tile_off_all[blockIdx.x];
+        tile_off = OWN_PREFIX ? before_tile(blockIdx.x, 0, 0) : tile_off_all[blockIdx.x];
     }
     int buf = 0;
     for (uint64_t c = blockIdx.x; c < n_tiles; c += g, buf ^= 1) {
@@ -459,7 +482,7 @@ __global__ __launch_bounds__(IND_NT) __attribute__((amdgpu_waves_per_eu(7, 7))) 
         pf = tile_prefetch(rowstart, P, deg, c + g < n_tiles, r_lo1, nr1);
         if (c + g < n_tiles) {
             if (wave == 0 && lane < IND_WORDS) kw = keepbits[(c + g) * IND_WORDS + lane];
-            tile_off = OWN_PREFIX ? tile_off_cur + sum_tiles(c, c + g) : tile_off_all[c + g];
+            tile_off = OWN_PREFIX ? before_tile(c + g, c, tile_off_cur) : tile_off_all[c + g];
         }
 
         // Survivors, in their order: the flat offsets of the set bits of the keep words are written to a list in LDS, each
@@ -607,21 +630,23 @@ int launch_typed(sgnn_ctx *ctx, const sgnn_graph *g, const int32_t *S, uint32_t 
         return sgnn_fail(ctx, SGNN_ERR_CAPACITY, "sgnn_induced_csr: scratch too small (%zu bytes needed): call sgnn_ctx_reserve",
                          ws.off);
 
+    const uint64_t expected_tiles = (uint64_t)((double)g->E * (double)B / (double)std::max<uint64_t>(g->N, 1) / IND_TILE);
+    const bool own_prefix = expected_tiles <= (max_tiles > SGNN_SCAN_SINGLE_MAX ? IND_OWN_PREFIX_3 : IND_OWN_PREFIX);
+    uint32_t *group_total = own_prefix ? tile_off : nullptr;        // no prefix sum then: its place is free
+    const unsigned n_groups = own_prefix ? (unsigned)(max_tiles / IND_GROUP + 1) : 0u;
     const unsigned n_coarse_wg = use_coarse ? (unsigned)std::min<uint64_t>(cdiv(W, 1024), 1024) : 0u;
     SGNN_LAUNCH(ctx, st, "induced_deg_kernel", SGNN_TAG, induced_deg_kernel<RP>, dim3(n_deg_wg + n_coarse_wg), dim3(256), 0, st, rowptr, S, B,
-                rg, deg, rowstart, deg_sum, total64, sgnn_spmm_plan_counter(out), n_deg_wg, bitmap, W, coarse);
+                rg, deg, rowstart, deg_sum, total64, sgnn_spmm_plan_counter(out), group_total, n_groups, n_deg_wg, bitmap, W, coarse);
     SGNN_LAUNCH(ctx, st, "induced_offsets_kernel", SGNN_TAG, induced_offsets_kernel, dim3(n_deg_wg), dim3(256), 0, st, deg, B,
                 deg_sum, P, tile_row);
     // Workgroups walk their tiles in a software pipeline (the next tile's row table is requested while the current
     // tile's edges are gathered).  Where the expected number of tiles, E B / N / 2048, is a few times the 2048
     // workgroups of the count pass that are resident at once, exactly those are launched (large graph: 94 -> 78 us);
     // with more tiles the larger grid measured better (the chip is then full anyway), as it does for the fill pass.
-    const uint64_t expected_tiles = (uint64_t)((double)g->E * (double)B / (double)std::max<uint64_t>(g->N, 1) / IND_TILE);
     const unsigned grid_fill = (unsigned)std::min<uint64_t>(max_tiles, IND_MAX_GRID);
     const unsigned grid = (expected_tiles >= 2048 && expected_tiles < IND_MAX_GRID) ? 2048u : grid_fill;
     SGNN_LAUNCH(ctx, st, "induced_count_kernel", SGNN_TAG, induced_count_kernel, dim3(grid), dim3(IND_NT), 0, st, rowstart, deg,
-                g->colidx, B, bitmap, coarse, rg, P, tile_row, tile_total, keepbits, n_tiles, total64);
-    const bool own_prefix = expected_tiles <= (max_tiles > SGNN_SCAN_SINGLE_MAX ? IND_OWN_PREFIX_3 : IND_OWN_PREFIX);
+                g->colidx, B, bitmap, coarse, rg, P, tile_row, tile_total, group_total, keepbits, n_tiles, total64);
     if (!own_prefix) {
         const int rc = sgnn_scan_u32_devn(ctx, tile_total, tile_off, n_tiles, max_tiles, scan_tmp, st);
         if (rc) return rc;
@@ -630,7 +655,7 @@ int launch_typed(sgnn_ctx *ctx, const sgnn_graph *g, const int32_t *S, uint32_t 
     if (rescale && B > 1) p = ((double)B - 1.0) / ((double)g->N - 1.0);
     SGNN_LAUNCH(ctx, st, "induced_fill_kernel", SGNN_TAG, (own_prefix ? induced_fill_kernel<RP, true> : induced_fill_kernel<RP, false>), dim3(grid_fill), dim3(IND_NT), 0, st, rowptr,
                 g->colidx, norm_mode == 0 ? g->val : nullptr, S, rowstart, deg, B, bitmap, rank, P, tile_row, own_prefix ? tile_total : tile_off,
-                n_tiles, keepbits, (float)(1.0 / p), norm_mode == 0 ? 1 : 0, out->rowptr, out->colidx, out->val,
+                group_total, n_tiles, keepbits, (float)(1.0 / p), norm_mode == 0 ? 1 : 0, out->rowptr, out->colidx, out->val,
                 out->capacity, out->nnz_dev, ctx->status, total64, sticky_capacity,
                 (rg.r0 <= 0 && rg.r1 >= (int64_t)g->N) ? 1 : 0);
     if (norm_mode == 1)

@@ -108,6 +108,23 @@ def test_far_more_tiles_than_expected():
     ctx().status()
 
 
+def test_groups_of_tiles_in_one_call_after_another():
+    # more tiles than are added up one by one, two samples in turn: the counts of the groups start at zero in every call
+    N, big, d = 4000, np.array([0, 7, 8, 1000, 1001, 2500, 3998, 3999]), 2800003
+    deg = np.ones(N, np.int64)
+    deg[big] = d
+    rowptr = np.concatenate([[0], np.cumsum(deg)])
+    colidx = np.random.default_rng(7).integers(0, N, rowptr[-1]).astype(np.int32)
+    ctx().reserve(N, len(colidx), 8, 8, 1 << 17)
+    for S in (big, big[:6], big[1:]):
+        assert len(S) * d // 2048 > 8192
+        rp, ci, v = oracle.induced_csr(N, rowptr, colidx, S)
+        out = sg.Csr(len(S), len(S), len(ci), DEV)
+        assert _induced(N, rowptr, colidx, S, out) == len(ci)
+        assert np.array_equal(out.rowptr.cpu().numpy(), rp) and np.array_equal(out.colidx.cpu().numpy(), ci)
+    ctx().status()
+
+
 def test_plan_of_a_matrix_that_is_filled_again():
     # the plan's counter starts at zero in every call: hub rows, two samples into one matrix, products with and without
     N = 6000
