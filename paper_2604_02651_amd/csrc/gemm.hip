@@ -1421,12 +1421,12 @@ __global__ __launch_bounds__(256) void splitk_reduce_kernel(const float *__restr
             // eight chains, combined in a fixed order: one chain over the 128 ranges of a layer of 32768 rows had a
             // larger error than the 64 ranges that such layers were cut into before
             float t[8] = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
-            for (int z = 0; z < splits; z += 8) {
-                float x[8];
+            for (int z = 0; z < splits; z += 32) {         // 32 loads in flight
+                float x[32];
 #pragma unroll
-                for (int u = 0; u < 8; ++u) x[u] = cs_partial[(int64_t)min(z + u, splits - 1) * N + col];
+                for (int u = 0; u < 32; ++u) x[u] = cs_partial[(int64_t)min(z + u, splits - 1) * N + col];
 #pragma unroll
-                for (int u = 0; u < 8; ++u) t[u] += z + u < splits ? x[u] : 0.f;
+                for (int u = 0; u < 32; ++u) t[u % 8] += z + u < splits ? x[u] : 0.f;
             }
             cs_out[col] = ((t[0] + t[1]) + (t[2] + t[3])) + ((t[4] + t[5]) + (t[6] + t[7]));
         }
