@@ -2,12 +2,14 @@
 // of the parts that matter are accumulated in fp32.
 //
 //   x = x1 + x2 + x3,  x1 = bf16(x), x2 = bf16(x - x1), x3 = x - x1 - x2     (round to nearest even: exact, 3 x 8 bits)
-//   a b = a1 b1 + (a1 b2 + a2 b1) + (a1 b3 + a2 b2 + a3 b1) + O(2^-26 |a b|)
+//   a b = a1 b1 + (a1 b2 + a2 b1) + (a1 b3 + a2 b2 + a3 b1) + up to 0.92 x 2^-24 |a b|  (the three products left out)
 //
-// The products of two parts are exact in fp32, so the error is that of the accumulation; the leading products and the five
+// The method is that of Henry, Tang and Heinecke, "Leveraging the bfloat16 Artificial Intelligence Datatype For Higher-Precision
+// Computations" (2019).  The products of two parts are exact in fp32; the leading products and the five
 // small ones have accumulators of their own, and the leading chain then has one rounding step per 16 reduction steps where
 // the fp32 instructions have eight.  Error against 64 bits (2-norm), fp32 instructions / here: 32768 x 256 x 256
-// 2.0e-7 / 0.7e-7, 65536 x 256 x 608 3.1e-7 / 1.1e-7, 256 x 256 x 32768 2.9e-7 / 1.3e-7.
+// 2.0e-7 / 0.7e-7, 65536 x 256 x 608 3.1e-7 / 1.1e-7, 256 x 256 x 32768 2.9e-7 / 1.3e-7.  What is left out shows where an entry is a
+// single product (a diagonal operand): its error is up to 1.72 x 2^-24, one rounding to fp32 up to 1.0.
 //
 // What bounds these products is the matrix pipe: the fp32 instructions reach 154 TFLOP/s on a large product, the bfloat16 ones
 // 1140, of which a sixth is 190.  32768 x 256 x 256: 47 us with the fp32 instructions, 33 here (30 with the splitting left
@@ -22,7 +24,9 @@
 // Where the split does not hold, the tile is computed again with the fp32 instructions: by a wavefront whose accumulators are
 // not all finite (an infinity or NaN in the operands, an overflow), by a workgroup that has staged a value below 2^-112 in
 // magnitude other than zero (the parts of such a value reach below the smallest bfloat16 number: the error would be 2^-134,
-// measured 1.7e-7 of the result for operands of about 2^-112, 5e-7 at 2^-114).
+// measured 1.7e-7 of the result for operands of about 2^-112, 5e-7 at 2^-114).  That costs time with such values, which are rare
+// (a softmax gradient has them where logits lie more than 65 apart): 32768 x 256 x 256 34 us, 122 if one tile or every
+// one holds one (fp32 instructions before: 47); 65536 x 256 x 608 134 us, 269 and 519 (189); 256 x 256 x 32768 42, 144 (48).
 #include <algorithm>
 
 #include "common.h"

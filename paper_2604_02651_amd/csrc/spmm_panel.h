@@ -6,8 +6,9 @@
 // instruction:
 //  - G lanes of 16 bytes cover one entry's share of a panel and 64 / G entries are gathered by one instruction, so the
 //    instruction moves up to 1 KB however narrow the row is (47 fp32 columns: 188 bytes before);
-//  - rows wider than 512 bytes are cut into panels, and the workgroups of one XCD (consecutive workgroups go to the
-//    eight XCDs in turn) work on one panel, so that the part of X an XCD's 4 MB L2 is asked for is that much narrower.
+//  - rows wider than 512 bytes are cut into panels, and where their number is even the workgroups of one XCD (consecutive
+//    workgroups go to the eight XCDs in turn) work on one panel, so that the part of X an XCD's 4 MB L2 is asked for is that much
+//    narrower; an odd number of them (608 fp32 columns: five) is gone through one after the other by all XCDs.
 // The sums of the 64 / G groups of lanes are added in registers when a row is complete, in a fixed order.
 // Rows that the plan lists as long are taken in items of up to 1024 entries (16 pieces of the plan); rows of several items
 // hand partial rows over as in spmm_main_kernel, with one ticket per row and panel.
@@ -27,7 +28,7 @@ struct spmm_panel_args {
     int64_t ldx;
     const int32_t *row_index;
     int d;
-    int panels, interleave;      // interleave: how many panels are worked on at a time (1, 2, 4 or 8, divides panels)
+    int panels, interleave;      // interleave: how many panels are worked on at a time (1, 2, 4 or 8, divides panels: 1 if odd)
     const uint32_t *n_chunks;    // plan header
     uint32_t mean_limit;         // entries a row from which on the matrix is this kernel's
     uint32_t max_chunks;

@@ -813,7 +813,7 @@ def test_whole_step_with_narrow_layers_and_a_long_batch():
 
 def test_whole_step_with_a_ragged_feature_width():
     # 100 features into 96 hidden units, transform-first, 4128 sampled vertices: the step pads the features to 128
-    # columns, and both products of the first layer gather their rows of X inside the direct-to-LDS kernels
+    # columns, and both products of the first layer gather their rows of X inside the fp32 kernels
     # (X[S] W_1 by tile row, X[S]^T dP by reduction row, a long reduction split into ranges)
     si.CONFIGS["ragged_wide"] = si.Config("ragged_wide", 16384, 131072, 100, 96, 2, 8, 4128)
     try:
