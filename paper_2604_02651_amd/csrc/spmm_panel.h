@@ -1,5 +1,5 @@
 // The sparse product for matrices with many entries a row: several entries per gather instruction, columns in panels.
-// Included by spmm.hip, inside its anonymous namespace.
+// Included by spmm_group.hip, inside its anonymous namespace.
 //
 // What bounds the product there is the gathers: every entry reads a row of X, nnz * d elements in all, many times the
 // size of X itself, out of L2 and the Infinity Cache.  Two things make them cheaper than one row per wavefront-wide
@@ -41,31 +41,32 @@ struct spmm_panel_args {
     int wide_epi;                // out, mask and add allow 16-byte (fp32) / 8-element accesses at every column that is a multiple of VEC
 };
 
-// Which matrices go this way: those with 13 entries a row or more, 32 or more where rows of X are 512 bytes and longer, there are
-// 32768 of them and X is under 96 MB.  The count itself is on the device; the host launches both kernels if the capacity is
-// 40 entries a row and 65536 more, which the capacity of a mini-batch matrix (twice the expected entries, sixteen more a
-// row and 65536 more) is from a mean of 12 on, or 60 a row (a mean of 22) under 8192 rows, where the second launch is a fifth of
-// the product: 1024 x 16 and 4096 x 20 19 us with both launches, whichever kernel works, 15 with one.  So a
-// matrix whose capacity is its entries takes the kernel from a mean of 40 (60) on.
-// Measured on R-MAT matrices, us here / with spmm_main_kernel:
-//   rows x mean     fp32 256 cols   bf16 256      fp32 100      fp32 47       bf16 64
-//   4096 x 80       39 / 56         44 / 56       28 / 50       21 / 48       21 / 49
-//   16384 x 40      78 / 102        85 / 98       52 / 83       34 / 76       35 / 76
-//   16384 x 13      40 / 43         43 / 39       27 / 35       23 / 32       24 / 33
-//   65536 x 24      186 / 166       168 / 135     107 / 111     84 / 87       88 / 91
-//   65536 x 12.5    127 / 101       118 / 82      73 / 70       62 / 63       65 / 63
-//   262144 x 24     630 / 742       347 / 417     304 / 361     225 / 281     213 / 283
-//   262144 x 16     483 / 517       275 / 297     236 / 252     197 / 198     195 / 199
-//   262144 x 12.5   428 / 415       257 / 243     210 / 203     187 / 164     186 / 166
-// Most rows of such a matrix are much shorter than the mean: the reduction across the groups of lanes and the row-by-row walk cost
-// more than they save there, most of all with one group or two (long rows of X), unless main's gathers miss the caches.
-// A wavefront alone adds up the partial rows of a hub row, one after the other.  65536 rows of 8 and 3000 of 180 more,
-// 47 fp32 columns: 65 / 55, the largest loss that is left.
+// Which matrices go this way: those with 28 entries a row or more where spmm_short_kernel takes the others, 13 or more where
+// spmm_main_kernel does (rows of three panels and more and the epilogues that spmm_short_kernel does not have), and there 32 or more where
+// rows of X are 512 bytes and longer, there are 32768 of them and X is under 96 MB.  The count itself is on the device; the host
+// launches both kernels if the capacity is 40 entries a row and 65536 more, which the capacity of a mini-batch matrix (twice the
+// expected entries, sixteen more a row and 65536 more) is from a mean of 12 on, or 60 a row (a mean of 22) under 8192 rows, where
+// the second launch is a fifth of the product: 1024 x 16 and 4096 x 20 19 us with both launches, whichever kernel works, 15 with one.
+// So a matrix whose capacity is its entries takes the kernel from a mean of 40 (60) on.
+// Measured on R-MAT matrices, us here / with spmm_short_kernel:
+//   rows x mean     bf16 256      bf16 128      bf16 47       fp32 256      fp32 100      fp32 47
+//   4096 x 30       27 / 21       19 / 15       18 / 18       22 / 19       18 / 17       18 / 14
+//   4096 x 80       43 / 47       28 / 52       22 / 62       38 / 49       26 / 38       20 / 39
+//   16384 x 13      42 / 25       24 / 21       26 / 20       39 / 31       26 / 21       20 / 17
+//   16384 x 24      59 / 40       33 / 38       29 / 32       54 / 48       35 / 33       24 / 30
+//   16384 x 40      79 / 67       45 / 50       37 / 45       73 / 73       46 / 55       31 / 39
+//   65536 x 60      190 / 246     125 / 182     118 / 132     276 / 351     151 / 206     106 / 149
+//   100000 x 20     160 / 118     119 / 81      120 / 68      214 / 188     122 / 102     101 / 71
+//   200000 x 30     300 / 352     209 / 235     215 / 179     551 / 602     273 / 310     191 / 200
+//   262144 x 24     344 / 351     246 / 209     257 / 157     625 / 625     307 / 320     226 / 181
+// and with spmm_main_kernel, rows x mean and fp32 256 columns: 4096 x 80 39 / 56, 16384 x 13 40 / 43, 65536 x 24 186 / 166, 65536 x 12.5 127 / 101,
+// 262144 x 16 483 / 517, 262144 x 12.5 428 / 415; fp32 47 columns: 16384 x 13 23 / 32, 65536 x 12.5 62 / 63, 262144 x 12.5 187 / 164.
 constexpr uint32_t spmm_panel_room(uint32_t rows) { return rows < 8192 ? 60 : 40; }
 constexpr int SPMM_PANEL_MAX = 16;
-template <typename XT> uint32_t spmm_panel_mean(const sgnn_csr *A, int64_t d)
+template <typename XT> uint32_t spmm_panel_mean(const sgnn_csr *A, int64_t d, bool or_short)
 {
     const uint64_t row = (uint64_t)d * sizeof(XT);
+    if (or_short) return 28u;
     return row >= 512 && A->rows >= 32768 && row * A->cols < (96ull << 20) ? 32u : 13u;
 }
 
@@ -121,7 +122,7 @@ template <int G> __device__ __forceinline__ float group_sum(float x)
 template <int G, typename XT, bool OFF32>
 __global__ __launch_bounds__(SPMM_NT, 4) void spmm_panel_kernel(spmm_panel_args a, const XT *__restrict__ X, spmm_epi ep)
 {
-    if (a.n_chunks[3] < a.mean_limit) return;          // short rows after all: spmm_main_kernel's matrix
+    if (a.n_chunks[3] < a.mean_limit) return;          // short rows after all: another kernel's matrix
     constexpr int VEC = panel_vec<XT>::VEC, NE = 64 / G, W = G * VEC;
     constexpr int U = 8;                               // gathers in flight per wavefront, 1 KB each
     const int lane = threadIdx.x & 63, k = lane % G, g = lane / G;
@@ -344,6 +345,23 @@ template <typename XT> bool spmm_panel_wanted(const sgnn_csr *A, int64_t d)
     return A->capacity >= (uint64_t)spmm_panel_room(A->rows) * A->rows + 65536 && d >= panel_vec<XT>::VEC && d <= (int64_t)SPMM_PANEL_MAX * 32 * panel_vec<XT>::VEC;
 }
 
+// The arguments but for the panels, the rows of a task and the limit; false if the scratch does not hold the partial rows
+inline bool panel_args(spmm_panel_args &a, const sgnn_csr *A, int64_t ldx, const int32_t *row_index, int d, int part_d, float *out,
+                       int64_t ldo, const spmm_epi &ep, ws_alloc *ws)
+{
+    a.rows = A->rows; a.rowptr = A->rowptr; a.rp64 = A->rowptr_is_i64; a.colidx = A->colidx; a.val = A->val;
+    a.cap = (int64_t)std::min<uint64_t>(A->capacity, 0x7fffffffffffffffull);
+    a.ldx = ldx; a.row_index = row_index; a.d = d; a.out = out; a.ldo = ldo;
+    a.max_chunks = spmm_max_chunks(A->rows, A->capacity);
+    const spmm_plan_view pv = plan_view(A->plan, A->rows, a.max_chunks);
+    a.part = ws->get<float>((size_t)a.max_chunks * (size_t)part_d);
+    a.n_chunks = pv.n_chunks; a.desc = pv.desc; a.ticket = pv.ticket;
+    const int ob = ep.out_bf16 ? 2 : 4, mb = ep.mask_bf16 ? 2 : 4;
+    auto fits = [](const void *p, int64_t ld, int bytes) { return !p || (reinterpret_cast<uintptr_t>(p) % (uintptr_t)(4 * bytes) == 0 && ld % 4 == 0); };
+    a.wide_epi = fits(out, ldo, ob) && fits(ep.mask, ep.ldm, mb) && fits(ep.add, ep.ldadd, 4);
+    return ws->ok;
+}
+
 template <int G, typename XT>
 int launch_panel_g(sgnn_ctx *ctx, const sgnn_csr *A, const XT *X, spmm_panel_args a, const spmm_epi &ep, hipStream_t st)
 {
@@ -367,21 +385,12 @@ int launch_panel_g(sgnn_ctx *ctx, const sgnn_csr *A, const XT *X, spmm_panel_arg
 
 template <typename XT>
 int launch_panel(sgnn_ctx *ctx, const sgnn_csr *A, const XT *X, int64_t ldx, const int32_t *row_index, int d, float *out, int64_t ldo,
-                 const spmm_epi &ep, ws_alloc *ws, hipStream_t st)
+                 const spmm_epi &ep, uint32_t mean_limit, ws_alloc *ws, hipStream_t st)
 {
     spmm_panel_args a = {};
-    a.rows = A->rows; a.rowptr = A->rowptr; a.rp64 = A->rowptr_is_i64; a.colidx = A->colidx; a.val = A->val;
-    a.cap = (int64_t)std::min<uint64_t>(A->capacity, 0x7fffffffffffffffull);
-    a.ldx = ldx; a.row_index = row_index; a.d = d; a.out = out; a.ldo = ldo;
-    a.max_chunks = spmm_max_chunks(A->rows, A->capacity);
-    const spmm_plan_view pv = plan_view(A->plan, A->rows, a.max_chunks);
-    a.part = ws->get<float>((size_t)a.max_chunks * (size_t)d);
-    if (!ws->ok)
+    if (!panel_args(a, A, ldx, row_index, d, d, out, ldo, ep, ws))
         return sgnn_fail(ctx, SGNN_ERR_CAPACITY, "sgnn_spmm: scratch too small (%zu bytes needed): call sgnn_ctx_reserve", ws->off);
-    a.n_chunks = pv.n_chunks; a.mean_limit = spmm_panel_mean<XT>(A, d); a.desc = pv.desc; a.ticket = pv.ticket;
-    const int ob = ep.out_bf16 ? 2 : 4, mb = ep.mask_bf16 ? 2 : 4;
-    auto fits = [](const void *p, int64_t ld, int bytes) { return !p || (reinterpret_cast<uintptr_t>(p) % (uintptr_t)(4 * bytes) == 0 && ld % 4 == 0); };
-    a.wide_epi = fits(out, ldo, ob) && fits(ep.mask, ep.ldm, mb) && fits(ep.add, ep.ldadd, 4);
+    a.mean_limit = mean_limit;
     // The narrowest panel that holds the row, 32 lanes (512 bytes) at most.  Narrower panels keep more of X in an XCD's L2
     // (dense-degree mini-batch, 256 fp32 columns: L2 misses 45 M a call in spmm_main_kernel, 21 M with panels of 16 lanes, 15 M
     // with 8) but read the matrix and reduce the rows once more per panel: 673 / 890 us with 16 / 8 lanes against 650.

@@ -1,0 +1,424 @@
+// The sparse product for matrices with few entries a row: a stream of rows for every group of lanes.  Included by spmm_group.hip,
+// inside its anonymous namespace.
+//
+// What bounds the product there is how many gathers are in flight, not their bytes: spmm_main_kernel has one row of X per
+// instruction of the wavefront (512 bytes where 256 columns are stored as bfloat16, 94 where 47 are) and steers every entry with
+// scalar code.  Here G lanes of 16 bytes cover an entry's share of a panel, as in the panel kernel, but each of the 64 / G groups of
+// a wavefront has rows of its own, so that nothing is added up across lanes and an instruction gathers 1 KB however narrow the
+// rows are:
+//  - a wavefront takes up to 8 rows for every group.  Their entries are staged in LDS, (byte offset in X, value) each, the last one of a
+//    row marked in the offset's free bit: a group walks its entries eight at a time and writes a row where it sees the mark;
+//  - ReLU masks and added rows of the block are requested first and go straight into LDS, nothing waits for them at a row's end;
+//  - rows that the plan lists as long are taken piece by piece, one piece for every group, in the same loop.  The pieces are the
+//    first blocks of the grid.  Where there are fewer pieces than wavefronts the groups of a wavefront share one: then the chain of gathers
+//    of a piece (eight for a group alone) is what the product waits for;
+//  - partial rows of a long row are handed over as in spmm_main_kernel, word i of lane k at i * G + k, so that a store instruction covers
+//    whole memory lines (columns in their order, 4 bytes in every 32: 20000 rows of 64 entries more 147 us instead of 101).
+// Measured, us (spmm_main_kernel / here), R-MAT rows x mean:
+//                      bf16 256       bf16 128       bf16 47        fp32 256       fp32 100
+//   2^20 x 1.27        254 / 208      190 / 112      158 / 120      428 / 422      264 / 237
+//   500000 x 3         190 / 145      125 / 78       110 / 68       287 / 275      169 / 141
+//   2^18 x 6.4         150 / 122      106 / 64       97 / 56        246 / 228      117 / 104
+//   65536 x 12         79 / 55        67 / 40        62 / 46        96 / 82        67 / 48
+//   32768 x 2.9        20 / 16        15 / 14        15 / 14        23 / 21        16 / 14
+// 2^18 rows of exactly six entries, 256 bfloat16 columns: 124 / 97, of which 9.7 TB/s arrive; a kernel that does nothing but such
+// gathers takes the same.  What the R-MAT matrix takes beyond it is the ragged end of rows and pieces.
+// Rejected: rows of up to 64 entries as rows of a group (2^18 x 6.4, 256 bfloat16 columns: 136 -> 145 us, 32768 x 2.9: 18 -> 25, the groups of a
+// wavefront wait for one another), four gathers in flight at five wavefronts a SIMD (156 against 149 at the time), panels of 256 bytes (132 against 120),
+// two pieces and more per partial row (125 -> 130, 141, 147 with two, five, eight).
+constexpr int SHORT_U = 8;                   // gathers in flight per wavefront, 1 KB each
+constexpr uint32_t SHORT_ITEMS = 64;         // partial rows of a long row, at most
+constexpr int SHORT_SUM = 4;                 // of which so many are read at a time
+constexpr uint32_t SHORT_SHARED = 4096;      // fewer pieces than this (a wavefront for each, four a SIMD): the groups share them
+constexpr uint64_t SHORT_GRID = 8192;        // workgroups of a panel, at most (2^20 rows of 1.27: 210 us, 218 and 222 with 4096 and 2048)
+constexpr int SHORT_ROWS = 8;                // rows that a group of lanes takes at a time, at most
+template <int G> struct short_window { static constexpr int LEN = G == 32 ? 256 : 512; };      // entries of a block in LDS at a time
+
+enum { SHORT_PLAIN, SHORT_MASK, SHORT_ADD, SHORT_BIAS };      // what happens to a finished row
+
+// Rows per group of lanes: about 48 entries, and no fewer than 4096 wavefronts while the rows last
+__device__ __forceinline__ int short_rows(uint32_t rows, uint32_t mean, int groups, int interleave)
+{
+    const uint64_t fill = (uint64_t)rows * (uint64_t)interleave / (4096u * (uint64_t)groups);
+    const uint64_t r = min((uint64_t)(48u / max(mean, 1u)), fill);
+    return (int)min(max(r, (uint64_t)1), (uint64_t)SHORT_ROWS);
+}
+
+// The offsets of two rows, requested together (a branch around each of them cost a round trip to memory)
+__device__ __forceinline__ void row_offsets(const spmm_panel_args &a, uint64_t i, uint64_t j, int64_t &x, int64_t &y)
+{
+    if (a.rp64) { const int64_t *r = static_cast<const int64_t *>(a.rowptr); x = r[i]; y = r[j]; }
+    else { const int32_t *r = static_cast<const int32_t *>(a.rowptr); x = r[i]; y = r[j]; }
+    y = min(y, a.cap);
+    x = min(x, y);
+}
+
+// Columns [skip, VEC) of the lane from element `elem` on; 16 bytes at a time, at any alignment (gfx950 global stores take it)
+template <int VEC> __device__ __forceinline__ void short_store(float *out, int64_t elem, const float (&v)[VEC], int skip, int out_bf16)
+{
+    typedef float f32x4_any __attribute__((ext_vector_type(4), aligned(4)));
+    typedef uint32_t u32x2_any __attribute__((ext_vector_type(2), aligned(2)));
+    if (skip == 0) {
+        if (out_bf16) {
+            uint32_t w[VEC / 2];
+#pragma unroll
+            for (int i = 0; i < VEC / 2; ++i)
+                w[i] = (uint32_t)__builtin_bit_cast(uint16_t, (__bf16)v[2 * i]) | (uint32_t)__builtin_bit_cast(uint16_t, (__bf16)v[2 * i + 1]) << 16;
+            uint16_t *p = reinterpret_cast<uint16_t *>(out) + elem;
+            if constexpr (VEC == 8) { const u32x4_any q = {w[0], w[1], w[2], w[3]}; *reinterpret_cast<u32x4_any *>(p) = q; }
+            else { const u32x2_any q = {w[0], w[1]}; *reinterpret_cast<u32x2_any *>(p) = q; }
+        } else {
+#pragma unroll
+            for (int h = 0; h < VEC; h += 4) { const f32x4_any q = {v[h], v[h + 1], v[h + 2], v[h + 3]}; *reinterpret_cast<f32x4_any *>(out + elem + h) = q; }
+        }
+        return;
+    }
+#pragma unroll
+    for (int i = 0; i < VEC; ++i)
+        if (i >= skip) {
+            const float one[1] = {v[i]};
+            vstore_out<1>(out, elem + i, one, out_bf16);
+        }
+}
+
+template <int G, typename XT, bool OFF32, int EPI>
+__global__ __launch_bounds__(SPMM_NT, 4) void spmm_short_kernel(spmm_panel_args a, const XT *__restrict__ X, spmm_epi ep)
+{
+    if (a.mean_limit && a.n_chunks[3] >= a.mean_limit) return;        // the panel kernel's matrix
+    constexpr int VEC = panel_vec<XT>::VEC, NE = 64 / G, W = G * VEC, U = SHORT_U, CAPW = short_window<G>::LEN;
+    __shared__ uint2 staged[SPMM_NT / 64][CAPW];
+    constexpr bool SIDE = EPI == SHORT_MASK || EPI == SHORT_ADD;         // a matrix beside X is read at the rows' ends
+    __shared__ __attribute__((aligned(16))) u32x4_any side[SIDE ? SPMM_NT / 64 : 1][SIDE ? SHORT_ROWS * 64 : 1];
+    const int lane = threadIdx.x & 63, k = lane % G, g = lane / G;
+    const int wv = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    uint2 *st = staged[wv];
+    // blocks of work: a piece of a long row for every group of lanes, then R rows for every group
+    const uint32_t n_pieces = min(*a.n_chunks, a.max_chunks);
+    const int long_len = (int)a.n_chunks[1];
+    const int rows_each = short_rows(a.rows, a.n_chunks[3], NE, a.interleave), rows_all = rows_each * NE;
+    // (with few pieces all groups share one: then the length of the chain of gathers counts, not the number of wavefronts)
+    const bool shared = n_pieces < SHORT_SHARED;
+    const uint32_t per_block = shared ? 1 : NE;
+    const uint64_t piece_blocks = (n_pieces + per_block - 1) / per_block, blocks = piece_blocks + (a.rows + (uint64_t)rows_all - 1) / rows_all;
+    const uint64_t first_block = (uint64_t)(blockIdx.x / (unsigned)a.interleave) * (SPMM_NT / 64) + wv;
+    const uint64_t nwaves = (uint64_t)(gridDim.x / (unsigned)a.interleave) * (SPMM_NT / 64);
+    const char *__restrict__ xb = reinterpret_cast<const char *>(X);
+    const int64_t row_bytes = a.ldx * (int64_t)sizeof(XT);          // below 2^32 if OFF32
+
+    const int p = (int)(blockIdx.x % (unsigned)a.interleave);       // as many panels at a time as there are
+    // the lane's columns, as in the panel kernel
+    const int col0 = p * W + k * VEC, colb = min(col0, a.d - VEC), skip = col0 - colb;
+    const bool on = col0 < a.d;
+    const uint32_t col_bytes = (uint32_t)colb * (uint32_t)sizeof(XT);
+    float acc[VEC];
+#pragma unroll
+    for (int i = 0; i < VEC; ++i) acc[i] = 0.f;
+    // a lane's bias values, from LDS at every row's end: held in registers they spilled
+    __shared__ __attribute__((aligned(16))) float bias[EPI == SHORT_BIAS ? W : 1];
+    if constexpr (EPI == SHORT_BIAS) {
+        if (threadIdx.x < G) {
+#pragma unroll
+            for (int i = 0; i < VEC; ++i) bias[k * VEC + i] = ep.bias ? ep.bias[colb + i] : 0.f;
+        }
+        __syncthreads();
+    }
+    const char *__restrict__ side_base = reinterpret_cast<const char *>(EPI == SHORT_ADD ? ep.add : ep.mask);
+    const int64_t side_row = (EPI == SHORT_ADD ? ep.ldadd : ep.ldm) * (int64_t)sizeof(XT);       // below 2^25
+    auto beside = [&](const u32x4_any &m) {
+#pragma unroll
+        for (int i = 0; i < VEC; ++i) {
+            if constexpr (EPI == SHORT_ADD) acc[i] += panel_vec<XT>::get(m, i);
+            else acc[i] = panel_vec<XT>::get(m, i) > 0.f ? acc[i] : 0.f;
+        }
+    };
+    // the lane's columns of a row that is complete in acc
+    auto store = [&](int64_t row) {
+        if constexpr (EPI == SHORT_BIAS) {
+#pragma unroll
+            for (int i = 0; i < VEC; ++i) {
+                acc[i] += bias[k * VEC + i];
+                if (ep.relu) acc[i] = fmaxf(acc[i], 0.f);
+            }
+        }
+        short_store<VEC>(a.out, row * a.ldo + colb, acc, skip, ep.out_bf16);
+    };
+
+    for (uint64_t block = first_block; block < blocks; block += nwaves) {
+        const bool pieces = block < piece_blocks;
+        const int R = pieces ? 1 : rows_each, RW = R * NE, gb = g * R;
+        const uint64_t u0 = pieces ? block * per_block : (block - piece_blocks) * rows_all;       // the first piece or row
+        if constexpr (SIDE) {
+            if (!pieces) {
+                const char *first_row = side_base + (int64_t)u0 * side_row;
+                const uint32_t last = (uint32_t)min((uint64_t)a.rows - 1 - u0, (uint64_t)63);
+                for (int r = 0; r < R; ++r) {
+                    const uint32_t off = min((uint32_t)(gb + r), last) * (uint32_t)side_row + col_bytes;
+                    __builtin_amdgcn_global_load_lds((const __attribute__((address_space(1))) void *)(first_row + off),
+                                                     (__attribute__((address_space(3))) void *)(side[wv] + r * 64), 16, 0, 0);
+                }
+            }
+        }
+        int len, so = 0, se = 0, limit;       // entries of the lane's unit; its place in the block's list (rows); entries to go through
+        int64_t s;                            // where they begin
+        uint64_t longs = 0;
+        uint32_t left = 0, none = 0;
+        uint32_t row = 0, pc = 0, nch = 1, ip = 1;
+        if (pieces) {
+            len = 0; s = 0;
+            if (lane < (int)per_block && u0 + lane < n_pieces) {
+                const uint2 rc = a.desc[u0 + lane];
+                int64_t rs, re;
+                row_offsets(a, rc.x, (uint64_t)rc.x + 1, rs, re);
+                const int64_t plen = spmm_piece_len(re - rs);
+                const int sh = 63 - __clzll(plen);
+                row = rc.x; pc = rc.y;
+                nch = min((uint32_t)((re - rs + plen - 1) >> sh), n_pieces - ((uint32_t)u0 + lane - pc));
+                ip = nch <= (uint32_t)a.panels ? nch : (nch + SHORT_ITEMS - 1) / SHORT_ITEMS;
+                s = rs + ((int64_t)pc << sh);
+                if (pc % ip == 0) len = (int)min(re - s, (int64_t)ip << sh);
+            }
+            limit = 0;
+#pragma unroll
+            for (int v = 0; v < NE; ++v) limit = max(limit, __builtin_amdgcn_readlane(len, v));
+        } else {
+            // lane l < RW holds row u0 + l, the lanes behind the block and behind the matrix a row without entries
+            const uint64_t k0 = min(u0 + min(lane, RW), (uint64_t)a.rows), k1 = min(u0 + min(lane + 1, RW), (uint64_t)a.rows);
+            int64_t rs, re;
+            row_offsets(a, k0, k1, rs, re);
+            s = readlane64(rs, 0);
+            len = (int)(re - rs);
+            const bool is_long = len > long_len;
+            // places in the block's list of entries, long rows left out: [so, se) for the lane's row
+            longs = __ballot(is_long);
+            so = (int)(rs - s);
+            for (uint64_t m = longs; m; m &= m - 1) {
+                const int l = __builtin_ctzll(m), n = __builtin_amdgcn_readlane(len, l);
+                if (lane > l) so -= n;
+            }
+            se = so + (is_long ? 0 : len);
+            limit = __builtin_amdgcn_readlane(se, 63);
+            const uint32_t group_rows = (1u << R) - 1u;
+            left = (uint32_t)(__ballot(len > 0 && !is_long) >> gb) & group_rows;
+            none = (uint32_t)(__ballot(k1 > k0 && len == 0) >> gb) & group_rows;
+        }
+        const int gu = shared ? 0 : g;        // the group's piece
+        const int glen = __shfl(len, gu, 64), begin = __shfl(so, gb, 64), end = __shfl(se, gb + R - 1, 64);
+
+        // the group's row r is complete in acc
+        auto emit = [&](uint32_t r) {
+            if constexpr (SIDE) beside(side[wv][r * 64 + lane]);
+            store((int64_t)u0 + gb + r);
+#pragma unroll
+            for (int i = 0; i < VEC; ++i) acc[i] = 0.f;
+        };
+
+        for (int w0 = 0; w0 < limit; w0 += pieces ? SPMM_CHUNK : CAPW) {
+            int at, stop;            // the group's entries in LDS
+            if (pieces) {            // up to 64 entries of every group's piece
+                int32_t c[NE];
+                float v[NE];
+                int n_j[NE];
+#pragma unroll
+                for (int j = 0; j < NE; ++j) {       // no branch round the loads: they are in flight together
+                    n_j[j] = __builtin_amdgcn_readlane(len, j) - w0;
+                    const int64_t e = readlane64(s, j) + (lane < n_j[j] ? w0 + lane : 0);
+                    c[j] = a.colidx[e];
+                    v[j] = a.val[e];
+                }
+                if (a.row_index) {
+#pragma unroll
+                    for (int j = 0; j < NE; ++j) c[j] = a.row_index[c[j]];
+                }
+#pragma unroll
+                for (int j = 0; j < NE; ++j) {
+                    if constexpr (OFF32) c[j] = (int32_t)((uint32_t)c[j] * (uint32_t)row_bytes);
+                    if (lane < n_j[j]) st[j * SPMM_CHUNK + lane] = make_uint2((uint32_t)c[j], __builtin_bit_cast(uint32_t, v[j]));
+                }
+                const int n = min(glen - w0, SPMM_CHUNK), part = (n + NE - 1) / NE;
+                at = shared ? min(g * part, n) : g * SPMM_CHUNK;
+                stop = shared ? min(at + part, n) : at + n;
+            } else {
+                const int cnt = min(limit - w0, CAPW);
+                for (int j0 = 0; j0 < cnt; j0 += 128) {
+                    int32_t c[2];
+                    float v[2];
+#pragma unroll
+                    for (int j = 0; j < 2; ++j) {
+                        const int q = w0 + min(j0 + j * 64 + lane, cnt - 1);
+                        int64_t e = s + q;
+                        for (uint64_t m = longs; m; m &= m - 1) {
+                            const int l = __builtin_ctzll(m), o = __builtin_amdgcn_readlane(so, l), n = __builtin_amdgcn_readlane(len, l);
+                            if (q >= o) e += n;
+                        }
+                        c[j] = a.colidx[e];
+                        v[j] = a.val[e];
+                    }
+                    if (a.row_index) {
+#pragma unroll
+                        for (int j = 0; j < 2; ++j) c[j] = a.row_index[c[j]];
+                    }
+#pragma unroll
+                    for (int j = 0; j < 2; ++j) {
+                        const int q = j0 + j * 64 + lane;
+                        if constexpr (OFF32) c[j] = (int32_t)((uint32_t)c[j] * (uint32_t)row_bytes);
+                        if (q < cnt) st[q] = make_uint2((uint32_t)c[j], __builtin_bit_cast(uint32_t, v[j]));
+                    }
+                }
+                __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+                __builtin_amdgcn_wave_barrier();
+                // the last entry of a row is marked: rows are an even number of bytes, so bit 0 of an offset is free, and so
+                // is the sign of a row number
+                if (se > so && se - 1 >= w0 && se - 1 < w0 + cnt) st[se - 1 - w0].x |= OFF32 ? 1u : 0x80000000u;
+                at = max(begin - w0, 0);
+                stop = min(end - w0, cnt);
+            }
+            if (!on) stop = 0;       // lanes right of the last column stand still
+            __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+            __builtin_amdgcn_wave_barrier();
+            for (; at < stop; at += U) {
+                uint2 w[U];
+                u32x4_any q[U];
+#pragma unroll
+                for (int t = 0; t < U; ++t) w[t] = st[min(at + t, stop - 1)];
+#pragma unroll
+                for (int t = 0; t < U; ++t)
+                    if (at + t < stop) {
+                        if constexpr (OFF32) q[t] = *reinterpret_cast<const u32x4_any *>(xb + (uint32_t)((w[t].x & ~1u) + col_bytes));
+                        else q[t] = *reinterpret_cast<const u32x4_any *>(xb + ((int64_t)(w[t].x & 0x7fffffffu) * row_bytes + col_bytes));
+                    }
+#pragma unroll
+                for (int t = 0; t < U; ++t)
+                    if (at + t < stop) {
+                        asm volatile("" : "+v"(q[t]));      // nothing of the widening moves up in front of the branch
+#pragma unroll
+                        for (int i = 0; i < VEC; ++i) acc[i] = fmaf(__builtin_bit_cast(float, w[t].y), panel_vec<XT>::get(q[t], i), acc[i]);
+                        if (OFF32 ? (w[t].x & 1u) != 0 : (int32_t)w[t].x < 0) {
+                            emit((uint32_t)__builtin_ctz(left));
+                            left &= left - 1;
+                        }
+                    }
+            }
+            __builtin_amdgcn_wave_barrier();
+        }
+        if (!pieces) {
+            if (on)
+                for (; none; none &= none - 1) emit((uint32_t)__builtin_ctz(none));
+            continue;
+        }
+
+        // the group's piece is complete in acc; of a shared one every group has the sum, and the first goes on with it
+        if (shared) {
+#pragma unroll
+            for (int i = 0; i < VEC; ++i) acc[i] = group_sum<G>(acc[i]);
+        }
+        const bool mine = on && glen > 0 && !(shared && g > 0);
+        const uint32_t grow = __shfl(row, gu, 64), gpc = __shfl(pc, gu, 64), gnch = __shfl(nch, gu, 64), gip = __shfl(ip, gu, 64);
+        const uint32_t first = (uint32_t)u0 + gu - gpc, items = (gnch + gip - 1) / gip;
+        bool whole = items <= 1;
+        if (mine && !whole) {
+            // partial row out with device-scope stores, then a ticket; the last ticket adds the partial rows up
+            // (word i of lane k at i * G + k: every store covers whole memory lines)
+            const int64_t stride = (int64_t)a.panels * W;
+            float *o = a.part + (int64_t)first * stride + p * W + k;
+#pragma unroll
+            for (int i = 0; i < VEC; ++i) __hip_atomic_store(o + (int64_t)gpc * stride + i * G, acc[i], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+            asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+            uint32_t t = 0;
+            if (k == 0) t = atomicAdd(&a.ticket[first + p], 1u);
+            whole = __shfl(t, g * G, 64) + 1 == items;
+            if (whole) {
+#pragma unroll
+                for (int i = 0; i < VEC; ++i) acc[i] = 0.f;
+                for (uint32_t it = 0; it < items; it += SHORT_SUM) {
+                    float v[SHORT_SUM][VEC];
+#pragma unroll
+                    for (int j = 0; j < SHORT_SUM; ++j)
+#pragma unroll
+                        for (int i = 0; i < VEC; ++i)
+                            v[j][i] = __hip_atomic_load(o + (int64_t)(min(it + j, items - 1) * gip) * stride + i * G, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+#pragma unroll
+                    for (int j = 0; j < SHORT_SUM; ++j)
+                        if (it + j < items) {
+#pragma unroll
+                            for (int i = 0; i < VEC; ++i) acc[i] += v[j][i];
+                        }
+                }
+                if (k == 0) a.ticket[first + p] = 0;
+            }
+        }
+        if (mine && whole) {
+            if constexpr (SIDE) beside(*reinterpret_cast<const u32x4_any *>(side_base + (int64_t)grow * side_row + col_bytes));
+            store(grow);
+        }
+#pragma unroll
+        for (int i = 0; i < VEC; ++i) acc[i] = 0.f;
+    }
+}
+
+// Which calls go this way: one panel or two (300 fp32 columns, three panels, one after the other: 200000 rows of 3 entries 75 us in
+// spmm_main_kernel, 79 here, 8192 of 4 20 and 44) with at most one of bias / ReLU, mask and added matrix, the last two of X's type
+// and in whole 16 bytes (they go into LDS by direct loads).
+// Not two panels of 400000 rows and more through a row index either: the panels read the two parts of a row of X, which is seldom read
+// again, at different times (200 fp32 columns: 500000 x 3 285 us in spmm_main_kernel, 298 here, 2^20 x 1.27 447 and 494; 2^18 x 6.4 245 and 239).
+template <typename XT> bool spmm_short_wanted(const sgnn_csr *A, const int32_t *row_index, int64_t d, const spmm_epi &ep)
+{
+    constexpr int VEC = panel_vec<XT>::VEC;
+    auto whole = [&](const void *p, int64_t ld) {
+        const int64_t row = ld * (int64_t)sizeof(XT);
+        return d % VEC == 0 && reinterpret_cast<uintptr_t>(p) % 16 == 0 && row % 16 == 0 && row < (1 << 25);
+    };
+    if (d < VEC || d > 2 * 32 * VEC || (row_index && d > 32 * VEC && A->rows >= 400000)) return false;
+    if (ep.mask) return !ep.add && !ep.bias && !ep.relu && (ep.mask_bf16 != 0) == (sizeof(XT) == 2) && whole(ep.mask, ep.ldm);
+    if (ep.add) return !ep.bias && !ep.relu && sizeof(XT) == 4 && whole(ep.add, ep.ldadd);
+    return true;
+}
+
+template <int G, typename XT>
+int launch_short_g(sgnn_ctx *ctx, const sgnn_csr *A, const XT *X, spmm_panel_args a, const spmm_epi &ep, hipStream_t st)
+{
+    constexpr int W = G * panel_vec<XT>::VEC, NE = 64 / G;
+    a.panels = (a.d + W - 1) / W;
+    a.interleave = a.panels;                   // one or two
+    // How many blocks of rows and pieces there are is known on the device only: workgroups for blocks of four rows a group and a wavefront each
+    // for 2048 pieces, the wavefronts stride over what is left.  Workgroups without a block cost as well: 32768 x 2.9, 256 fp32
+    // columns, with 8192 a panel 30 us, with the 1540 of this rule 21.
+    const uint64_t want = cdiv(A->rows, (SPMM_NT / 64) * NE * SHORT_ROWS / 2) + std::min<uint64_t>(cdiv(a.max_chunks, SPMM_NT / 64), 512);
+    const unsigned grid = (unsigned)std::min<uint64_t>(want, SHORT_GRID) * (unsigned)a.interleave;
+    char tag[56];
+    snprintf(tag, sizeof(tag), "%ux%u d=%d G=%d in=%d out=%d%s", A->rows, A->cols, a.d, G, (int)sizeof(XT), ep.out_bf16 ? 2 : 4,
+             ep.mask ? (ep.mask_bf16 ? " m=2" : " m=4") : "");
+    const bool off32 = !a.row_index && (uint64_t)A->cols * (uint64_t)a.ldx * sizeof(XT) <= 0xffffffffull;
+#define SGNN_SHORT(E)                                                                                                                        \
+    do {                                                                                                                                     \
+        if (off32) SGNN_LAUNCH(ctx, st, "spmm_short_kernel", tag, (spmm_short_kernel<G, XT, true, E>), dim3(grid), dim3(SPMM_NT), 0, st, a, X, ep); \
+        else SGNN_LAUNCH(ctx, st, "spmm_short_kernel", tag, (spmm_short_kernel<G, XT, false, E>), dim3(grid), dim3(SPMM_NT), 0, st, a, X, ep);      \
+    } while (0)
+    if (ep.mask) SGNN_SHORT(SHORT_MASK);
+    else if (ep.bias || ep.relu) SGNN_SHORT(SHORT_BIAS);
+    else if (!ep.add) SGNN_SHORT(SHORT_PLAIN);
+    else if constexpr (sizeof(XT) == 4) SGNN_SHORT(SHORT_ADD);
+#undef SGNN_SHORT
+    return SGNN_OK;
+}
+
+// columns of a partial row: whole panels
+template <typename XT> int spmm_short_frame(int64_t d)
+{
+    constexpr int VEC = panel_vec<XT>::VEC;
+    const int w = (d <= 8 * VEC ? 8 : (d <= 16 * VEC ? 16 : 32)) * VEC;
+    return (int)((d + w - 1) / w) * w;
+}
+
+template <typename XT>
+int launch_short(sgnn_ctx *ctx, const sgnn_csr *A, const XT *X, int64_t ldx, const int32_t *row_index, int d, float *out, int64_t ldo,
+                 const spmm_epi &ep, uint32_t mean_limit, ws_alloc *ws, hipStream_t st)
+{
+    constexpr int VEC = panel_vec<XT>::VEC;
+    spmm_panel_args a = {};
+    if (!panel_args(a, A, ldx, row_index, d, spmm_short_frame<XT>(d), out, ldo, ep, ws))
+        return sgnn_fail(ctx, SGNN_ERR_CAPACITY, "sgnn_spmm: scratch too small (%zu bytes needed): call sgnn_ctx_reserve", ws->off);
+    a.mean_limit = mean_limit;
+    if (d <= 8 * VEC) return launch_short_g<8, XT>(ctx, A, X, a, ep, st);
+    if (d <= 16 * VEC) return launch_short_g<16, XT>(ctx, A, X, a, ep, st);
+    return launch_short_g<32, XT>(ctx, A, X, a, ep, st);
+}

@@ -1,0 +1,125 @@
+"""Sparse product of matrices with few entries a row (a stream of rows for every group of lanes) against the oracle: widths around
+the group and panel edges, every storage type and epilogue, rows of every length class, unaligned operands, 32-bit and 64-bit offsets."""
+import numpy as np
+import pytest
+import torch
+
+import oracle
+import paper_2604_02651_amd as sg
+from gpu_util import DEV, TOL_F32, ctx, dev, rel_err
+from test_gpu_spmm_panel import TOL_OUT, _np, _operand
+
+pytestmark = pytest.mark.gpu
+
+
+def _csr(lens, cols, seed):
+    rng = np.random.default_rng(seed)
+    rp = np.concatenate([[0], np.cumsum(lens)]).astype(np.int32)
+    ci = rng.integers(0, cols, rp[-1]).astype(np.int32)
+    return rp, ci, rng.standard_normal(len(ci)).astype(np.float32)
+
+
+def _few_pieces():
+    # pieces shared by the groups of a wavefront: empty rows (first, last, whole blocks), pieces of 1, 63 and 64 entries, two pieces,
+    # more than 64 pieces (two to a partial row), more than 256 (longer pieces)
+    lens = np.random.default_rng(1).integers(0, 9, 3001)
+    lens[[0, 3000]] = 0
+    lens[100:180] = 0
+    lens[[1, 2, 50, 51, 52, 53, 54, 700, 1500]] = [65, 64, 63, 128, 129, 300, 9, 4097, 17000]
+    return lens
+
+
+def _many_pieces():
+    # a piece for every group: more than 4096 of them
+    lens = np.random.default_rng(2).integers(0, 3, 40001)
+    lens[np.random.default_rng(3).permutation(40001)[:4500]] = 16
+    lens[[5, 6, 39999]] = [200, 65, 5000]
+    return lens
+
+
+def _full_blocks():
+    # rows just under the length from which they count as long, side by side: a block's entries in several parts
+    lens = np.random.default_rng(4).integers(14, 20, 40001)
+    lens[1000:3000] = 64
+    return lens
+
+
+MATRICES = {"few": _few_pieces, "many": _many_pieces, "full": _full_blocks}
+
+
+@pytest.mark.parametrize("name", MATRICES)
+@pytest.mark.parametrize("x_dtype,d", [(torch.float32, d) for d in (4, 31, 32, 33, 64, 65, 128, 129, 200, 256)] +
+                         [(torch.bfloat16, d) for d in (8, 47, 64, 65, 128, 129, 256, 257, 510)])
+def test_widths(name, x_dtype, d):
+    lens, cols = MATRICES[name](), 2500
+    rows = len(lens)
+    rp, ci, v = _csr(lens, cols, d)
+    A = sg.Csr.from_arrays(rows, cols, rp, ci, v, DEV, with_plan=d % 2 == 0)
+    if A.plan is not None:
+        sg.sgnn_csr_plan(ctx(), A)
+    ctx().reserve(rows, len(ci), rows, 512, len(ci))
+    X = _operand(cols, d, x_dtype, d + d % 3, d, offset=d % 5)
+    ref = oracle.spmm(rp, ci, v, _np(X))
+    out = torch.full((rows + 1, d), 7.0, device=DEV)
+    sg.sgnn_spmm(ctx(), A, X, out[:rows])
+    assert rel_err(out[:rows].cpu().numpy(), ref) < TOL_F32
+    assert torch.all(out[rows] == 7.0)
+    again = torch.empty_like(out)
+    sg.sgnn_spmm(ctx(), A, X, again[:rows])                                  # the tickets are back where they were
+    assert torch.equal(again[:rows], out[:rows])
+    # through a row index (64-bit offsets), the result stored as bfloat16; a matrix added, in whole 16 bytes and not
+    perm = np.random.default_rng(d).permutation(cols).astype(np.int32)
+    inv = torch.empty(cols, dtype=torch.int64, device=DEV)
+    inv[dev(perm).long()] = torch.arange(cols, device=DEV)
+    out16 = torch.empty((rows, d + 3), dtype=torch.bfloat16, device=DEV)[:, :d]
+    sg.sgnn_spmm(ctx(), A, X[inv].contiguous(), out16, row_index=dev(perm))
+    assert rel_err(_np(out16), ref) < TOL_OUT[torch.bfloat16]
+    for ld in (d + 4, d + 5):
+        add = _operand(rows, d, torch.float32, ld, 3)
+        sg.sgnn_spmm(ctx(), A, X, out[:rows], add=add)
+        assert rel_err(out[:rows].cpu().numpy(), ref + _np(add)) < TOL_F32
+
+
+@pytest.mark.parametrize("name", MATRICES)
+@pytest.mark.parametrize("bf16", [False, True])
+@pytest.mark.parametrize("d", [40, 47, 200])
+def test_layer_epilogues(name, d, bf16):
+    # bias and ReLU of a transform-first layer, and the ReLU mask of the layer below in the transposed product
+    lens = MATRICES[name]()
+    n = len(lens)
+    rp, ci, v = _csr(lens, n, d)
+    A = sg.Csr.from_arrays(n, n, rp, ci, v, DEV)
+    ctx().reserve(n, len(ci), n, 256, len(ci))
+    act = torch.bfloat16 if bf16 else torch.float32
+    tol = 2e-2 if bf16 else TOL_F32
+    flags = sg.SGNN_RELU | (sg.SGNN_BF16_MFMA if bf16 else 0)
+    d_in = d + 24
+    H, W, b = _operand(n, d_in, act, d_in, 1), _operand(d_in, d, torch.float32, d, 2), _operand(1, d, torch.float32, d, 3)[0]
+    Y = torch.empty((n, d), dtype=act, device=DEV)
+    sg.sgnn_gcn_fwd(ctx(), A, H, W, b, flags | sg.SGNN_XFORM_FIRST, Y, None)
+    ref = np.maximum(oracle.spmm(rp, ci, v, _np(H) @ _np(W)) + _np(b), 0)
+    assert rel_err(_np(Y), ref) < tol
+    dY, Hin = _operand(n, d_in, act, d_in, 4), _operand(n, d, act, d, 5)
+    T, dH, W2 = _operand(n, d, act, d, 6), torch.empty((n, d), dtype=act, device=DEV), _operand(d, d_in, torch.float32, d_in, 7)
+    sg.sgnn_gcn_bwd(ctx(), A, T, W2, None, dY, flags | sg.SGNN_DY_MASKED, dH, None, None, H_in=Hin)
+    ref = oracle.spmm(rp, ci, v, _np(dY) @ _np(W2).T) * (_np(Hin) > 0)
+    assert rel_err(_np(dH), ref) < tol
+
+
+@pytest.mark.parametrize("x_dtype", [torch.float32, torch.bfloat16])
+def test_infinities_stay_in_their_rows(x_dtype):
+    lens, cols = _few_pieces(), 2500
+    rp, ci, v = _csr(lens, cols, 9)
+    A = sg.Csr.from_arrays(len(lens), cols, rp, ci, v, DEV)
+    X = _operand(cols, 47, x_dtype, 48, 9)
+    X[0] = float("inf")
+    X[int(ci[-1]), 3] = float("nan")
+    X[int(ci[5]), 46] = -float("inf")
+    out = torch.empty((len(lens), 47), device=DEV)
+    sg.sgnn_spmm(ctx(), A, X, out)
+    with np.errstate(invalid="ignore"):
+        ref = oracle.spmm(rp, ci, v, _np(X))
+    got = _np(out)
+    assert np.array_equal(np.isnan(got), np.isnan(ref)) and np.array_equal(np.isinf(got), np.isinf(ref))
+    fine = np.isfinite(ref)
+    assert rel_err(got[fine], ref[fine]) < TOL_F32
