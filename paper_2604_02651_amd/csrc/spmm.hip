@@ -16,7 +16,8 @@
 //                       ticket adds the partial rows of the row up, in piece order, and writes the row.
 // Most products take one of two other kernels (spmm_group.hip), whose groups of lanes gather several rows of X by one instruction:
 // spmm_short_kernel, or spmm_panel_kernel for matrices with many entries a row.  The main kernel has the rest: three column panels
-// and more of few entries a row, fewer columns than 16 bytes, several epilogues at once, and the loss in the epilogue.
+// and more of few entries a row, fewer columns than 16 bytes, several epilogues at once, and the loss in the epilogue where
+// the row is wider than one panel.
 // No atomics touch floating-point data and the order of every sum is fixed: results are
 // bit-reproducible.  Nothing waits on another wavefront.  Two products that use the same plan must
 // not run at the same time (they would share the tickets).
@@ -720,6 +721,36 @@ static int launch_x(sgnn_ctx *ctx, const sgnn_csr *A, const XT *X, int64_t ldx, 
     return launch_v<1, XT>(ctx, A, X, ldx, row_index, (int)d, out, ldo, ep, ws, st, mean_limit);
 }
 
+// The product with the loss by groups of lanes; SGNN_ERR_UNSUPPORTED, without a launch, for widths outside it and with too little scratch
+template <typename XT>
+static int launch_short_xent(sgnn_ctx *ctx, const sgnn_csr *A_in, const XT *X, int64_t ldx, int64_t d, float *out, int64_t ldo, const spmm_epi &ep_in,
+                             float *loss, float *colsum, ws_alloc *ws, hipStream_t st)
+{
+    constexpr int x16 = sizeof(XT) == 2;
+    const int frame = sgnn_spmm_short_xent_frame(d, x16);
+    if (!frame) return SGNN_ERR_UNSUPPORTED;
+    sgnn_csr A = *A_in;
+    spmm_epi ep = ep_in;
+    ws_alloc w2 = *ws;
+    if (!A.plan) A.plan = w2.get<uint8_t>(sgnn_csr_plan_bytes(A.rows, A.capacity));
+    const unsigned grid = sgnn_spmm_short_xent_grid(&A), nfix = (unsigned)(XENT_SLOTS * (d + 1));
+    ep.loss_partial = w2.get<float>(grid);
+    ep.cs_partial = colsum ? w2.get<float>((size_t)grid * d) : nullptr;
+    ep.fix = w2.get<unsigned long long>(nfix);
+    ws_alloc w3 = w2;
+    w3.get<float>((size_t)spmm_max_chunks(A.rows, A.capacity) * (size_t)frame);
+    if (!w3.ok) return SGNN_ERR_UNSUPPORTED;
+    if (!A_in->plan) {
+        const int rc = build_plan(ctx, A_in, A.plan, false, st);
+        if (rc) return rc;
+    }
+    SGNN_LAUNCH(ctx, st, "spmm_xent_clear_kernel", SGNN_TAG, spmm_xent_clear_kernel, dim3(cdiv(nfix, 256)), dim3(256), 0, st, ep.fix, nfix);
+    const int rc = sgnn_launch_spmm_short_xent(ctx, &A, X, x16, ldx, (int)d, out, ldo, ep, &w2, st);
+    if (rc || !(loss || colsum)) return rc;
+    return sgnn_launch_xent_final(ctx, ep.loss_partial, (int)grid, ep.inv_rows, loss, ep.cs_partial, (int)d, colsum, ep.fix, XENT_SLOTS,
+                                  1.0 / XENT_FIX_CS, 1.0 / XENT_FIX_LOSS, st);
+}
+
 // O = A X + bias with the softmax cross-entropy of O's rows in the epilogue (see spmm_row_xent).  Returns
 // SGNN_ERR_UNSUPPORTED without launching anything for widths or alignments the fused kernels are not built for
 // (more than 512 columns, rows that do not allow the vector width the column count asks for): the caller then
@@ -737,6 +768,11 @@ static int launch_xent_x(sgnn_ctx *ctx, const sgnn_csr *A, const XT *X, int64_t 
                fits(ep.dO, ep.lddo, ep.dO_bf16 ? 2 : 4, vec);
     };
     const bool ok4 = ok(4), ok2 = ok(2);
+    if (!(d <= 64 || (d <= 128 && ok2) || (d <= 512 && ok4))) return SGNN_ERR_UNSUPPORTED;
+    if (A->capacity > (uint64_t)SPMM_SHORT) {
+        const int rc = launch_short_xent(ctx, A, X, ldx, d, out, ldo, ep, loss, colsum, ws, st);
+        if (rc != SGNN_ERR_UNSUPPORTED) return rc;
+    }
     if (d <= 64) return launch_vc<1, 1, XT, true>(ctx, A, X, ldx, nullptr, (int)d, out, ldo, ep, ws, st, loss, colsum);
     if (d <= 128 && ok2) return launch_vc<2, 1, XT, true>(ctx, A, X, ldx, nullptr, (int)d, out, ldo, ep, ws, st, loss, colsum);
     if (d <= 256 && ok4) return launch_vc<4, 1, XT, true>(ctx, A, X, ldx, nullptr, (int)d, out, ldo, ep, ws, st, loss, colsum);

@@ -281,3 +281,9 @@ bool sgnn_spmm_short_wanted(const sgnn_csr *A, const int32_t *row_index, int64_t
 int sgnn_spmm_short_frame(int64_t d, int x_bf16);      // columns of a partial row
 int sgnn_launch_spmm_short(sgnn_ctx *ctx, const sgnn_csr *A, const void *X, int x_bf16, int64_t ldx, const int32_t *row_index, int d, float *out,
                            int64_t ldo, const spmm::spmm_epi &ep, uint32_t mean_limit, ws_alloc *ws, hipStream_t st);
+// The product with the loss in its epilogue; ep's partial sums have a row per workgroup.  A partial row has `frame` columns, 0 for a
+// width that the kernel is not built for.
+int sgnn_spmm_short_xent_frame(int64_t d, int x_bf16);
+unsigned sgnn_spmm_short_xent_grid(const sgnn_csr *A);
+int sgnn_launch_spmm_short_xent(sgnn_ctx *ctx, const sgnn_csr *A, const void *X, int x_bf16, int64_t ldx, int d, float *out, int64_t ldo,
+                                const spmm::spmm_epi &ep, ws_alloc *ws, hipStream_t st);

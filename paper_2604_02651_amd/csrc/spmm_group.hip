@@ -40,3 +40,14 @@ int sgnn_launch_spmm_short(sgnn_ctx *ctx, const sgnn_csr *A, const void *X, int 
     if (x_bf16) return launch_short(ctx, A, static_cast<const bf16_bits *>(X), ldx, row_index, d, out, ldo, ep, mean_limit, ws, st);
     return launch_short(ctx, A, static_cast<const float *>(X), ldx, row_index, d, out, ldo, ep, mean_limit, ws, st);
 }
+
+int sgnn_spmm_short_xent_frame(int64_t d, int x_bf16) { return x_bf16 ? xent_frame<bf16_bits>(d) : xent_frame<float>(d); }
+
+unsigned sgnn_spmm_short_xent_grid(const sgnn_csr *A) { return spmm_short_xent_grid(A); }
+
+int sgnn_launch_spmm_short_xent(sgnn_ctx *ctx, const sgnn_csr *A, const void *X, int x_bf16, int64_t ldx, int d, float *out, int64_t ldo,
+                                const spmm_epi &ep, ws_alloc *ws, hipStream_t st)
+{
+    if (x_bf16) return launch_short_xent(ctx, A, static_cast<const bf16_bits *>(X), ldx, d, out, ldo, ep, ws, st);
+    return launch_short_xent(ctx, A, static_cast<const float *>(X), ldx, d, out, ldo, ep, ws, st);
+}

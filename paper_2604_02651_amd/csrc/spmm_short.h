@@ -23,6 +23,14 @@
 //   32768 x 2.9        20 / 16        15 / 14        15 / 14        23 / 21        16 / 14
 // 2^18 rows of exactly six entries, 256 bfloat16 columns: 124 / 97, of which 9.7 TB/s arrive; a kernel that does nothing but such
 // gathers takes the same.  What the R-MAT matrix takes beyond it is the ragged end of rows and pieces.
+// With the loss in the epilogue a group holds a whole row of logits (one panel): its maximum and sum are reductions over the group's lanes,
+// two to eight rows at a time, where spmm_main_kernel has one row on 64 lanes of one to four columns.
+//                      bf16 172       bf16 100       bf16 47        fp32 100       fp32 47
+//   2^20 x 1.27        406 / 326      284 / 209      234 / 133      322 / 280      253 / 158
+//   2^18 x 6.4         207 / 161      147 / 123      132 / 90       155 / 136      131 / 91
+//   32768 x 2.9        51 / 36        30 / 29        28 / 26        31 / 30        27 / 25
+// The lanes at the right edge store 16 bytes like the others, over columns of their neighbour's; column by column 2^20 x 1.27 with
+// 172 columns took 400.  Three chunks a lane and eight lanes a row (fewer instructions a row, twice the registers): 474, 356 for 2^18 x 6.4.
 // Rejected: rows of up to 64 entries as rows of a group (2^18 x 6.4, 256 bfloat16 columns: 136 -> 145 us, 32768 x 2.9: 18 -> 25, the groups of a
 // wavefront wait for one another), four gathers in flight at five wavefronts a SIMD (156 against 149 at the time), panels of 256 bytes (132 against 120),
 // two pieces and more per partial row (125 -> 130, 141, 147 with two, five, eight).
@@ -34,7 +42,24 @@ constexpr uint64_t SHORT_GRID = 8192;        // workgroups of a panel, at most (
 constexpr int SHORT_ROWS = 8;                // rows that a group of lanes takes at a time, at most
 template <int G> struct short_window { static constexpr int LEN = G == 32 ? 256 : 512; };      // entries of a block in LDS at a time
 
-enum { SHORT_PLAIN, SHORT_MASK, SHORT_ADD, SHORT_BIAS };      // what happens to a finished row
+enum { SHORT_PLAIN, SHORT_MASK, SHORT_ADD, SHORT_BIAS, SHORT_XENT };      // what happens to a finished row
+
+// x over the G lanes of a group (lane / G), in each of them
+template <int G, bool MAX> __device__ __forceinline__ float lanes_reduce(float x)
+{
+    auto op = [](float a, float b) { return MAX ? fmaxf(a, b) : a + b; };
+    x = op(x, dpp_f32<0xB1>(x));                              // quad_perm [1, 0, 3, 2]
+    x = op(x, dpp_f32<0x4E>(x));                              // quad_perm [2, 3, 0, 1]
+    x = op(x, dpp_f32<0x141>(x));                             // row_half_mirror
+    if constexpr (G >= 16) x = op(x, dpp_f32<0x140>(x));      // row_mirror
+    if constexpr (G >= 32) {
+        uint32_t u = __builtin_bit_cast(uint32_t, x), w = u;
+        asm("" : "+v"(w));
+        const auto r = __builtin_amdgcn_permlane16_swap(u, w, false, false);
+        x = op(__builtin_bit_cast(float, (uint32_t)r[0]), __builtin_bit_cast(float, (uint32_t)r[1]));
+    }
+    return x;
+}
 
 // Rows per group of lanes: about 48 entries, and no fewer than 4096 wavefronts while the rows last
 __device__ __forceinline__ int short_rows(uint32_t rows, uint32_t mean, int groups, int interleave)
@@ -53,32 +78,24 @@ __device__ __forceinline__ void row_offsets(const spmm_panel_args &a, uint64_t i
     x = min(x, y);
 }
 
-// Columns [skip, VEC) of the lane from element `elem` on; 16 bytes at a time, at any alignment (gfx950 global stores take it)
-template <int VEC> __device__ __forceinline__ void short_store(float *out, int64_t elem, const float (&v)[VEC], int skip, int out_bf16)
+// The lane's columns, from element `elem` on, 16 bytes at a time at any alignment (gfx950 global stores take it).  At the right edge the
+// first of them are the lane's before as well: both write the same bytes.
+template <int VEC> __device__ __forceinline__ void short_store(float *out, int64_t elem, const float (&v)[VEC], int out_bf16)
 {
     typedef float f32x4_any __attribute__((ext_vector_type(4), aligned(4)));
     typedef uint32_t u32x2_any __attribute__((ext_vector_type(2), aligned(2)));
-    if (skip == 0) {
-        if (out_bf16) {
-            uint32_t w[VEC / 2];
+    if (out_bf16) {
+        uint32_t w[VEC / 2];
 #pragma unroll
-            for (int i = 0; i < VEC / 2; ++i)
-                w[i] = (uint32_t)__builtin_bit_cast(uint16_t, (__bf16)v[2 * i]) | (uint32_t)__builtin_bit_cast(uint16_t, (__bf16)v[2 * i + 1]) << 16;
-            uint16_t *p = reinterpret_cast<uint16_t *>(out) + elem;
-            if constexpr (VEC == 8) { const u32x4_any q = {w[0], w[1], w[2], w[3]}; *reinterpret_cast<u32x4_any *>(p) = q; }
-            else { const u32x2_any q = {w[0], w[1]}; *reinterpret_cast<u32x2_any *>(p) = q; }
-        } else {
+        for (int i = 0; i < VEC / 2; ++i)
+            w[i] = (uint32_t)__builtin_bit_cast(uint16_t, (__bf16)v[2 * i]) | (uint32_t)__builtin_bit_cast(uint16_t, (__bf16)v[2 * i + 1]) << 16;
+        uint16_t *p = reinterpret_cast<uint16_t *>(out) + elem;
+        if constexpr (VEC == 8) { const u32x4_any q = {w[0], w[1], w[2], w[3]}; *reinterpret_cast<u32x4_any *>(p) = q; }
+        else { const u32x2_any q = {w[0], w[1]}; *reinterpret_cast<u32x2_any *>(p) = q; }
+    } else {
 #pragma unroll
-            for (int h = 0; h < VEC; h += 4) { const f32x4_any q = {v[h], v[h + 1], v[h + 2], v[h + 3]}; *reinterpret_cast<f32x4_any *>(out + elem + h) = q; }
-        }
-        return;
+        for (int h = 0; h < VEC; h += 4) { const f32x4_any q = {v[h], v[h + 1], v[h + 2], v[h + 3]}; *reinterpret_cast<f32x4_any *>(out + elem + h) = q; }
     }
-#pragma unroll
-    for (int i = 0; i < VEC; ++i)
-        if (i >= skip) {
-            const float one[1] = {v[i]};
-            vstore_out<1>(out, elem + i, one, out_bf16);
-        }
 }
 
 template <int G, typename XT, bool OFF32, int EPI>
@@ -86,6 +103,7 @@ __global__ __launch_bounds__(SPMM_NT, 4) void spmm_short_kernel(spmm_panel_args 
 {
     if (a.mean_limit && a.n_chunks[3] >= a.mean_limit) return;        // the panel kernel's matrix
     constexpr int VEC = panel_vec<XT>::VEC, NE = 64 / G, W = G * VEC, U = SHORT_U, CAPW = short_window<G>::LEN;
+    constexpr bool XENT = EPI == SHORT_XENT;
     __shared__ uint2 staged[SPMM_NT / 64][CAPW];
     constexpr bool SIDE = EPI == SHORT_MASK || EPI == SHORT_ADD;         // a matrix beside X is read at the rows' ends
     __shared__ __attribute__((aligned(16))) u32x4_any side[SIDE ? SPMM_NT / 64 : 1][SIDE ? SHORT_ROWS * 64 : 1];
@@ -113,15 +131,63 @@ __global__ __launch_bounds__(SPMM_NT, 4) void spmm_short_kernel(spmm_panel_args 
     float acc[VEC];
 #pragma unroll
     for (int i = 0; i < VEC; ++i) acc[i] = 0.f;
+    // The wavefront's sums of the loss and of the gradient's columns, and the labels of a block's rows.  Which wavefront has a long row
+    // goes with the timing of the plan kernel: such rows are added up as integers, in any order the same, over the workgroup (word
+    // i * G + k is value i of lane k) and then over the workgroups.  (Straight into memory, 22 lines a row: 2^18 x 6.4 with
+    // 172 columns 213 us instead of 161.)
+    __shared__ unsigned long long fixed[XENT ? W + 1 : 1];
+    __shared__ int32_t labels[XENT ? SPMM_NT / 64 : 1][XENT ? 64 : 1];
     // a lane's bias values, from LDS at every row's end: held in registers they spilled
-    __shared__ __attribute__((aligned(16))) float bias[EPI == SHORT_BIAS ? W : 1];
-    if constexpr (EPI == SHORT_BIAS) {
+    __shared__ __attribute__((aligned(16))) float bias[EPI == SHORT_BIAS || XENT ? W : 1];
+    if constexpr (EPI == SHORT_BIAS || XENT) {
         if (threadIdx.x < G) {
 #pragma unroll
             for (int i = 0; i < VEC; ++i) bias[k * VEC + i] = ep.bias ? ep.bias[colb + i] : 0.f;
         }
+        if constexpr (XENT)
+            for (int i = threadIdx.x; i <= W; i += SPMM_NT) fixed[i] = 0;
         __syncthreads();
     }
+    float loss = 0.f, cs[XENT ? VEC : 1] = {};
+    // Loss and gradient of the row of logits in acc: spmm_row_xent with a group of lanes a row.  The columns below `skip` are in
+    // the lane before too: they count in the maximum, where that does not matter, and not in the sums.
+    auto xent = [&](int64_t row, int32_t y, auto shared_row) {
+        constexpr bool SHARED = decltype(shared_row)::value;
+        auto add_loss = [&](float t) {
+            if constexpr (SHARED) atomicAdd(&fixed[W], (unsigned long long)(long long)llrint((double)t * XENT_FIX_LOSS));
+            else loss += t;
+        };
+        float mx = -INFINITY;
+#pragma unroll
+        for (int i = 0; i < VEC; ++i) {
+            acc[i] += bias[k * VEC + i];
+            mx = fmaxf(mx, acc[i]);
+        }
+        if (ep.write_out && on) short_store<VEC>(a.out, row * a.ldo + colb, acc, 0);
+        mx = lanes_reduce<G, true>(mx);
+        const int rel = y - colb;
+        const bool has_y = rel >= skip && rel < VEC;
+        float sum = 0.f, vy = acc[0];
+#pragma unroll
+        for (int i = 0; i < VEC; ++i) {
+            vy = rel == i ? acc[i] : vy;
+            acc[i] = exp_neg(acc[i] - mx);
+            sum += i >= skip ? acc[i] : 0.f;
+        }
+        sum = lanes_reduce<G, false>(sum);
+        const float inv = __builtin_amdgcn_rcpf(sum), lse = log_ge1(sum);       // 1 ulp each
+        if (has_y) add_loss(lse - (vy - mx));
+        if ((uint32_t)y >= (uint32_t)a.d && k == 0) add_loss(mx + lse);
+#pragma unroll
+        for (int i = 0; i < VEC; ++i) {
+            acc[i] = fmaf(acc[i], inv, rel == i ? -1.f : 0.f) * ep.inv_rows;
+            const float stored = ep.dO_bf16 ? (float)(__bf16)acc[i] : acc[i];       // the column sums add what is stored
+            if constexpr (SHARED) {
+                atomicAdd(&fixed[i * G + k], (unsigned long long)(long long)llrint((double)stored * XENT_FIX_CS));
+            } else cs[i] += stored;
+        }
+        if (ep.dO && on) short_store<VEC>(static_cast<float *>(ep.dO), row * ep.lddo + colb, acc, ep.dO_bf16);
+    };
     const char *__restrict__ side_base = reinterpret_cast<const char *>(EPI == SHORT_ADD ? ep.add : ep.mask);
     const int64_t side_row = (EPI == SHORT_ADD ? ep.ldadd : ep.ldm) * (int64_t)sizeof(XT);       // below 2^25
     auto beside = [&](const u32x4_any &m) {
@@ -140,7 +206,7 @@ __global__ __launch_bounds__(SPMM_NT, 4) void spmm_short_kernel(spmm_panel_args 
                 if (ep.relu) acc[i] = fmaxf(acc[i], 0.f);
             }
         }
-        short_store<VEC>(a.out, row * a.ldo + colb, acc, skip, ep.out_bf16);
+        short_store<VEC>(a.out, row * a.ldo + colb, acc, ep.out_bf16);
     };
 
     for (uint64_t block = first_block; block < blocks; block += nwaves) {
@@ -184,6 +250,7 @@ __global__ __launch_bounds__(SPMM_NT, 4) void spmm_short_kernel(spmm_panel_args 
             // lane l < RW holds row u0 + l, the lanes behind the block and behind the matrix a row without entries
             const uint64_t k0 = min(u0 + min(lane, RW), (uint64_t)a.rows), k1 = min(u0 + min(lane + 1, RW), (uint64_t)a.rows);
             int64_t rs, re;
+            if constexpr (XENT) labels[wv][lane] = ep.labels[min(k0, (uint64_t)a.rows - 1)];
             row_offsets(a, k0, k1, rs, re);
             s = readlane64(rs, 0);
             len = (int)(re - rs);
@@ -207,7 +274,8 @@ __global__ __launch_bounds__(SPMM_NT, 4) void spmm_short_kernel(spmm_panel_args 
         // the group's row r is complete in acc
         auto emit = [&](uint32_t r) {
             if constexpr (SIDE) beside(side[wv][r * 64 + lane]);
-            store((int64_t)u0 + gb + r);
+            if constexpr (XENT) xent((int64_t)u0 + gb + r, labels[wv][gb + r], std::false_type{});
+            else store((int64_t)u0 + gb + r);
 #pragma unroll
             for (int i = 0; i < VEC; ++i) acc[i] = 0.f;
         };
@@ -272,7 +340,8 @@ __global__ __launch_bounds__(SPMM_NT, 4) void spmm_short_kernel(spmm_panel_args 
                 at = max(begin - w0, 0);
                 stop = min(end - w0, cnt);
             }
-            if (!on) stop = 0;       // lanes right of the last column stand still
+            // lanes right of the last column stand still (with the loss they read the last columns once more: its sums go over all lanes)
+            if (!XENT && !on) stop = 0;
             __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
             __builtin_amdgcn_wave_barrier();
             for (; at < stop; at += U) {
@@ -301,7 +370,7 @@ __global__ __launch_bounds__(SPMM_NT, 4) void spmm_short_kernel(spmm_panel_args 
             __builtin_amdgcn_wave_barrier();
         }
         if (!pieces) {
-            if (on)
+            if (XENT || on)
                 for (; none; none &= none - 1) emit((uint32_t)__builtin_ctz(none));
             continue;
         }
@@ -311,7 +380,7 @@ __global__ __launch_bounds__(SPMM_NT, 4) void spmm_short_kernel(spmm_panel_args 
 #pragma unroll
             for (int i = 0; i < VEC; ++i) acc[i] = group_sum<G>(acc[i]);
         }
-        const bool mine = on && glen > 0 && !(shared && g > 0);
+        const bool mine = (XENT || on) && glen > 0 && !(shared && g > 0);
         const uint32_t grow = __shfl(row, gu, 64), gpc = __shfl(pc, gu, 64), gnch = __shfl(nch, gu, 64), gip = __shfl(ip, gu, 64);
         const uint32_t first = (uint32_t)u0 + gu - gpc, items = (gnch + gip - 1) / gip;
         bool whole = items <= 1;
@@ -348,10 +417,41 @@ __global__ __launch_bounds__(SPMM_NT, 4) void spmm_short_kernel(spmm_panel_args 
         }
         if (mine && whole) {
             if constexpr (SIDE) beside(*reinterpret_cast<const u32x4_any *>(side_base + (int64_t)grow * side_row + col_bytes));
-            store(grow);
+            // (the numbering of the pieces goes with the timing of the plan kernel: sums of such rows through the slots)
+            if constexpr (XENT) xent(grow, ep.labels[grow], std::true_type{});
+            else store(grow);
         }
 #pragma unroll
         for (int i = 0; i < VEC; ++i) acc[i] = 0.f;
+    }
+    if constexpr (XENT) {
+        // the wavefronts' sums, added in a fixed order, leave as the workgroup's
+        __shared__ float loss_sums[SPMM_NT / 64], column_sums[SPMM_NT / 64][W];
+        loss = wave_sum(loss);
+        if (lane == 0) loss_sums[wv] = loss;
+#pragma unroll
+        for (int i = 0; i < VEC; ++i) {
+            const float t = group_sum<G>(cs[i]);
+            if (g == 0 && i >= skip) column_sums[wv][colb + i] = t;
+        }
+        __syncthreads();
+        if (threadIdx.x == 0) {
+            float t = 0.f;
+            for (int w = 0; w < SPMM_NT / 64; ++w) t += loss_sums[w];
+            ep.loss_partial[blockIdx.x] = t;
+        }
+        unsigned long long *slot = ep.fix + (uint64_t)(blockIdx.x % XENT_SLOTS) * (uint64_t)(a.d + 1);
+        for (int w = threadIdx.x; w <= W; w += SPMM_NT) {
+            const unsigned long long t = fixed[w];
+            const int kc = (w % G) * VEC, b = min(kc, a.d - VEC), c = w < W ? b + w / G : a.d;
+            if (t && (w == W || w / G >= kc - b)) atomicAdd(slot + c, t);
+        }
+        if (ep.cs_partial)
+            for (int c = threadIdx.x; c < a.d; c += SPMM_NT) {
+                float t = 0.f;
+                for (int w = 0; w < SPMM_NT / 64; ++w) t += column_sums[w][c];
+                ep.cs_partial[(int64_t)blockIdx.x * a.d + c] = t;
+            }
     }
 }
 
@@ -421,4 +521,41 @@ int launch_short(sgnn_ctx *ctx, const sgnn_csr *A, const XT *X, int64_t ldx, con
     if (d <= 8 * VEC) return launch_short_g<8, XT>(ctx, A, X, a, ep, st);
     if (d <= 16 * VEC) return launch_short_g<16, XT>(ctx, A, X, a, ep, st);
     return launch_short_g<32, XT>(ctx, A, X, a, ep, st);
+}
+
+// The loss in the epilogue: a group of lanes holds the whole row
+template <typename XT> int xent_frame(int64_t d)
+{
+    constexpr int VEC = panel_vec<XT>::VEC;
+    return d < VEC || d > 32 * VEC ? 0 : spmm_short_frame<XT>(d);
+}
+
+// Workgroups: each leaves a row of partial sums to the final kernel
+inline unsigned spmm_short_xent_grid(const sgnn_csr *A) { return std::min<unsigned>(cdiv(A->rows, 64) + 512u, 4096u); }
+
+template <int G, typename XT>
+int launch_short_xent_g(sgnn_ctx *ctx, const sgnn_csr *A, const XT *X, const spmm_panel_args &a, const spmm_epi &ep, hipStream_t st)
+{
+    char tag[56];
+    snprintf(tag, sizeof(tag), "%ux%u d=%d G=%d in=%d out=%d xent dO=%d", A->rows, A->cols, a.d, G, (int)sizeof(XT), ep.write_out ? 4 : 0,
+             ep.dO ? (ep.dO_bf16 ? 2 : 4) : 0);
+    const unsigned grid = spmm_short_xent_grid(A);
+    const bool off32 = (uint64_t)A->cols * (uint64_t)a.ldx * sizeof(XT) <= 0xffffffffull;
+    if (off32) SGNN_LAUNCH(ctx, st, "spmm_short_kernel", tag, (spmm_short_kernel<G, XT, true, SHORT_XENT>), dim3(grid), dim3(SPMM_NT), 0, st, a, X, ep);
+    else SGNN_LAUNCH(ctx, st, "spmm_short_kernel", tag, (spmm_short_kernel<G, XT, false, SHORT_XENT>), dim3(grid), dim3(SPMM_NT), 0, st, a, X, ep);
+    return SGNN_OK;
+}
+
+template <typename XT>
+int launch_short_xent(sgnn_ctx *ctx, const sgnn_csr *A, const XT *X, int64_t ldx, int d, float *out, int64_t ldo, const spmm_epi &ep, ws_alloc *ws,
+                      hipStream_t st)
+{
+    constexpr int VEC = panel_vec<XT>::VEC;
+    spmm_panel_args a = {};
+    if (!panel_args(a, A, ldx, nullptr, d, spmm_short_frame<XT>(d), out, ldo, ep, ws))
+        return sgnn_fail(ctx, SGNN_ERR_CAPACITY, "sgnn_spmm_xent: scratch too small (%zu bytes needed): call sgnn_ctx_reserve", ws->off);
+    a.panels = a.interleave = 1;
+    if (d <= 8 * VEC) return launch_short_xent_g<8, XT>(ctx, A, X, a, ep, st);
+    if (d <= 16 * VEC) return launch_short_xent_g<16, XT>(ctx, A, X, a, ep, st);
+    return launch_short_xent_g<32, XT>(ctx, A, X, a, ep, st);
 }

@@ -123,3 +123,46 @@ def test_infinities_stay_in_their_rows(x_dtype):
     assert np.array_equal(np.isnan(got), np.isnan(ref)) and np.array_equal(np.isinf(got), np.isinf(ref))
     fine = np.isfinite(ref)
     assert rel_err(got[fine], ref[fine]) < TOL_F32
+
+
+@pytest.mark.parametrize("name", MATRICES)
+@pytest.mark.parametrize("x_dtype,d", [(torch.float32, d) for d in (4, 7, 32, 33, 64, 66, 100, 128)] +
+                         [(torch.bfloat16, d) for d in (8, 47, 64, 66, 128, 132, 172, 256)])
+def test_loss_in_the_epilogue(name, x_dtype, d):
+    lens = MATRICES[name]()
+    n = len(lens)
+    rp, ci, v = _csr(lens, n, d)
+    v = v * np.float32(0.1)      # logits of a few units: exp(x - max) keeps the tolerance of the product
+    A = sg.Csr.from_arrays(n, n, rp, ci, v, DEV, with_plan=True)
+    ctx().reserve(n, len(ci), n, 256, len(ci))
+    X, b = _operand(n, d, x_dtype, d + 4 - d % 4, d), _operand(1, d, torch.float32, d, 3)[0]
+    y = np.random.default_rng(d).integers(0, d, n).astype(np.int32)
+    y[[0, 40, n - 1]] = [d - 1, 0, d]                                         # the last: no class, the log-sum-exp alone
+    O = oracle.spmm(rp, ci, v, _np(X)) + _np(b)
+    m = O.max(1, keepdims=True)
+    e = np.exp(O - m)
+    s = e.sum(1, keepdims=True)
+    inside = y < d
+    hit = np.zeros_like(O)
+    hit[np.arange(n)[inside], y[inside]] = 1
+    dO_ref = (e / s - hit) / n
+    loss_ref = ((m + np.log(s))[:, 0] - (O * hit).sum(1)).mean()
+    bf16 = x_dtype == torch.bfloat16
+    first = None
+    for keep in (True, False, False):
+        sg.sgnn_csr_plan(ctx(), A)                                            # the pieces are numbered anew
+        loss, db = torch.zeros(1, device=DEV), torch.empty(d, device=DEV)
+        dO = torch.full((n + 1, d + 4 - d % 4), 7.0, dtype=x_dtype, device=DEV)[:, :d]
+        logits = torch.empty((n, d), device=DEV) if keep else None
+        sg.sgnn_spmm_xent(ctx(), A, X, b, dev(y), loss, dO[:n], O=logits, dO_colsum=db)
+        if keep:
+            assert rel_err(_np(logits), O) < TOL_F32
+        assert torch.all(dO[n] == 7.0)
+        # one rounding of every entry where dO is bfloat16; the column sums add what is stored
+        assert rel_err(_np(dO[:n]), dO_ref) < (2.0 ** -8 if bf16 else TOL_F32)
+        got = _np(dO[:n])
+        assert np.abs(_np(db) - got.sum(0)).max() < 1e-5 * np.abs(got).sum(0).max()
+        assert abs(loss.item() - loss_ref) < TOL_F32 * abs(loss_ref)
+        if first is None:
+            first = (loss.clone(), db.clone(), dO.clone())
+        assert torch.equal(loss, first[0]) and torch.equal(db, first[1]) and torch.equal(dO, first[2])
