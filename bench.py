@@ -207,9 +207,9 @@ def measure(args, sg, si, torch, cfg, g, X, labels, weights, use_graph_req: str,
     nnz_avg = nnz_total / nprof
     groups = {}
     # widths whose products are launched for the panel kernel too; of the two kernels the one runs that the mean row
-    # length names (12 entries), the other leaves at once
+    # length names (28 entries where the other is the one for short rows, 12 where it is the main one), the other leaves at once
     panel_widths = {tag.split("d=")[1].split()[0] for name, tag, _, _ in recs if name == "spmm_panel_kernel"}
-    panels_run = nnz_avg >= 12 * cfg.B
+    short_widths = {tag.split("d=")[1].split()[0] for name, tag, _, _ in recs if name == "spmm_short_kernel" and " dO=" not in tag}
     for name, tag, calls, ms in recs:
         key = name   # one group per kernel symbol, as rocprofv3 lists them
         if name == "gemm_kernel":
@@ -220,6 +220,8 @@ def measure(args, sg, si, torch, cfg, g, X, labels, weights, use_graph_req: str,
         elif name == "spmm_main_kernel":
             # the instantiation with the loss in its epilogue (tag: "... dO=<bytes>") is a kernel symbol of its own
             key = name + (tag.split()[2][:-1] + ",xent>" if " dO=" in tag else tag.split()[2])
+        elif name == "spmm_short_kernel":
+            key = name + "<%s%s>" % (tag.split("G=")[1].split()[0], ",xent" if " dO=" in tag else "")
         gq = groups.setdefault(key, {"calls": 0, "ms": 0.0, "flops": 0.0, "bytes": 0.0})
         gq["calls"] += calls
         gq["ms"] += ms
@@ -243,18 +245,19 @@ def measure(args, sg, si, torch, cfg, g, X, labels, weights, use_graph_req: str,
             eb = next((float(w[2:]) for w in p if w.startswith("b=")), 2.0)
             gq["bytes"] += calls * k_ * (ea * m_ + eb * n_)
             gq["flops"] += calls * 2.0 * m_ * n_ * k_
-        elif name in ("spmm_main_kernel", "spmm_panel_kernel"):
+        elif name in ("spmm_main_kernel", "spmm_short_kernel", "spmm_panel_kernel"):
             d = int(tag.split("d=")[1].split()[0])
             w = tag.split()
             ein = next((float(x[3:]) for x in w if x.startswith("in=")), 2.0 if "bf16 in" in tag else 4.0)
             eout = next((float(x[4:]) for x in w if x.startswith("out=")), 4.0)
             edo = next((float(x[3:]) for x in w if x.startswith("dO=")), 0.0)      # the loss epilogue also writes the gradient rows
             # compulsory traffic: CSR once, every input row once, the output once
+            panels_run = nnz_avg >= (28 if str(d) in short_widths else 12) * cfg.B
             runs = panels_run if name == "spmm_panel_kernel" else not (panels_run and " dO=" not in tag and str(d) in panel_widths)
             gq["bytes"] += runs * calls * (8.0 * nnz_avg + 4.0 * (cfg.B + 1) + cfg.B * d * (ein + eout + edo))
     total_ms = sum(v["ms"] for v in groups.values())
     dom_name, dom = max(groups.items(), key=lambda kv: kv[1]["ms"])
-    sp = [v for k, v in groups.items() if k.startswith(("spmm_main_kernel", "spmm_panel_kernel"))]
+    sp = [v for k, v in groups.items() if k.startswith(("spmm_main_kernel", "spmm_short_kernel", "spmm_panel_kernel"))]
     sparse_ms, sparse_bytes = sum(v["ms"] for v in sp), sum(v["bytes"] for v in sp)
     if args.breakdown:
         for name, tag, calls, ms in recs:

@@ -138,10 +138,10 @@ def bench_eval(cfg, args):
     torch.cuda.synchronize()
     wall_ms = 1e3 * (time.perf_counter() - t0) / reps
     ks = _kernels(recs, reps)
-    sp_ms = sum(ms for n, t, c, ms in recs if n in ("spmm_main_kernel", "spmm_panel_kernel")) / reps
+    sp_ms = sum(ms for n, t, c, ms in recs if n in ("spmm_main_kernel", "spmm_short_kernel", "spmm_panel_kernel")) / reps
     sp_bytes = sp_gather = 0.0
     for n, t, c, ms in recs:
-        if n == "spmm_main_kernel":
+        if n in ("spmm_main_kernel", "spmm_short_kernel"):       # one of them per product, the panel kernel next to it
             d = int(t.split("d=")[1].split()[0])
             xb = 2 if (cfg.bf16_features and d == cfg.d_in) else 4
             sp_bytes += (c / reps) * (8.0 * E + 4.0 * (cfg.N + 1) + cfg.N * d * (4 + xb))
