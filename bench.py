@@ -227,7 +227,7 @@ def measure(args, sg, si, torch, cfg, g, X, labels, weights, use_graph_req: str,
         gq["ms"] += ms
         if name in ("gemm_kernel", "gemm_split_kernel"):
             gq["flops"] += gemm_flops(tag) * calls
-        elif name == "gemm_skinny_bf16_kernel":
+        elif name in ("gemm_skinny_bf16_kernel", "gemm_rows_kernel"):
             # tall operand streamed once, small operand resident: bound by reading A and writing C.
             # tag: "NN|NT skinny MxNxK bf16 [a=<bytes>] [c=<bytes>]" (element sizes of the tall operand and of the
             # result as stored; 4 where not stated)
