@@ -530,8 +530,9 @@ template <typename XT> int xent_frame(int64_t d)
     return d < VEC || d > 32 * VEC ? 0 : spmm_short_frame<XT>(d);
 }
 
-// Workgroups: each leaves a row of partial sums to the final kernel
-inline unsigned spmm_short_xent_grid(const sgnn_csr *A) { return std::min<unsigned>(cdiv(A->rows, 64) + 512u, 4096u); }
+// Workgroups: each leaves a row of partial sums to the final kernel.  Twice what the chip holds at four a compute unit.  us with 4096 / 2048 / 1536 /
+// 1024: 2^20 x 1.27, 172 columns 332 / 331 / 335 / 342, 47 columns 135 / 129 / 135 / 131; 2^18 x 6.4, 47 columns 89 / 88 / 86 / 80, fp32 91 / 83 / 95 / 82.
+inline unsigned spmm_short_xent_grid(const sgnn_csr *A) { return std::min<unsigned>(cdiv(A->rows, 64) + 512u, 2048u); }
 
 template <int G, typename XT>
 int launch_short_xent_g(sgnn_ctx *ctx, const sgnn_csr *A, const XT *X, const spmm_panel_args &a, const spmm_epi &ep, hipStream_t st)
