@@ -11,8 +11,9 @@
 //    registers; after an exchange between the halves of the wavefront it holds 8 and stores, or reads of the mask, 16 bytes.  With C
 //    in the usual orientation a lane holds one column of 16 rows: 64 stores of 4 bytes a lane and block, and ballots to bring the mask's
 //    bits to the lanes that need them;
-//  - rows behind the last one repeat it (the same bytes to the same place), columns behind the last are dropped by the bounds of
-//    the buffer: no branch round a load or store, so that the waits count exactly.
+//  - in a wavefront with rows of its own, rows behind the last one repeat it (the same bytes to the same place by the same
+//    instruction), columns behind the last are dropped by the bounds of the buffer: no branch round a load or store, so that the waits count
+//    exactly.  A wavefront without rows leaves: with C in the place of the mask or of A it would read a row that another has overwritten.
 // Measured, us (gemm_skinny_bf16_kernel / here, K x N), 40000 rows: 256 x 256 23 / 20, with a mask 28 / 23; 172 x 256 21 / 17, 25 / 21; 256 x 172 19 / 18,
 // 22 / 18; 128 x 128 12 / 12, 13 / 13.  131072 rows: 256 x 256 38 / 35, 52 / 43; 172 x 256 32 / 29, 46 / 40; 200 x 200 36 / 31, 51 / 43; 128 x 128 17 / 16, 24 / 21.
 // Not for what does not stay in the Infinity Cache, see the launcher: its loads and stores cover 32 bytes of a row at a time, the other kernel's
@@ -120,6 +121,8 @@ __global__ __launch_bounds__(64 * ROWS_WAVES, 2) void gemm_rows_kernel(rows_args
     const bool ragged = K % 64 != 0, half_chunk = N % 8 != 0;
     constexpr uint32_t BEYOND = 0x80000000u;      // an offset outside the buffer of a wavefront's rows: the store is dropped
     for (uint32_t rb = blockIdx.x; rb < row_blocks; rb += gridDim.x) {
+        const int64_t wrow = (int64_t)rb * (32 * ROWS_WAVES) + wave * 32;       // the wavefront's first row
+        if (wrow >= a.M) break;
         f32x16 acc[NT8];
         const int64_t row = row_of(rb);
         const u16 *mp = MASK ? a.mask + row * a.ldm : nullptr;
@@ -159,7 +162,6 @@ __global__ __launch_bounds__(64 * ROWS_WAVES, 2) void gemm_rows_kernel(rows_args
             issue(s);                                        // of the next block
         }
         // register 4 g + i of lane (li, kh) of tile j: row li, column 32 j + 8 g + 4 kh + i
-        const int64_t wrow = min((int64_t)rb * (32 * ROWS_WAVES) + wave * 32, a.M - 1);
         const auto rsrc = __builtin_amdgcn_make_buffer_rsrc(a.C + wrow * a.ldc, 0, 0x7fffffff, 0x00020000);
         const uint32_t row_off = (uint32_t)(row - wrow) * (uint32_t)(a.ldc * 2);
 #pragma unroll

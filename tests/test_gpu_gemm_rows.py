@@ -40,6 +40,24 @@ def test_against_float64(M, N, K, tb):
         assert torch.all(C[M] == 7.0) and torch.all(C[:, N:] == 7.0)
 
 
+@pytest.mark.parametrize("M,N,K", [(4097, 128, 128), (4128, 256, 256), (4321, 172, 172), (66000, 72, 72)])
+def test_result_in_the_place_of_an_operand(M, N, K):
+    # every row is read by the wavefront that writes it and by no other, the last one too (M % 256 from 1 to 224: wavefronts without rows)
+    gen = torch.Generator().manual_seed(M)
+    A = torch.randn(M, K, generator=gen).to(DEV).bfloat16()
+    B = torch.randn(K, N, generator=gen).to(DEV)
+    mask = torch.randn(M, N, generator=gen).to(DEV).bfloat16()
+    ref, scale = A.double() @ B.bfloat16().double(), A.double().abs() @ B.bfloat16().double().abs()
+    masked = ref * (mask.double() > 0)
+    for _ in range(4):
+        C = mask.clone()
+        sg.sgnn_gemm(ctx(), False, False, A, B, None, sg.SGNN_BF16_MFMA, C, mask=C)
+        assert torch.all((C.double() - masked).abs() <= K * 2.0 ** -23 * scale + 2.0 ** -8 * masked.abs())
+        C = A.clone()
+        sg.sgnn_gemm(ctx(), False, False, C, B, None, sg.SGNN_BF16_MFMA, C)
+        assert torch.all((C.double() - ref).abs() <= K * 2.0 ** -23 * scale + 2.0 ** -8 * ref.abs())
+
+
 def test_infinities_beyond_the_reduction_do_not_count():
     # the last 16 bytes of a row of A reach over the end of a piece: what is there is not multiplied with zeros
     M, N, K = 4099, 100, 68
