@@ -35,8 +35,13 @@
 // wavefront wait for one another), four gathers in flight at five wavefronts a SIMD (156 against 149 at the time), panels of 256 bytes (132 against 120),
 // two pieces and more per partial row (125 -> 130, 141, 147 with two, five, eight).
 constexpr int SHORT_U = 8;                   // gathers in flight per wavefront, 1 KB each
-constexpr uint32_t SHORT_ITEMS = 64;         // partial rows of a long row, at most
-constexpr int SHORT_SUM = 4;                 // of which so many are read at a time
+// Partial rows of a long row: 64, more where each would be the sum of more than 256 entries and the plan has the pieces for it.  A partial
+// row is one chain of gathers, reading a partial row back is one more trip to memory.  65536 rows of 6 entries and 8 rows of 1e5, 256 / 128 / 47
+// bfloat16 columns, us: 186 / 110 / 78 with 64 whatever the length, 110 / 69 / 55 with this rule, 100 / 52 / 37 with all groups of the last
+// wavefront adding partial rows up (spmm_main_kernel 113 / 87 / 65).  Every piece a partial row: 8 rows of 2e4 instead, 47 columns, 37 instead of 30.
+constexpr uint32_t SHORT_ITEMS = 64;
+constexpr uint32_t SHORT_ITEM_LEN = 256;
+constexpr int SHORT_SUM = 4;                 // of which a group reads so many at a time
 constexpr uint32_t SHORT_SHARED = 4096;      // fewer pieces than this (a wavefront for each, four a SIMD): the groups share them
 constexpr uint64_t SHORT_GRID = 8192;        // workgroups of a panel, at most (2^20 rows of 1.27: 210 us, 218 and 222 with 4096 and 2048)
 constexpr int SHORT_ROWS = 8;                // rows that a group of lanes takes at a time, at most
@@ -239,7 +244,7 @@ __global__ __launch_bounds__(SPMM_NT, 4) void spmm_short_kernel(spmm_panel_args 
                 const int sh = 63 - __clzll(plen);
                 row = rc.x; pc = rc.y;
                 nch = min((uint32_t)((re - rs + plen - 1) >> sh), n_pieces - ((uint32_t)u0 + lane - pc));
-                ip = nch <= (uint32_t)a.panels ? nch : (nch + SHORT_ITEMS - 1) / SHORT_ITEMS;
+                ip = nch <= (uint32_t)a.panels ? nch : min((nch + SHORT_ITEMS - 1) / SHORT_ITEMS, max(SHORT_ITEM_LEN >> sh, 1u));
                 s = rs + ((int64_t)pc << sh);
                 if (pc % ip == 0) len = (int)min(re - s, (int64_t)ip << sh);
             }
@@ -384,21 +389,26 @@ __global__ __launch_bounds__(SPMM_NT, 4) void spmm_short_kernel(spmm_panel_args 
         const uint32_t grow = __shfl(row, gu, 64), gpc = __shfl(pc, gu, 64), gnch = __shfl(nch, gu, 64), gip = __shfl(ip, gu, 64);
         const uint32_t first = (uint32_t)u0 + gu - gpc, items = (gnch + gip - 1) / gip;
         bool whole = items <= 1;
-        if (mine && !whole) {
+        if (!whole) {
             // partial row out with device-scope stores, then a ticket; the last ticket adds the partial rows up
             // (word i of lane k at i * G + k: every store covers whole memory lines)
             const int64_t stride = (int64_t)a.panels * W;
             float *o = a.part + (int64_t)first * stride + p * W + k;
+            int last = 0;
+            if (mine) {
 #pragma unroll
-            for (int i = 0; i < VEC; ++i) __hip_atomic_store(o + (int64_t)gpc * stride + i * G, acc[i], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-            asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
-            uint32_t t = 0;
-            if (k == 0) t = atomicAdd(&a.ticket[first + p], 1u);
-            whole = __shfl(t, g * G, 64) + 1 == items;
-            if (whole) {
+                for (int i = 0; i < VEC; ++i) __hip_atomic_store(o + (int64_t)gpc * stride + i * G, acc[i], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+                asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+                uint32_t t = 0;
+                if (k == 0) t = atomicAdd(&a.ticket[first + p], 1u);
+                last = __shfl(t, g * G, 64) + 1 == items;
+            }
+            // (of a shared piece the other groups, too, add some of them up)
+            if (shared) last = __shfl(last, 0, 64);
+            if (last && (XENT || on)) {
 #pragma unroll
                 for (int i = 0; i < VEC; ++i) acc[i] = 0.f;
-                for (uint32_t it = 0; it < items; it += SHORT_SUM) {
+                for (uint32_t it = shared ? g * SHORT_SUM : 0; it < items; it += shared ? NE * SHORT_SUM : SHORT_SUM) {
                     float v[SHORT_SUM][VEC];
 #pragma unroll
                     for (int j = 0; j < SHORT_SUM; ++j)
@@ -412,8 +422,13 @@ __global__ __launch_bounds__(SPMM_NT, 4) void spmm_short_kernel(spmm_panel_args 
                             for (int i = 0; i < VEC; ++i) acc[i] += v[j][i];
                         }
                 }
-                if (k == 0) a.ticket[first + p] = 0;
+                if (k == 0 && mine) a.ticket[first + p] = 0;
             }
+            if (shared && last) {
+#pragma unroll
+                for (int i = 0; i < VEC; ++i) acc[i] = group_sum<G>(acc[i]);
+            }
+            whole = last;
         }
         if (mine && whole) {
             if constexpr (SIDE) beside(*reinterpret_cast<const u32x4_any *>(side_base + (int64_t)grow * side_row + col_bytes));

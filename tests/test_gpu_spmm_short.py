@@ -37,6 +37,27 @@ def _many_pieces():
     return lens
 
 
+def _hubs():
+    # few pieces, some of rows of 64 partial rows and more: pieces of 64, 128, 256 and 512 entries
+    lens = np.random.default_rng(5).integers(0, 9, 20001)
+    lens[[7, 8, 3000, 20000]] = [10000, 17000, 40000, 100000]
+    return lens
+
+
+def _pieces(lens):
+    # pieces of long rows, those of more than four times the mean (and eight): 64 entries, doubled until a row has 256 of them at most
+    long = lens[lens > max(4 * (lens.sum() // len(lens)), 8)]
+    return sum(-(-n // next(c for c in (64 << i for i in range(20)) if n <= 256 * c)) for n in long)
+
+
+def _hubs_and_many_pieces():
+    lens = _many_pieces()
+    lens[lens == 16] = 48
+    lens[[7, 8, 3000, 40000]] = [10000, 17000, 40000, 100000]
+    assert _pieces(lens) >= 4096             # a piece for every group of lanes
+    return lens
+
+
 def _full_blocks():
     # rows just under the length from which they count as long, side by side: a block's entries in several parts
     lens = np.random.default_rng(4).integers(14, 20, 40001)
@@ -45,6 +66,7 @@ def _full_blocks():
 
 
 MATRICES = {"few": _few_pieces, "many": _many_pieces, "full": _full_blocks}
+HUBS = {"hubs": _hubs, "hubs_many": _hubs_and_many_pieces}
 
 
 @pytest.mark.parametrize("name", MATRICES)
@@ -78,6 +100,49 @@ def test_widths(name, x_dtype, d):
         add = _operand(rows, d, torch.float32, ld, 3)
         sg.sgnn_spmm(ctx(), A, X, out[:rows], add=add)
         assert rel_err(out[:rows].cpu().numpy(), ref + _np(add)) < TOL_F32
+
+
+@pytest.mark.parametrize("name", HUBS)
+@pytest.mark.parametrize("x_dtype,d", [(torch.float32, 33), (torch.float32, 200), (torch.bfloat16, 47), (torch.bfloat16, 256), (torch.bfloat16, 400)])
+def test_hub_rows(name, x_dtype, d):
+    lens, cols = HUBS[name](), 2500
+    rows = len(lens)
+    rp, ci, v = _csr(lens, cols, d)
+    A = sg.Csr.from_arrays(rows, cols, rp, ci, v, DEV, with_plan=True)
+    ctx().reserve(rows, len(ci), rows, 512, len(ci))
+    X = _operand(cols, d, x_dtype, d, d)
+    ref = oracle.spmm(rp, ci, v, _np(X))
+    first = None
+    for _ in range(3):
+        sg.sgnn_csr_plan(ctx(), A)                                           # the pieces are numbered anew
+        out = torch.full((rows, d), 7.0, device=DEV)
+        sg.sgnn_spmm(ctx(), A, X, out)
+        assert rel_err(out.cpu().numpy(), ref) < TOL_F32
+        first = out if first is None else first
+        assert torch.equal(out, first)
+
+
+@pytest.mark.parametrize("x_dtype,d", [(torch.float32, 40), (torch.float32, 100), (torch.bfloat16, 48), (torch.bfloat16, 256)])
+def test_long_rows_are_added_up_in_short_chains(x_dtype, d):
+    # a row of 1e5 entries in a matrix with a piece for every group of lanes: pieces of 512 entries, a chain of gathers each.  A chain
+    # that begins with 2^24 loses every one after it (2^24 + 1 rounds to 2^24), the others are exact: what is missing is the chain's length.
+    lens, cols = _hubs_and_many_pieces(), 2500
+    lens[[7, 8, 3000, 40000, 77]] = [1, 1, 1, 1, 100000]
+    assert _pieces(lens) >= 4096
+    rows = len(lens)
+    rp, ci, v = _csr(lens, cols, 1)
+    ci[ci == 0] = 1
+    ci[rp[77]] = 0
+    v[:] = 1
+    A = sg.Csr.from_arrays(rows, cols, rp, ci, v, DEV)
+    X = torch.ones((cols, d), device=DEV, dtype=x_dtype)
+    X[0] = 2.0 ** 24
+    out = torch.empty((rows, d), device=DEV)
+    sg.sgnn_spmm(ctx(), A, X, out)
+    missing = 2.0 ** 24 + 99999 - out[77].double()
+    assert torch.all(missing >= -2) and torch.all(missing <= 512 + 2)        # 2: sums over 2^24 are even
+    out[77] = 0
+    assert torch.equal(out.cpu(), torch.as_tensor(np.where(np.arange(rows) == 77, 0, lens), dtype=torch.float32)[:, None].expand(rows, d))
 
 
 @pytest.mark.parametrize("name", MATRICES)
