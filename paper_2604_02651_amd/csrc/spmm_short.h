@@ -74,6 +74,22 @@ __device__ __forceinline__ int short_rows(uint32_t rows, uint32_t mean, int grou
     return (int)min(max(r, (uint64_t)1), (uint64_t)SHORT_ROWS);
 }
 
+// Whether the groups of a wavefront share every row as they share a piece: where there are too few rows for the chip and a group's chain
+// of gathers through a row, longer with the mean and with the values a lane adds up per entry, is what the product waits for.  us, spmm_main_kernel /
+// one row a group / shared, R-MAT rows x mean, matrices of which the host does not know that they have many entries:
+//                     bf16 47            bf16 256          fp32 47           fp32 256         with the loss, bf16 47
+//   1024 x 30         16 / 19 / 14       19 / 15 / 16      16 / 14 / 14      18 / 14 / 14     27 / 34 / 24
+//   1024 x 110        48 / 105 / 14      54 / 74 / 23      47 / 57 / 14      52 / 54 / 20     59 / 131 / 26
+//   2048 x 60         40 / 78 / 14       45 / 56 / 25      40 / 37 / 15      43 / 42 / 21     51 / 90 / 29
+//   4096 x 60         36 / 42 / 17       38 / 29 / 28      36 / 22 / 17      41 / 28 / 28     47 / 58 / 32
+//   8192 x 80         74 / 94 / 37       87 / 96 / 57      74 / 54 / 36      92 / 97 / 97     88 / 112 / 52
+//   16384 x 50        77 / 54 / 46       95 / 84 / 87      77 / 46 / 46      109 / 97 / 97    92 / 68 / 63
+// A quarter and a half of the factor: the same or slower at every size (8192 x 60, 47 bfloat16 columns 61 and 31 us, 30 with this one).
+__device__ __forceinline__ bool short_shares_rows(uint32_t rows, uint32_t mean, int values)
+{
+    return rows <= 65536u && 7ull * mean * (uint64_t)values > rows;
+}
+
 // The offsets of two rows, requested together (a branch around each of them cost a round trip to memory)
 __device__ __forceinline__ void row_offsets(const spmm_panel_args &a, uint64_t i, uint64_t j, int64_t &x, int64_t &y)
 {
@@ -120,9 +136,10 @@ __global__ __launch_bounds__(SPMM_NT, 4) void spmm_short_kernel(spmm_panel_args 
     const int long_len = (int)a.n_chunks[1];
     const int rows_each = short_rows(a.rows, a.n_chunks[3], NE, a.interleave), rows_all = rows_each * NE;
     // (with few pieces all groups share one: then the length of the chain of gathers counts, not the number of wavefronts)
-    const bool shared = n_pieces < SHORT_SHARED;
-    const uint32_t per_block = shared ? 1 : NE;
-    const uint64_t piece_blocks = (n_pieces + per_block - 1) / per_block, blocks = piece_blocks + (a.rows + (uint64_t)rows_all - 1) / rows_all;
+    const bool shared_rows = short_shares_rows(a.rows, a.n_chunks[3], NE * VEC), shared = shared_rows || n_pieces < SHORT_SHARED;
+    const uint32_t per_block = shared ? 1 : NE, n_units = n_pieces + (shared_rows ? a.rows : 0);      // pieces, and rows that are shared like them
+    const uint64_t piece_blocks = ((uint64_t)n_units + per_block - 1) / per_block,
+                   blocks = piece_blocks + (shared_rows ? 0 : (a.rows + (uint64_t)rows_all - 1) / rows_all);
     const uint64_t first_block = (uint64_t)(blockIdx.x / (unsigned)a.interleave) * (SPMM_NT / 64) + wv;
     const uint64_t nwaves = (uint64_t)(gridDim.x / (unsigned)a.interleave) * (SPMM_NT / 64);
     const char *__restrict__ xb = reinterpret_cast<const char *>(X);
@@ -234,9 +251,16 @@ __global__ __launch_bounds__(SPMM_NT, 4) void spmm_short_kernel(spmm_panel_args 
         uint64_t longs = 0;
         uint32_t left = 0, none = 0;
         uint32_t row = 0, pc = 0, nch = 1, ip = 1;
+        int work = 0;                         // the lane's unit has something to add up or to write
         if (pieces) {
             len = 0; s = 0;
-            if (lane < (int)per_block && u0 + lane < n_pieces) {
+            if (shared_rows && u0 >= n_pieces) {
+                int64_t re;
+                row = (uint32_t)u0 - n_pieces;
+                row_offsets(a, row, (uint64_t)row + 1, s, re);
+                work = re - s <= long_len;
+                len = work && lane == 0 ? (int)(re - s) : 0;
+            } else if (lane < (int)per_block && u0 + lane < n_pieces) {
                 const uint2 rc = a.desc[u0 + lane];
                 int64_t rs, re;
                 row_offsets(a, rc.x, (uint64_t)rc.x + 1, rs, re);
@@ -247,6 +271,7 @@ __global__ __launch_bounds__(SPMM_NT, 4) void spmm_short_kernel(spmm_panel_args 
                 ip = nch <= (uint32_t)a.panels ? nch : min((nch + SHORT_ITEMS - 1) / SHORT_ITEMS, max(SHORT_ITEM_LEN >> sh, 1u));
                 s = rs + ((int64_t)pc << sh);
                 if (pc % ip == 0) len = (int)min(re - s, (int64_t)ip << sh);
+                work = len > 0;
             }
             limit = 0;
 #pragma unroll
@@ -385,8 +410,9 @@ __global__ __launch_bounds__(SPMM_NT, 4) void spmm_short_kernel(spmm_panel_args 
 #pragma unroll
             for (int i = 0; i < VEC; ++i) acc[i] = group_sum<G>(acc[i]);
         }
-        const bool mine = (XENT || on) && glen > 0 && !(shared && g > 0);
         const uint32_t grow = __shfl(row, gu, 64), gpc = __shfl(pc, gu, 64), gnch = __shfl(nch, gu, 64), gip = __shfl(ip, gu, 64);
+        const int gwork = __shfl(work, gu, 64);       // by all lanes: the one it is read from may have no columns
+        const bool mine = (XENT || on) && gwork && !(shared && g > 0);
         const uint32_t first = (uint32_t)u0 + gu - gpc, items = (gnch + gip - 1) / gip;
         bool whole = items <= 1;
         if (!whole) {
@@ -433,8 +459,10 @@ __global__ __launch_bounds__(SPMM_NT, 4) void spmm_short_kernel(spmm_panel_args 
         if (mine && whole) {
             if constexpr (SIDE) beside(*reinterpret_cast<const u32x4_any *>(side_base + (int64_t)grow * side_row + col_bytes));
             // (the numbering of the pieces goes with the timing of the plan kernel: sums of such rows through the slots)
-            if constexpr (XENT) xent(grow, ep.labels[grow], std::true_type{});
-            else store(grow);
+            if constexpr (XENT) {
+                if (u0 < n_pieces) xent(grow, ep.labels[grow], std::true_type{});
+                else xent(grow, ep.labels[grow], std::false_type{});
+            } else store(grow);
         }
 #pragma unroll
         for (int i = 0; i < VEC; ++i) acc[i] = 0.f;

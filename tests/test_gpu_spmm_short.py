@@ -122,6 +122,65 @@ def test_hub_rows(name, x_dtype, d):
         assert torch.equal(out, first)
 
 
+def _few_rows(rows):
+    # few rows of many entries, of very different lengths: the groups of a wavefront share every row.  Empty rows (first, last, side by side), one
+    # entry, a full fetch and one more, rows just under and over the length from which they count as long (four times the mean), a hub
+    lens = np.random.default_rng(rows).integers(0, 120, rows)
+    lens[[0, rows - 1]] = 0
+    lens[10:20] = 0
+    lens[[1, 2, 3, 4, 5, 6, 7, 8]] = [1, 8, 9, 63, 64, 65, 128, 129]
+    lens[[30, 31, 32, 33]] = [236, 237, 300, 5000]
+    return lens
+
+
+@pytest.mark.parametrize("rows", [257, 1024, 1500])
+@pytest.mark.parametrize("x_dtype,d", [(torch.float32, 4), (torch.float32, 47), (torch.float32, 128), (torch.float32, 200),
+                                       (torch.bfloat16, 8), (torch.bfloat16, 47), (torch.bfloat16, 100), (torch.bfloat16, 256), (torch.bfloat16, 257)])
+def test_few_rows_of_many_entries(rows, x_dtype, d):
+    lens, cols = _few_rows(rows), 2500
+    assert rows < 7 * (lens.sum() // rows) * 8                                # 8: the fewest values a wavefront adds up side by side
+    rp, ci, v = _csr(lens, cols, d)
+    A = sg.Csr.from_arrays(rows, cols, rp, ci, v, DEV, with_plan=True)
+    assert A.capacity < 60 * rows + 65536                                     # not launched for the panel kernel as well
+    ctx().reserve(rows, len(ci), rows, 512, len(ci))
+    X = _operand(cols, d, x_dtype, d + d % 3, d, offset=d % 5)
+    ref = oracle.spmm(rp, ci, v, _np(X))
+    first = None
+    for _ in range(2):
+        sg.sgnn_csr_plan(ctx(), A)
+        out = torch.full((rows + 1, d), 7.0, device=DEV)
+        sg.sgnn_spmm(ctx(), A, X, out[:rows])
+        assert rel_err(out[:rows].cpu().numpy(), ref) < TOL_F32
+        assert torch.all(out[rows] == 7.0)
+        first = out if first is None else first
+        assert torch.equal(out, first)
+    perm = np.random.default_rng(d).permutation(cols).astype(np.int32)
+    inv = torch.empty(cols, dtype=torch.int64, device=DEV)
+    inv[dev(perm).long()] = torch.arange(cols, device=DEV)
+    sg.sgnn_spmm(ctx(), A, X[inv].contiguous(), out[:rows], row_index=dev(perm))
+    assert rel_err(out[:rows].cpu().numpy(), ref) < TOL_F32
+    add = _operand(rows, d, torch.float32, d + 4, 3)
+    sg.sgnn_spmm(ctx(), A, X, out[:rows], add=add)
+    assert rel_err(out[:rows].cpu().numpy(), ref + _np(add)) < TOL_F32
+
+
+@pytest.mark.parametrize("x_dtype,d", [(torch.float32, 40), (torch.bfloat16, 48), (torch.bfloat16, 100)])
+def test_few_rows_are_added_up_in_short_chains(x_dtype, d):
+    # rows of 400 entries, see the next test: every group of lanes has its share of each fetch of 64, a half of it where rows of X are widest
+    rows, n = 1000, 400
+    ci = np.random.default_rng(1).integers(1, rows, rows * n).astype(np.int32)
+    ci[::n] = 0
+    A = sg.Csr.from_arrays(rows, rows, np.arange(rows + 1) * n, ci, np.ones(rows * n, np.float32), DEV, with_plan=True)
+    X = torch.ones((rows, d), device=DEV, dtype=x_dtype)
+    X[0] = 2.0 ** 24
+    out = torch.empty((rows, d), device=DEV)
+    y, loss = torch.zeros(rows, dtype=torch.int32, device=DEV), torch.zeros(1, device=DEV)
+    sg.sgnn_csr_plan(ctx(), A)
+    sg.sgnn_spmm_xent(ctx(), A, X, None, y, loss, None, O=out)
+    missing = 2.0 ** 24 + n - 1 - out.double()
+    assert torch.all(missing >= -2) and torch.all(missing <= n // 2 + 32)
+
+
 @pytest.mark.parametrize("x_dtype,d", [(torch.float32, 40), (torch.float32, 100), (torch.bfloat16, 48), (torch.bfloat16, 256)])
 def test_long_rows_are_added_up_in_short_chains(x_dtype, d):
     # a row of 1e5 entries in a matrix with a piece for every group of lanes: pieces of 512 entries, a chain of gathers each.  A chain
@@ -145,12 +204,12 @@ def test_long_rows_are_added_up_in_short_chains(x_dtype, d):
     assert torch.equal(out.cpu(), torch.as_tensor(np.where(np.arange(rows) == 77, 0, lens), dtype=torch.float32)[:, None].expand(rows, d))
 
 
-@pytest.mark.parametrize("name", MATRICES)
+@pytest.mark.parametrize("name", [*MATRICES, "few_rows"])
 @pytest.mark.parametrize("bf16", [False, True])
 @pytest.mark.parametrize("d", [40, 47, 200])
 def test_layer_epilogues(name, d, bf16):
     # bias and ReLU of a transform-first layer, and the ReLU mask of the layer below in the transposed product
-    lens = MATRICES[name]()
+    lens = MATRICES[name]() if name in MATRICES else _few_rows(1024)
     n = len(lens)
     rp, ci, v = _csr(lens, n, d)
     A = sg.Csr.from_arrays(n, n, rp, ci, v, DEV)
@@ -190,11 +249,11 @@ def test_infinities_stay_in_their_rows(x_dtype):
     assert rel_err(got[fine], ref[fine]) < TOL_F32
 
 
-@pytest.mark.parametrize("name", MATRICES)
+@pytest.mark.parametrize("name", [*MATRICES, *HUBS, "few_rows"])
 @pytest.mark.parametrize("x_dtype,d", [(torch.float32, d) for d in (4, 7, 32, 33, 64, 66, 100, 128)] +
                          [(torch.bfloat16, d) for d in (8, 47, 64, 66, 128, 132, 172, 256)])
 def test_loss_in_the_epilogue(name, x_dtype, d):
-    lens = MATRICES[name]()
+    lens = {**MATRICES, **HUBS, "few_rows": lambda: _few_rows(1024)}[name]()
     n = len(lens)
     rp, ci, v = _csr(lens, n, d)
     v = v * np.float32(0.1)      # logits of a few units: exp(x - max) keeps the tolerance of the product
