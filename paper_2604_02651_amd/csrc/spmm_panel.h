@@ -41,34 +41,35 @@ struct spmm_panel_args {
     int wide_epi;                // out, mask and add allow 16-byte (fp32) / 8-element accesses at every column that is a multiple of VEC
 };
 
-// Which matrices go this way: those with 28 entries a row or more where spmm_short_kernel takes the others, 13 or more where
-// spmm_main_kernel does (rows of three panels and more and the epilogues that spmm_short_kernel does not have), and there 32 or more where
-// rows of X are 512 bytes and longer, there are 32768 of them and X is under 96 MB.  The count itself is on the device; the host
+// Which matrices go this way: those with as many entries a row as spmm_panel_mean says.  The count itself is on the device; the host
 // launches both kernels if the capacity is 40 entries a row and 65536 more, which the capacity of a mini-batch matrix (twice the
 // expected entries, sixteen more a row and 65536 more) is from a mean of 12 on, or 60 a row (a mean of 22) under 8192 rows, where
-// the second launch is a fifth of the product: 1024 x 16 and 4096 x 20 19 us with both launches, whichever kernel works, 15 with one.
+// the second launch is a fifth of the product: 1024 x 16 and 4096 x 20 17 us with both launches, whichever kernel works, 14 with one.
 // So a matrix whose capacity is its entries takes the kernel from a mean of 40 (60) on.
-// Measured on R-MAT matrices, us here / with spmm_short_kernel:
-//   rows x mean     bf16 256      bf16 128      bf16 47       fp32 256      fp32 100      fp32 47
-//   4096 x 30       27 / 21       19 / 15       18 / 18       22 / 19       18 / 17       18 / 14
-//   4096 x 80       43 / 47       28 / 52       22 / 62       38 / 49       26 / 38       20 / 39
-//   16384 x 13      42 / 25       24 / 21       26 / 20       39 / 31       26 / 21       20 / 17
-//   16384 x 24      59 / 40       33 / 38       29 / 32       54 / 48       35 / 33       24 / 30
-//   16384 x 40      79 / 67       45 / 50       37 / 45       73 / 73       46 / 55       31 / 39
-//   65536 x 60      190 / 246     125 / 182     118 / 132     276 / 351     151 / 206     106 / 149
-//   100000 x 20     160 / 118     119 / 81      120 / 68      214 / 188     122 / 102     101 / 71
-//   200000 x 30     300 / 352     209 / 235     215 / 179     551 / 602     273 / 310     191 / 200
-//   262144 x 24     344 / 351     246 / 209     257 / 157     625 / 625     307 / 320     226 / 181
-// and with spmm_main_kernel, rows x mean and fp32 256 columns: 4096 x 80 39 / 56, 16384 x 13 40 / 43, 65536 x 24 186 / 166, 65536 x 12.5 127 / 101,
+// Measured on R-MAT matrices of such a capacity, us here / with spmm_short_kernel, rows x mean:
+//                  bf16 47     bf16 128    bf16 256    fp32 47     fp32 100    fp32 256
+//   4096 x 42       18 / 17     21 / 18     32 / 24     17 / 17     21 / 21     23 / 24
+//   4096 x 70       19 / 22     24 / 23     40 / 34     17 / 20     24 / 31     31 / 38
+//   8192 x 28       19 / 21     24 / 24     38 / 31     17 / 19     23 / 25     32 / 37
+//   16384 x 16      26 / 22     26 / 28     47 / 32     20 / 22     29 / 27     43 / 42
+//   16384 x 24      29 / 30     33 / 38     56 / 42     23 / 30     34 / 35     53 / 50
+//   16384 x 42      37 / 42     51 / 54     86 / 72     33 / 41     52 / 59     81 / 88
+//   24000 x 42      56 / 46     69 / 54    115 / 72     47 / 44     67 / 61    108 / 95
+//   65536 x 34     108 / 76    115 / 100   173 / 146    91 / 81    121 / 124   201 / 211
+//   65536 x 55     118 / 129   126 / 164   190 / 217   106 / 129   149 / 180   262 / 320
+//   131072 x 24    155 / 93    146 / 110   198 / 171   130 / 92    164 / 151   302 / 292
+//   131072 x 28    156 / 120   153 / 151   215 / 232   133 / 123   175 / 201   328 / 376
+//   262144 x 24    257 / 138   244 / 193   339 / 351   223 / 162   305 / 321   626 / 616
+//   262144 x 34    286 / 210   285 / 296   436 / 504   261 / 246   411 / 454   836 / 873
+//   600000 x 20    528 / 340   502 / 480   731 / 771   455 / 401   683 / 713  1400 / 1404
+//   600000 x 28    588 / 544   578 / 720   955 / 1084  528 / 605   898 / 994  1895 / 1948
+// Where a group of lanes of spmm_short_kernel walks a row alone, 8192 to 20000 rows or so leave it waiting for the longest of them, less with
+// two rows a wavefront than with four or eight; with more rows it is the size of X that counts, this kernel having the better hold on the
+// caches.  (Rows of equal lengths: the two are within 5 % of each other from 65536 rows on, 16384 x 20 with 47 columns 19 to 22 here and 17.)
+// Against spmm_main_kernel, rows x mean and fp32 256 columns: 4096 x 80 39 / 56, 16384 x 13 40 / 43, 65536 x 24 186 / 166, 65536 x 12.5 127 / 101,
 // 262144 x 16 483 / 517, 262144 x 12.5 428 / 415; fp32 47 columns: 16384 x 13 23 / 32, 65536 x 12.5 62 / 63, 262144 x 12.5 187 / 164.
 constexpr uint32_t spmm_panel_room(uint32_t rows) { return rows < 8192 ? 60 : 40; }
 constexpr int SPMM_PANEL_MAX = 16;
-template <typename XT> uint32_t spmm_panel_mean(const sgnn_csr *A, int64_t d, bool or_short)
-{
-    const uint64_t row = (uint64_t)d * sizeof(XT);
-    if (or_short) return 28u;
-    return row >= 512 && A->rows >= 32768 && row * A->cols < (96ull << 20) ? 32u : 13u;
-}
 
 // Plan pieces that make up an item of a long row of `nch` pieces of `plen` entries: up to 1024 entries, fewer on a matrix with so few
 // pieces that they would not give every wavefront of the machine one.  A row with fewer pieces than there are panels is one
@@ -338,6 +339,16 @@ __global__ __launch_bounds__(SPMM_NT, 4) void spmm_panel_kernel(spmm_panel_args 
             }
         }
     }
+}
+
+// Entries a row from which on a matrix is this kernel's.  or_short: spmm_short_kernel has the others; else spmm_main_kernel, for rows of three
+// panels and more and the epilogues that spmm_short_kernel does not have.
+template <typename XT> uint32_t spmm_panel_mean(const sgnn_csr *A, int64_t d, bool or_short)
+{
+    const uint64_t row = (uint64_t)d * sizeof(XT), x = row * A->cols;
+    if (!or_short) return row >= 512 && A->rows >= 32768 && x < (96ull << 20) ? 32u : 13u;
+    if (A->rows >= 8192 && A->rows <= 20480) return d <= 16 * panel_vec<XT>::VEC ? 16u : (sizeof(XT) == 4 ? 24u : 42u);
+    return A->rows < 8192 || x <= (32ull << 20) ? 42u : (x <= (80ull << 20) ? 28u : (x <= (160ull << 20) ? 24u : 20u));
 }
 
 template <typename XT> bool spmm_panel_wanted(const sgnn_csr *A, int64_t d)

@@ -90,7 +90,7 @@ def test_layer_epilogues(matrix, d, bf16):
 
 @pytest.mark.parametrize("mean", [0, 3, 11, 12])
 def test_room_for_more_entries_than_there_are(mean):
-    # the host sees the capacity, the device the entries: on either side of the limit one of the two kernels does the work
+    # the host sees the capacity, the device the entries: both kernels are launched and the one for short rows does the work
     rows, cap = 900, 130000
     rng = np.random.default_rng(mean)
     lens = np.full(rows, mean)
@@ -112,7 +112,7 @@ def test_room_for_more_entries_than_there_are(mean):
 
 @pytest.mark.parametrize("rows,d,mean", [(32768, 47, 12), (32768, 47, 13), (32768, 127, 13), (32767, 128, 13), (32768, 128, 13), (32768, 128, 31), (32768, 128, 32)])
 def test_either_side_of_the_limit(rows, d, mean):
-    # room for 40 entries a row and 65536 more: the device decides by the mean, at a limit that goes with rows and width
+    # room for 40 entries a row and 65536 more: the device decides by the mean (for these widths the limits are those of the next test)
     rng = np.random.default_rng(mean)
     lens = np.full(rows, mean)
     lens[5], lens[10:10 + 900] = lens[5] + 900, lens[10:10 + 900] - 1
@@ -128,6 +128,47 @@ def test_either_side_of_the_limit(rows, d, mean):
     out = torch.full((rows, d), 7.0, device=DEV)
     sg.sgnn_spmm(ctx(), A, X, out)
     assert rel_err(out.cpu().numpy(), oracle.spmm(rp, ci, v, _np(X))) < TOL_F32
+
+
+def _with_mean(rows, cols, mean, capacity, seed):
+    """rows x cols with exactly rows * mean entries, rows of different lengths, and room for `capacity`."""
+    gen = torch.Generator(device=DEV).manual_seed(seed)
+    lens = torch.full((rows,), mean, device=DEV)
+    lens[5] += 900
+    lens[10:910] -= 1
+    A = sg.Csr(rows, cols, capacity, DEV)
+    A.rowptr[1:] = lens.cumsum(0)
+    n = rows * mean
+    A.colidx[:n] = torch.randint(0, cols, (n,), generator=gen, device=DEV, dtype=torch.int32)
+    A.val[:n] = torch.randn(n, generator=gen, device=DEV)
+    sg.sgnn_csr_plan(ctx(), A)
+    return A
+
+
+@pytest.mark.parametrize("rows,cols,x_dtype,d,add,limit", [
+    (4096, 4096, torch.float32, 47, False, 42), (8191, 8191, torch.bfloat16, 128, False, 42),
+    (8192, 8192, torch.float32, 64, False, 16), (20480, 20480, torch.bfloat16, 128, False, 16), (20480, 5000, torch.float32, 65, False, 24),
+    (8192, 8192, torch.bfloat16, 129, False, 42), (20481, 20481, torch.float32, 47, False, 42), (24576, 65536, torch.bfloat16, 256, False, 42),
+    (24576, 65537, torch.bfloat16, 256, False, 28), (131072, 131072, torch.bfloat16, 256, False, 28), (65536, 327680, torch.float32, 64, False, 28),
+    (65536, 327681, torch.float32, 64, False, 24), (65536, 163841, torch.float32, 256, False, 20), (262144, 262144, torch.float32, 100, False, 24),
+    # three panels, or a matrix added that is not in whole 16 bytes: the other kernel is the main one
+    (32767, 32767, torch.float32, 300, False, 13), (32768, 32768, torch.float32, 300, False, 32), (32768, 100000, torch.float32, 300, False, 13),
+    (32768, 32768, torch.float32, 47, True, 13)])
+def test_which_kernel_works(rows, cols, x_dtype, d, add, limit):
+    # Both kernels are launched.  Below the limit the result is bit for bit the one of the other kernel alone (a matrix without room for 40
+    # entries a row, 60 under 8192 rows, is not launched for the panel kernel); from the limit on the sums have another order.
+    room = (60 if rows < 8192 else 40) * rows + 65536
+    X = _operand(cols, d, x_dtype, d, 1)
+    extra = _operand(rows, d, torch.float32, d + 1, 2) if add else None
+    ctx().reserve(rows, room, rows, 512, room)
+    for mean in (limit - 1, limit):
+        out = [torch.full((rows, d), 7.0, device=DEV) for _ in range(2)]
+        for o, capacity in zip(out, (room, rows * mean)):
+            assert (capacity < room) == (o is out[1])
+            sg.sgnn_spmm(ctx(), _with_mean(rows, cols, mean, capacity, 3), X, o, add=extra)
+        assert torch.equal(out[0], out[1]) == (mean < limit)
+        # fp32 sums of at most 942 terms of a standard normal distribution, rel_err's bar as everywhere
+        assert (out[0] - out[1]).norm() < TOL_F32 * out[1].norm() and (out[0] - out[1]).abs().max() < TOL_F32 * out[1].abs().max()
 
 
 @pytest.mark.parametrize("x_dtype", [torch.float32, torch.bfloat16])
