@@ -69,6 +69,13 @@ void sgnn_prof_end(sgnn_ctx *ctx, hipStream_t st);
         SGNN_LAUNCH_CHECK(ctx, name);                                                           \
     } while (0)
 
+// Dynamic LDS of `bytes` for a kernel.  The attribute belongs to the kernel on the device that is current (the context's, which every entry
+// point binds), so it is set at every launch: remembered once a process it would be missing on a second device.
+template <class K> static inline hipError_t sgnn_allow_lds(K kernel, size_t bytes)
+{
+    return hipFuncSetAttribute(reinterpret_cast<const void *>(kernel), hipFuncAttributeMaxDynamicSharedMemorySize, (int)bytes);
+}
+
 // Bump allocator over the context scratch, reset at the start of every API call.
 struct ws_alloc {
     uint8_t *base;

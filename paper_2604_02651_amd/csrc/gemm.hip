@@ -1139,15 +1139,6 @@ template <int NT8, int S, bool TAIL>
 int launch_skinny_ns(sgnn_ctx *ctx, const gemm_args &a, int tb, const skinny_tail &tl, hipStream_t st)
 {
     const size_t lds = skinny_lds_bytes(NT8, 32 * S + 8);
-    static bool attr_set = false;
-    if (!attr_set) {
-        SGNN_HIP(ctx, hipFuncSetAttribute(reinterpret_cast<const void *>(&gemm_skinny_bf16_kernel<NT8, S, TAIL, false>),
-                                          hipFuncAttributeMaxDynamicSharedMemorySize, 160 * 1024));
-        if constexpr (!TAIL)
-            SGNN_HIP(ctx, hipFuncSetAttribute(reinterpret_cast<const void *>(&gemm_skinny_bf16_kernel<NT8, S, false, true>),
-                                              hipFuncAttributeMaxDynamicSharedMemorySize, 160 * 1024));
-        attr_set = true;
-    }
     const uint32_t n_rowblocks = (uint32_t)cdiv(a.M, 32 * SKINNY_WAVES);
     char tag[56];
     const bool vmask = !TAIL && a.mask && a.vecM;      // the mask in chunks of four; else element by element
@@ -1156,33 +1147,25 @@ int launch_skinny_ns(sgnn_ctx *ctx, const gemm_args &a, int tb, const skinny_tai
     const dim3 grid(std::min<uint32_t>(n_rowblocks, 256)), block(64 * SKINNY_WAVES);
     if constexpr (!TAIL) {
         if (a.a_bf16 && vmask) {
-            static bool attr16m = false;
-            if (!attr16m) {
-                SGNN_HIP(ctx, hipFuncSetAttribute(reinterpret_cast<const void *>(&gemm_skinny_bf16_kernel<NT8, S, false, true, true>),
-                                                  hipFuncAttributeMaxDynamicSharedMemorySize, 160 * 1024));
-                attr16m = true;
-            }
+            SGNN_HIP(ctx, sgnn_allow_lds(&gemm_skinny_bf16_kernel<NT8, S, false, true, true>, lds));
             SGNN_LAUNCH(ctx, st, "gemm_skinny_bf16_kernel", tag, (gemm_skinny_bf16_kernel<NT8, S, false, true, true>), grid, block, lds,
                         st, a, tb, n_rowblocks, tl);
             return SGNN_OK;
         }
         if (a.a_bf16) {
-            static bool attr16 = false;
-            if (!attr16) {
-                SGNN_HIP(ctx, hipFuncSetAttribute(reinterpret_cast<const void *>(&gemm_skinny_bf16_kernel<NT8, S, false, false, true>),
-                                                  hipFuncAttributeMaxDynamicSharedMemorySize, 160 * 1024));
-                attr16 = true;
-            }
+            SGNN_HIP(ctx, sgnn_allow_lds(&gemm_skinny_bf16_kernel<NT8, S, false, false, true>, lds));
             SGNN_LAUNCH(ctx, st, "gemm_skinny_bf16_kernel", tag, (gemm_skinny_bf16_kernel<NT8, S, false, false, true>), grid, block, lds,
                         st, a, tb, n_rowblocks, tl);
             return SGNN_OK;
         }
         if (vmask) {
+            SGNN_HIP(ctx, sgnn_allow_lds(&gemm_skinny_bf16_kernel<NT8, S, false, true>, lds));
             SGNN_LAUNCH(ctx, st, "gemm_skinny_bf16_kernel", tag, (gemm_skinny_bf16_kernel<NT8, S, false, true>), grid, block, lds, st, a,
                         tb, n_rowblocks, tl);
             return SGNN_OK;
         }
     }
+    SGNN_HIP(ctx, sgnn_allow_lds(&gemm_skinny_bf16_kernel<NT8, S, TAIL, false>, lds));
     SGNN_LAUNCH(ctx, st, "gemm_skinny_bf16_kernel", tag, (gemm_skinny_bf16_kernel<NT8, S, TAIL, false>), grid, block, lds, st, a, tb,
                 n_rowblocks, tl);
     return SGNN_OK;

@@ -42,3 +42,11 @@ def test_product_never_imports_the_oracle():
             if f.endswith((".py", ".hip", ".h", ".cpp")):
                 src = open(os.path.join(dirpath, f)).read()
                 assert "oracle" not in src.lower(), f
+
+
+def test_launchers_remember_nothing_for_the_whole_process():
+    # attributes of kernels belong to a device: a flag of the process would hold for the first one only
+    csrc = os.path.join(ROOT, "paper_2604_02651_amd", "csrc")
+    for f in sorted(os.listdir(csrc)):
+        found = re.findall(r"^\s+static\s+(?:const\s+)?(?:bool|int|hipError_t)\s+\w+\s*=.*$", open(os.path.join(csrc, f)).read(), flags=re.M)
+        assert not [x for x in found if "constexpr" not in x], (f, found)
