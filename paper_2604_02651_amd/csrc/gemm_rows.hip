@@ -256,6 +256,19 @@ int sgnn_launch_gemm_rows(sgnn_ctx *ctx, int tb, int64_t M, int64_t N, int64_t K
     // 262144 x 172 x 128 (157 MB) 39 / 36, 262144 x 256 x 48 (159) 36 / 32; 262144 x 172 x 172 (180) 55 / 58, 262144 x 100 x 256 (187) 47 / 52,
     // 262144 x 256 x 256 (268) 71 / 71, masked (403) 113 / 116, 2^20 x 256 x 256 250 / 272; 262144 x 64 x 256 35 / 42, 131072 x 48 x 256 18 / 24.
     if (N <= 64 || 2 * M * (K + N * (mask ? 2 : 1)) > (int64_t)160 << 20) return SGNN_ERR_UNSUPPORTED;
+    // Nor narrow results where rows of A are a multiple of 128 bytes apart.  A load covers 32 bytes of 32 rows; then these lie at the same place of
+    // their lines, and the loads take half as long again (4096 x 72 x 256: 13.4 us, 9.6 with rows 528 bytes apart; the other kernel reads
+    // whole lines, 11.7 and 11.5).  Up to 128 columns there is too little else to do.  us there / here, rows of K values, plain and masked:
+    //   4096 x 72 x 256   11.7 / 13.4  13.6 / 14.2     4096 x 128 x 256   12.1 / 14.0  14.5 / 15.3     16384 x 128 x 192  11.5 / 12.4  14.6 / 14.0
+    //   16384 x 100 x 256 13.4 / 14.6  16.1 / 15.7     65536 x 128 x 256  18.9 / 19.8  24.7 / 26.9     65536 x 72 x 192   13.5 / 13.6  16.4 / 15.6
+    //   4096 x 160 x 256  15.9 / 15.5  18.9 / 17.7     110000 x 100 x 192 25.4 / 23.7  35.4 / 31.5     4096 x 72 x 128     8.2 / 8.0   10.2 / 9.0
+    //   110000 x 128 x 256 29.1 / 30.2 40.9 / 38.2     132000 x 96 x 256  33.2 / 36.9  44.6 / 44.0     110000 x 192 x 256 35.9 / 37.2  55.4 / 51.6
+    //   132000 x 192 x 256 47.4 / 52.5 64.8 / 65.1     132000 x 160 x 256 44.2 / 47.4  61.7 / 63.2     132000 x 192 x 192 42.8 / 44.1  58.8 / 60.8
+    //   132000 x 256 x 256 57.5 / 57.6 81.3 / 82.1     (rows of 248 values: 72 to 256 columns 3 to 20 % faster here, 65536 masked rows of 160 and more even)
+    if (lda % 64 == 0) {
+        const int narrow = K > 192 ? (!mask && M > 110000 ? 192 : (!mask || M <= 65536 ? 128 : 0)) : (K > 128 && !mask && M <= 65536 ? 128 : 0);
+        if (N <= narrow) return SGNN_ERR_UNSUPPORTED;
+    }
     // four values at a time on every side; offsets of a wavefront's 32 rows of C in 31 bits
     if (M < 4096 || N > 256 || N % 4 || K < 8 || K > 256 || K % 4 || ldc >= (1 << 20) || (reinterpret_cast<uintptr_t>(C) & 3) || ldc % 2)
         return SGNN_ERR_UNSUPPORTED;
