@@ -46,26 +46,7 @@ struct spmm_panel_args {
 // expected entries, sixteen more a row and 65536 more) is from a mean of 12 on, or 60 a row (a mean of 22) under 8192 rows, where
 // the second launch is a fifth of the product: 1024 x 16 and 4096 x 20 17 us with both launches, whichever kernel works, 14 with one.
 // So a matrix whose capacity is its entries takes the kernel from a mean of 40 (60) on.
-// Measured on R-MAT matrices of such a capacity, us here / with spmm_short_kernel, rows x mean:
-//                  bf16 47     bf16 128    bf16 256    fp32 47     fp32 100    fp32 256
-//   4096 x 42       18 / 17     21 / 18     32 / 24     17 / 17     21 / 21     23 / 24
-//   4096 x 70       19 / 22     24 / 23     40 / 34     17 / 20     24 / 31     31 / 38
-//   8192 x 28       19 / 21     24 / 24     38 / 31     17 / 19     23 / 25     32 / 37
-//   16384 x 16      26 / 22     26 / 28     47 / 32     20 / 22     29 / 27     43 / 42
-//   16384 x 24      29 / 30     33 / 38     56 / 42     23 / 30     34 / 35     53 / 50
-//   16384 x 42      37 / 42     51 / 54     86 / 72     33 / 41     52 / 59     81 / 88
-//   24000 x 42      56 / 46     69 / 54    115 / 72     47 / 44     67 / 61    108 / 95
-//   65536 x 34     108 / 76    115 / 100   173 / 146    91 / 81    121 / 124   201 / 211
-//   65536 x 55     118 / 129   126 / 164   190 / 217   106 / 129   149 / 180   262 / 320
-//   131072 x 24    155 / 93    146 / 110   198 / 171   130 / 92    164 / 151   302 / 292
-//   131072 x 28    156 / 120   153 / 151   215 / 232   133 / 123   175 / 201   328 / 376
-//   262144 x 24    257 / 138   244 / 193   339 / 351   223 / 162   305 / 321   626 / 616
-//   262144 x 34    286 / 210   285 / 296   436 / 504   261 / 246   411 / 454   836 / 873
-//   600000 x 20    528 / 340   502 / 480   731 / 771   455 / 401   683 / 713  1400 / 1404
-//   600000 x 28    588 / 544   578 / 720   955 / 1084  528 / 605   898 / 994  1895 / 1948
-// Where a group of lanes of spmm_short_kernel walks a row alone, 8192 to 20000 rows or so leave it waiting for the longest of them, less with
-// two rows a wavefront than with four or eight; with more rows it is the size of X that counts, this kernel having the better hold on the
-// caches.  (Rows of equal lengths: the two are within 5 % of each other from 65536 rows on, 16384 x 20 with 47 columns 19 to 22 here and 17.)
+// The limits against spmm_short_kernel stand at PANEL_BANDS.
 // Against spmm_main_kernel, rows x mean and fp32 256 columns: 4096 x 80 39 / 56, 16384 x 13 40 / 43, 65536 x 24 186 / 166, 65536 x 12.5 127 / 101,
 // 262144 x 16 483 / 517, 262144 x 12.5 428 / 415; fp32 47 columns: 16384 x 13 23 / 32, 65536 x 12.5 62 / 63, 262144 x 12.5 187 / 164.
 constexpr uint32_t spmm_panel_room(uint32_t rows) { return rows < 8192 ? 60 : 40; }
@@ -341,14 +322,52 @@ __global__ __launch_bounds__(SPMM_NT, 4) void spmm_panel_kernel(spmm_panel_args 
     }
 }
 
+// Entries a row from which on this kernel is the faster one of the two by groups of lanes, by rows of the matrix, type of X and how spmm_short_kernel
+// covers a row: groups of 8, 16 or 32 lanes, two panels.  A group of lanes walks a row alone there: with few rows it is the chains of gathers that count,
+// longest with four values a lane and eight rows a wavefront (all groups of a wavefront share a row here, and there where rows are very few).  With many rows it is how
+// the two take hub rows: from 1.5 million entries or so on there are so many pieces that spmm_short_kernel has a group for each, and this kernel
+// has the better hold on the caches, the more so the larger X is.
+// Each number is the middle of the range in which the sum of what is lost on either side is least, over some 7000 R-MAT matrices of 1000 to 500000 rows and 8 to 250
+// entries a row; the rule loses 0.6 % to the faster kernel in the mean and more than 10 % in one matrix of fifty, beside a limit.  us here / there, rows x mean:
+//                  bf16 47      bf16 100     bf16 256     fp32 32      fp32 47      fp32 100     fp32 256
+//   2048 x 22      14 / 12      15 / 13      20 / 14      10 / 11      11 / 12      14 / 14      14 / 15
+//   2048 x 48      16 / 14      18 / 17      24 / 24      10 / 12      14 / 14      18 / 19      18 / 20
+//   4096 x 34      17 / 15      19 / 16      30 / 23      11 / 13      15 / 17      19 / 19      21 / 21
+//   8191 x 22      18 / 20      21 / 21      32 / 27      12 / 17      16 / 18      20 / 22      27 / 32
+//   8191 x 42      22 / 26      27 / 28      47 / 47      14 / 21      19 / 25      28 / 36      39 / 50
+//   12000 x 18     22 / 21      23 / 25      38 / 30      14 / 16      17 / 20      23 / 25      36 / 34
+//   16384 x 30     31 / 37      35 / 40      63 / 53      21 / 28      26 / 31      39 / 43      62 / 61
+//   20480 x 34     42 / 47      56 / 54      90 / 69      26 / 33      38 / 42      56 / 57      86 / 82
+//   32768 x 34     65 / 49      75 / 52      114 / 77     41 / 36      56 / 44      72 / 64      124 / 108
+//   49152 x 34     83 / 70      93 / 80      120 / 110    55 / 54      72 / 67      88 / 94      147 / 154
+//   49152 x 48     99 / 87      112 / 112    156 / 150    66 / 65      86 / 91      112 / 127    181 / 208
+//   65536 x 26     90 / 66      103 / 84     138 / 111    58 / 48      78 / 69      98 / 95      159 / 166
+//   65536 x 42     112 / 97     124 / 129    169 / 180    74 / 72      98 / 106     125 / 152    206 / 255
+//   91000 x 30     126 / 107    141 / 118    184 / 176    82 / 77      108 / 97     136 / 150    224 / 259
+//   91000 x 42     136 / 143    149 / 176    204 / 230    88 / 102     121 / 143    162 / 196    284 / 340
+//   131072 x 22    137 / 88     145 / 108    177 / 163    88 / 64      117 / 91     142 / 142    255 / 260
+//   131072 x 34    165 / 137    177 / 172    226 / 250    110 / 93     147 / 142    187 / 215    353 / 402
+//   262144 x 22    227 / 149    245 / 193    304 / 338    145 / 102    202 / 168    267 / 294    530 / 553
+//   262144 x 34    273 / 242    302 / 309    414 / 496    177 / 170    258 / 269    390 / 438    787 / 840
+//   262144 x 48    324 / 320    369 / 431    561 / 676    212 / 224    323 / 362    536 / 607    1112 / 1156
+struct panel_band { uint32_t rows; uint8_t limit[2][4]; };       // up to so many rows; fp32, bfloat16; none: by entries, see spmm_panel_mean
+constexpr panel_band PANEL_BANDS[] = {
+    {2499, {{54, 56, 34, 30}, {100, 100, 100, 100}}}, {6499, {{10, 16, 28, 20}, {36, 64, 90, 120}}},  {16999, {{12, 12, 22, 22}, {16, 12, 46, 44}}},
+    {22499, {{16, 26, 32, 50}, {22, 30, 80, 90}}},    {44999, {}},                                      {61999, {{54, 38, 32, 32}, {58, 44, 48, 38}}},
+    {119999, {{36, 32, 28, 28}, {38, 36, 32, 30}}},   {0xffffffffu, {{40, 30, 20, 20}, {44, 28, 24, 20}}}};
+
 // Entries a row from which on a matrix is this kernel's.  or_short: spmm_short_kernel has the others; else spmm_main_kernel, for rows of three
 // panels and more and the epilogues that spmm_short_kernel does not have.
 template <typename XT> uint32_t spmm_panel_mean(const sgnn_csr *A, int64_t d, bool or_short)
 {
-    const uint64_t row = (uint64_t)d * sizeof(XT), x = row * A->cols;
-    if (!or_short) return row >= 512 && A->rows >= 32768 && x < (96ull << 20) ? 32u : 13u;
-    if (A->rows >= 8192 && A->rows <= 20480) return d <= 16 * panel_vec<XT>::VEC ? 16u : (sizeof(XT) == 4 ? 24u : 42u);
-    return A->rows < 8192 || x <= (32ull << 20) ? 42u : (x <= (80ull << 20) ? 28u : (x <= (160ull << 20) ? 24u : 20u));
+    constexpr int VEC = panel_vec<XT>::VEC;
+    const uint64_t row = (uint64_t)d * sizeof(XT);
+    if (!or_short) return row >= 512 && A->rows >= 32768 && row * A->cols < (96ull << 20) ? 32u : 13u;
+    const int cover = d <= 8 * VEC ? 0 : (d <= 16 * VEC ? 1 : (d <= 32 * VEC ? 2 : 3));
+    const panel_band *b = PANEL_BANDS;
+    while (A->rows > b->rows) ++b;
+    if (!b->limit[0][0]) return (cover >= 2 && sizeof(XT) == 4 ? 1600000u : 1900000u) / A->rows;
+    return b->limit[sizeof(XT) == 2][cover];
 }
 
 template <typename XT> bool spmm_panel_wanted(const sgnn_csr *A, int64_t d)

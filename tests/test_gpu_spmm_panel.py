@@ -146,11 +146,14 @@ def _with_mean(rows, cols, mean, capacity, seed):
 
 
 @pytest.mark.parametrize("rows,cols,x_dtype,d,add,limit", [
-    (4096, 4096, torch.float32, 47, False, 42), (8191, 8191, torch.bfloat16, 128, False, 42),
-    (8192, 8192, torch.float32, 64, False, 16), (20480, 20480, torch.bfloat16, 128, False, 16), (20480, 5000, torch.float32, 65, False, 24),
-    (8192, 8192, torch.bfloat16, 129, False, 42), (20481, 20481, torch.float32, 47, False, 42), (24576, 65536, torch.bfloat16, 256, False, 42),
-    (24576, 65537, torch.bfloat16, 256, False, 28), (131072, 131072, torch.bfloat16, 256, False, 28), (65536, 327680, torch.float32, 64, False, 28),
-    (65536, 327681, torch.float32, 64, False, 24), (65536, 163841, torch.float32, 256, False, 20), (262144, 262144, torch.float32, 100, False, 24),
+    (2499, 2499, torch.float32, 47, False, 56), (2500, 2500, torch.float32, 47, False, 16), (2500, 9000, torch.float32, 32, False, 10),
+    (6499, 6499, torch.bfloat16, 64, False, 36), (6499, 6499, torch.bfloat16, 65, False, 64), (6500, 6500, torch.bfloat16, 64, False, 16),
+    (8192, 8192, torch.float32, 64, False, 12), (8192, 8192, torch.bfloat16, 129, False, 46), (8192, 8192, torch.bfloat16, 257, False, 44),
+    (16999, 16999, torch.bfloat16, 128, False, 12), (17000, 17000, torch.bfloat16, 128, False, 30), (22499, 5000, torch.float32, 65, False, 32),
+    (40000, 40000, torch.float32, 100, False, 40), (44999, 44999, torch.float32, 256, False, 35),
+    (45000, 45000, torch.float32, 129, False, 32), (61999, 61999, torch.float32, 65, False, 32), (62000, 62000, torch.float32, 128, False, 28),
+    (65536, 65536, torch.bfloat16, 47, False, 38), (119999, 119999, torch.bfloat16, 256, False, 32), (120000, 120000, torch.bfloat16, 256, False, 24),
+    (120000, 120000, torch.float32, 64, False, 30), (131072, 131072, torch.bfloat16, 400, False, 20), (262144, 262144, torch.float32, 256, False, 20),
     # three panels, or a matrix added that is not in whole 16 bytes: the other kernel is the main one
     (32767, 32767, torch.float32, 300, False, 13), (32768, 32768, torch.float32, 300, False, 32), (32768, 100000, torch.float32, 300, False, 13),
     (32768, 32768, torch.float32, 47, True, 13)])
