@@ -58,14 +58,37 @@ def _hubs_and_many_pieces():
     return lens
 
 
-def _full_blocks():
-    # rows just under the length from which they count as long, side by side: a block's entries in several parts
-    lens = np.random.default_rng(4).integers(14, 20, 40001)
-    lens[1000:3000] = 64
+def _blocks(lens, groups, panels=1):
+    """Rows that are not long of every block of a wavefront of so many groups: what a block walks, and with the long ones in place."""
+    mean, long_len = lens.sum() // len(lens), max(4 * (lens.sum() // len(lens)), 8)
+    rows = min(max(min(48 // mean, len(lens) * panels // (4096 * groups)), 1), 8) * groups
+    lens = np.pad(lens, (0, -len(lens) % rows)).reshape(-1, rows)
+    return np.where(lens > long_len, 0, lens).sum(1), (lens > long_len).any(1), (lens == 0).any(1)
+
+
+def _blocks_in_parts(low, high, row, *shapes):
+    # rows of the length up to which they do not count as long side by side: the entries of a block do not fit the part of LDS they go
+    # through, a row begins in one part and ends in the next, with empty rows and long ones in such blocks too
+    lens = np.random.default_rng(4).integers(low, high, 40001)
+    lens[1000:3000] = row
+    lens[1003:3000:37] = 0
+    lens[1018:3000:37] = 300
+    for groups, panels, entries in shapes:
+        walked, has_long, has_empty = _blocks(lens, groups, panels)
+        parts = walked > entries
+        assert (parts & has_long).any() and (parts & has_empty).any() and (parts & ~has_long & ~has_empty).any()
     return lens
 
 
-MATRICES = {"few": _few_pieces, "many": _many_pieces, "full": _full_blocks}
+def _full_blocks():
+    return _blocks_in_parts(14, 19, 76, (8, 1, 512), (4, 1, 512))       # groups of 8 and of 16 lanes: 512 entries in LDS at a time
+
+
+def _full_wide_blocks():
+    return _blocks_in_parts(8, 13, 48, (2, 1, 256), (2, 2, 256))        # groups of 32 lanes: 256
+
+
+MATRICES = {"few": _few_pieces, "many": _many_pieces, "full": _full_blocks, "full_wide": _full_wide_blocks}
 HUBS = {"hubs": _hubs, "hubs_many": _hubs_and_many_pieces}
 
 
@@ -290,3 +313,103 @@ def test_loss_in_the_epilogue(name, x_dtype, d):
         if first is None:
             first = (loss.clone(), db.clone(), dO.clone())
         assert torch.equal(loss, first[0]) and torch.equal(db, first[1]) and torch.equal(dO, first[2])
+
+
+def _products(call, entries):
+    """The sparse-product kernels of a call in a context with scratch for so many entries; None where it refuses for want of scratch."""
+    c = sg.Context(0)
+    try:
+        c.reserve(1, 1, 1, 1, entries)
+        c.profile(True)
+        try:
+            call(c)
+        except sg.SgnnError as e:
+            assert "scratch too small" in str(e)
+            return None
+        return [name for name, *_ in c.profile_read() if name in ("spmm_main_kernel", "spmm_short_kernel")]
+    finally:
+        c.close()
+
+
+def _least_scratch(wanted):
+    """The smallest number of entries that a bisection finds to satisfy `wanted`."""
+    low, high = 0, 1 << 22
+    assert not wanted(low) and wanted(high)
+    while high - low > 1:
+        mid = (low + high) // 2
+        low, high = (low, mid) if wanted(mid) else (mid, high)
+    return high
+
+
+@pytest.mark.parametrize("with_plan", [False, True])
+def test_scratch_for_the_main_kernel_only(with_plan):
+    # partial rows of 129 columns: three times 64 in the main kernel where rows are not aligned, two panels of 128 here
+    lens, cols, d = _few_pieces(), 2500, 129
+    rows = len(lens)
+    rp, ci, v = _csr(lens, cols, 1)
+    A = sg.Csr.from_arrays(rows, cols, rp, ci, v, DEV, with_plan=with_plan)
+    if with_plan:
+        sg.sgnn_csr_plan(ctx(), A)
+    X = _operand(cols, d, torch.float32, d, 1)
+    ref = oracle.spmm(rp, ci, v, _np(X))
+    out = torch.empty((rows, d), device=DEV)
+    call = lambda c: sg.sgnn_spmm(c, A, X, out)
+    least = _least_scratch(lambda n: _products(call, n) is not None)
+    for entries, kernel in ((least, "spmm_main_kernel"), (_least_scratch(lambda n: _products(call, n) == ["spmm_short_kernel"]), "spmm_short_kernel")):
+        out.fill_(7)
+        assert _products(call, entries) == [kernel]
+        assert rel_err(_np(out), ref) < TOL_F32
+
+
+@pytest.mark.parametrize("x_dtype,d", [(torch.float32, 47), (torch.float32, 100), (torch.bfloat16, 47), (torch.bfloat16, 100), (torch.bfloat16, 172)])
+@pytest.mark.parametrize("entries", [8, 100001])
+def test_loss_of_the_main_kernel(x_dtype, d, entries):
+    # a matrix of eight entries at most has no long rows and no plan; with 1e5 rows of one entry the main kernel leaves fewer partial sums than
+    # the other and takes the call where there is scratch for those only
+    n = min(entries * 500, 100001)
+    rp = np.minimum(np.arange(n + 1) * entries // n, entries)
+    rng = np.random.default_rng(d)
+    ci, v = rng.integers(0, n, entries).astype(np.int32), rng.standard_normal(entries).astype(np.float32)
+    A = sg.Csr.from_arrays(n, n, rp, ci, v, DEV, with_plan=True)
+    sg.sgnn_csr_plan(ctx(), A)
+    X, b = _operand(n, d, x_dtype, d + 4 - d % 4, d), _operand(1, d, torch.float32, d, 3)[0]
+    y = rng.integers(0, d, n)
+    O = torch.as_tensor(oracle.spmm(rp, ci, v, _np(X)) + _np(b))
+    dO_ref = (torch.softmax(O, 1) - torch.nn.functional.one_hot(torch.as_tensor(y), d)) / n
+    loss_ref = torch.nn.functional.cross_entropy(O, torch.as_tensor(y)).item()
+    loss, db, dO = torch.zeros(1, device=DEV), torch.empty(d, device=DEV), torch.empty((n, d + 4 - d % 4), dtype=x_dtype, device=DEV)[:, :d]
+    call = lambda c: sg.sgnn_spmm_xent(c, A, X, b, dev(y.astype(np.int32)), loss, dO, dO_colsum=db)
+    scratch = 1 << 22 if entries == 8 else _least_scratch(lambda k: _products(call, k) is not None)
+    loss.zero_()
+    dO.fill_(7)
+    assert _products(call, scratch) == ["spmm_main_kernel"]
+    assert entries == 8 or _products(call, 1 << 22) == ["spmm_short_kernel"]
+    got = _np(dO)
+    # one rounding of every entry where dO is bfloat16; the column sums add what is stored
+    assert rel_err(got, dO_ref.numpy()) < (2.0 ** -8 if x_dtype == torch.bfloat16 else TOL_F32)
+    assert np.abs(_np(db) - got.sum(0)).max() < 1e-5 * np.abs(got).sum(0).max()
+    assert abs(loss.item() - loss_ref) < TOL_F32 * abs(loss_ref)
+
+
+@pytest.mark.parametrize("x_dtype,d", [(torch.float32, 47), (torch.float32, 128), (torch.bfloat16, 47), (torch.bfloat16, 100), (torch.bfloat16, 172)])
+def test_loss_with_rows_of_x_beyond_4_gb(x_dtype, d):
+    lens, cols = _few_pieces(), (1 << 20) + 77
+    n, ld = len(lens), 4096
+    rp, ci, v = _csr(lens, cols, d)
+    v = v * np.float32(0.1)
+    assert int(ci.max()) * ld * x_dtype.itemsize > 1 << 32
+    A = sg.Csr.from_arrays(n, cols, rp, ci, v, DEV, with_plan=True)
+    sg.sgnn_csr_plan(ctx(), A)
+    ctx().reserve(n, len(ci), n, 256, len(ci))
+    X = torch.empty((cols, ld), dtype=x_dtype, device=DEV)[:, :d]
+    X.copy_(torch.randn((cols, d), generator=torch.Generator(device=DEV).manual_seed(d), device=DEV))
+    y = np.random.default_rng(d).integers(0, d, n)
+    O = torch.as_tensor(oracle.spmm(rp, ci, v, _np(X)))
+    dO_ref = (torch.softmax(O, 1) - torch.nn.functional.one_hot(torch.as_tensor(y), d)) / n
+    loss_ref = torch.nn.functional.cross_entropy(O, torch.as_tensor(y)).item()
+    loss, db, dO = torch.zeros(1, device=DEV), torch.empty(d, device=DEV), torch.empty((n, d + 4 - d % 4), dtype=x_dtype, device=DEV)[:, :d]
+    sg.sgnn_spmm_xent(ctx(), A, X, None, dev(y.astype(np.int32)), loss, dO, dO_colsum=db)
+    got = _np(dO)
+    assert rel_err(got, dO_ref.numpy()) < (2.0 ** -8 if x_dtype == torch.bfloat16 else TOL_F32)
+    assert np.abs(_np(db) - got.sum(0)).max() < 1e-5 * np.abs(got).sum(0).max()
+    assert abs(loss.item() - loss_ref) < TOL_F32 * abs(loss_ref)
