@@ -138,10 +138,11 @@ __global__ __launch_bounds__(SPMM_NT, 4) void spmm_short_kernel(spmm_panel_args 
     // (with few pieces all groups share one: then the length of the chain of gathers counts, not the number of wavefronts)
     const bool shared_rows = short_shares_rows(a.rows, a.n_chunks[3], NE * VEC), shared = shared_rows || n_pieces < SHORT_SHARED;
     const uint32_t per_block = shared ? 1 : NE, n_units = n_pieces + (shared_rows ? a.rows : 0);      // pieces, and rows that are shared like them
-    const uint64_t piece_blocks = ((uint64_t)n_units + per_block - 1) / per_block,
-                   blocks = piece_blocks + (shared_rows ? 0 : (a.rows + (uint64_t)rows_all - 1) / rows_all);
-    const uint64_t first_block = (uint64_t)(blockIdx.x / (unsigned)a.interleave) * (SPMM_NT / 64) + wv;
-    const uint64_t nwaves = (uint64_t)(gridDim.x / (unsigned)a.interleave) * (SPMM_NT / 64);
+    // (32 bits: at most 2^24 pieces and 2^31 blocks of two rows.  Scalars are short here: held in 64 bits the loss forms spilled more)
+    const uint32_t piece_blocks = (n_units + per_block - 1) / per_block;
+    const uint32_t blocks = piece_blocks + (shared_rows ? 0 : (uint32_t)((a.rows + (uint64_t)rows_all - 1) / rows_all));
+    const uint32_t first_block = blockIdx.x / (unsigned)a.interleave * (SPMM_NT / 64) + wv;
+    const uint32_t nwaves = gridDim.x / (unsigned)a.interleave * (SPMM_NT / 64);
     const char *__restrict__ xb = reinterpret_cast<const char *>(X);
     const int64_t row_bytes = a.ldx * (int64_t)sizeof(XT);          // below 2^32 if OFF32
 
@@ -231,10 +232,10 @@ __global__ __launch_bounds__(SPMM_NT, 4) void spmm_short_kernel(spmm_panel_args 
         short_store<VEC>(a.out, row * a.ldo + colb, acc, ep.out_bf16);
     };
 
-    for (uint64_t block = first_block; block < blocks; block += nwaves) {
+    for (uint32_t block = first_block; block < blocks; block += nwaves) {
         const bool pieces = block < piece_blocks;
         const int R = pieces ? 1 : rows_each, RW = R * NE, gb = g * R;
-        const uint64_t u0 = pieces ? block * per_block : (block - piece_blocks) * rows_all;       // the first piece or row
+        const uint64_t u0 = pieces ? (uint64_t)block * per_block : (uint64_t)(block - piece_blocks) * rows_all;       // the first piece or row
         if constexpr (SIDE) {
             if (!pieces) {
                 const char *first_row = side_base + (int64_t)u0 * side_row;
@@ -250,16 +251,15 @@ __global__ __launch_bounds__(SPMM_NT, 4) void spmm_short_kernel(spmm_panel_args 
         int64_t s;                            // where they begin
         uint64_t longs = 0;
         uint32_t left = 0, none = 0;
-        uint32_t row = 0, pc = 0, nch = 1, ip = 1;
-        int work = 0;                         // the lane's unit has something to add up or to write
+        uint32_t row = 0, pc = 0, nch = 0, ip = 1;       // nch: 0 where the lane's unit has nothing to add up or to write
         if (pieces) {
             len = 0; s = 0;
-            if (shared_rows && u0 >= n_pieces) {
+            if (u0 >= n_pieces) {             // a row that is shared
                 int64_t re;
                 row = (uint32_t)u0 - n_pieces;
                 row_offsets(a, row, (uint64_t)row + 1, s, re);
-                work = re - s <= long_len;
-                len = work && lane == 0 ? (int)(re - s) : 0;
+                nch = re - s <= long_len;
+                len = nch && lane == 0 ? (int)(re - s) : 0;
             } else if (lane < (int)per_block && u0 + lane < n_pieces) {
                 const uint2 rc = a.desc[u0 + lane];
                 int64_t rs, re;
@@ -271,7 +271,7 @@ __global__ __launch_bounds__(SPMM_NT, 4) void spmm_short_kernel(spmm_panel_args 
                 ip = nch <= (uint32_t)a.panels ? nch : min((nch + SHORT_ITEMS - 1) / SHORT_ITEMS, max(SHORT_ITEM_LEN >> sh, 1u));
                 s = rs + ((int64_t)pc << sh);
                 if (pc % ip == 0) len = (int)min(re - s, (int64_t)ip << sh);
-                work = len > 0;
+                if (len == 0) nch = 0;
             }
             limit = 0;
 #pragma unroll
@@ -411,8 +411,7 @@ __global__ __launch_bounds__(SPMM_NT, 4) void spmm_short_kernel(spmm_panel_args 
             for (int i = 0; i < VEC; ++i) acc[i] = group_sum<G>(acc[i]);
         }
         const uint32_t grow = __shfl(row, gu, 64), gpc = __shfl(pc, gu, 64), gnch = __shfl(nch, gu, 64), gip = __shfl(ip, gu, 64);
-        const int gwork = __shfl(work, gu, 64);       // by all lanes: the one it is read from may have no columns
-        const bool mine = (XENT || on) && gwork && !(shared && g > 0);
+        const bool mine = (XENT || on) && gnch && !(shared && g > 0);
         const uint32_t first = (uint32_t)u0 + gu - gpc, items = (gnch + gip - 1) / gip;
         bool whole = items <= 1;
         if (!whole) {
