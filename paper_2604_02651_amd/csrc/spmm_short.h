@@ -84,10 +84,12 @@ __device__ __forceinline__ int short_rows(uint32_t rows, uint32_t mean, int grou
 //   4096 x 60         36 / 42 / 17       38 / 29 / 28      36 / 22 / 17      41 / 28 / 28     47 / 58 / 32
 //   8192 x 80         74 / 94 / 37       87 / 96 / 57      74 / 54 / 36      92 / 97 / 97     88 / 112 / 52
 //   16384 x 50        77 / 54 / 46       95 / 84 / 87      77 / 46 / 46      109 / 97 / 97    92 / 68 / 63
+// From 14000 rows on only with more entries a row (alone / shared, with the loss, 12 bfloat16 columns): 16384 x 40 45 / 52, 16384 x 60 80 / 62,
+// 24000 x 60 57 / 84, 24000 x 100 95 / 108, 24000 x 150 155 / 142, 32768 x 100 120 / 131, 32768 x 150 201 / 162; 12000 x 40 48 / 43.
 // A quarter and a half of the factor: the same or slower at every size (8192 x 60, 47 bfloat16 columns 61 and 31 us, 30 with this one).
 __device__ __forceinline__ bool short_shares_rows(uint32_t rows, uint32_t mean, int values)
 {
-    return rows <= 65536u && 7ull * mean * (uint64_t)values > rows;
+    return rows <= 65536u && 7ull * mean * (uint64_t)values > rows && mean >= (rows > 20000u ? 128u : (rows > 14000u ? 50u : 0u));
 }
 
 // The offsets of two rows, requested together (a branch around each of them cost a round trip to memory)
