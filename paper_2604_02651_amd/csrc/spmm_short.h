@@ -16,19 +16,19 @@
 //    whole memory lines (columns in their order, 4 bytes in every 32: 20000 rows of 64 entries more 147 us instead of 101).
 // Measured, us (spmm_main_kernel / here), R-MAT rows x mean:
 //                      bf16 256       bf16 128       bf16 47        fp32 256       fp32 100
-//   2^20 x 1.27        254 / 208      190 / 112      158 / 120      428 / 422      264 / 237
-//   500000 x 3         190 / 145      125 / 78       110 / 68       287 / 275      169 / 141
-//   2^18 x 6.4         150 / 122      106 / 64       97 / 56        246 / 228      117 / 104
-//   65536 x 12         79 / 55        67 / 40        62 / 46        96 / 82        67 / 48
-//   32768 x 2.9        20 / 16        15 / 14        15 / 14        23 / 21        16 / 14
+//   2^20 x 1.27        246 / 218      160 / 118      136 / 60       400 / 423      217 / 200
+//   500000 x 3         170 / 144      119 / 68       109 / 50       294 / 279      140 / 122
+//   2^18 x 6.4         129 / 103      106 / 57       96 / 46        218 / 204      123 / 93
+//   65536 x 12         76 / 51        65 / 36        60 / 40        90 / 76        64 / 43
+//   32768 x 2.9        27 / 16        21 / 13        17 / 12        28 / 20        24 / 13
 // 2^18 rows of exactly six entries, 256 bfloat16 columns: 124 / 97, of which 9.7 TB/s arrive; a kernel that does nothing but such
 // gathers takes the same.  What the R-MAT matrix takes beyond it is the ragged end of rows and pieces.
 // With the loss in the epilogue a group holds a whole row of logits (one panel): its maximum and sum are reductions over the group's lanes,
 // two to eight rows at a time, where spmm_main_kernel has one row on 64 lanes of one to four columns.
 //                      bf16 172       bf16 100       bf16 47        fp32 100       fp32 47
-//   2^20 x 1.27        406 / 326      284 / 209      234 / 133      322 / 280      253 / 158
-//   2^18 x 6.4         207 / 161      147 / 123      132 / 90       155 / 136      131 / 91
-//   32768 x 2.9        51 / 36        30 / 29        28 / 26        31 / 30        27 / 25
+//   2^20 x 1.27        407 / 325      274 / 211      228 / 132      309 / 270      233 / 152
+//   2^18 x 6.4         204 / 156      146 / 108      129 / 83       149 / 128      128 / 80
+//   32768 x 2.9        54 / 36        33 / 30        29 / 28        37 / 31        29 / 26
 // The lanes at the right edge store 16 bytes like the others, over columns of their neighbour's; column by column 2^20 x 1.27 with
 // 172 columns took 400.  Three chunks a lane and eight lanes a row (fewer instructions a row, twice the registers): 474, 356 for 2^18 x 6.4.
 // Rejected: rows of up to 64 entries as rows of a group (2^18 x 6.4, 256 bfloat16 columns: 136 -> 145 us, 32768 x 2.9: 18 -> 25, the groups of a

@@ -5,6 +5,8 @@
     python3 profile_summary.py traffic  <fetch>_counter_collection.csv <write>_counter_collection.csv OUT.txt \
                                         --workload xlarge --cmd "<the two commands>"
     python3 profile_summary.py counters <pmc>_counter_collection.csv OUT.txt --cmd "<command>" [--durations STATS.txt]
+    rocprofv3 --kernel-trace -f csv -d <dir> -o CASE -- python3 profile_summary.py run CASE
+    python3 profile_summary.py calls    <dir>/CASE_kernel_trace.csv ... OUT.txt
 
 stats:    per-kernel calls / total / average / share from `rocprofv3 --kernel-trace --stats` (libsgnn's kernels only).
 traffic:  HBM bytes per launch from two `rocprofv3 --pmc` runs (FETCH_SIZE, then WRITE_SIZE; KiB per dispatch), each
@@ -12,6 +14,8 @@ traffic:  HBM bytes per launch from two `rocprofv3 --pmc` runs (FETCH_SIZE, then
           Lines "traffic <kernel> <bytes>" are read back by bench.py (roofline.traffic).
 counters: per-kernel averages of whatever counters a `--pmc` run collected, and the ratios SQ_VALU_MFMA_BUSY_CYCLES /
           SQ_BUSY_CU_CYCLES (matrix pipe busy share) and SQ_WAIT_INST_ANY / SQ_WAVE_CYCLES where both are present.
+run:      PASSES passes of a call of perf/cases.py, behind a copy_f32_kernel that ends its preparation.
+calls:    median and shortest duration of every kernel of such runs, and how often a pass launches it.
 Kernel names are shortened the way bench.py names its groups (tile, transposes, operand type for the GEMMs).
 """
 from __future__ import annotations
@@ -21,6 +25,7 @@ import collections
 import csv
 import re
 
+PASSES = 8
 SKIP = ("at::", "rocprim", "Cijk", "__amd_rocclr", "vectorized", "elementwise_kernel", "hipcub", "radix", "index_")
 
 
@@ -163,10 +168,47 @@ def cmd_counters(args):
     print("\n".join(lines[:14]))
 
 
+def cmd_run(args):
+    import torch
+
+    import paper_2604_02651_amd as sg
+    from perf import cases
+    state = cases.prepare(next(c for c in cases.listed() if c["name"] == args.out), 1)
+    a = torch.zeros(1024, device="cuda:0")
+    torch.cuda.synchronize()
+    sg.sgnn_copy_f32(sg.Context(0), a, torch.empty_like(a))
+    for _ in range(PASSES):
+        cases.run(state)
+        torch.cuda.synchronize()
+    print(args.out, "done", flush=True)
+
+
+def cmd_calls(args):
+    lines = ["# rocprofv3 --kernel-trace (kernels of libsgnn): %d passes of each call of perf/cases.py, median and shortest duration of a kernel, us, and launches a pass" % PASSES,
+             "# commands: cd /tmp && export TMPDIR=/tmp && cd <repo>; for every CASE",
+             "#   rocprofv3 --kernel-trace -f csv -d <dir> -o CASE -- python3 profile_summary.py run CASE",
+             "#   python3 profile_summary.py calls <dir>/*_kernel_trace.csv OUT.txt"]
+    for path in args.inputs:
+        rows = sorted((r for r in csv.DictReader(open(path))), key=lambda r: int(r["Start_Timestamp"]))
+        marks = [i for i, r in enumerate(rows) if short(r["Kernel_Name"]) == "copy_f32_kernel"]
+        agg = collections.OrderedDict()
+        for r in rows[marks[0] + 1:]:
+            if ours(r["Kernel_Name"]):
+                n = re.sub(r"\(anonymous namespace\)::|spmm::|^void ", "", r["Kernel_Name"]).split("(")[0]
+                agg.setdefault(n if "spmm_short" in n or "spmm_panel" in n else short(r["Kernel_Name"]), []).append(
+                    (int(r["End_Timestamp"]) - int(r["Start_Timestamp"])) / 1e3)
+        lines += ["", re.sub(r".*/|_kernel_trace\.csv$", "", path)]
+        for k, v in agg.items():
+            v.sort()
+            lines.append("  %-60s %9.1f %9.1f  x %.2f" % (k[:60], v[len(v) // 2], v[0], len(v) / PASSES))
+    open(args.out, "w").write("\n".join(lines) + "\n")
+    print("\n".join(lines))
+
+
 def main():
     ap = argparse.ArgumentParser()
-    ap.add_argument("what", choices=["stats", "traffic", "counters"])
-    ap.add_argument("inputs", nargs="+")
+    ap.add_argument("what", choices=["stats", "traffic", "counters", "run", "calls"])
+    ap.add_argument("inputs", nargs="+")      # the last one: where the summary goes (run: the name of the call)
     ap.add_argument("--cmd", default="")
     ap.add_argument("--note", default="")
     ap.add_argument("--workload", default="")
@@ -174,7 +216,7 @@ def main():
     ap.add_argument("--durations", default="", help="counters: a stats summary of the same workload (adds mfma_share)")
     args = ap.parse_args()
     args.out = args.inputs.pop()
-    {"stats": cmd_stats, "traffic": cmd_traffic, "counters": cmd_counters}[args.what](args)
+    {"stats": cmd_stats, "traffic": cmd_traffic, "counters": cmd_counters, "run": cmd_run, "calls": cmd_calls}[args.what](args)
 
 
 if __name__ == "__main__":
