@@ -5,6 +5,8 @@
 #include <stdint.h>
 #include <stdio.h>
 
+#include <atomic>
+
 #include "sgnn.h"
 
 #define SGNN_WAVE 64
@@ -69,11 +71,16 @@ void sgnn_prof_end(sgnn_ctx *ctx, hipStream_t st);
         SGNN_LAUNCH_CHECK(ctx, name);                                                           \
     } while (0)
 
-// Dynamic LDS of `bytes` for a kernel.  The attribute belongs to the kernel on the device that is current (the context's, which every entry
-// point binds), so it is set at every launch: remembered once a process it would be missing on a second device.
-template <class K> static inline hipError_t sgnn_allow_lds(K kernel, size_t bytes)
+// Dynamic LDS of `bytes` (the same at every call) for a kernel.  The attribute belongs to the kernel on one device, here the context's, which every
+// entry point has made the current one: set at the first launch on each device (by several threads at once, if so, to the same value).
+template <auto K> static inline hipError_t sgnn_allow_lds(const sgnn_ctx *ctx, size_t bytes)
 {
-    return hipFuncSetAttribute(reinterpret_cast<const void *>(kernel), hipFuncAttributeMaxDynamicSharedMemorySize, (int)bytes);
+    static std::atomic<uint64_t> devices{0};
+    const uint64_t bit = ctx->device < 64 ? 1ull << ctx->device : 0;
+    if (devices.load(std::memory_order_relaxed) & bit) return hipSuccess;
+    const hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void *>(K), hipFuncAttributeMaxDynamicSharedMemorySize, (int)bytes);
+    if (e == hipSuccess) devices.fetch_or(bit, std::memory_order_relaxed);
+    return e;
 }
 
 // Bump allocator over the context scratch, reset at the start of every API call.

@@ -1147,25 +1147,25 @@ int launch_skinny_ns(sgnn_ctx *ctx, const gemm_args &a, int tb, const skinny_tai
     const dim3 grid(std::min<uint32_t>(n_rowblocks, 256)), block(64 * SKINNY_WAVES);
     if constexpr (!TAIL) {
         if (a.a_bf16 && vmask) {
-            SGNN_HIP(ctx, sgnn_allow_lds(&gemm_skinny_bf16_kernel<NT8, S, false, true, true>, lds));
+            SGNN_HIP(ctx, (sgnn_allow_lds<&gemm_skinny_bf16_kernel<NT8, S, false, true, true>>(ctx, lds)));
             SGNN_LAUNCH(ctx, st, "gemm_skinny_bf16_kernel", tag, (gemm_skinny_bf16_kernel<NT8, S, false, true, true>), grid, block, lds,
                         st, a, tb, n_rowblocks, tl);
             return SGNN_OK;
         }
         if (a.a_bf16) {
-            SGNN_HIP(ctx, sgnn_allow_lds(&gemm_skinny_bf16_kernel<NT8, S, false, false, true>, lds));
+            SGNN_HIP(ctx, (sgnn_allow_lds<&gemm_skinny_bf16_kernel<NT8, S, false, false, true>>(ctx, lds)));
             SGNN_LAUNCH(ctx, st, "gemm_skinny_bf16_kernel", tag, (gemm_skinny_bf16_kernel<NT8, S, false, false, true>), grid, block, lds,
                         st, a, tb, n_rowblocks, tl);
             return SGNN_OK;
         }
         if (vmask) {
-            SGNN_HIP(ctx, sgnn_allow_lds(&gemm_skinny_bf16_kernel<NT8, S, false, true>, lds));
+            SGNN_HIP(ctx, (sgnn_allow_lds<&gemm_skinny_bf16_kernel<NT8, S, false, true>>(ctx, lds)));
             SGNN_LAUNCH(ctx, st, "gemm_skinny_bf16_kernel", tag, (gemm_skinny_bf16_kernel<NT8, S, false, true>), grid, block, lds, st, a,
                         tb, n_rowblocks, tl);
             return SGNN_OK;
         }
     }
-    SGNN_HIP(ctx, sgnn_allow_lds(&gemm_skinny_bf16_kernel<NT8, S, TAIL, false>, lds));
+    SGNN_HIP(ctx, (sgnn_allow_lds<&gemm_skinny_bf16_kernel<NT8, S, TAIL, false>>(ctx, lds)));
     SGNN_LAUNCH(ctx, st, "gemm_skinny_bf16_kernel", tag, (gemm_skinny_bf16_kernel<NT8, S, TAIL, false>), grid, block, lds, st, a, tb,
                 n_rowblocks, tl);
     return SGNN_OK;

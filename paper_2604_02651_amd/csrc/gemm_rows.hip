@@ -218,10 +218,10 @@ template <int NT8, int S, bool TB> int launch_rows(sgnn_ctx *ctx, const rows_arg
     char tag[56];
     snprintf(tag, sizeof(tag), "N%c rows %lldx%dx%d bf16 a=2 c=2%s", TB ? 'T' : 'N', (long long)a.M, a.N, a.K, a.mask ? " mask m=2" : "");
     if (a.mask) {
-        SGNN_HIP(ctx, sgnn_allow_lds(&gemm_rows_kernel<NT8, S, TB, true>, lds));
+        SGNN_HIP(ctx, (sgnn_allow_lds<&gemm_rows_kernel<NT8, S, TB, true>>(ctx, lds)));
         SGNN_LAUNCH(ctx, st, "gemm_rows_kernel", tag, (gemm_rows_kernel<NT8, S, TB, true>), grid, block, lds, st, a, blocks);
     } else {
-        SGNN_HIP(ctx, sgnn_allow_lds(&gemm_rows_kernel<NT8, S, TB, false>, lds));
+        SGNN_HIP(ctx, (sgnn_allow_lds<&gemm_rows_kernel<NT8, S, TB, false>>(ctx, lds)));
         SGNN_LAUNCH(ctx, st, "gemm_rows_kernel", tag, (gemm_rows_kernel<NT8, S, TB, false>), grid, block, lds, st, a, blocks);
     }
     return SGNN_OK;

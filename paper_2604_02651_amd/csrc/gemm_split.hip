@@ -437,7 +437,7 @@ int launch_split(sgnn_ctx *ctx, int ta, int tb, split_args a, hipStream_t st)
     const bool g = a.ridx != nullptr;
 #define SGNN_SPLIT_CASE(TA_, TB_, G_)                                                                              \
     if (ta == TA_ && tb == TB_ && g == G_) {                                                                       \
-        SGNN_HIP(ctx, sgnn_allow_lds(&gemm_split_kernel<BM, BN, WM, WN, !TA_, TB_, G_>, LDS));                     \
+        SGNN_HIP(ctx, (sgnn_allow_lds<&gemm_split_kernel<BM, BN, WM, WN, !TA_, TB_, G_>>(ctx, LDS)));                     \
         SGNN_LAUNCH(ctx, st, "gemm_split_kernel", tag, (gemm_split_kernel<BM, BN, WM, WN, !TA_, TB_, G_>), grid, block, LDS, st, a); \
         return SGNN_OK;                                                                                            \
     }

@@ -204,7 +204,7 @@ __global__ __launch_bounds__(64 * TNS_WAVES) void gemm_tn_stream_kernel(tns_args
 template <int FA, int FB, int WM, int WN> int launch_tns(sgnn_ctx *ctx, const tns_args &a, unsigned grid, hipStream_t st)
 {
     constexpr int lds = TNS_STAGES * tns_stage_bytes<FA, FB>();
-    SGNN_HIP(ctx, sgnn_allow_lds(&gemm_tn_stream_kernel<FA, FB, WM, WN>, lds));
+    SGNN_HIP(ctx, (sgnn_allow_lds<&gemm_tn_stream_kernel<FA, FB, WM, WN>>(ctx, lds)));
     char tag[56];
     snprintf(tag, sizeof(tag), "TN stream %dx%dx%lld bf16 a=2 b=2", a.M, a.N, (long long)a.K);
     SGNN_LAUNCH(ctx, st, "gemm_tn_stream_kernel", tag, (gemm_tn_stream_kernel<FA, FB, WM, WN>), dim3(grid), dim3(64 * TNS_WAVES), lds, st, a);
