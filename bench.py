@@ -245,6 +245,11 @@ def measure(args, sg, si, torch, cfg, g, X, labels, weights, use_graph_req: str,
             eb = next((float(w[2:]) for w in p if w.startswith("b=")), 2.0)
             gq["bytes"] += calls * k_ * (ea * m_ + eb * n_)
             gq["flops"] += calls * 2.0 * m_ * n_ * k_
+        elif name == "gemm_bwd_kernel":
+            # both products of a backward pass, every tall matrix streamed once (tag: "bwd MxNxK bf16"): X, D and the K x M gradient
+            m_, n_, k_ = (float(x) for x in tag.split()[1].split("x"))
+            gq["bytes"] += calls * (2.0 * k_ * (2.0 * m_ + n_) + 4.0 * m_ * n_)
+            gq["flops"] += calls * 4.0 * m_ * n_ * k_
         elif name in ("spmm_main_kernel", "spmm_short_kernel", "spmm_panel_kernel"):
             d = int(tag.split("d=")[1].split()[0])
             w = tag.split()

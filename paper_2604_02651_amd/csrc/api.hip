@@ -505,20 +505,40 @@ int sgnn_gcn_bwd(sgnn_ctx *ctx, const sgnn_csr *A_T, const sgnn_mat *T, const sg
         if (rc) return rc;
         if (mask_here) { dZ = dZbuf; lddz = ld_out; dz16 = 0; }
     }
+    const float *Wp = static_cast<const float *>(W->ptr);
     if (!xform_first) {
+        // dW = T^T dZ and dT = dZ W^T together where both are wanted and everything is stored as bfloat16 (ws: the partial results of dW are
+        // done with when the sparse product starts, dT is not)
+        float *dT = nullptr;
+        bool both = false;
+        if (dW && dH && t16 && dz16) {
+            const size_t off = ws.off;
+            dT = ws.get<float>(((size_t)Bn * ld_in + 1) / 2);
+            if (ws.ok) {
+                const size_t after = ws.off;
+                rc = sgnn_launch_gemm_bwd(ctx, d_in, d_out, Bn, T->ptr, T->ld, dZ, lddz, Wp, W->ld, dT, ld_in, true, false, dW,
+                                          db_in_gemm ? dbias : nullptr, &ws, st);
+                if (rc != SGNN_OK && rc != SGNN_ERR_UNSUPPORTED) return rc;
+                both = rc == SGNN_OK;
+                ws.off = after;
+            }
+            if (!both) { ws.off = off; ws.ok = true; }
+        }
         // dW = T^T dZ
-        if (dW) {
+        if (dW && !both) {
             rc = sgnn_launch_gemm_x(ctx, 1, 0, d_in, d_out, Bn, T->ptr, t16, T->ld, nullptr, dZ, dz16, lddz, nullptr, mfma, dW, 0, d_out,
                                     nullptr, 0, 0, db_in_gemm ? dbias : nullptr, &ws, st);
             if (rc) return rc;
         }
         if (dH) {
             // dT = dZ W^T, dH = A^T dT
-            float *dT = ws.get<float>(dt16 ? ((size_t)Bn * ld_in + 1) / 2 : (size_t)Bn * ld_in);
-            if (!ws.ok) return sgnn_fail(ctx, SGNN_ERR_CAPACITY, "sgnn_gcn_bwd: scratch too small: call sgnn_ctx_reserve");
-            rc = sgnn_launch_gemm_x(ctx, 0, 1, Bn, d_in, d_out, dZ, dz16, lddz, nullptr, W->ptr, 0, W->ld, nullptr, mfma, dT, dt16, ld_in,
-                                    nullptr, 0, 0, nullptr, &ws, st);
-            if (rc) return rc;
+            if (!both) {
+                dT = ws.get<float>(dt16 ? ((size_t)Bn * ld_in + 1) / 2 : (size_t)Bn * ld_in);
+                if (!ws.ok) return sgnn_fail(ctx, SGNN_ERR_CAPACITY, "sgnn_gcn_bwd: scratch too small: call sgnn_ctx_reserve");
+                rc = sgnn_launch_gemm_x(ctx, 0, 1, Bn, d_in, d_out, dZ, dz16, lddz, nullptr, Wp, 0, W->ld, nullptr, mfma, dT, dt16, ld_in,
+                                        nullptr, 0, 0, nullptr, &ws, st);
+                if (rc) return rc;
+            }
             rc = sgnn_launch_spmm_x(ctx, A_T, dT, dt16, ld_in, nullptr, d_in, dH->ptr, dh16, dH->ld, nullptr, 0, hmask, hm16, ldhm,
                                     nullptr, 0, &ws, st);
             if (rc) return rc;
@@ -533,13 +553,20 @@ int sgnn_gcn_bwd(sgnn_ctx *ctx, const sgnn_csr *A_T, const sgnn_mat *T, const sg
     if (!ws.ok) return sgnn_fail(ctx, SGNN_ERR_CAPACITY, "sgnn_gcn_bwd: scratch too small: call sgnn_ctx_reserve");
     rc = sgnn_launch_spmm_x(ctx, A_T, dZ, dz16, lddz, nullptr, d_out, dP, p16, ld_out, nullptr, 0, nullptr, 0, 0, nullptr, 0, &ws, st);
     if (rc) return rc;
+    // both products of dP together where all of it is stored as bfloat16; the mask of dH is the layer's input itself or none
+    if (dW && dH && p16 && dh16 && !T->row_index && (!H_in || (hmask == T->ptr && hm16 && ldhm == T->ld))) {
+        const size_t off = ws.off;
+        rc = sgnn_launch_gemm_bwd(ctx, d_in, d_out, Bn, T->ptr, T->ld, dP, ld_out, Wp, W->ld, dH->ptr, dH->ld, false, H_in != nullptr, dW, nullptr, &ws, st);
+        if (rc != SGNN_ERR_UNSUPPORTED) return rc;
+        ws.off = off;
+    }
     if (dW) {
         rc = sgnn_launch_gemm_x(ctx, 1, 0, d_in, d_out, Bn, T->ptr, t16, T->ld, T->row_index, dP, p16, ld_out, nullptr, mfma, dW, 0, d_out,
                                 nullptr, 0, 0, nullptr, &ws, st);
         if (rc) return rc;
     }
     if (dH)
-        rc = sgnn_launch_gemm_x(ctx, 0, 1, Bn, d_in, d_out, dP, p16, ld_out, nullptr, W->ptr, 0, W->ld, nullptr, mfma, dH->ptr, dh16, dH->ld,
+        rc = sgnn_launch_gemm_x(ctx, 0, 1, Bn, d_in, d_out, dP, p16, ld_out, nullptr, Wp, 0, W->ld, nullptr, mfma, dH->ptr, dh16, dH->ld,
                                 hmask, hm16, ldhm, nullptr, &ws, st);
     return rc;
 }

@@ -152,6 +152,10 @@ int sgnn_launch_gemm_rows(sgnn_ctx *ctx, int tb, int64_t M, int64_t N, int64_t K
 // A^T B, both operands bfloat16, result up to 256 x 256, long reduction: SGNN_ERR_UNSUPPORTED (nothing launched) outside its range
 int sgnn_launch_gemm_tn_stream(sgnn_ctx *ctx, int64_t M, int64_t N, int64_t K, const void *A, int64_t lda, const void *B, int64_t ldb,
                                float *C, int64_t ldc, float *b_colsum, ws_alloc *ws, hipStream_t st);
+// C = X^T D (and the column sums of D) and G = D W^T, masked by X on request, in one pass over X and D (gemm_bwd.hip): SGNN_ERR_UNSUPPORTED (nothing
+// launched) outside its range.  g_pad: the columns of G between M and ldg may be written
+int sgnn_launch_gemm_bwd(sgnn_ctx *ctx, int64_t M, int64_t N, int64_t K, const void *X, int64_t ldx, const void *D, int64_t ldd, const float *W,
+                         int64_t ldw, void *G, int64_t ldg, bool g_pad, bool mask, float *C, float *d_colsum, ws_alloc *ws, hipStream_t st);
 int sgnn_launch_gemm_tail(sgnn_ctx *ctx, int64_t M, int64_t N, int64_t K, const float *A, int64_t lda, const float *W,
                           int64_t ldw, const float *gamma, float eps, const float *R, int64_t ldr, float q, uint64_t seed,
                           uint32_t layer, uint64_t step, float *Z, int64_t ldz, float *Y, int64_t ldy, float *inv_rms,

@@ -1,0 +1,30 @@
+// What the kernels that stream rows of bfloat16 matrices through LDS share.
+#pragma once
+
+#include "common.h"
+
+typedef float f32x4 __attribute__((ext_vector_type(4)));
+typedef float f32x16 __attribute__((ext_vector_type(16)));
+typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
+typedef short i16x4 __attribute__((ext_vector_type(4)));
+typedef float f32x4_any __attribute__((ext_vector_type(4), aligned(4)));      // gfx950 global loads take any alignment
+typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
+typedef unsigned short u16;
+
+#define STREAM_GPTR(p) ((const __attribute__((address_space(1))) void *)(p))
+#define STREAM_LPTR(p) ((__attribute__((address_space(3))) void *)(p))
+// s_waitcnt vmcnt(n) only (expcnt and lgkmcnt left at their maxima), gfx9 encoding
+#define STREAM_WAIT_VMCNT(n) __builtin_amdgcn_s_waitcnt(((n) & 15) | (((n) >> 4) << 14) | 0x0F70)
+
+// ds_read_b64_tr_b16: sixteen lanes read 4 rows x 16 columns and each gets the four values of one column.  __restrict__ says that the
+// read is of nothing that a direct load may still be writing (the kernels' own waits see to that); without it the compiler waits for all direct
+// loads, the ones just issued among them, in front of such a read, and nothing is in flight behind the slice being multiplied.
+__device__ __forceinline__ uint2 read_tr(const unsigned char *__restrict__ p)
+{
+    return __builtin_bit_cast(uint2, __builtin_amdgcn_ds_read_tr16_b64_v4i16((__attribute__((address_space(3))) i16x4 *)(p)));
+}
+
+__device__ __forceinline__ uint32_t pack_bf16(float lo, float hi)
+{
+    return (uint32_t)__builtin_bit_cast(u16, (__bf16)lo) | (uint32_t)__builtin_bit_cast(u16, (__bf16)hi) << 16;
+}
