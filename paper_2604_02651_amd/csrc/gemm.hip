@@ -1391,44 +1391,6 @@ __global__ __launch_bounds__(256) void gemm_smallk_nt_kernel(gemm_args a)
     }
 }
 
-// Sum of the split-K partial products in a fixed order (bit-reproducible).
-__global__ __launch_bounds__(256) void splitk_reduce_kernel(const float *__restrict__ partial, int splits, int64_t MN,
-                                                            int64_t N, float *__restrict__ C, int64_t ldc,
-                                                            const float *__restrict__ cs_partial, float *__restrict__ cs_out)
-{
-    const int64_t i = (int64_t)blockIdx.x * 256 + threadIdx.x;
-    if (i >= MN) {
-        // the threads behind the matrix add up the column sums of B, split by split
-        const int64_t col = i - MN;
-        if (cs_partial && col < N) {
-            // eight chains, combined in a fixed order: one chain over the 128 ranges of a layer of 32768 rows had a
-            // larger error than the 64 ranges that such layers were cut into before
-            float t[8] = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
-            for (int z = 0; z < splits; z += 32) {         // 32 loads in flight
-                float x[32];
-#pragma unroll
-                for (int u = 0; u < 32; ++u) x[u] = cs_partial[(int64_t)min(z + u, splits - 1) * N + col];
-#pragma unroll
-                for (int u = 0; u < 32; ++u) t[u % 8] += z + u < splits ? x[u] : 0.f;
-            }
-            cs_out[col] = ((t[0] + t[1]) + (t[2] + t[3])) + ((t[4] + t[5]) + (t[6] + t[7]));
-        }
-        return;
-    }
-    // four interleaved chains, combined in a fixed order
-    float s0 = 0.f, s1 = 0.f, s2 = 0.f, s3 = 0.f;
-    int z = 0;
-#pragma unroll 2
-    for (; z + 3 < splits; z += 4) {
-        s0 += partial[(int64_t)z * MN + i];
-        s1 += partial[(int64_t)(z + 1) * MN + i];
-        s2 += partial[(int64_t)(z + 2) * MN + i];
-        s3 += partial[(int64_t)(z + 3) * MN + i];
-    }
-    for (; z < splits; ++z) s0 += partial[(int64_t)z * MN + i];
-    C[(i / N) * ldc + (i % N)] = (s0 + s1) + (s2 + s3);
-}
-
 template <int BM, int BN, int WM, int WN>
 int launch_cfg(sgnn_ctx *ctx, int ta, int tb, int bf16, gemm_args a, int splits, hipStream_t st)
 {
@@ -1517,15 +1479,6 @@ __global__ __launch_bounds__(256) void narrow_bf16_kernel(const float *__restric
 size_t sgnn_gemm_ws_bytes(uint32_t d_max) { return (size_t)256 * d_max * d_max * 4 + (size_t)256 * d_max * 4 + 512; }
 
 static inline int64_t gemm_pad4(int64_t d) { return (d + 3) & ~int64_t(3); }
-
-// C = sum of `splits` partial products [splits][M][N] in a fixed order; cs_out = the same for [splits][N] column sums.
-int sgnn_launch_splitk_reduce(sgnn_ctx *ctx, const float *partial, int splits, int64_t M, int64_t N, float *C, int64_t ldc,
-                              const float *cs_partial, float *cs_out, hipStream_t st)
-{
-    SGNN_LAUNCH(ctx, st, "splitk_reduce_kernel", SGNN_TAG, splitk_reduce_kernel, dim3(cdiv(M * N + (cs_partial ? N : 0), 256)), dim3(256),
-                0, st, partial, splits, M * N, N, C, ldc, cs_partial, cs_out);
-    return SGNN_OK;
-}
 
 int sgnn_launch_gemm(sgnn_ctx *ctx, int ta, int tb, int64_t M, int64_t N, int64_t K, const float *A, int64_t lda,
                      const int32_t *a_row_index, const float *B, int64_t ldb, const float *bias, int flags, float *C,
@@ -1676,9 +1629,7 @@ int sgnn_launch_gemm_x(sgnn_ctx *ctx, int ta, int tb, int64_t M, int64_t N, int6
         const dim3 grid((unsigned)(cdiv(splits, 8) * 8 * tiles)), block(64 * THIN_WAVES);
         if (a_row_index) { SGNN_LAUNCH(ctx, st, "gemm_kernel", tag, gemm_thin_tn_kernel<true>, grid, block, 0, st, a); }
         else             { SGNN_LAUNCH(ctx, st, "gemm_kernel", tag, gemm_thin_tn_kernel<false>, grid, block, 0, st, a); }
-        SGNN_LAUNCH(ctx, st, "splitk_reduce_kernel", SGNN_TAG, splitk_reduce_kernel, dim3(cdiv(M * N + (cs_part ? N : 0), 256)),
-                    dim3(256), 0, st, a.partial, (int)splits, M * N, N, C, ldc, cs_part, b_colsum);
-        return SGNN_OK;
+        return sgnn_launch_splitk_reduce(ctx, a.partial, (int)splits, M, N, C, ldc, cs_part, b_colsum, st);
     }
 
     // every other fp32 product: split into bfloat16 parts (gemm_split.hip), except the transforms onto up to 32 columns, which
@@ -1734,8 +1685,8 @@ int sgnn_launch_gemm_x(sgnn_ctx *ctx, int ta, int tb, int64_t M, int64_t N, int6
     else rc = launch_cfg<256, 32, 64, 32>(ctx, ta, tb, bf16, a, splits, st);
     if (rc) return rc;
     if (splits > 1) {
-        SGNN_LAUNCH(ctx, st, "splitk_reduce_kernel", SGNN_TAG, splitk_reduce_kernel, dim3(cdiv(M * N + (cs_partial ? N : 0), 256)),
-                    dim3(256), 0, st, a.partial, splits, M * N, N, C, ldc, cs_partial, b_colsum);
+        rc = sgnn_launch_splitk_reduce(ctx, a.partial, splits, M, N, C, ldc, cs_partial, b_colsum, st);
+        if (rc) return rc;
     }
     if (b_colsum && !cs_fused)
         return sgnn_launch_relu_bwd_bias(ctx, nullptr, 0, 0, B, ldb, 0, K, N, nullptr, 0, b_colsum, ws, st);
