@@ -149,6 +149,9 @@ int sgnn_launch_splitk_reduce(sgnn_ctx *ctx, const float *partial, int splits, i
 // gemm_rows.hip: tall bfloat16 A times a small B, result (and mask) bfloat16
 int sgnn_launch_gemm_rows(sgnn_ctx *ctx, int tb, int64_t M, int64_t N, int64_t K, const void *A, int64_t lda, const int32_t *row_index, const float *B,
                           int64_t ldb, const float *bias, int relu, void *C, int64_t ldc, const void *mask, int64_t ldm, hipStream_t st);
+// gemm_tall.hip: tall bfloat16 A times a small B, result bfloat16, no mask and no row gather
+int sgnn_launch_gemm_tall(sgnn_ctx *ctx, int64_t M, int64_t N, int64_t K, const void *A, int64_t lda, const float *B, int64_t ldb,
+                         const float *bias, int relu, void *C, int64_t ldc, hipStream_t st);
 // A^T B, both operands bfloat16, result up to 256 x 256, long reduction: SGNN_ERR_UNSUPPORTED (nothing launched) outside its range
 int sgnn_launch_gemm_tn_stream(sgnn_ctx *ctx, int64_t M, int64_t N, int64_t K, const void *A, int64_t lda, const void *B, int64_t ldb,
                                float *C, int64_t ldc, float *b_colsum, ws_alloc *ws, hipStream_t st);

@@ -1528,6 +1528,11 @@ int sgnn_launch_gemm_x(sgnn_ctx *ctx, int ta, int tb, int64_t M, int64_t N, int6
         const int rc = sgnn_launch_gemm_rows(ctx, tb, M, N, K, Av, lda, a_row_index, B, ldb, bias, (flags & SGNN_RELU) ? 1 : 0, Cv, ldc, maskv, ldm, st);
         if (rc != SGNN_ERR_UNSUPPORTED) return rc;
     }
+    // tall A and C 16-bit, nothing beside them
+    if (skinny_shape && a_bf16 && c_bf16 && !tb && !maskv && !a_row_index && !b_colsum) {
+        const int rc = sgnn_launch_gemm_tall(ctx, M, N, K, Av, lda, B, ldb, bias, (flags & SGNN_RELU) ? 1 : 0, Cv, ldc, st);
+        if (rc != SGNN_ERR_UNSUPPORTED) return rc;
+    }
     const bool cm_native = skinny_shape && (a_bf16 ? a_native : ((reinterpret_cast<uintptr_t>(Av) & 15) == 0 && lda % 4 == 0));
     const float *A = static_cast<const float *>(Av);
     if (a_bf16 && !a_native) {
