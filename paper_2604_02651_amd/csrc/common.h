@@ -144,6 +144,9 @@ int sgnn_launch_gemm_x(sgnn_ctx *ctx, int ta, int tb, int64_t M, int64_t N, int6
 int sgnn_launch_gemm_split(sgnn_ctx *ctx, int ta, int tb, int64_t M, int64_t N, int64_t K, const float *A, int64_t lda, const int32_t *ridx,
                            const float *B, int64_t ldb, const float *bias, int relu, float *C, int64_t ldc, const float *mask, int64_t ldm,
                            float *b_colsum, ws_alloc *ws, hipStream_t st);
+// its form for a tall A and a small B (gemm_split_tall.hip)
+int sgnn_launch_gemm_split_tall(sgnn_ctx *ctx, int tb, int64_t M, int64_t N, int64_t K, const float *A, int64_t lda, const float *B, int64_t ldb,
+                                const float *bias, int relu, float *C, int64_t ldc, hipStream_t st);
 int sgnn_launch_splitk_reduce(sgnn_ctx *ctx, const float *partial, int splits, int64_t M, int64_t N, float *C, int64_t ldc,
                               const float *cs_partial, float *cs_out, hipStream_t st);
 // gemm_rows.hip: tall bfloat16 A times a small B, result (and mask) bfloat16

@@ -33,13 +33,7 @@
 
 namespace {
 
-typedef float f32x16 __attribute__((ext_vector_type(16)));
-typedef float f32x4 __attribute__((ext_vector_type(4)));
-typedef float f32x2 __attribute__((ext_vector_type(2)));
-typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
-typedef __bf16 bf16x2 __attribute__((ext_vector_type(2)));
-// 16 bytes at any multiple of four (gfx950 global loads take any alignment)
-typedef float f32x4_any __attribute__((ext_vector_type(4), aligned(4)));
+#include "split_parts.h"
 
 struct split_args {
     int64_t M, N, K;
@@ -57,7 +51,6 @@ struct split_args {
 };
 
 constexpr int SBK = 32;                                     // slice of the reduction
-constexpr uint32_t TINY = 2u * ((127u - 112u) << 23) - 1u;   // tiny_key() of 2^-112
 
 template <int R> struct plane {
     static constexpr int BLOCK = 32 * SBK * 2 + 64;         // bytes of a block of 32 rows; 64 more, so that row l of different
@@ -66,32 +59,6 @@ template <int R> struct plane {
 // byte offset in a plane of the 16-byte chunk `c` (eight reduction values) of row l of block b: chunks are swizzled so that
 // the rows which a wavefront reads together fall into different banks
 __device__ __forceinline__ int chunk_at(int block_bytes, int b, int l, int c) { return b * block_bytes + l * (SBK * 2) + ((c ^ (l >> 1)) & 3) * 16; }
-
-// four values -> their three parts, packed
-struct parts4 { uint2 p[3]; };
-__device__ __forceinline__ uint32_t cvt2(float a, float b) { return __builtin_bit_cast(uint32_t, __builtin_convertvector(f32x2{a, b}, bf16x2)); }
-__device__ __forceinline__ float lo16(uint32_t w) { return __builtin_bit_cast(float, w << 16); }
-__device__ __forceinline__ float hi16(uint32_t w) { return __builtin_bit_cast(float, w & 0xffff0000u); }
-__device__ __forceinline__ void split2(float x, float y, uint32_t &p1, uint32_t &p2, uint32_t &p3)
-{
-    p1 = cvt2(x, y);
-    x -= lo16(p1); y -= hi16(p1);
-    p2 = cvt2(x, y);
-    x -= lo16(p2); y -= hi16(p2);
-    p3 = cvt2(x, y);
-}
-// a value's bits without the sign, shifted left, less one: in the order of the magnitudes, but zero is the largest
-__device__ __forceinline__ uint32_t tiny_key(float x) { return 2u * __builtin_bit_cast(uint32_t, x) - 1u; }
-__device__ __forceinline__ parts4 split4(const float (&v)[4], uint32_t &tiny)
-{
-    parts4 r;
-    split2(v[0], v[1], r.p[0].x, r.p[1].x, r.p[2].x);
-    split2(v[2], v[3], r.p[0].y, r.p[1].y, r.p[2].y);
-    // smallest key seen: of the values themselves, because a value of up to 2^-134 has a zero for its first part
-    asm("v_min3_u32 %0, %0, %1, %2" : "+v"(tiny) : "v"(tiny_key(v[0])), "v"(tiny_key(v[1])));
-    asm("v_min3_u32 %0, %0, %1, %2" : "+v"(tiny) : "v"(tiny_key(v[2])), "v"(tiny_key(v[3])));
-    return r;
-}
 
 // One operand: R rows of the tile, stored [row][reduction] (KC) or [reduction][row].  A thread holds PER units of 16 bytes (KC:
 // four reduction steps of a row) or of four times 16 bytes (else: four reduction steps x four rows).  Every load is issued,
@@ -477,6 +444,12 @@ int sgnn_launch_gemm_split(sgnn_ctx *ctx, int ta, int tb, int64_t M, int64_t N, 
     else if (N > 64 && (ta ? M > 64 && (K >= 8192 || t128 >= 160) : t128 >= 160)) bm = 128, bn = 128;
     else if (long_ab && M > 128) bm = N > 64 ? 256 : 128, bn = N > 64 ? 128 : 64;
     else if (!long_ab && ((int64_t)cdiv(M, 128) * cdiv(N, 64) >= 256 || (ta && M > 64 && K >= 4096))) bm = 128;
+    // More tiles than compute units: the second round is a whole one however few they are, where the kernel for a tall A goes on slice by slice.  us
+    // there / here, N = 256: 16384 x 256 22 / 25, 20000 x 256 37 / 28 (128 x 128 tiles up to there), 32768 x 256 32 / 33, 40000 x 256 59 / 43, 200000 x 128 127 / 91.
+    if (!ta && !ridx && !mask && bn == 128 && (bm == 256 ? t256 : t128) > 256) {
+        const int rc = sgnn_launch_gemm_split_tall(ctx, tb, M, N, K, A, lda, B, ldb, bias, relu, C, ldc, st);
+        if (rc != SGNN_ERR_UNSUPPORTED) return rc;
+    }
     // A long reduction onto few tiles is split, to at most 128 ranges of 128 steps or more (each writes its partial product, and
     // a second kernel reads them all: 256 x 256 x 32768 43 us with 128 ranges, 59 with 256; 608 x 256 x 65536 277 us with 42,
     // 205 with 128).  A B and A B^T take as many as give every compute unit a tile, a multiple of eight (the ranges are dealt to
