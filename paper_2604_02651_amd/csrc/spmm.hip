@@ -29,16 +29,18 @@ namespace {
 
 __global__ void spmm_plan_clear_kernel(uint32_t *n_chunks) { *n_chunks = 0; }
 
-// One thread per row: the long rows of a wavefront reserve their chunk numbers with one atomic add,
-// each records its first one in part_base[row] and writes one (row, chunk) descriptor per chunk.  The chunk
-// numbering depends on timing; the values computed from it do not.
+// One thread per row: the long rows of a workgroup reserve their chunk numbers with one atomic add and
+// record their first one in part_base[row].  The (row, chunk) descriptors are then written by all threads in turn, each finding the row of
+// a chunk by a search over the rows' first ones in LDS: a hub row has up to 256 of them, and written by its own thread they
+// were most of the kernel (2^18 rows of 6.4 entries, one row of 8000: 13 us).  The chunk numbering depends on timing; the values
+// computed from it do not.
 __global__ __launch_bounds__(SPMM_PLAN_NT) void spmm_plan_kernel(uint32_t rows, const void *__restrict__ rowptr, int rp64, uint64_t capacity,
                                                         uint32_t *__restrict__ n_chunks,
                                                         uint32_t max_chunks, uint32_t *__restrict__ part_base,
                                                         uint2 *__restrict__ desc, uint32_t *__restrict__ ticket)
 {
     __shared__ uint32_t scan_lds[SPMM_PLAN_NT / 64 + 1];
-    __shared__ uint32_t wg_base;
+    __shared__ uint32_t wg_base, first[SPMM_PLAN_NT];
     const uint32_t row = blockIdx.x * SPMM_PLAN_NT + threadIdx.x;
     // the row's offsets are requested together with the count of entries, which the length of a long row depends on
     const uint64_t r0 = min(row, rows - 1);
@@ -58,14 +60,18 @@ __global__ __launch_bounds__(SPMM_PLAN_NT) void spmm_plan_kernel(uint32_t rows, 
     // them): the long rows of the workgroup take consecutive piece numbers
     uint32_t wg_total;
     const uint32_t excl = block_excl_scan<uint32_t, SPMM_PLAN_NT>(nch, &wg_total, scan_lds);
-    if (threadIdx.x == 0) wg_base = wg_total ? atomicAdd(n_chunks, wg_total) : 0u;
+    if (wg_total == 0) return;
+    if (threadIdx.x == 0) wg_base = atomicAdd(n_chunks, wg_total);
+    first[threadIdx.x] = excl;
     __syncthreads();
-    if (nch == 0) return;
-    const uint32_t base = wg_base + excl;
-    part_base[row] = base;
-    for (uint32_t c = 0; c < nch && base + c < max_chunks; ++c) {
-        desc[base + c] = make_uint2(row, c);
-        ticket[base + c] = 0;      // the first one of a row is its ticket, the panel kernel has one per panel
+    if (nch) part_base[row] = wg_base + excl;
+    for (uint32_t p = threadIdx.x; p < wg_total && wg_base + p < max_chunks; p += SPMM_PLAN_NT) {
+        uint32_t t = 0;                // the last row whose first chunk is p or one before (rows without chunks have their successor's)
+#pragma unroll
+        for (uint32_t step = SPMM_PLAN_NT / 2; step; step /= 2)
+            if (first[t + step] <= p) t += step;
+        desc[wg_base + p] = make_uint2(blockIdx.x * SPMM_PLAN_NT + t, p - first[t]);
+        ticket[wg_base + p] = 0;       // the first one of a row is its ticket, the panel kernel has one per panel
     }
 }
 
