@@ -247,13 +247,9 @@ __global__ __launch_bounds__(1024) void xent_final_kernel(const float *__restric
         long long f = 0;
         if (fix)
             for (int k = threadIdx.x; k < fix_slots; k += 1024) f += (long long)fix[(int64_t)k * (cols + 1) + cols];
-        lfix[threadIdx.x] = f;
-        __syncthreads();
-        if (threadIdx.x == 0) {
-            long long ft = 0;
-            for (int k = 0; k < 1024; ++k) ft += lfix[k];          // integers: the order does not matter
-            *loss = (s + (float)((double)ft * loss_unit)) * invB;
-        }
+        // integers: the order does not matter (added up by one thread they were half of the kernel: 1024 rows of 8 classes 7.5 us)
+        f = block_sum<long long, 1024>(f, lfix);
+        if (threadIdx.x == 0) *loss = (s + (float)((double)f * loss_unit)) * invB;
         return;
     }
     // 16 columns x 64 groups of partial rows per workgroup: with 64 columns and 16 groups the three or four workgroups
