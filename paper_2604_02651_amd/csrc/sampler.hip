@@ -588,6 +588,109 @@ __global__ __launch_bounds__(SAMP_NT) void sampler_rank_kernel(const uint64_t *_
     if (blockIdx.x == gridDim.x - 1 && threadIdx.x == 0 && running != B) atomicOr(status, SGNN_ST_CAND_OVERFLOW);
 }
 
+// All of it by one workgroup, for graphs of up to SMALL_N vertices: a thread keeps the keys of up to eight pairs of vertices in registers, and
+// histogram, candidates and bitmap stay in LDS.  Bound by barriers in a row, the fetching of its own code and one compute unit's Philox (0.3 us a
+// thousand vertices), where five launches cost 17 to 19 us: 4096 vertices 18.4 -> 6.9 us, 16384 19.0 -> 10.7.  With sixteen pairs a thread
+// it took 17.8 us for 32768 vertices (19.2 by the five) and 2 us more than this for all smaller ones: the longer code.
+constexpr uint64_t SMALL_N = 16384;
+__global__ __launch_bounds__(SCAN_NT) void sampler_small_kernel(uint32_t N, uint32_t B, uint64_t seed, uint64_t step, int32_t *__restrict__ S,
+                                                                uint64_t *__restrict__ bitmap, uint32_t *__restrict__ rank,
+                                                                uint32_t *__restrict__ status)
+{
+    constexpr int Q = (int)(SMALL_N / 2 / SCAN_NT);
+    __shared__ __attribute__((aligned(8))) uint32_t lh[HIST_BINS];
+    __shared__ uint32_t bits[SMALL_N / 32];
+    __shared__ uint64_t list_key[THR_LIST];
+    __shared__ uint32_t list_v[THR_LIST], list_below[THR_LIST];
+    __shared__ uint32_t lds[SCAN_NT / 64 + 1], sel[3], n_list, found_v;
+    __shared__ uint64_t found_key;
+    const uint32_t t = threadIdx.x, J = (N + 1) >> 1;
+    uint64_t ke[Q], ko[Q];
+#pragma unroll
+    for (int q = 0; q < Q; ++q) {
+        ke[q] = ko[q] = 0;
+        if (q * SCAN_NT < J) vertex_pair_keys(q * SCAN_NT + t, seed, step, ke[q], ko[q]);
+    }
+    // f(key, vertex) for every vertex whose key agrees with the decided bits
+    uint64_t pk = 0;
+    int kd = 0;
+    auto agrees = [&](uint64_t k) { return kd == 0 || (k >> (64 - kd)) == (pk >> (64 - kd)); };
+    auto for_agreeing = [&](auto f) {
+#pragma unroll
+        for (int q = 0; q < Q; ++q) {
+            const uint32_t v = 2 * (q * SCAN_NT + t);
+            if (v < N && agrees(ke[q])) f(ke[q], v);
+            if (v + 1 < N && agrees(ko[q])) f(ko[q], v + 1);
+        }
+    };
+    // the bits of the B-th smallest key, eleven at a time until no more than THR_LIST keys agree with them (once for keys of a generator)
+    uint32_t r = B, m;
+    if (t < THR_LIST) list_below[t] = 0;
+    if (t < SMALL_N / 32) bits[t] = 0;
+    if (t == 0) n_list = found_v = 0, found_key = 0; // kept, and reported, if one key had more vertices than the list holds
+    do {
+        const int width = min(HIST_BITS, 64 - kd), lo = 64 - kd - width;
+        reinterpret_cast<uint2 *>(lh)[t] = make_uint2(0u, 0u);
+        __syncthreads();
+        for_agreeing([&](uint64_t k, uint32_t) { atomicAdd(&lh[(uint32_t)(k >> lo) & ((1u << width) - 1u)], 1u); });
+        __syncthreads();
+        const uint2 h = reinterpret_cast<const uint2 *>(lh)[t];
+        uint32_t total;
+        const uint32_t ex = block_excl_scan<uint32_t, SCAN_NT>(h.x + h.y, &total, lds);
+        if (ex < r && r <= ex + h.x) { sel[0] = 2 * t; sel[1] = r - ex; sel[2] = h.x; }
+        else if (ex + h.x < r && r <= ex + h.x + h.y) { sel[0] = 2 * t + 1; sel[1] = r - ex - h.x; sel[2] = h.y; }
+        __syncthreads();
+        pk |= (uint64_t)sel[0] << lo;
+        kd += width;
+        r = sel[1];
+        m = sel[2];
+    } while (m > THR_LIST && kd < 64);
+    if (m <= THR_LIST) {
+        for_agreeing([&](uint64_t k, uint32_t v) {
+            const uint32_t at = atomicAdd(&n_list, 1u);
+            list_key[at] = k;
+            list_v[at] = v;
+        });
+        __syncthreads();
+        // the vertices differ, so exactly one candidate has r - 1 others below it; the candidates an entry is compared with are shared out
+        // among 1024 / m2 threads
+        uint32_t m2 = 64;
+        while (m2 < m) m2 *= 2;
+        const uint32_t c = t & (m2 - 1), parts = SCAN_NT / m2;
+        if (c < m) {
+            const uint64_t k = list_key[c];
+            const uint32_t v = list_v[c];
+            uint32_t below = 0;
+            for (uint32_t i = t / m2; i < m; i += parts) below += (list_key[i] < k) | ((list_key[i] == k) & (list_v[i] < v));
+            if (below) atomicAdd(&list_below[c], below);
+        }
+        __syncthreads();
+        if (t < m && list_below[t] == r - 1) { found_key = list_key[t]; found_v = list_v[t]; }
+    }
+    __syncthreads();
+    const uint64_t tk = found_key;
+    const uint32_t tv = found_v;
+#pragma unroll
+    for (int q = 0; q < Q; ++q) {
+        const uint32_t j = q * SCAN_NT + t, v = 2 * j;
+        const uint32_t ie = v < N && (ke[q] < tk || (ke[q] == tk && v <= tv)), io = v + 1 < N && (ko[q] < tk || (ko[q] == tk && v + 1 <= tv));
+        if (ie | io) atomicOr(&bits[j >> 4], (ie | io << 1) << (2 * (j & 15)));
+    }
+    __syncthreads();
+    // a thread has sixteen vertices
+    uint32_t x = (bits[t >> 1] >> (16 * (t & 1))) & 0xffffu, total;
+    uint32_t ex = block_excl_scan<uint32_t, SCAN_NT>(__popc(x), &total, lds);
+    const uint32_t w = t / 4;
+    if (t % 4 == 0 && w * 64 < N) {
+        rank[w] = ex;
+        bitmap[w] = (uint64_t)bits[2 * w] | (uint64_t)bits[2 * w + 1] << 32;
+    }
+    for (; x; x &= x - 1, ++ex)
+        if (ex < B) S[ex] = (int32_t)(16 * t + __ffs(x) - 1);
+    if (t == 0 && total != B) atomicOr(status, SGNN_ST_CAND_OVERFLOW);
+}
+static_assert(SMALL_N / 16 == SCAN_NT && THR_LIST == SCAN_NT, "sixteen vertices and an entry of the list a thread");
+
 } // namespace
 
 // scratch layout of the sampler inside the context's persistent area
@@ -639,6 +742,10 @@ static int sampler_launches(sgnn_ctx *ctx, uint64_t N, uint32_t B, uint64_t seed
                             uint32_t *cand_v, uint32_t cap, uint32_t *wg_count, uint32_t *status, uint32_t *prefix,
                             sampler_window win, hipStream_t st)
 {
+    if (N <= SMALL_N) {
+        SAMP_LAUNCH("sampler_small_kernel", sampler_small_kernel, dim3(1), dim3(SCAN_NT), (uint32_t)N, B, seed, step, S, bitmap, rank, status);
+        return SGNN_OK;
+    }
     const uint64_t J = (N + 1) >> 1;
     const unsigned grid =
         (unsigned)std::min<uint64_t>(cdiv(J, SCAN_NT), std::min<uint64_t>(std::max<uint64_t>(256, N >> 19), 2048));
