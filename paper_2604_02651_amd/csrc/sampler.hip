@@ -284,35 +284,33 @@ __global__ __launch_bounds__(SCAN_NT) void sampler_collect_kernel(uint64_t N, ui
     cand_flush<LCAP, SCAN_NT>(cl, ncand, cand_key, cand_v, cap, status);
 }
 
-// Exact r-th smallest (key, v) among the candidates of the threshold's bin.  One workgroup, and what it costs is the
+// Exact r-th smallest (key, v) among the candidates of the threshold's bin, by one workgroup; what it costs is the
 // trips to memory, the barriers in a row and, at a few hundred candidates, the fetching of its own code.  So: one radix
-// pass over the 8 bits below the 11 that the bin has decided (none if the list is short to begin with), then the
+// pass over the 8 bits below the 11 that the bin has decided (none if there are no more than FEW: without it 1000 candidates cost 1000
+// comparisons of each with all, 20 us), then the
 // candidates that still agree - one in 256 of those in the bin - move to a list in LDS, and the ones below each are counted
-// by as many threads as there are for it.  A thread requests THR_BATCH keys at a time.  Where more than THR_LIST remain
-// (vertex counts beyond 2^29) another eight bits are decided first.
-// 4 10^7 vertices (39 thousand candidates): 33 -> 16.5 us, what is left is one compute unit's rate of reads and
-// LDS atomics; 2.4 10^6 vertices and fewer: 5 to 7 us before and after.  With 32 keys a thread in registers it spilled (24 us).
-// Leaves the histogram zeroed for the next call.
+// by as many threads as there are for it.  A thread requests THR_BATCH keys at a time.  Where more than NT remain
+// (vertex counts beyond 2^29 for 1024 threads) another eight bits are decided first.
+// A launch of its own (1024 threads), 4 10^7 vertices (39 thousand candidates): 33 -> 16.5 us, what is left is one compute unit's rate
+// of reads and LDS atomics; 2.4 10^6 vertices and fewer: 5 to 7 us before and after.  With 32 keys a thread in registers it spilled (24 us).
 constexpr int THR_BATCH = 16;
-constexpr uint32_t THR_LIST = 1024;
 
-__global__ __launch_bounds__(1024) void sampler_threshold_kernel(sampler_state *__restrict__ state, uint32_t *__restrict__ bin_hist,
-                                                                 const uint64_t *__restrict__ cand_key,
-                                                                 const uint32_t *__restrict__ cand_v, uint32_t cap)
+template <int NT>
+__device__ __forceinline__ void select_threshold(uint32_t n, uint32_t bin, uint32_t r, const uint64_t *__restrict__ cand_key,
+                                                 const uint32_t *__restrict__ cand_v, uint64_t &thr_key, uint32_t &thr_v)
 {
+    constexpr uint32_t FEW = 64;
+    static_assert(NT >= 256, "a digit a thread, and an entry of the list a thread");
     __shared__ uint32_t hist[256];
     __shared__ uint32_t sel_digit, sel_r;
     __shared__ uint64_t found_key;
     __shared__ uint32_t found_v;
-    __shared__ uint64_t list_key[THR_LIST];
-    __shared__ uint32_t list_v[THR_LIST], list_below[THR_LIST];
+    __shared__ uint64_t list_key[NT];
+    __shared__ uint32_t list_v[NT], list_below[NT];
     __shared__ uint32_t n_list;
-    const uint32_t n = min(state->fallback ? state->ncand_fb : state->ncand, cap);
-    uint32_t r = state->r;
-    uint64_t pk = (uint64_t)state->bin << (64 - HIST_BITS);   // decided high bits of the key
+    uint64_t pk = (uint64_t)bin << (64 - HIST_BITS);          // decided high bits of the key
     uint32_t pv = 0;                                          // decided high bits of the vertex
     int kd = HIST_BITS;                                       // how many of them are decided
-    reinterpret_cast<uint2 *>(bin_hist)[threadIdx.x] = make_uint2(0u, 0u);
     list_below[threadIdx.x] = 0;
     if (threadIdx.x < 256) hist[threadIdx.x] = 0;
     if (threadIdx.x == 0) { sel_digit = 0; sel_r = 1; n_list = 0; found_key = 0; found_v = 0; }
@@ -321,18 +319,18 @@ __global__ __launch_bounds__(1024) void sampler_threshold_kernel(sampler_state *
     // f(key, index) for every candidate whose key agrees with the decided bits; a thread's first batch stays in registers
     auto fetch = [&](uint32_t i0, uint64_t (&k)[THR_BATCH]) {
 #pragma unroll
-        for (int q = 0; q < THR_BATCH; ++q) k[q] = cand_key[min(i0 + q * 1024 + threadIdx.x, n - 1)];
+        for (int q = 0; q < THR_BATCH; ++q) k[q] = cand_key[min(i0 + q * NT + threadIdx.x, n - 1)];
     };
     uint64_t first[THR_BATCH];
     if (n) fetch(0, first);
     auto for_agreeing = [&](auto f) {
-        for (uint32_t i0 = 0; i0 < n; i0 += THR_BATCH * 1024) {
+        for (uint32_t i0 = 0; i0 < n; i0 += THR_BATCH * NT) {
             uint64_t k[THR_BATCH];
             if (i0) fetch(i0, k);
 #pragma unroll
             for (int q = 0; q < THR_BATCH; ++q) {
                 k[q] = i0 ? k[q] : first[q];
-                if (i0 + q * 1024 + threadIdx.x < n && (k[q] >> (64 - kd)) == (pk >> (64 - kd))) f(k[q], i0 + q * 1024 + threadIdx.x);
+                if (i0 + q * NT + threadIdx.x < n && (k[q] >> (64 - kd)) == (pk >> (64 - kd))) f(k[q], i0 + q * NT + threadIdx.x);
             }
         }
     };
@@ -355,7 +353,7 @@ __global__ __launch_bounds__(1024) void sampler_threshold_kernel(sampler_state *
         r = sel_r;
     };
     bool found = false;
-    for (bool radix = n > THR_LIST; !found && !(radix && kd == 64); radix = true) {
+    for (bool radix = n > FEW; !found && !(radix && kd == 64); radix = true) {
         if (radix) {
             const int width = min(8, 64 - kd), lo = 64 - kd - width;
             for_agreeing([&](uint64_t k, uint32_t) { atomicAdd(&hist[(uint32_t)(k >> lo) & ((1u << width) - 1u)], 1u); });
@@ -366,17 +364,17 @@ __global__ __launch_bounds__(1024) void sampler_threshold_kernel(sampler_state *
         }
         for_agreeing([&](uint64_t k, uint32_t i) {
             const uint32_t at = atomicAdd(&n_list, 1u);
-            if (at < THR_LIST) { list_key[at] = k; list_v[at] = cand_v[i]; }
+            if (at < NT) { list_key[at] = k; list_v[at] = cand_v[i]; }
         });
         __syncthreads();
         const uint32_t m = n_list;
-        found = m <= THR_LIST;
+        found = m <= NT;
         if (found) {
             // the vertices differ, so exactly one candidate has r - 1 others below it; the candidates an entry is
             // compared with are shared out among 1024 / m2 threads
             uint32_t m2 = 64;
             while (m2 < m) m2 *= 2;
-            const uint32_t t = threadIdx.x & (m2 - 1), part = threadIdx.x / m2, parts = 1024 / m2;
+            const uint32_t t = threadIdx.x & (m2 - 1), part = threadIdx.x / m2, parts = NT / m2;
             if (t < m) {
                 const uint64_t k = list_key[t];
                 const uint32_t v = list_v[t];
@@ -410,11 +408,51 @@ __global__ __launch_bounds__(1024) void sampler_threshold_kernel(sampler_state *
         if (threadIdx.x < 256) hist[threadIdx.x] = 0;
         __syncthreads();
     }
+    thr_key = pk;
+    thr_v = pv;
+}
+
+// A launch of its own, where there are too many candidates for every workgroup of the emit pass to look at all of them.
+// Leaves the histogram zeroed for the next call.
+__global__ __launch_bounds__(1024) void sampler_threshold_kernel(sampler_state *__restrict__ state, uint32_t *__restrict__ bin_hist,
+                                                                 const uint64_t *__restrict__ cand_key,
+                                                                 const uint32_t *__restrict__ cand_v, uint32_t cap)
+{
+    const uint32_t n = min(state->fallback ? state->ncand_fb : state->ncand, cap);
+    reinterpret_cast<uint2 *>(bin_hist)[threadIdx.x] = make_uint2(0u, 0u);
+    uint64_t tk;
+    uint32_t tv;
+    select_threshold<1024>(n, state->bin, state->r, cand_key, cand_v, tk, tv);
     if (threadIdx.x == 0) {
-        state->thr_key = pk;
-        state->thr_v = pv;
+        state->thr_key = tk;
+        state->thr_v = tv;
         state->nmark = n;
         state->ncand = 0;      // every thread read it long ago (barriers above): the list is empty for the next call
+    }
+}
+
+// The threshold at the head of the emit pass: every workgroup selects it for itself, and the first zeroes the histogram for the next call
+// (the rank pass empties the list).  Instead of a launch for one workgroup, whose 2 to 5 us of work and gap the others waited for, every
+// workgroup reads the candidates, up to 2048 of them at this N: with the grids of sampler_launches 2.6 10^5 vertices 24.1 -> 18.2 us the whole sample, 10^6 46 -> 26,
+// 2.4 10^6 36.1 -> 32.3.
+constexpr uint64_t FUSED_THR_MAX_N = 1ull << 22;
+struct thr_src {
+    const uint64_t *key;
+    const uint32_t *v;
+    uint32_t *bin_hist;
+    uint32_t cap;
+};
+
+template <bool FUSED>
+__device__ __forceinline__ void emit_threshold(const sampler_state *__restrict__ state, const thr_src &src, uint64_t &tk, uint32_t &tv)
+{
+    if constexpr (FUSED) {
+        if (blockIdx.x == 0)
+            for (int i = threadIdx.x; i < HIST_BINS; i += SAMP_NT) src.bin_hist[i] = 0;
+        select_threshold<SAMP_NT>(min(state->ncand, src.cap), state->bin, state->r, src.key, src.v, tk, tv);
+    } else {
+        tk = state->thr_key;
+        tv = state->thr_v;
     }
 }
 
@@ -435,19 +473,21 @@ __global__ __launch_bounds__(SAMP_NT) void sampler_mark_kernel(const sampler_sta
 }
 
 // Workgroup g owns bitmap words [g*wpw, (g+1)*wpw), wpw a multiple of 8.  A wavefront takes 64 words
-// at a time and builds two of them per iteration: lane l evaluates vertices 2j and 2j+1 of Philox block
+// (a quarter of the workgroup's, if that is fewer) at a time and builds two of them per iteration: lane l evaluates vertices 2j and 2j+1 of Philox block
 // j = 32*w0 + l.  Lane l keeps word l of the 64, so that the wave writes them with one 512-byte store:
 // an 8-byte store by a single lane per word reached memory as a partial write of its own, a quarter of a
 // million of them at a rate of about one per nanosecond.
 // windowed: the bitmap is complete unless the call fell back, and only the workgroup's count is left to take.
+template <bool FUSED>
 __global__ __launch_bounds__(SAMP_NT) void sampler_emit_kernel(uint64_t N, uint64_t seed, uint64_t step,
                                                                const sampler_state *__restrict__ state,
                                                                uint64_t *__restrict__ bitmap, uint64_t W, uint64_t wpw,
-                                                               uint32_t *__restrict__ wg_count, int windowed)
+                                                               uint32_t *__restrict__ wg_count, int windowed, thr_src src)
 {
     __shared__ uint32_t lds[SAMP_NT / 64];
-    const uint64_t tk = state->thr_key;
-    const uint32_t tv = state->thr_v;
+    uint64_t tk;
+    uint32_t tv;
+    emit_threshold<FUSED>(state, src, tk, tv);
     const uint64_t wbeg = (uint64_t)blockIdx.x * wpw;
     const uint64_t wend = min(W, wbeg + wpw);
     const unsigned wave = threadIdx.x >> 6, lane = lane_id();
@@ -458,9 +498,10 @@ __global__ __launch_bounds__(SAMP_NT) void sampler_emit_kernel(uint64_t N, uint6
         if (threadIdx.x == 0) wg_count[blockIdx.x] = cnt;
         return;
     }
-    for (uint64_t chunk = wbeg + 64 * wave; chunk < wend; chunk += 64 * (SAMP_NT / 64)) {
+    const unsigned span = (unsigned)min((uint64_t)64, wpw / (SAMP_NT / 64));     // words a wavefront takes at a time: an even number, as wpw is a multiple of 8
+    for (uint64_t chunk = wbeg + span * wave; chunk < wend; chunk += span * (SAMP_NT / 64)) {
         uint64_t mine = 0;
-        for (unsigned it = 0; it < 32; ++it) {
+        for (unsigned it = 0; it < span / 2; ++it) {
             const uint64_t w0 = chunk + 2 * it;
             if (w0 >= wend) break;
             const uint64_t j = w0 * 32 + lane;
@@ -479,7 +520,7 @@ __global__ __launch_bounds__(SAMP_NT) void sampler_emit_kernel(uint64_t N, uint6
             if (lane == 2 * it + 1) mine = word1;
             cnt += __popcll(word0) + __popcll(word1);
         }
-        if (chunk + lane < wend) bitmap[chunk + lane] = mine;
+        if (lane < span && chunk + lane < wend) bitmap[chunk + lane] = mine;
     }
     if (lane == 0) lds[wave] = cnt;
     __syncthreads();
@@ -495,16 +536,18 @@ __global__ __launch_bounds__(SAMP_NT) void sampler_emit_kernel(uint64_t N, uint6
 // bitmap (a prefix below the threshold's is in, one above is out, an equal one - 2^-16 of the vertices - has its key
 // computed again); the 64 bytes pass through a wavefront-private strip of LDS, from which lanes 0 .. 7 read and
 // write their eight words with one 64-byte store.  No scalar bit interleaving, no key arithmetic.
+template <bool FUSED>
 __global__ __launch_bounds__(SAMP_NT) void sampler_emit_prefix_kernel(uint64_t N, uint64_t seed, uint64_t step,
                                                                       const sampler_state *__restrict__ state,
                                                                       uint64_t *__restrict__ bitmap, uint64_t W, uint64_t wpw,
                                                                       uint32_t *__restrict__ wg_count,
-                                                                      const uint32_t *__restrict__ prefix)
+                                                                      const uint32_t *__restrict__ prefix, thr_src src)
 {
     __shared__ uint32_t lds[SAMP_NT / 64];
     __shared__ __attribute__((aligned(8))) uint8_t strip[SAMP_NT / 64][64];
-    const uint64_t tk = state->thr_key;
-    const uint32_t tv = state->thr_v;
+    uint64_t tk;
+    uint32_t tv;
+    emit_threshold<FUSED>(state, src, tk, tv);
     const uint32_t tp = (uint32_t)(tk >> 48);
     const uint64_t wbeg = (uint64_t)blockIdx.x * wpw;
     const uint64_t wend = min(W, wbeg + wpw);
@@ -559,24 +602,28 @@ __global__ __launch_bounds__(SAMP_NT) void sampler_emit_prefix_kernel(uint64_t N
     }
 }
 
+template <int P>
 __global__ __launch_bounds__(SAMP_NT) void sampler_rank_kernel(const uint64_t *__restrict__ bitmap, uint64_t W,
                                                                uint64_t wpw, const uint32_t *__restrict__ wg_count,
                                                                uint32_t B, uint32_t *__restrict__ rank,
-                                                               int32_t *__restrict__ S, uint32_t *__restrict__ status)
+                                                               int32_t *__restrict__ S, uint32_t *__restrict__ status, uint32_t *__restrict__ ncand)
 {
     __shared__ uint32_t lds[SAMP_NT / 64 + 1];
+    if (blockIdx.x == 0 && threadIdx.x == 0) *ncand = 0;            // the list is empty for the next call
     // sampled vertices in all earlier workgroups
     uint32_t part = 0;
     for (unsigned i = threadIdx.x; i < blockIdx.x; i += SAMP_NT) part += wg_count[i];
     uint32_t running = block_sum<uint32_t, SAMP_NT>(part, lds);
     const uint64_t wbeg = (uint64_t)blockIdx.x * wpw;
     const uint64_t wend = min(W, wbeg + wpw);
-    for (uint64_t base = wbeg; base < wend; base += SAMP_NT) {
-        const uint64_t w = base + threadIdx.x;
+    for (uint64_t base = wbeg; base < wend; base += SAMP_NT / P) {
+        const uint64_t w = base + threadIdx.x / P;
         uint64_t word = w < wend ? bitmap[w] : 0ull;
+        const int at = 64 / P * (threadIdx.x % P);
+        if constexpr (P > 1) word &= ((1ull << (64 / P)) - 1) << at;
         uint32_t total;
         uint32_t ex = block_excl_scan<uint32_t, SAMP_NT>(__popcll(word), &total, lds) + running;
-        if (w < wend) rank[w] = ex;
+        if (w < wend && at == 0) rank[w] = ex;
         while (word) {
             const int b = __ffsll((unsigned long long)word) - 1;
             if (ex < B) S[ex] = (int32_t)(w * 64 + b);
@@ -598,6 +645,7 @@ __global__ __launch_bounds__(SCAN_NT) void sampler_small_kernel(uint32_t N, uint
                                                                 uint32_t *__restrict__ status)
 {
     constexpr int Q = (int)(SMALL_N / 2 / SCAN_NT);
+    constexpr uint32_t THR_LIST = SCAN_NT;
     __shared__ __attribute__((aligned(8))) uint32_t lh[HIST_BINS];
     __shared__ uint32_t bits[SMALL_N / 32];
     __shared__ uint64_t list_key[THR_LIST];
@@ -689,7 +737,7 @@ __global__ __launch_bounds__(SCAN_NT) void sampler_small_kernel(uint32_t N, uint
         if (ex < B) S[ex] = (int32_t)(16 * t + __ffs(x) - 1);
     if (t == 0 && total != B) atomicOr(status, SGNN_ST_CAND_OVERFLOW);
 }
-static_assert(SMALL_N / 16 == SCAN_NT && THR_LIST == SCAN_NT, "sixteen vertices and an entry of the list a thread");
+static_assert(SMALL_N / 16 == SCAN_NT, "sixteen vertices a thread");
 
 } // namespace
 
@@ -750,7 +798,10 @@ static int sampler_launches(sgnn_ctx *ctx, uint64_t N, uint32_t B, uint64_t seed
     const unsigned grid =
         (unsigned)std::min<uint64_t>(cdiv(J, SCAN_NT), std::min<uint64_t>(std::max<uint64_t>(256, N >> 19), 2048));
     const uint64_t W = (N + 63) / 64;
-    const unsigned egrid = (unsigned)std::min<uint64_t>(cdiv(W, 8), EMIT_MAX_WG);
+        // a workgroup of the emit pass has a threshold to select before its 2048 vertices or more: 5.2 10^5 vertices by 256 workgroups 21.4 us the
+    // whole sample, by 1024 23.9; 4 10^6 45.1 and 39.6
+    const unsigned egrid =
+        (unsigned)std::min<uint64_t>(cdiv(W, 8), std::min<uint64_t>(std::max<uint64_t>(256, N >> 11), EMIT_MAX_WG));
     const uint64_t wpw = (uint64_t)cdiv(cdiv(W, egrid), 8) * 8;
     if (win.on) {
         // one pass over the keys; the collect pass leaves at once and the emit pass only counts unless the threshold's
@@ -763,29 +814,35 @@ static int sampler_launches(sgnn_ctx *ctx, uint64_t N, uint32_t B, uint64_t seed
                     (const uint32_t *)cand_v, cap);
         SAMP_LAUNCH("sampler_mark_kernel", sampler_mark_kernel, dim3(64), dim3(SAMP_NT), (const sampler_state *)state,
                     (const uint64_t *)cand_key, (const uint32_t *)cand_v, bitmap);
-        SAMP_LAUNCH("sampler_emit_kernel", sampler_emit_kernel, dim3(egrid), dim3(SAMP_NT), N, seed, step, state, bitmap, W, wpw,
-                    wg_count, 1);
-        SAMP_LAUNCH("sampler_rank_kernel", sampler_rank_kernel, dim3(egrid), dim3(SAMP_NT), bitmap, W, wpw, wg_count, B, rank, S,
-                    status);
+        SAMP_LAUNCH("sampler_emit_kernel", sampler_emit_kernel<false>, dim3(egrid), dim3(SAMP_NT), N, seed, step, state, bitmap, W, wpw,
+                    wg_count, 1, thr_src{});
+        SAMP_LAUNCH("sampler_rank_kernel", wpw * 4 <= SAMP_NT ? sampler_rank_kernel<4> : sampler_rank_kernel<1>, dim3(egrid), dim3(SAMP_NT), bitmap, W, wpw, wg_count, B, rank, S,
+                    status, &state->ncand);
         return SGNN_OK;
     }
-    SAMP_LAUNCH("sampler_hist_kernel", sampler_hist_kernel, dim3(grid), dim3(SCAN_NT), N, seed, step, hist, prefix, state);
+    // a workgroup's merge costs up to 2048 atomics however few keys it had (the comment at the kernel): 64 workgroups for 5.2 10^5 vertices
+    // 23.1 us the whole sample, 256 26.9; 4 10^6 45.5 and 37.3
+    const unsigned hgrid = std::min(grid, (unsigned)std::max<uint64_t>(64, N >> 13));
+    SAMP_LAUNCH("sampler_hist_kernel", sampler_hist_kernel, dim3(hgrid), dim3(SCAN_NT), N, seed, step, hist, prefix, state);
     if (prefix)
         SAMP_LAUNCH("sampler_collect_kernel", sampler_collect_kernel<true>, dim3(grid), dim3(SCAN_NT), N, B, seed, step,
                     (const uint32_t *)hist, state, cand_key, cand_v, cap, status, (const uint32_t *)prefix, 0, 0u, 0u);
     else
         SAMP_LAUNCH("sampler_collect_kernel", sampler_collect_kernel<false>, dim3(grid), dim3(SCAN_NT), N, B, seed, step,
                     (const uint32_t *)hist, state, cand_key, cand_v, cap, status, (const uint32_t *)nullptr, 0, 0u, 0u);
-    SAMP_LAUNCH("sampler_threshold_kernel", sampler_threshold_kernel, dim3(1), dim3(1024), state, hist, (const uint64_t *)cand_key,
-                (const uint32_t *)cand_v, cap);
+    const bool fused = N <= FUSED_THR_MAX_N;
+    const thr_src src = {cand_key, cand_v, hist, cap};
+    if (!fused)
+        SAMP_LAUNCH("sampler_threshold_kernel", sampler_threshold_kernel, dim3(1), dim3(1024), state, hist, (const uint64_t *)cand_key,
+                    (const uint32_t *)cand_v, cap);
     if (prefix)
-        SAMP_LAUNCH("sampler_emit_kernel", sampler_emit_prefix_kernel, dim3(egrid), dim3(SAMP_NT), N, seed, step, state, bitmap, W,
-                    wpw, wg_count, (const uint32_t *)prefix);
+        SAMP_LAUNCH("sampler_emit_kernel", fused ? sampler_emit_prefix_kernel<true> : sampler_emit_prefix_kernel<false>, dim3(egrid),
+                    dim3(SAMP_NT), N, seed, step, state, bitmap, W, wpw, wg_count, (const uint32_t *)prefix, src);
     else
-        SAMP_LAUNCH("sampler_emit_kernel", sampler_emit_kernel, dim3(egrid), dim3(SAMP_NT), N, seed, step, state, bitmap, W, wpw,
-                    wg_count, 0);
-    SAMP_LAUNCH("sampler_rank_kernel", sampler_rank_kernel, dim3(egrid), dim3(SAMP_NT), bitmap, W, wpw, wg_count, B, rank, S,
-                status);
+        SAMP_LAUNCH("sampler_emit_kernel", fused ? sampler_emit_kernel<true> : sampler_emit_kernel<false>, dim3(egrid), dim3(SAMP_NT), N,
+                    seed, step, state, bitmap, W, wpw, wg_count, 0, src);
+    SAMP_LAUNCH("sampler_rank_kernel", wpw * 4 <= SAMP_NT ? sampler_rank_kernel<4> : sampler_rank_kernel<1>, dim3(egrid), dim3(SAMP_NT), bitmap, W, wpw, wg_count, B, rank, S,
+                status, &state->ncand);
     return SGNN_OK;
 }
 

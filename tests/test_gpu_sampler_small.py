@@ -1,4 +1,5 @@
-"""The sampler of graphs whose keys one workgroup holds (up to 16384 vertices) and the first sizes beyond it."""
+"""The sampler of graphs whose keys one workgroup holds (up to 16384 vertices), and of those (up to 4194304) whose threshold every
+workgroup of the emit pass selects for itself."""
 import numpy as np
 import pytest
 
@@ -16,6 +17,19 @@ def test_small_sample_matches_oracle(N, part):
     for step in (0, 2**33 + 1):
         S, bitmap, rank = gpu_sample(N, B, 5, step)
         S_ref = oracle.sample_uniform(N, B, 5, step)
+        assert np.array_equal(S.cpu().numpy(), S_ref)
+        words, rk = bitmap_rank_from_sample(N, S_ref)
+        assert np.array_equal(bitmap.cpu().numpy(), words) and np.array_equal(rank.cpu().numpy(), rk)
+
+
+# a word, two or more a wavefront; the last dense sample that selects in the emit pass and the first with a launch of its own for it,
+# the sparse one (another list) between two dense ones
+@pytest.mark.parametrize("N,B", [(65537, 65536), (300001, 100), (524289, 200000), (1048575, 400000), (1048577, 500000),
+                                 (4194304, 2097152), (4194304, 4096), (4194304, 2097153), (4194305, 2097152)])
+def test_threshold_in_the_emit_pass(N, B):
+    for step in (1, 2):
+        S, bitmap, rank = gpu_sample(N, B, 9, step)
+        S_ref = oracle.sample_uniform(N, B, 9, step)
         assert np.array_equal(S.cpu().numpy(), S_ref)
         words, rk = bitmap_rank_from_sample(N, S_ref)
         assert np.array_equal(bitmap.cpu().numpy(), words) and np.array_equal(rank.cpu().numpy(), rk)
