@@ -8,15 +8,15 @@
 // later passes read those instead: they decide all but 2^-11 (candidates) and 2^-16 (ties with the
 // threshold's prefix) of the vertices, and only for these is the key computed again.
 //
-// Sparse samples of large graphs take pass 1 in the form of sampler_hist_window_kernel (which also appends the candidates
-// and sets the bits of the vertices that are in for certain); pass 2 then only finds the bin and pass 4 only counts.
-//
 //   1. sampler_hist_kernel     histogram of the top 11 key bits (LDS histograms, one merge)
 //   2. sampler_collect_kernel  the bin b* that holds the B-th smallest key and the rank r inside (every workgroup for
 //                              itself), and (key, v) of every vertex in bin b* -> candidate list (about N/2048)
-//   3. sampler_threshold_kernel exact r-th smallest (key, v) of the candidates
+//   3. sampler_threshold_kernel exact r-th smallest (key, v) of the candidates; up to 2^22 vertices a part of the next pass
 //   4. sampler_emit_kernel     bitmap word per 64 vertices from wave ballots + per-workgroup counts
 //   5. sampler_rank_kernel     rank prefix per bitmap word and the ascending list S
+//
+// Up to SMALL_N vertices one workgroup does all of it (sampler_small_kernel).  Sparse samples of large graphs know the bin of the threshold
+// beforehand and go through the keys once: sampler_hist_window_kernel, sampler_mark_kernel, sampler_count_kernel, sampler_rank_kernel.
 #include "block_prims.h"
 #include <algorithm>
 #include <cmath>
@@ -40,15 +40,15 @@ struct sampler_state {
     uint32_t ncand;     // candidates appended by the collect pass
     uint32_t thr_v;     // threshold vertex
     uint64_t thr_key;   // threshold key
-    uint32_t fallback;  // windowed call whose threshold bin fell outside the window: the recomputing passes run instead
-    uint32_t nmark;     // candidates the threshold pass looked at (ncand is zero again when it ends)
-    uint32_t ncand_fb;  // candidates appended by the collect pass of a windowed call that fell back
+    uint32_t fallback;  // windowed call whose threshold's bin fell outside the window
+    uint32_t nfew;      // windowed call: candidates in the threshold's part of its bin
 };
 
-// keys of vertices 2j (even) and 2j+1 (odd)
+// Keys of vertices 2j (even) and 2j+1 (odd).  There are fewer than 2^31 vertices: the upper half of the counter's j is the constant 0, which
+// leaves 18 of the 20 products to the vector unit.
 __device__ __forceinline__ void vertex_pair_keys(uint64_t j, uint64_t seed, uint64_t step, uint64_t &ke, uint64_t &ko)
 {
-    philox_out o = philox4x32_10((uint32_t)j, (uint32_t)(j >> 32), (uint32_t)step, (uint32_t)(step >> 32),
+    philox_out o = philox4x32_10((uint32_t)j, 0u, (uint32_t)step, (uint32_t)(step >> 32),
                                  (uint32_t)seed, (uint32_t)(seed >> 32));
     ke = ((uint64_t)o.w1 << 32) | o.w0;
     ko = ((uint64_t)o.w3 << 32) | o.w2;
@@ -142,26 +142,32 @@ __device__ __forceinline__ void cand_flush(cand_lds<LCAP> &l, uint32_t *__restri
 // known before any key is: the B-th smallest of N uniform keys lies at B/N of the key range, give or take
 // sqrt(B (1 - B/N)) / N of it, so the host names a window [b_lo, b_hi] of one or two histogram bins that holds it
 // (six standard deviations either side).  This pass then does three things with every key while it has it: counts
-// its bin, appends it to the candidate list if the bin is in the window, and sets the vertex's bit in the output
-// bitmap if the bin lies below the window (such a vertex is in the sample whatever the threshold turns out to be).
-// Nothing per vertex is stored for later passes - no key prefixes - and no later pass touches a key again: the
-// threshold comes from the candidates, the candidates at or below it get their bits set (sampler_mark_kernel), and
-// the bitmap is complete.  If the threshold's bin is outside the window after all
-// (pick_bin, at the head of the collect pass, checks), the recomputing passes run instead and overwrite everything.
+// it if it is below the window (below[w]: those of workgroup w), appends it to the candidate list if its bin is in the window, and sets the
+// vertex's bit in the output bitmap if the bin lies below the window (such a vertex is in the sample whatever the threshold turns out to be).
+// Nothing per vertex is stored for later passes - no key prefixes - and no later pass touches a key again.  The histogram is one of the
+// candidates: a bin of the window in 1024 parts (window_part), so that the next pass has the part of the threshold, and few candidates are in it.
+// What bounds the pass is the vector unit, 18 products of 16 clocks and 18 three-way xors a Philox call: 4 10^7 vertices 58.3 -> 50.5 us with the
+// xors in one instruction each; the whole sample 93 -> 69 without a launch of one workgroup that selects among all candidates.
 constexpr uint32_t WIN_LCAP = 2048;
+constexpr unsigned WIN_MAX_WG = 512;                      // two a compute unit: what it holds
+// a candidate's place in the histogram: the window has one bin or two
+__device__ __forceinline__ uint32_t window_part(uint64_t k, uint32_t b_lo)
+{
+    return (uint32_t)(k >> (64 - HIST_BITS - 10)) - (b_lo << 10);
+}
 __global__ __launch_bounds__(SCAN_NT) void sampler_hist_window_kernel(uint64_t N, uint64_t seed, uint64_t step,
-                                                                      uint32_t *__restrict__ hist, uint32_t b_lo, uint32_t b_hi,
+                                                                      uint32_t *__restrict__ hist, uint32_t *__restrict__ below,
+                                                                      uint32_t b_lo, uint32_t b_hi,
                                                                       sampler_state *__restrict__ state,
                                                                       uint64_t *__restrict__ cand_key, uint32_t *__restrict__ cand_v,
                                                                       uint32_t cap, uint32_t *__restrict__ status,
                                                                       uint64_t *__restrict__ bitmap, uint64_t W)
 {
-    __shared__ uint32_t lh[HIST_BINS];
+    __shared__ uint32_t lds[SCAN_NT / 64];
     __shared__ cand_lds<WIN_LCAP> cl;
     __shared__ __attribute__((aligned(8))) uint8_t strip[SCAN_NT / 64][64];
-    for (int i = threadIdx.x; i < HIST_BINS; i += SCAN_NT) lh[i] = 0;
     if (threadIdx.x == 0) { cl.n = 0; cl.fail = 0xffffffffu; }
-    if (blockIdx.x == 0 && threadIdx.x == 0) state->ncand_fb = 0;
+    if (blockIdx.x == 0 && threadIdx.x == 0) state->nfew = 0;
     __syncthreads();
     const unsigned wave = threadIdx.x >> 6, lane = lane_id();
     // A wavefront takes eight bitmap words (512 vertices) per round: lane l computes the keys of vertices 8l .. 8l+7 of
@@ -170,6 +176,7 @@ __global__ __launch_bounds__(SCAN_NT) void sampler_hist_window_kernel(uint64_t N
     // (as the emit pass over stored prefixes does: no bit interleaving of ballots).
     volatile uint8_t *my_bytes = strip[wave];
     volatile uint64_t *my_words = reinterpret_cast<volatile uint64_t *>(strip[wave]);
+    uint32_t n_below = 0;
     const uint64_t W8 = (W + 7) & ~7ull;
     for (uint64_t wb = ((uint64_t)blockIdx.x * (SCAN_NT / 64) + wave) * 8; wb < W8; wb += (uint64_t)gridDim.x * (SCAN_NT / 64) * 8) {
         const uint64_t v0 = wb * 64 + 8 * lane;                  // first of the lane's eight vertices
@@ -181,18 +188,19 @@ __global__ __launch_bounds__(SCAN_NT) void sampler_hist_window_kernel(uint64_t N
                 uint64_t ke, ko;
                 vertex_pair_keys(ve >> 1, seed, step, ke, ko);
                 const uint32_t be_ = (uint32_t)(ke >> (64 - HIST_BITS)), bo_ = (uint32_t)(ko >> (64 - HIST_BITS));
-                atomicAdd(&lh[be_], 1u);
                 const bool me = be_ >= b_lo && be_ <= b_hi;
                 bool mo = false;
                 byte |= (be_ < b_lo ? 1u : 0u) << (2 * q);
                 if (vo < N) {
-                    atomicAdd(&lh[bo_], 1u);
                     mo = bo_ >= b_lo && bo_ <= b_hi;
                     byte |= (bo_ < b_lo ? 1u : 0u) << (2 * q + 1);
                 }
+                if (me) atomicAdd(&hist[window_part(ke, b_lo)], 1u);
+                if (mo) atomicAdd(&hist[window_part(ko, b_lo)], 1u);
                 cand_append(cl, me, mo, ke, ko, ve >> 1, &state->ncand, cand_key, cand_v, cap, status);
             }
         }
+        n_below += __popc(byte);
         my_bytes[lane] = (uint8_t)byte;          // volatile: written and read in program order; LDS serves a wavefront in order
         if (lane < 8) {
             const uint64_t word = my_words[lane];
@@ -200,10 +208,8 @@ __global__ __launch_bounds__(SCAN_NT) void sampler_hist_window_kernel(uint64_t N
         }
     }
     cand_flush<WIN_LCAP, SCAN_NT>(cl, &state->ncand, cand_key, cand_v, cap, status);
-    for (int i = threadIdx.x; i < HIST_BINS; i += SCAN_NT) {
-        uint32_t c = lh[i];
-        if (c) atomicAdd(&hist[i], c);
-    }
+    n_below = block_sum<uint32_t, SCAN_NT>(n_below, lds);
+    if (threadIdx.x == 0) below[blockIdx.x] = n_below;
 }
 
 // Bin of the B-th smallest key and its rank in there, from the histogram: 1024 threads, two bins a thread.  Every workgroup
@@ -225,9 +231,6 @@ __device__ __forceinline__ void pick_bin(uint32_t B, const uint32_t *__restrict_
 }
 static_assert(HIST_BINS == 2 * SCAN_NT, "two bins a thread");
 
-// windowed: the candidates of bins b_lo .. b_hi are in the list already; they stay if the threshold's bin is one of
-// those (r counts inside the threshold's bin as always: the threshold pass looks only at the candidates of that bin), otherwise
-// the call falls back to this pass, which writes the list anew with a counter of its own.
 template <bool PREFIX>
 __global__ __launch_bounds__(SCAN_NT) void sampler_collect_kernel(uint64_t N, uint32_t B, uint64_t seed, uint64_t step,
                                                                   const uint32_t *__restrict__ hist,
@@ -235,27 +238,22 @@ __global__ __launch_bounds__(SCAN_NT) void sampler_collect_kernel(uint64_t N, ui
                                                                   uint64_t *__restrict__ cand_key,
                                                                   uint32_t *__restrict__ cand_v, uint32_t cap,
                                                                   uint32_t *__restrict__ status,
-                                                                  const uint32_t *__restrict__ prefix, int windowed, uint32_t b_lo,
-                                                                  uint32_t b_hi)
+                                                                  const uint32_t *__restrict__ prefix)
 {
     // Matches are rare (one vertex in 2048): gathered per workgroup (cand_lds).
     constexpr uint32_t LCAP = 1024;
     __shared__ cand_lds<LCAP> cl;
     uint32_t bin, r;
     pick_bin(B, hist, bin, r);
-    const bool miss = windowed && (bin < b_lo || bin > b_hi);
     if (blockIdx.x == 0 && threadIdx.x == 0) {
         state->bin = bin;
         state->r = r;
-        state->fallback = miss ? 1u : 0u;
     }
-    if (windowed && !miss) return;                         // a windowed call that found its threshold bin in the window
-    uint32_t *ncand = windowed ? &state->ncand_fb : &state->ncand;
     const uint64_t J = (N + 1) >> 1;
     if (threadIdx.x == 0) { cl.n = 0; cl.fail = 0xffffffffu; }
     __syncthreads();
     auto append = [&](bool me, bool mo, uint64_t ke, uint64_t ko, uint64_t j) {
-        cand_append(cl, me, mo, ke, ko, j, ncand, cand_key, cand_v, cap, status);
+        cand_append(cl, me, mo, ke, ko, j, &state->ncand, cand_key, cand_v, cap, status);
     };
     const uint64_t J_rounds = PREFIX ? (J + 3) / 4 : J;      // loop items: quads of prefix words, or Philox blocks
     for (uint64_t j = (uint64_t)blockIdx.x * SCAN_NT + threadIdx.x; j < J_rounds; j += (uint64_t)gridDim.x * SCAN_NT) {
@@ -281,7 +279,7 @@ __global__ __launch_bounds__(SCAN_NT) void sampler_collect_kernel(uint64_t N, ui
             append((uint32_t)(ke >> (64 - HIST_BITS)) == bin, (2 * j + 1 < N) && (uint32_t)(ko >> (64 - HIST_BITS)) == bin, ke, ko, j);
         }
     }
-    cand_flush<LCAP, SCAN_NT>(cl, ncand, cand_key, cand_v, cap, status);
+    cand_flush<LCAP, SCAN_NT>(cl, &state->ncand, cand_key, cand_v, cap, status);
 }
 
 // Exact r-th smallest (key, v) among the candidates of the threshold's bin, by one workgroup; what it costs is the
@@ -296,8 +294,8 @@ __global__ __launch_bounds__(SCAN_NT) void sampler_collect_kernel(uint64_t N, ui
 constexpr int THR_BATCH = 16;
 
 template <int NT>
-__device__ __forceinline__ void select_threshold(uint32_t n, uint32_t bin, uint32_t r, const uint64_t *__restrict__ cand_key,
-                                                 const uint32_t *__restrict__ cand_v, uint64_t &thr_key, uint32_t &thr_v)
+__device__ __forceinline__ void select_threshold(uint32_t n, uint32_t bin, uint32_t r, const uint64_t *cand_key, const uint32_t *cand_v,
+                                                 uint64_t &thr_key, uint32_t &thr_v)
 {
     constexpr uint32_t FEW = 64;
     static_assert(NT >= 256, "a digit a thread, and an entry of the list a thread");
@@ -414,19 +412,18 @@ __device__ __forceinline__ void select_threshold(uint32_t n, uint32_t bin, uint3
 
 // A launch of its own, where there are too many candidates for every workgroup of the emit pass to look at all of them.
 // Leaves the histogram zeroed for the next call.
-__global__ __launch_bounds__(1024) void sampler_threshold_kernel(sampler_state *__restrict__ state, uint32_t *__restrict__ bin_hist,
+__global__ __launch_bounds__(SCAN_NT) void sampler_threshold_kernel(sampler_state *__restrict__ state, uint32_t *__restrict__ bin_hist,
                                                                  const uint64_t *__restrict__ cand_key,
                                                                  const uint32_t *__restrict__ cand_v, uint32_t cap)
 {
-    const uint32_t n = min(state->fallback ? state->ncand_fb : state->ncand, cap);
+    const uint32_t n = min(state->ncand, cap);
     reinterpret_cast<uint2 *>(bin_hist)[threadIdx.x] = make_uint2(0u, 0u);
     uint64_t tk;
     uint32_t tv;
-    select_threshold<1024>(n, state->bin, state->r, cand_key, cand_v, tk, tv);
+    select_threshold<SCAN_NT>(n, state->bin, state->r, cand_key, cand_v, tk, tv);
     if (threadIdx.x == 0) {
         state->thr_key = tk;
         state->thr_v = tv;
-        state->nmark = n;
         state->ncand = 0;      // every thread read it long ago (barriers above): the list is empty for the next call
     }
 }
@@ -456,19 +453,71 @@ __device__ __forceinline__ void emit_threshold(const sampler_state *__restrict__
     }
 }
 
-// Windowed calls: the candidates at or below the threshold get their bits (the vertices of the bins below the window
-// have theirs from the key pass).
-__global__ __launch_bounds__(SAMP_NT) void sampler_mark_kernel(const sampler_state *__restrict__ state,
-                                                               const uint64_t *__restrict__ cand_key,
-                                                               const uint32_t *__restrict__ cand_v, uint64_t *__restrict__ bitmap)
+// Windowed calls, second pass: the part of the window that holds the threshold, from the counts of the first pass, by every workgroup for itself; the
+// candidates of the parts below it get their bits (the vertices of the bins below the window have theirs from the key pass), the places of those
+// in it go to the list `few`.
+// The window misses the threshold once in 10^9 calls.  Then the first workgroup goes through the keys by itself, twice (20 ms for 4 10^7
+// vertices), for the bin and for its candidates, and selects the threshold; the count pass recomputes the keys and overwrites the bitmap.
+// (Passes of the whole chip for it would be launches that every call pays for: one that left at once cost 4.5 us.)
+// Candidates are written and read here: no __restrict__.
+__global__ __launch_bounds__(SCAN_NT) void sampler_mark_kernel(uint64_t N, uint32_t B, uint64_t seed, uint64_t step, sampler_state *state,
+                                                               const uint32_t *hist, const uint32_t *below, uint32_t n_wg, uint32_t b_lo,
+                                                               uint64_t *cand_key, uint32_t *cand_v, uint32_t cap, uint64_t *bitmap,
+                                                               uint32_t *few, uint32_t few_cap, uint32_t *status)
 {
-    if (state->fallback) return;
-    const uint64_t tk = state->thr_key;
-    const uint32_t tv = state->thr_v, n = state->nmark;
-    for (uint32_t i = blockIdx.x * SAMP_NT + threadIdx.x; i < n; i += gridDim.x * SAMP_NT) {
-        const uint64_t k = cand_key[i];
-        const uint32_t v = cand_v[i];
-        if (k < tk || (k == tk && v <= tv)) atomicOr((unsigned long long *)&bitmap[v >> 6], 1ull << (v & 63));
+    __shared__ uint32_t lds[SCAN_NT / 64];
+    uint32_t nb = 0;
+    for (uint32_t i = threadIdx.x; i < n_wg; i += SCAN_NT) nb += below[i];
+    nb = block_sum<uint32_t, SCAN_NT>(nb, lds);
+    uint32_t n = state->ncand, bin, r;
+    const bool miss = B <= nb || B - nb > n;
+    n = min(n, cap);
+    if (!miss) {
+        pick_bin(B - nb, hist, bin, r);
+        if (blockIdx.x == 0 && threadIdx.x == 0) { state->r = r; state->fallback = 0; }
+        for (uint32_t i = blockIdx.x * SCAN_NT + threadIdx.x; i < n; i += gridDim.x * SCAN_NT) {
+            const uint32_t part = window_part(cand_key[i], b_lo), v = cand_v[i];
+            if (part < bin) atomicOr((unsigned long long *)&bitmap[v >> 6], 1ull << (v & 63));
+            if (part != bin) continue;
+            const uint32_t at = atomicAdd(&state->nfew, 1u);
+            if (at < few_cap) few[at] = i;
+            else atomicOr(status, SGNN_ST_CAND_OVERFLOW);
+        }
+        return;
+    }
+    if (blockIdx.x) return;
+    constexpr uint32_t LCAP = 1024;
+    __shared__ cand_lds<LCAP> cl;
+    __shared__ uint32_t lh[HIST_BINS], n_list;
+    reinterpret_cast<uint2 *>(lh)[threadIdx.x] = make_uint2(0u, 0u);
+    if (threadIdx.x == 0) { cl.n = 0; cl.fail = 0xffffffffu; state->nfew = 0; }         // nfew: the length of this list
+    __syncthreads();
+    const uint64_t J = (N + 1) >> 1;
+    for (uint64_t j = threadIdx.x; j < J; j += SCAN_NT) {
+        uint64_t ke, ko;
+        vertex_pair_keys(j, seed, step, ke, ko);
+        atomicAdd(&lh[ke >> (64 - HIST_BITS)], 1u);
+        if (2 * j + 1 < N) atomicAdd(&lh[ko >> (64 - HIST_BITS)], 1u);
+    }
+    __syncthreads();
+    pick_bin(B, lh, bin, r);
+    for (uint64_t j = threadIdx.x; j < J; j += SCAN_NT) {
+        uint64_t ke, ko;
+        vertex_pair_keys(j, seed, step, ke, ko);
+        cand_append(cl, (uint32_t)(ke >> (64 - HIST_BITS)) == bin, (2 * j + 1 < N) && (uint32_t)(ko >> (64 - HIST_BITS)) == bin, ke, ko, j,
+                    &state->nfew, cand_key, cand_v, cap, status);
+    }
+    cand_flush<LCAP, SCAN_NT>(cl, &state->nfew, cand_key, cand_v, cap, status);
+    __syncthreads();
+    if (threadIdx.x == 0) n_list = atomicAdd(&state->nfew, 0u);
+    __syncthreads();
+    uint64_t tk;
+    uint32_t tv;
+    select_threshold<SCAN_NT>(min(n_list, cap), bin, r, cand_key, cand_v, tk, tv);
+    if (threadIdx.x == 0) {
+        state->thr_key = tk;
+        state->thr_v = tv;
+        state->fallback = 1;
     }
 }
 
@@ -477,27 +526,14 @@ __global__ __launch_bounds__(SAMP_NT) void sampler_mark_kernel(const sampler_sta
 // j = 32*w0 + l.  Lane l keeps word l of the 64, so that the wave writes them with one 512-byte store:
 // an 8-byte store by a single lane per word reached memory as a partial write of its own, a quarter of a
 // million of them at a rate of about one per nanosecond.
-// windowed: the bitmap is complete unless the call fell back, and only the workgroup's count is left to take.
-template <bool FUSED>
-__global__ __launch_bounds__(SAMP_NT) void sampler_emit_kernel(uint64_t N, uint64_t seed, uint64_t step,
-                                                               const sampler_state *__restrict__ state,
-                                                               uint64_t *__restrict__ bitmap, uint64_t W, uint64_t wpw,
-                                                               uint32_t *__restrict__ wg_count, int windowed, thr_src src)
+__device__ __forceinline__ void emit_words(uint64_t N, uint64_t seed, uint64_t step, uint64_t tk, uint32_t tv, uint64_t *__restrict__ bitmap,
+                                           uint64_t W, uint64_t wpw, uint32_t *__restrict__ wg_count)
 {
     __shared__ uint32_t lds[SAMP_NT / 64];
-    uint64_t tk;
-    uint32_t tv;
-    emit_threshold<FUSED>(state, src, tk, tv);
     const uint64_t wbeg = (uint64_t)blockIdx.x * wpw;
     const uint64_t wend = min(W, wbeg + wpw);
     const unsigned wave = threadIdx.x >> 6, lane = lane_id();
     uint32_t cnt = 0;
-    if (windowed && !state->fallback) {
-        for (uint64_t w = wbeg + threadIdx.x; w < wend; w += SAMP_NT) cnt += (uint32_t)__popcll(bitmap[w]);
-        cnt = block_sum<uint32_t, SAMP_NT>(cnt, lds);
-        if (threadIdx.x == 0) wg_count[blockIdx.x] = cnt;
-        return;
-    }
     const unsigned span = (unsigned)min((uint64_t)64, wpw / (SAMP_NT / 64));     // words a wavefront takes at a time: an even number, as wpw is a multiple of 8
     for (uint64_t chunk = wbeg + span * wave; chunk < wend; chunk += span * (SAMP_NT / 64)) {
         uint64_t mine = 0;
@@ -529,6 +565,75 @@ __global__ __launch_bounds__(SAMP_NT) void sampler_emit_kernel(uint64_t N, uint6
         for (int i = 0; i < SAMP_NT / 64; ++i) t += lds[i];
         wg_count[blockIdx.x] = t;
     }
+}
+
+template <bool FUSED>
+__global__ __launch_bounds__(SAMP_NT) void sampler_emit_kernel(uint64_t N, uint64_t seed, uint64_t step,
+                                                               const sampler_state *__restrict__ state,
+                                                               uint64_t *__restrict__ bitmap, uint64_t W, uint64_t wpw,
+                                                               uint32_t *__restrict__ wg_count, thr_src src)
+{
+    uint64_t tk;
+    uint32_t tv;
+    emit_threshold<FUSED>(state, src, tk, tv);
+    emit_words(N, seed, step, tk, tv, bitmap, W, wpw, wg_count);
+}
+
+// Windowed calls, last but one: every workgroup counts its words, finds the threshold among the few candidates of its part and sets the bits of
+// those of them that are in and in its words.  Leaves the histogram zeroed for the next call (the rank pass empties the candidates' list).
+__global__ __launch_bounds__(SAMP_NT) void sampler_count_kernel(uint64_t N, uint64_t seed, uint64_t step,
+                                                                const sampler_state *__restrict__ state, uint32_t *__restrict__ hist,
+                                                                const uint64_t *__restrict__ cand_key, const uint32_t *__restrict__ cand_v,
+                                                                const uint32_t *__restrict__ few, uint32_t few_cap, uint64_t *bitmap,
+                                                                uint64_t W, uint64_t wpw, uint32_t *__restrict__ wg_count)
+{
+    constexpr uint32_t TILE = 32;                          // 4 10^7 vertices have 20 candidates in a part, 10^8 50
+    __shared__ uint32_t lds[SAMP_NT / 64];
+    __shared__ uint64_t tile_key[TILE], found_key;
+    __shared__ uint32_t tile_v[TILE], found_v;
+    if (blockIdx.x == 0)
+        for (int i = threadIdx.x; i < HIST_BINS; i += SAMP_NT) hist[i] = 0;
+    if (state->fallback) {
+        emit_words(N, seed, step, state->thr_key, state->thr_v, bitmap, W, wpw, wg_count);
+        return;
+    }
+    const uint32_t m = min(state->nfew, few_cap), r = state->r;
+    const uint64_t wbeg = (uint64_t)blockIdx.x * wpw;
+    const uint64_t wend = min(W, wbeg + wpw);
+    uint32_t cnt = 0;
+    for (uint64_t w = wbeg + threadIdx.x; w < wend; w += SAMP_NT) cnt += (uint32_t)__popcll(bitmap[w]);
+    if (threadIdx.x == 0) { found_key = 0; found_v = 0; }
+    // the vertices differ, so exactly one has r - 1 others below it
+    for (uint32_t i0 = 0; i0 < m; i0 += SAMP_NT) {
+        const uint32_t i = i0 + threadIdx.x, c = few[min(i, m - 1)], v = cand_v[c];
+        const uint64_t k = cand_key[c];
+        uint32_t less = 0;
+        for (uint32_t j0 = 0; j0 < m; j0 += TILE) {
+            const uint32_t nj = min(TILE, m - j0);
+            __syncthreads();
+            if (threadIdx.x < nj) {
+                const uint32_t cj = few[j0 + threadIdx.x];
+                tile_key[threadIdx.x] = cand_key[cj];
+                tile_v[threadIdx.x] = cand_v[cj];
+            }
+            __syncthreads();
+            if (i < m)
+                for (uint32_t j = 0; j < nj; ++j) less += (tile_key[j] < k) | ((tile_key[j] == k) & (tile_v[j] < v));
+        }
+        if (i < m && less == r - 1) { found_key = k; found_v = v; }
+    }
+    __syncthreads();
+    const uint64_t tk = found_key;
+    const uint32_t tv = found_v;
+    for (uint32_t i = threadIdx.x; i < m; i += SAMP_NT) {
+        const uint32_t c = few[i], v = cand_v[c];
+        const uint64_t k = cand_key[c];
+        if ((v >> 6) < wbeg || (v >> 6) >= wend || k > tk || (k == tk && v > tv)) continue;
+        atomicOr((unsigned long long *)&bitmap[v >> 6], 1ull << (v & 63));
+        ++cnt;
+    }
+    cnt = block_sum<uint32_t, SAMP_NT>(cnt, lds);
+    if (threadIdx.x == 0) wg_count[blockIdx.x] = cnt;
 }
 
 // The same from the stored key prefixes.  A wavefront takes eight bitmap words (512 vertices) per round: lane l
@@ -804,18 +909,14 @@ static int sampler_launches(sgnn_ctx *ctx, uint64_t N, uint32_t B, uint64_t seed
         (unsigned)std::min<uint64_t>(cdiv(W, 8), std::min<uint64_t>(std::max<uint64_t>(256, N >> 11), EMIT_MAX_WG));
     const uint64_t wpw = (uint64_t)cdiv(cdiv(W, egrid), 8) * 8;
     if (win.on) {
-        // one pass over the keys; the collect pass leaves at once and the emit pass only counts unless the threshold's
-        // bin missed the window
-        SAMP_LAUNCH("sampler_hist_window_kernel", sampler_hist_window_kernel, dim3(grid), dim3(SCAN_NT), N, seed, step, hist, win.b_lo, win.b_hi,
-                    state, cand_key, cand_v, cap, status, bitmap, W);
-        SAMP_LAUNCH("sampler_collect_kernel", sampler_collect_kernel<false>, dim3(grid), dim3(SCAN_NT), N, B, seed, step,
-                    (const uint32_t *)hist, state, cand_key, cand_v, cap, status, (const uint32_t *)nullptr, 1, win.b_lo, win.b_hi);
-        SAMP_LAUNCH("sampler_threshold_kernel", sampler_threshold_kernel, dim3(1), dim3(1024), state, hist, (const uint64_t *)cand_key,
-                    (const uint32_t *)cand_v, cap);
-        SAMP_LAUNCH("sampler_mark_kernel", sampler_mark_kernel, dim3(64), dim3(SAMP_NT), (const sampler_state *)state,
-                    (const uint64_t *)cand_key, (const uint32_t *)cand_v, bitmap);
-        SAMP_LAUNCH("sampler_emit_kernel", sampler_emit_kernel<false>, dim3(egrid), dim3(SAMP_NT), N, seed, step, state, bitmap, W, wpw,
-                    wg_count, 1, thr_src{});
+        // one pass over the keys; the array of ranks, which the last pass writes, holds the list `few` until then
+        const unsigned wgrid = (unsigned)std::min<uint64_t>(cdiv(J, SCAN_NT), WIN_MAX_WG);
+        SAMP_LAUNCH("sampler_hist_window_kernel", sampler_hist_window_kernel, dim3(wgrid), dim3(SCAN_NT), N, seed, step, hist, wg_count, win.b_lo,
+                    win.b_hi, state, cand_key, cand_v, cap, status, bitmap, W);
+        SAMP_LAUNCH("sampler_mark_kernel", sampler_mark_kernel, dim3(64), dim3(SCAN_NT), N, B, seed, step, state, (const uint32_t *)hist,
+                    (const uint32_t *)wg_count, wgrid, win.b_lo, cand_key, cand_v, cap, bitmap, rank, (uint32_t)W, status);
+        SAMP_LAUNCH("sampler_count_kernel", sampler_count_kernel, dim3(egrid), dim3(SAMP_NT), N, seed, step, (const sampler_state *)state, hist,
+                    (const uint64_t *)cand_key, (const uint32_t *)cand_v, (const uint32_t *)rank, (uint32_t)W, bitmap, W, wpw, wg_count);
         SAMP_LAUNCH("sampler_rank_kernel", wpw * 4 <= SAMP_NT ? sampler_rank_kernel<4> : sampler_rank_kernel<1>, dim3(egrid), dim3(SAMP_NT), bitmap, W, wpw, wg_count, B, rank, S,
                     status, &state->ncand);
         return SGNN_OK;
@@ -826,21 +927,21 @@ static int sampler_launches(sgnn_ctx *ctx, uint64_t N, uint32_t B, uint64_t seed
     SAMP_LAUNCH("sampler_hist_kernel", sampler_hist_kernel, dim3(hgrid), dim3(SCAN_NT), N, seed, step, hist, prefix, state);
     if (prefix)
         SAMP_LAUNCH("sampler_collect_kernel", sampler_collect_kernel<true>, dim3(grid), dim3(SCAN_NT), N, B, seed, step,
-                    (const uint32_t *)hist, state, cand_key, cand_v, cap, status, (const uint32_t *)prefix, 0, 0u, 0u);
+                    (const uint32_t *)hist, state, cand_key, cand_v, cap, status, (const uint32_t *)prefix);
     else
         SAMP_LAUNCH("sampler_collect_kernel", sampler_collect_kernel<false>, dim3(grid), dim3(SCAN_NT), N, B, seed, step,
-                    (const uint32_t *)hist, state, cand_key, cand_v, cap, status, (const uint32_t *)nullptr, 0, 0u, 0u);
+                    (const uint32_t *)hist, state, cand_key, cand_v, cap, status, (const uint32_t *)nullptr);
     const bool fused = N <= FUSED_THR_MAX_N;
     const thr_src src = {cand_key, cand_v, hist, cap};
     if (!fused)
-        SAMP_LAUNCH("sampler_threshold_kernel", sampler_threshold_kernel, dim3(1), dim3(1024), state, hist, (const uint64_t *)cand_key,
+        SAMP_LAUNCH("sampler_threshold_kernel", sampler_threshold_kernel, dim3(1), dim3(SCAN_NT), state, hist, (const uint64_t *)cand_key,
                     (const uint32_t *)cand_v, cap);
     if (prefix)
         SAMP_LAUNCH("sampler_emit_kernel", fused ? sampler_emit_prefix_kernel<true> : sampler_emit_prefix_kernel<false>, dim3(egrid),
                     dim3(SAMP_NT), N, seed, step, state, bitmap, W, wpw, wg_count, (const uint32_t *)prefix, src);
     else
         SAMP_LAUNCH("sampler_emit_kernel", fused ? sampler_emit_kernel<true> : sampler_emit_kernel<false>, dim3(egrid), dim3(SAMP_NT), N,
-                    seed, step, state, bitmap, W, wpw, wg_count, 0, src);
+                    seed, step, state, bitmap, W, wpw, wg_count, src);
     SAMP_LAUNCH("sampler_rank_kernel", wpw * 4 <= SAMP_NT ? sampler_rank_kernel<4> : sampler_rank_kernel<1>, dim3(egrid), dim3(SAMP_NT), bitmap, W, wpw, wg_count, B, rank, S,
                 status, &state->ncand);
     return SGNN_OK;

@@ -33,3 +33,15 @@ def test_threshold_in_the_emit_pass(N, B):
         assert np.array_equal(S.cpu().numpy(), S_ref)
         words, rk = bitmap_rank_from_sample(N, S_ref)
         assert np.array_equal(bitmap.cpu().numpy(), words) and np.array_equal(rank.cpu().numpy(), rk)
+
+
+# one pass over the keys: a window of one bin and of two, the first and the last vertices, a ragged last word, several tiles of candidates in the
+# threshold's part (the largest)
+@pytest.mark.parametrize("N,B", [(1048576 + 63, 1), (1048576, 262144 // 2048), (8388607, 131072), (8388607, 4096 * 17), (100000007, 1000000)])
+def test_sparse_sample_in_one_pass_over_the_keys(N, B):
+    for step in (3, 4):
+        S, bitmap, rank = gpu_sample(N, B, 12, step)
+        S_ref = oracle.sample_uniform(N, B, 12, step)
+        assert np.array_equal(S.cpu().numpy(), S_ref)
+        words, rk = bitmap_rank_from_sample(N, S_ref)
+        assert np.array_equal(bitmap.cpu().numpy(), words) and np.array_equal(rank.cpu().numpy(), rk)
