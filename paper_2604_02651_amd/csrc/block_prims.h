@@ -63,16 +63,15 @@ template <class T, int NT> __device__ __forceinline__ T block_sum(T x, T *lds)
 }
 
 // exp(x) for x <= 0 to about 2 ulp with one hardware exponential: 2^(x log2 e), the rounding error of that product
-// (and the low part of log2 e) carried as a first-order correction.  The library expf costs some forty instructions:
+// (x - t ln 2, with ln 2 in two parts) carried as a first-order correction.  The library expf costs some forty instructions:
 // a softmax over 172 classes of a million rows is then bound by them, not by memory.
 __device__ __forceinline__ float exp_neg(float x)
 {
-    const float l2e_hi = 1.44269502162933349609375f, l2e_lo = 1.925963033500011e-8f;
-    const float t = x * l2e_hi;
-    float r = fmaf(x, l2e_hi, -t);
-    r = fmaf(x, l2e_lo, r);
+    const float ln2_hi = 0.693147182464599609375f, ln2_lo = -1.90465429995776804e-9f;
+    const float t = x * 1.44269502162933349609375f;
+    const float r = fmaf(t, -ln2_lo, fmaf(t, -ln2_hi, x));
     const float e = __builtin_amdgcn_exp2f(t);        // 0 below 2^-126: such a probability is 0 in fp32 anyway
-    return fmaf(e, r * 0.693147182464599609375f, e);
+    return fmaf(e, r, e);
 }
 
 // log(s) for s >= 1 with the hardware logarithm (1 ulp of log2 s)

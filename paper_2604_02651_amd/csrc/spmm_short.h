@@ -53,10 +53,21 @@ enum { SHORT_PLAIN, SHORT_MASK, SHORT_ADD, SHORT_BIAS, SHORT_XENT };      // wha
 template <int G, bool MAX> __device__ __forceinline__ float lanes_reduce(float x)
 {
     auto op = [](float a, float b) { return MAX ? fmaxf(a, b) : a + b; };
-    x = op(x, dpp_f32<0xB1>(x));                              // quad_perm [1, 0, 3, 2]
-    x = op(x, dpp_f32<0x4E>(x));                              // quad_perm [2, 3, 0, 1]
-    x = op(x, dpp_f32<0x141>(x));                             // row_half_mirror
-    if constexpr (G >= 16) x = op(x, dpp_f32<0x140>(x));      // row_mirror
+    if constexpr (MAX) {
+        // in assembler: fmaxf makes its operands canonical first, four instructions a step.  (Two wait states lie between
+        // a register's write and its read by another lane; the lanes of a group are active together.)
+#define SGNN_MAX_STEP(CTRL) asm("s_nop 1\n\tv_max_f32_dpp %0, %1, %1 " CTRL " row_mask:0xf bank_mask:0xf" : "=v"(x) : "v"(x))
+        SGNN_MAX_STEP("quad_perm:[1,0,3,2]");
+        SGNN_MAX_STEP("quad_perm:[2,3,0,1]");
+        SGNN_MAX_STEP("row_half_mirror");
+        if constexpr (G >= 16) SGNN_MAX_STEP("row_mirror");
+#undef SGNN_MAX_STEP
+    } else {
+        x += dpp_f32<0xB1>(x);                              // quad_perm [1, 0, 3, 2]
+        x += dpp_f32<0x4E>(x);                              // quad_perm [2, 3, 0, 1]
+        x += dpp_f32<0x141>(x);                             // row_half_mirror
+        if constexpr (G >= 16) x += dpp_f32<0x140>(x);      // row_mirror
+    }
     if constexpr (G >= 32) {
         uint32_t u = __builtin_bit_cast(uint32_t, x), w = u;
         asm("" : "+v"(w));
@@ -101,31 +112,62 @@ __device__ __forceinline__ void row_offsets(const spmm_panel_args &a, uint64_t i
     x = min(x, y);
 }
 
-// The lane's columns, from element `elem` on, 16 bytes at a time at any alignment (gfx950 global stores take it).  At the right edge the
+// A lane's VEC values of a row of X: 16 bytes, or 12, from an address that is a multiple of the element size only
+template <int DWORDS> struct __attribute__((packed, aligned(2))) short_chunk { uint32_t q[DWORDS]; };
+
+template <typename XT> __device__ __forceinline__ float chunk_get(uint32_t w, int i)
+{
+    if constexpr (sizeof(XT) == 4) return __builtin_bit_cast(float, w);
+    else return __builtin_bit_cast(float, (i & 1) ? (w & 0xffff0000u) : (w << 16));
+}
+
+// Two values rounded to nearest even, in one instruction
+__device__ __forceinline__ uint32_t bf16_pair(float a, float b)
+{
+    typedef float f32x2 __attribute__((ext_vector_type(2)));
+    typedef __bf16 bf16x2 __attribute__((ext_vector_type(2)));
+    const f32x2 v = {a, b};
+    return __builtin_bit_cast(uint32_t, __builtin_convertvector(v, bf16x2));
+}
+
+// The lane's columns, from element `elem` on, up to 16 bytes at a time at any alignment (gfx950 global stores take it).  At the right edge the
 // first of them are the lane's before as well: both write the same bytes.
+template <int VEC> __device__ __forceinline__ void short_store_bf16(float *out, int64_t elem, const uint32_t (&w)[VEC / 2])
+{
+    short_chunk<VEC / 2> c;
+#pragma unroll
+    for (int i = 0; i < VEC / 2; ++i) c.q[i] = w[i];
+    *reinterpret_cast<short_chunk<VEC / 2> *>(reinterpret_cast<uint16_t *>(out) + elem) = c;
+}
 template <int VEC> __device__ __forceinline__ void short_store(float *out, int64_t elem, const float (&v)[VEC], int out_bf16)
 {
     typedef float f32x4_any __attribute__((ext_vector_type(4), aligned(4)));
-    typedef uint32_t u32x2_any __attribute__((ext_vector_type(2), aligned(2)));
+    typedef float f32x2_any __attribute__((ext_vector_type(2), aligned(4)));
     if (out_bf16) {
         uint32_t w[VEC / 2];
 #pragma unroll
-        for (int i = 0; i < VEC / 2; ++i)
-            w[i] = (uint32_t)__builtin_bit_cast(uint16_t, (__bf16)v[2 * i]) | (uint32_t)__builtin_bit_cast(uint16_t, (__bf16)v[2 * i + 1]) << 16;
-        uint16_t *p = reinterpret_cast<uint16_t *>(out) + elem;
-        if constexpr (VEC == 8) { const u32x4_any q = {w[0], w[1], w[2], w[3]}; *reinterpret_cast<u32x4_any *>(p) = q; }
-        else { const u32x2_any q = {w[0], w[1]}; *reinterpret_cast<u32x2_any *>(p) = q; }
+        for (int i = 0; i < VEC / 2; ++i) w[i] = bf16_pair(v[2 * i], v[2 * i + 1]);
+        short_store_bf16<VEC>(out, elem, w);
     } else {
 #pragma unroll
-        for (int h = 0; h < VEC; h += 4) { const f32x4_any q = {v[h], v[h + 1], v[h + 2], v[h + 3]}; *reinterpret_cast<f32x4_any *>(out + elem + h) = q; }
+        for (int h = 0; h + 4 <= VEC; h += 4) { const f32x4_any q = {v[h], v[h + 1], v[h + 2], v[h + 3]}; *reinterpret_cast<f32x4_any *>(out + elem + h) = q; }
+        if constexpr (VEC % 4) { const f32x2_any q = {v[VEC - 2], v[VEC - 1]}; *reinterpret_cast<f32x2_any *>(out + elem + VEC - 2) = q; }
     }
 }
 
-template <int G, typename XT, bool OFF32, int EPI>
+// r * ld for r < 64 and ld < 2^56: one full product of 32 bits and one of 24, where a 64-bit product takes three of 32, each four times as long as an addition
+__device__ __forceinline__ int64_t row_offset(uint32_t r, int64_t ld)
+{
+    return (int64_t)((uint64_t)r * (uint32_t)ld + ((uint64_t)((r & 63u) * ((uint32_t)((uint64_t)ld >> 32) & 0xffffffu)) << 32));
+}
+
+// VEC: values a lane holds, 16 bytes or (six bfloat16 values, with the loss) 12.
+template <int G, typename XT, bool OFF32, int EPI, int VEC = panel_vec<XT>::VEC>
 __global__ __launch_bounds__(SPMM_NT, 4) void spmm_short_kernel(spmm_panel_args a, const XT *__restrict__ X, spmm_epi ep)
 {
     if (a.mean_limit && a.n_chunks[3] >= a.mean_limit) return;        // the panel kernel's matrix
-    constexpr int VEC = panel_vec<XT>::VEC, NE = 64 / G, W = G * VEC, U = SHORT_U, CAPW = short_window<G>::LEN;
+    constexpr int NE = 64 / G, W = G * VEC, U = SHORT_U, CAPW = short_window<G>::LEN;
+    typedef short_chunk<VEC * (int)sizeof(XT) / 4> chunk;
     constexpr bool XENT = EPI == SHORT_XENT;
     __shared__ uint2 staged[SPMM_NT / 64][CAPW];
     constexpr bool SIDE = EPI == SHORT_MASK || EPI == SHORT_ADD;         // a matrix beside X is read at the rows' ends
@@ -138,7 +180,7 @@ __global__ __launch_bounds__(SPMM_NT, 4) void spmm_short_kernel(spmm_panel_args 
     const int long_len = (int)a.n_chunks[1];
     const int rows_each = short_rows(a.rows, a.n_chunks[3], NE, a.interleave), rows_all = rows_each * NE;
     // (with few pieces all groups share one: then the length of the chain of gathers counts, not the number of wavefronts)
-    const bool shared_rows = short_shares_rows(a.rows, a.n_chunks[3], NE * VEC), shared = shared_rows || n_pieces < SHORT_SHARED;
+    const bool shared_rows = short_shares_rows(a.rows, a.n_chunks[3], NE * panel_vec<XT>::VEC), shared = shared_rows || n_pieces < SHORT_SHARED;
     const uint32_t per_block = shared ? 1 : NE, n_units = n_pieces + (shared_rows ? a.rows : 0);      // pieces, and rows that are shared like them
     // (32 bits: at most 2^24 pieces and 2^31 blocks of two rows.  Scalars are short here: held in 64 bits the loss forms spilled more)
     const uint32_t piece_blocks = (n_units + per_block - 1) / per_block;
@@ -176,7 +218,7 @@ __global__ __launch_bounds__(SPMM_NT, 4) void spmm_short_kernel(spmm_panel_args 
     float loss = 0.f, cs[XENT ? VEC : 1] = {};
     // Loss and gradient of the row of logits in acc: spmm_row_xent with a group of lanes a row.  The columns below `skip` are in
     // the lane before too: they count in the maximum, where that does not matter, and not in the sums.
-    auto xent = [&](int64_t row, int32_t y, auto shared_row) {
+    auto xent = [&](auto elem_of, int32_t y, auto shared_row) {
         constexpr bool SHARED = decltype(shared_row)::value;
         auto add_loss = [&](float t) {
             if constexpr (SHARED) atomicAdd(&fixed[W], (unsigned long long)(long long)llrint((double)t * XENT_FIX_LOSS));
@@ -188,7 +230,7 @@ __global__ __launch_bounds__(SPMM_NT, 4) void spmm_short_kernel(spmm_panel_args 
             acc[i] += bias[k * VEC + i];
             mx = fmaxf(mx, acc[i]);
         }
-        if (ep.write_out && on) short_store<VEC>(a.out, row * a.ldo + colb, acc, 0);
+        if (ep.write_out && on) short_store<VEC>(a.out, elem_of(a.ldo), acc, 0);
         mx = lanes_reduce<G, true>(mx);
         const int rel = y - colb;
         const bool has_y = rel >= skip && rel < VEC;
@@ -204,14 +246,28 @@ __global__ __launch_bounds__(SPMM_NT, 4) void spmm_short_kernel(spmm_panel_args 
         if (has_y) add_loss(lse - (vy - mx));
         if ((uint32_t)y >= (uint32_t)a.d && k == 0) add_loss(mx + lse);
 #pragma unroll
-        for (int i = 0; i < VEC; ++i) {
-            acc[i] = fmaf(acc[i], inv, rel == i ? -1.f : 0.f) * ep.inv_rows;
-            const float stored = ep.dO_bf16 ? (float)(__bf16)acc[i] : acc[i];       // the column sums add what is stored
-            if constexpr (SHARED) {
-                atomicAdd(&fixed[i * G + k], (unsigned long long)(long long)llrint((double)stored * XENT_FIX_CS));
-            } else cs[i] += stored;
+        for (int i = 0; i < VEC; ++i) acc[i] = fmaf(acc[i], inv, rel == i ? -1.f : 0.f) * ep.inv_rows;
+        auto add_columns = [&]() {      // the column sums add what is stored
+#pragma unroll
+            for (int i = 0; i < VEC; ++i) {
+                if constexpr (SHARED) atomicAdd(&fixed[i * G + k], (unsigned long long)(long long)llrint((double)acc[i] * XENT_FIX_CS));
+                else cs[i] += acc[i];
+            }
+        };
+        if (ep.dO_bf16) {
+            uint32_t w[VEC / 2];
+#pragma unroll
+            for (int i = 0; i < VEC / 2; ++i) {
+                w[i] = bf16_pair(acc[2 * i], acc[2 * i + 1]);
+                acc[2 * i] = chunk_get<bf16_bits>(w[i], 0);
+                acc[2 * i + 1] = chunk_get<bf16_bits>(w[i], 1);
+            }
+            if (ep.dO && on) short_store_bf16<VEC>(static_cast<float *>(ep.dO), elem_of(ep.lddo), w);
+            add_columns();
+        } else {
+            if (ep.dO && on) short_store<VEC>(static_cast<float *>(ep.dO), elem_of(ep.lddo), acc, 0);
+            add_columns();
         }
-        if (ep.dO && on) short_store<VEC>(static_cast<float *>(ep.dO), row * ep.lddo + colb, acc, ep.dO_bf16);
     };
     const char *__restrict__ side_base = reinterpret_cast<const char *>(EPI == SHORT_ADD ? ep.add : ep.mask);
     const int64_t side_row = (EPI == SHORT_ADD ? ep.ldadd : ep.ldm) * (int64_t)sizeof(XT);       // below 2^25
@@ -223,7 +279,7 @@ __global__ __launch_bounds__(SPMM_NT, 4) void spmm_short_kernel(spmm_panel_args 
         }
     };
     // the lane's columns of a row that is complete in acc
-    auto store = [&](int64_t row) {
+    auto store = [&](auto elem_of) {
         if constexpr (EPI == SHORT_BIAS) {
 #pragma unroll
             for (int i = 0; i < VEC; ++i) {
@@ -231,7 +287,7 @@ __global__ __launch_bounds__(SPMM_NT, 4) void spmm_short_kernel(spmm_panel_args 
                 if (ep.relu) acc[i] = fmaxf(acc[i], 0.f);
             }
         }
-        short_store<VEC>(a.out, row * a.ldo + colb, acc, ep.out_bf16);
+        short_store<VEC>(a.out, elem_of(a.ldo), acc, ep.out_bf16);
     };
 
     for (uint32_t block = first_block; block < blocks; block += nwaves) {
@@ -306,8 +362,9 @@ __global__ __launch_bounds__(SPMM_NT, 4) void spmm_short_kernel(spmm_panel_args 
         // the group's row r is complete in acc
         auto emit = [&](uint32_t r) {
             if constexpr (SIDE) beside(side[wv][r * 64 + lane]);
-            if constexpr (XENT) xent((int64_t)u0 + gb + r, labels[wv][gb + r], std::false_type{});
-            else store((int64_t)u0 + gb + r);
+            auto elem_of = [&](int64_t ld) { return (int64_t)u0 * ld + row_offset((uint32_t)gb + r, ld) + colb; };
+            if constexpr (XENT) xent(elem_of, labels[wv][gb + r], std::false_type{});
+            else store(elem_of);
 #pragma unroll
             for (int i = 0; i < VEC; ++i) acc[i] = 0.f;
         };
@@ -378,21 +435,22 @@ __global__ __launch_bounds__(SPMM_NT, 4) void spmm_short_kernel(spmm_panel_args 
             __builtin_amdgcn_wave_barrier();
             for (; at < stop; at += U) {
                 uint2 w[U];
-                u32x4_any q[U];
+                chunk q[U];
 #pragma unroll
                 for (int t = 0; t < U; ++t) w[t] = st[min(at + t, stop - 1)];
 #pragma unroll
                 for (int t = 0; t < U; ++t)
                     if (at + t < stop) {
-                        if constexpr (OFF32) q[t] = *reinterpret_cast<const u32x4_any *>(xb + (uint32_t)((w[t].x & ~1u) + col_bytes));
-                        else q[t] = *reinterpret_cast<const u32x4_any *>(xb + ((int64_t)(w[t].x & 0x7fffffffu) * row_bytes + col_bytes));
+                        if constexpr (OFF32) q[t] = *reinterpret_cast<const chunk *>(xb + (uint32_t)((w[t].x & ~1u) + col_bytes));
+                        else q[t] = *reinterpret_cast<const chunk *>(xb + ((int64_t)(w[t].x & 0x7fffffffu) * row_bytes + col_bytes));
                     }
 #pragma unroll
                 for (int t = 0; t < U; ++t)
                     if (at + t < stop) {
-                        asm volatile("" : "+v"(q[t]));      // nothing of the widening moves up in front of the branch
 #pragma unroll
-                        for (int i = 0; i < VEC; ++i) acc[i] = fmaf(__builtin_bit_cast(float, w[t].y), panel_vec<XT>::get(q[t], i), acc[i]);
+                        for (int i = 0; i < VEC * (int)sizeof(XT) / 4; ++i) asm volatile("" : "+v"(q[t].q[i]));      // nothing of the widening moves up in front of the branch
+#pragma unroll
+                        for (int i = 0; i < VEC; ++i) acc[i] = fmaf(__builtin_bit_cast(float, w[t].y), chunk_get<XT>(q[t].q[i * (int)sizeof(XT) / 4], i), acc[i]);
                         if (OFF32 ? (w[t].x & 1u) != 0 : (int32_t)w[t].x < 0) {
                             emit((uint32_t)__builtin_ctz(left));
                             left &= left - 1;
@@ -460,10 +518,11 @@ __global__ __launch_bounds__(SPMM_NT, 4) void spmm_short_kernel(spmm_panel_args 
         if (mine && whole) {
             if constexpr (SIDE) beside(*reinterpret_cast<const u32x4_any *>(side_base + (int64_t)grow * side_row + col_bytes));
             // (the numbering of the pieces goes with the timing of the plan kernel: sums of such rows through the slots)
+            auto elem_of = [&](int64_t ld) { return (int64_t)grow * ld + colb; };
             if constexpr (XENT) {
-                if (u0 < n_pieces) xent(grow, ep.labels[grow], std::true_type{});
-                else xent(grow, ep.labels[grow], std::false_type{});
-            } else store(grow);
+                if (u0 < n_pieces) xent(elem_of, ep.labels[grow], std::true_type{});
+                else xent(elem_of, ep.labels[grow], std::false_type{});
+            } else store(elem_of);
         }
 #pragma unroll
         for (int i = 0; i < VEC; ++i) acc[i] = 0.f;
@@ -578,7 +637,7 @@ template <typename XT> int xent_frame(int64_t d)
 // 1024: 2^20 x 1.27, 172 columns 332 / 331 / 335 / 342, 47 columns 135 / 129 / 135 / 131; 2^18 x 6.4, 47 columns 89 / 88 / 86 / 80, fp32 91 / 83 / 95 / 82.
 inline unsigned spmm_short_xent_grid(const sgnn_csr *A) { return std::min<unsigned>(cdiv(A->rows, 64) + 512u, 2048u); }
 
-template <int G, typename XT>
+template <int G, typename XT, int VEC = panel_vec<XT>::VEC>
 int launch_short_xent_g(sgnn_ctx *ctx, const sgnn_csr *A, const XT *X, const spmm_panel_args &a, const spmm_epi &ep, hipStream_t st)
 {
     char tag[56];
@@ -586,8 +645,8 @@ int launch_short_xent_g(sgnn_ctx *ctx, const sgnn_csr *A, const XT *X, const spm
              ep.dO ? (ep.dO_bf16 ? 2 : 4) : 0);
     const unsigned grid = spmm_short_xent_grid(A);
     const bool off32 = (uint64_t)A->cols * (uint64_t)a.ldx * sizeof(XT) <= 0xffffffffull;
-    if (off32) SGNN_LAUNCH(ctx, st, "spmm_short_kernel", tag, (spmm_short_kernel<G, XT, true, SHORT_XENT>), dim3(grid), dim3(SPMM_NT), 0, st, a, X, ep);
-    else SGNN_LAUNCH(ctx, st, "spmm_short_kernel", tag, (spmm_short_kernel<G, XT, false, SHORT_XENT>), dim3(grid), dim3(SPMM_NT), 0, st, a, X, ep);
+    if (off32) SGNN_LAUNCH(ctx, st, "spmm_short_kernel", tag, (spmm_short_kernel<G, XT, true, SHORT_XENT, VEC>), dim3(grid), dim3(SPMM_NT), 0, st, a, X, ep);
+    else SGNN_LAUNCH(ctx, st, "spmm_short_kernel", tag, (spmm_short_kernel<G, XT, false, SHORT_XENT, VEC>), dim3(grid), dim3(SPMM_NT), 0, st, a, X, ep);
     return SGNN_OK;
 }
 
@@ -600,7 +659,16 @@ int launch_short_xent(sgnn_ctx *ctx, const sgnn_csr *A, const XT *X, int64_t ldx
     if (!panel_args(a, A, ldx, nullptr, d, spmm_short_frame<XT>(d), out, ldo, ep, ws))
         return sgnn_fail(ctx, SGNN_ERR_CAPACITY, "sgnn_spmm_xent: scratch too small (%zu bytes needed): call sgnn_ctx_reserve", ws->off);
     a.panels = a.interleave = 1;
-    if (d <= 8 * VEC) return launch_short_xent_g<8, XT>(ctx, A, X, a, ep, st);
-    if (d <= 16 * VEC) return launch_short_xent_g<16, XT>(ctx, A, X, a, ep, st);
+    const int g = d <= 8 * VEC ? 8 : (d <= 16 * VEC ? 16 : 32);
+    // six values a lane where as many lanes cover the row with them: the epilogue's instructions are per value of a lane, used or not
+    if constexpr (sizeof(XT) == 2) {
+        if (d > 4 * g && d <= 6 * g) {
+            if (g == 8) return launch_short_xent_g<8, XT, 6>(ctx, A, X, a, ep, st);
+            if (g == 16) return launch_short_xent_g<16, XT, 6>(ctx, A, X, a, ep, st);
+            return launch_short_xent_g<32, XT, 6>(ctx, A, X, a, ep, st);
+        }
+    }
+    if (g == 8) return launch_short_xent_g<8, XT>(ctx, A, X, a, ep, st);
+    if (g == 16) return launch_short_xent_g<16, XT>(ctx, A, X, a, ep, st);
     return launch_short_xent_g<32, XT>(ctx, A, X, a, ep, st);
 }

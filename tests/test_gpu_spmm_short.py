@@ -315,6 +315,13 @@ def test_loss_in_the_epilogue(name, x_dtype, d):
         assert torch.equal(loss, first[0]) and torch.equal(db, first[1]) and torch.equal(dO, first[2])
 
 
+# six values a lane: from one column above half of a group's lanes' sixteen bytes to the last that six values cover, and one more
+@pytest.mark.parametrize("name", ["few", "many", "full", "hubs", "few_rows"])
+@pytest.mark.parametrize("d", [33, 46, 48, 49, 65, 95, 96, 97, 129, 131, 191, 192, 193])
+def test_loss_with_six_values_a_lane(name, d):
+    test_loss_in_the_epilogue(name, torch.bfloat16, d)
+
+
 def _products(call, entries):
     """The sparse-product kernels of a call in a context with scratch for so many entries; None where it refuses for want of scratch."""
     c = sg.Context(0)
