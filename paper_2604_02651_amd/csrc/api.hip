@@ -100,7 +100,7 @@ int sgnn_ctx_create(sgnn_ctx **out, int device)
         delete ctx;
         return SGNN_ERR_HIP;
     }
-    ctx->status = reinterpret_cast<uint32_t *>(ctx->persist + PERSIST_BYTES - 256);
+    ctx->status = reinterpret_cast<uint32_t *>(ctx->persist + SGNN_PERSIST_STATUS_OFF);
     sgnn_static_scratch_init(device);     // address of the allocation-free sampler's scratch on this device (failure is
                                           // reported by that entry point itself)
     *out = ctx;

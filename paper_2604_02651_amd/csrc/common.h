@@ -31,11 +31,15 @@ struct sgnn_ctx {
     uint32_t *status;   // device uint32[4]: [0] sticky error bits set by kernels
     uint64_t res_N, res_E;
     uint32_t res_B, res_d;
+    bool xent_dirty;    // a call failed between the kernel that adds to the loss slots and the one that makes them zero again
 };
 
-// Offset in the persistent area of the SpMM chunk counter (uint32, zero between calls).
-#define SGNN_PERSIST_BYTES 32768
-#define SGNN_PERSIST_SPMM_OFF 12288
+// The persistent area: the sampler's histogram and state, the status words at SGNN_PERSIST_STATUS_OFF, and from SGNN_PERSIST_XENT_OFF on the
+// integer sums of the fused loss, 256 rows of up to 512 columns and the loss (zero between calls, as the histogram is).
+#define SGNN_PERSIST_STATUS_OFF (32768 - 256)
+#define SGNN_PERSIST_XENT_OFF 32768
+#define SGNN_PERSIST_XENT_BYTES (256 * 513 * 8)
+#define SGNN_PERSIST_BYTES (SGNN_PERSIST_XENT_OFF + SGNN_PERSIST_XENT_BYTES)
 
 // status bits
 #define SGNN_ST_CAND_OVERFLOW 1u
@@ -188,7 +192,7 @@ int sgnn_launch_copy(sgnn_ctx *ctx, const float *src, float *dst, int64_t n, hip
 // fix (may be null): fix_slots rows of cols + 1 fixed-point sums (64-bit integers; column `cols` holds loss terms) that are
 // added in as well, scaled by cs_unit / loss_unit
 int sgnn_launch_xent_final(sgnn_ctx *ctx, const float *partial, int n, float inv_rows, float *loss, const float *cs_partial, int cols,
-                           float *colsum, const unsigned long long *fix, int fix_slots, double cs_unit, double loss_unit, hipStream_t st);
+                           float *colsum, unsigned long long *fix, int fix_slots, double cs_unit, double loss_unit, hipStream_t st);
 // O = A X + bias, mean softmax cross-entropy of O against labels and its gradient, in one kernel (SGNN_ERR_UNSUPPORTED,
 // nothing launched, for shapes the fused kernels do not take); out may be null (logits not kept)
 int sgnn_launch_spmm_xent(sgnn_ctx *ctx, const sgnn_csr *A, const void *X, int x_bf16, int64_t ldx, int64_t d, const float *bias,

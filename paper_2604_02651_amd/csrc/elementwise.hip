@@ -234,19 +234,26 @@ __global__ __launch_bounds__(256) void xent_kernel(const float *__restrict__ O, 
 __global__ __launch_bounds__(1024) void xent_final_kernel(const float *__restrict__ partial, int n, float invB,
                                                           float *__restrict__ loss, const float *__restrict__ cs_partial,
                                                           int cols, float *__restrict__ colsum,
-                                                          const unsigned long long *__restrict__ fix, int fix_slots, double cs_unit,
+                                                          unsigned long long *__restrict__ fix, int fix_slots, double cs_unit,
                                                           double loss_unit)
 {
+    // the slots of integer sums are zero again when this ends, whichever of the sums are wanted: the next product with a loss adds to them as
+    // they are (a launch that cleared them before every product took 4 to 5 us)
+    auto take = [&](int64_t i) {
+        const long long t = (long long)fix[i];
+        fix[i] = 0;
+        return t;
+    };
     __shared__ float lds[1024];
     __shared__ long long lfix[1024];
     if (blockIdx.x == 0) {
+        long long f = 0;
+        if (fix)
+            for (int k = threadIdx.x; k < fix_slots; k += 1024) f += take((int64_t)k * (cols + 1) + cols);
         if (!loss) return;
         float s = 0.f;
         for (int i = threadIdx.x; i < n; i += 1024) s += partial[i];
         s = block_sum<float, 1024>(s, lds);
-        long long f = 0;
-        if (fix)
-            for (int k = threadIdx.x; k < fix_slots; k += 1024) f += (long long)fix[(int64_t)k * (cols + 1) + cols];
         // integers: the order does not matter (added up by one thread they were half of the kernel: 1024 rows of 8 classes 7.5 us)
         f = block_sum<long long, 1024>(f, lfix);
         if (threadIdx.x == 0) *loss = (s + (float)((double)f * loss_unit)) * invB;
@@ -257,14 +264,19 @@ __global__ __launch_bounds__(1024) void xent_final_kernel(const float *__restric
     const int tx = threadIdx.x & 15, ty = threadIdx.x >> 4;
     const int col = (blockIdx.x - 1) * 16 + tx;
     float s = 0.f;
-    if (col < cols) {
-#pragma unroll 8
-        for (int w = ty; w < n; w += 64) s += cs_partial[(int64_t)w * cols + col];
-    }
-    lds[threadIdx.x] = s;
     long long f = 0;
     if (fix && col < cols)
-        for (int k = ty; k < fix_slots; k += 64) f += (long long)fix[(int64_t)k * (cols + 1) + col];
+        for (int k = ty; k < fix_slots; k += 64) f += take((int64_t)k * (cols + 1) + col);
+    if (!colsum) return;
+    if (col < cols)
+        for (int w = ty; w < n; w += 1024) {          // 16 loads in flight
+            float x[16];
+#pragma unroll
+            for (int u = 0; u < 16; ++u) x[u] = cs_partial[(int64_t)min(w + 64 * u, n - 1) * cols + col];
+#pragma unroll
+            for (int u = 0; u < 16; ++u) s = w + 64 * u < n ? s + x[u] : s;
+        }
+    lds[threadIdx.x] = s;
     lfix[threadIdx.x] = f;
     __syncthreads();
     if (ty == 0 && col < cols) {
@@ -412,16 +424,17 @@ int sgnn_launch_xent(sgnn_ctx *ctx, const float *O, int64_t ldo, const int32_t *
 #undef SGNN_XENT
     if (loss || dO_colsum) {
         SGNN_LAUNCH(ctx, st, "xent_final_kernel", SGNN_TAG, xent_final_kernel, dim3(1 + (dO_colsum ? cdiv(C, 16) : 0)), dim3(1024), 0, st,
-                    partial, (int)nwg, 1.f / (float)B, loss, cs_partial, (int)C, dO_colsum, (const unsigned long long *)nullptr, 0, 0.0, 0.0);
+                    partial, (int)nwg, 1.f / (float)B, loss, cs_partial, (int)C, dO_colsum, (unsigned long long *)nullptr, 0, 0.0, 0.0);
     }
     return SGNN_OK;
 }
 
 int sgnn_launch_xent_final(sgnn_ctx *ctx, const float *partial, int n, float inv_rows, float *loss, const float *cs_partial, int cols,
-                           float *colsum, const unsigned long long *fix, int fix_slots, double cs_unit, double loss_unit, hipStream_t st)
+                           float *colsum, unsigned long long *fix, int fix_slots, double cs_unit, double loss_unit, hipStream_t st)
 {
-    SGNN_LAUNCH(ctx, st, "xent_final_kernel", SGNN_TAG, xent_final_kernel, dim3(1 + ((colsum && cs_partial) ? cdiv(cols, 16) : 0)), dim3(1024),
-                0, st, partial, n, inv_rows, loss, cs_partial, cols, colsum, fix, fix_slots, cs_unit, loss_unit);
+    if (!cs_partial) colsum = nullptr;
+    SGNN_LAUNCH(ctx, st, "xent_final_kernel", SGNN_TAG, xent_final_kernel, dim3(1 + cdiv(cols, 16)), dim3(1024), 0,
+                st, partial, n, inv_rows, loss, cs_partial, cols, colsum, fix, fix_slots, cs_unit, loss_unit);
     return SGNN_OK;
 }
 
@@ -452,6 +465,6 @@ int sgnn_launch_bce(sgnn_ctx *ctx, const float *O, int64_t ldo, const float *Y, 
     SGNN_LAUNCH(ctx, st, "bce_kernel", SGNN_TAG, bce_kernel, dim3(nwg), dim3(256), 0, st, O, ldo, Y, ldy, B, C, inv, dO, lddo, partial);
     if (loss)
         SGNN_LAUNCH(ctx, st, "xent_final_kernel", SGNN_TAG, xent_final_kernel, dim3(1), dim3(1024), 0, st, partial, (int)nwg, inv, loss,
-                    (const float *)nullptr, 0, (float *)nullptr, (const unsigned long long *)nullptr, 0, 0.0, 0.0);
+                    (const float *)nullptr, 0, (float *)nullptr, (unsigned long long *)nullptr, 0, 0.0, 0.0);
     return SGNN_OK;
 }

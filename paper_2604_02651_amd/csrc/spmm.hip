@@ -558,6 +558,25 @@ __global__ __launch_bounds__(256) void spmm_xent_clear_kernel(unsigned long long
     if (i < n) p[i] = 0ull;
 }
 
+// The slots of the loss's integer sums: in the context's persistent area, zero between calls (xent_final_kernel sees to it)
+static_assert(SGNN_PERSIST_XENT_BYTES == XENT_SLOTS * 513 * sizeof(unsigned long long), "slots of up to 512 columns");
+int xent_slots(sgnn_ctx *ctx, unsigned long long **fix, hipStream_t st)
+{
+    *fix = reinterpret_cast<unsigned long long *>(ctx->persist + SGNN_PERSIST_XENT_OFF);
+    constexpr unsigned n = SGNN_PERSIST_XENT_BYTES / sizeof(unsigned long long);
+    if (ctx->xent_dirty) SGNN_LAUNCH(ctx, st, "spmm_xent_clear_kernel", SGNN_TAG, spmm_xent_clear_kernel, dim3(cdiv(n, 256)), dim3(256), 0, st, *fix, n);
+    ctx->xent_dirty = true;
+    return SGNN_OK;
+}
+
+int xent_final(sgnn_ctx *ctx, const spmm_epi &ep, unsigned grid, int d, float *loss, float *colsum, hipStream_t st)
+{
+    const int rc = sgnn_launch_xent_final(ctx, ep.loss_partial, (int)grid, ep.inv_rows, loss, ep.cs_partial, d, colsum, ep.fix, XENT_SLOTS,
+                                          1.0 / XENT_FIX_CS, 1.0 / XENT_FIX_LOSS, st);
+    if (rc == SGNN_OK) ctx->xent_dirty = false;
+    return rc;
+}
+
 int build_plan(sgnn_ctx *ctx, const sgnn_csr *A, void *plan, bool cleared, hipStream_t st)
 {
     const uint32_t max_chunks = spmm_max_chunks(A->rows, A->capacity);
@@ -622,19 +641,15 @@ int launch_vc(sgnn_ctx *ctx, const sgnn_csr *A, const XT *X, int64_t ldx, const 
     if (XENT) {
         ep.loss_partial = ws->get<float>(grid);
         ep.cs_partial = colsum_out ? ws->get<float>((size_t)grid * d) : nullptr;
-        ep.fix = ws->get<unsigned long long>((size_t)XENT_SLOTS * (d + 1));
         if (!ws->ok)
             return sgnn_fail(ctx, SGNN_ERR_CAPACITY, "sgnn_spmm_xent: scratch too small (%zu bytes needed): call sgnn_ctx_reserve", ws->off);
-        const unsigned nfix = (unsigned)(XENT_SLOTS * (d + 1));
-        SGNN_LAUNCH(ctx, st, "spmm_xent_clear_kernel", SGNN_TAG, spmm_xent_clear_kernel, dim3(cdiv(nfix, 256)), dim3(256), 0, st, ep.fix, nfix);
+        const int rc = xent_slots(ctx, &ep.fix, st);
+        if (rc) return rc;
     }
     SGNN_LAUNCH(ctx, st, "spmm_main_kernel", tag, (spmm_main_kernel<VEC, CH, XT, XENT>), dim3(grid),
                 dim3(SPMM_NT), 0, st, A->rows, A->rowptr, A->rowptr_is_i64, A->colidx, A->val, A->capacity, X, ldx, row_index, d,
                 n_piece_waves, pv.n_chunks, max_chunks, pv.desc, pv.ticket, part, out, ldo, ep, rows_per_wave, mean_limit);
-    if (XENT && (loss_out || colsum_out))
-        return sgnn_launch_xent_final(ctx, ep.loss_partial, (int)grid, ep.inv_rows, loss_out, ep.cs_partial, d, colsum_out, ep.fix, XENT_SLOTS,
-                                      1.0 / XENT_FIX_CS, 1.0 / XENT_FIX_LOSS, st);
-    return SGNN_OK;
+    return XENT ? xent_final(ctx, ep, grid, d, loss_out, colsum_out, st) : SGNN_OK;
 }
 
 template <int VEC, typename XT>
@@ -739,10 +754,9 @@ static int launch_short_xent(sgnn_ctx *ctx, const sgnn_csr *A_in, const XT *X, i
     spmm_epi ep = ep_in;
     ws_alloc w2 = *ws;
     if (!A.plan) A.plan = w2.get<uint8_t>(sgnn_csr_plan_bytes(A.rows, A.capacity));
-    const unsigned grid = sgnn_spmm_short_xent_grid(&A), nfix = (unsigned)(XENT_SLOTS * (d + 1));
+    const unsigned grid = sgnn_spmm_short_xent_grid(&A);
     ep.loss_partial = w2.get<float>(grid);
     ep.cs_partial = colsum ? w2.get<float>((size_t)grid * d) : nullptr;
-    ep.fix = w2.get<unsigned long long>(nfix);
     ws_alloc w3 = w2;
     w3.get<float>((size_t)spmm_max_chunks(A.rows, A.capacity) * (size_t)frame);
     if (!w3.ok) return SGNN_ERR_UNSUPPORTED;
@@ -750,11 +764,9 @@ static int launch_short_xent(sgnn_ctx *ctx, const sgnn_csr *A_in, const XT *X, i
         const int rc = build_plan(ctx, A_in, A.plan, false, st);
         if (rc) return rc;
     }
-    SGNN_LAUNCH(ctx, st, "spmm_xent_clear_kernel", SGNN_TAG, spmm_xent_clear_kernel, dim3(cdiv(nfix, 256)), dim3(256), 0, st, ep.fix, nfix);
-    const int rc = sgnn_launch_spmm_short_xent(ctx, &A, X, x16, ldx, (int)d, out, ldo, ep, &w2, st);
-    if (rc || !(loss || colsum)) return rc;
-    return sgnn_launch_xent_final(ctx, ep.loss_partial, (int)grid, ep.inv_rows, loss, ep.cs_partial, (int)d, colsum, ep.fix, XENT_SLOTS,
-                                  1.0 / XENT_FIX_CS, 1.0 / XENT_FIX_LOSS, st);
+    int rc = xent_slots(ctx, &ep.fix, st);
+    if (!rc) rc = sgnn_launch_spmm_short_xent(ctx, &A, X, x16, ldx, (int)d, out, ldo, ep, &w2, st);
+    return rc ? rc : xent_final(ctx, ep, grid, (int)d, loss, colsum, st);
 }
 
 // O = A X + bias with the softmax cross-entropy of O's rows in the epilogue (see spmm_row_xent).  Returns

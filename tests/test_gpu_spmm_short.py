@@ -322,6 +322,52 @@ def test_loss_with_six_values_a_lane(name, d):
     test_loss_in_the_epilogue(name, torch.bfloat16, d)
 
 
+# The integer sums of long rows (both kernels) begin at zero whatever the call before wanted, at another width, and on every replay of a graph
+@pytest.mark.parametrize("d", [47, 172, 300])
+def test_loss_after_other_calls(d):
+    lens = _hubs()
+    n = len(lens)
+    rp, ci, v = _csr(lens, n, 5)
+    A = sg.Csr.from_arrays(n, n, rp, ci, v * np.float32(0.1), DEV, with_plan=True)
+    ctx().reserve(n, len(ci), n, 512, len(ci))
+    sg.sgnn_csr_plan(ctx(), A)
+    y = dev(np.random.default_rng(d).integers(0, d, n).astype(np.int32))
+    x = {w: _operand(n, w, torch.float32, w + 4 - w % 4, w) for w in (d, 64)}
+
+    def call(c, w, loss, dO, db):
+        out = [torch.full((1,), 3.0, device=DEV), torch.empty((n, w + 4 - w % 4), device=DEV)[:, :w], torch.full((w,), 3.0, device=DEV)]
+        sg.sgnn_spmm_xent(c, A, x[w], None, y.clamp(max=w - 1), out[0] if loss else None, out[1] if dO else None, dO_colsum=out[2] if db else None)
+        return out
+
+    def context():
+        c = sg.Context(0)
+        c.reserve(n, len(ci), n, 512, len(ci))
+        return c
+
+    c = context()
+    want = call(c, d, True, True, True)
+    torch.cuda.synchronize()
+    for other in ((d, True, False, False), (d, False, True, True), (64, False, True, False), (64, False, False, False), (d, True, True, True)):
+        call(c, *other)
+        got = call(c, d, True, True, True)
+        assert [torch.equal(g, t) for g, t in zip(got, want)] == [True] * 3, other
+    stream = torch.cuda.Stream()
+    stream.wait_stream(torch.cuda.current_stream())
+    graph = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(graph, stream=stream):
+        got = call(c, d, True, True, True)
+    for _ in range(3):
+        for t in got:
+            t.fill_(3.0)
+        graph.replay()
+        torch.cuda.synchronize()
+        assert all(torch.equal(g, t) for g, t in zip(got, want))
+        again = call(c, d, True, True, True)
+        torch.cuda.synchronize()
+        assert all(torch.equal(g, t) for g, t in zip(again, want))
+    c.close()
+
+
 def _products(call, entries):
     """The sparse-product kernels of a call in a context with scratch for so many entries; None where it refuses for want of scratch."""
     c = sg.Context(0)
