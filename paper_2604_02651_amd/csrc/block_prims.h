@@ -69,7 +69,8 @@ __device__ __forceinline__ float exp_neg(float x)
 {
     const float ln2_hi = 0.693147182464599609375f, ln2_lo = -1.90465429995776804e-9f;
     const float t = x * 1.44269502162933349609375f;
-    const float r = fmaf(t, -ln2_lo, fmaf(t, -ln2_hi, x));
+    // between -1 and 1: where t is infinite the correction is not finite, and e is 0 (a NaN comes through in e)
+    const float r = __builtin_amdgcn_fmed3f(fmaf(t, -ln2_lo, fmaf(t, -ln2_hi, x)), -1.f, 1.f);
     const float e = __builtin_amdgcn_exp2f(t);        // 0 below 2^-126: such a probability is 0 in fp32 anyway
     return fmaf(e, r, e);
 }

@@ -771,7 +771,7 @@ static int launch_short_xent(sgnn_ctx *ctx, const sgnn_csr *A_in, const XT *X, i
 
 // O = A X + bias with the softmax cross-entropy of O's rows in the epilogue (see spmm_row_xent).  Returns
 // SGNN_ERR_UNSUPPORTED without launching anything for widths or alignments the fused kernels are not built for
-// (more than 512 columns, rows that do not allow the vector width the column count asks for): the caller then
+// (more than 512 columns; rows that do not allow the vector width the column count asks for, where the kernel for short rows does not take them): the caller then
 // runs the product and the loss kernel one after the other.
 template <typename XT>
 static int launch_xent_x(sgnn_ctx *ctx, const sgnn_csr *A, const XT *X, int64_t ldx, int64_t d, float *out, int64_t ldo,
@@ -786,11 +786,15 @@ static int launch_xent_x(sgnn_ctx *ctx, const sgnn_csr *A, const XT *X, int64_t 
                fits(ep.dO, ep.lddo, ep.dO_bf16 ? 2 : 4, vec);
     };
     const bool ok4 = ok(4), ok2 = ok(2);
-    if (!(d <= 64 || (d <= 128 && ok2) || (d <= 512 && ok4))) return SGNN_ERR_UNSUPPORTED;
-    if (A->capacity > (uint64_t)SPMM_SHORT) {
+    const bool main_kernel = d <= 64 || (d <= 128 && ok2) || (d <= 512 && ok4);
+    // The kernel for short rows takes any width and alignment.  Where spmm_main_kernel does not and the matrix may have many entries a row, the product by the
+    // panel kernel and then the loss.  us, product and loss / here, bfloat16 95 / 130 / 190 columns: 2^20 x 1.27 370 / 163, 528 / 258, 641 / 269;
+    // 2^18 x 6.4 116 / 97, 201 / 136, 231 / 137; 32768 x 2.9 38 / 27, 42 / 31, 43 / 32.
+    if (A->capacity > (uint64_t)SPMM_SHORT && (main_kernel || !sgnn_spmm_panel_wanted(A, d, sizeof(XT) == 2))) {
         const int rc = launch_short_xent(ctx, A, X, ldx, d, out, ldo, ep, loss, colsum, ws, st);
         if (rc != SGNN_ERR_UNSUPPORTED) return rc;
     }
+    if (!main_kernel) return SGNN_ERR_UNSUPPORTED;
     if (d <= 64) return launch_vc<1, 1, XT, true>(ctx, A, X, ldx, nullptr, (int)d, out, ldo, ep, ws, st, loss, colsum);
     if (d <= 128 && ok2) return launch_vc<2, 1, XT, true>(ctx, A, X, ldx, nullptr, (int)d, out, ldo, ep, ws, st, loss, colsum);
     if (d <= 256 && ok4) return launch_vc<4, 1, XT, true>(ctx, A, X, ldx, nullptr, (int)d, out, ldo, ep, ws, st, loss, colsum);

@@ -236,7 +236,7 @@ struct spmm_epi {
     // A long row is finished by whichever of its piece wavefronts comes last, so its share of the sums cannot go into
     // that wavefront's running sums (the result would depend on the race).  It is added, as 64-bit fixed-point
     // integers, to one of XENT_SLOTS rows of d + 1 counters chosen by the row number: integer addition is exact in
-    // any order, and the final kernel adds the slots up.  [slot][d + 1], column d holds the loss terms.
+    // any order, and the final kernel adds the slots up and leaves zeros.  [slot][d + 1], column d holds the loss terms.
     unsigned long long *fix;
 };
 constexpr int XENT_SLOTS = 256;

@@ -29,6 +29,14 @@
 //   2^20 x 1.27        407 / 325      274 / 211      228 / 132      309 / 270      233 / 152
 //   2^18 x 6.4         204 / 156      146 / 108      129 / 83       149 / 128      128 / 80
 //   32768 x 2.9        54 / 36        33 / 30        29 / 28        37 / 31        29 / 26
+// What bounds it then is the instructions of a row's end (counters: vector unit active 78 % of the time, 117 instructions a row of which the product is 39).
+// Six bfloat16 values a lane where they cover the row, two values rounded at once, a maximum without canonical operands, the correction of the
+// exponential in two products: from one call to the next, the final sum included, before / after, us:
+//                      bf16 256   bf16 172   bf16 100   bf16 70    bf16 47    fp32 100   fp32 47
+//   2^20 x 1.27        338 / 299  330 / 270  211 / 194  203 / 163  134 / 110  283 / 275  158 / 151
+//   2^18 x 6.4         180 / 167  165 / 136  120 / 107  119 / 95   94 / 74    142 / 138  88 / 80
+//   32768 x 2.9        41 / 34    40 / 31    34 / 28    34 / 28    32 / 25    33 / 30    29 / 25
+// Rejected: 16 rows a block for groups of 16 and 32 lanes (2^20 x 172: 277 instead of 289, the products without a loss 2 % slower).
 // The lanes at the right edge store 16 bytes like the others, over columns of their neighbour's; column by column 2^20 x 1.27 with
 // 172 columns took 400.  Three chunks a lane and eight lanes a row (fewer instructions a row, twice the registers): 474, 356 for 2^18 x 6.4.
 // Rejected: rows of up to 64 entries as rows of a group (2^18 x 6.4, 256 bfloat16 columns: 136 -> 145 us, 32768 x 2.9: 18 -> 25, the groups of a
@@ -661,6 +669,7 @@ int launch_short_xent(sgnn_ctx *ctx, const sgnn_csr *A, const XT *X, int64_t ldx
     a.panels = a.interleave = 1;
     const int g = d <= 8 * VEC ? 8 : (d <= 16 * VEC ? 16 : 32);
     // six values a lane where as many lanes cover the row with them: the epilogue's instructions are per value of a lane, used or not
+    // (172 columns: 29 of 32 lanes instead of 22)
     if constexpr (sizeof(XT) == 2) {
         if (d > 4 * g && d <= 6 * g) {
             if (g == 8) return launch_short_xent_g<8, XT, 6>(ctx, A, X, a, ep, st);

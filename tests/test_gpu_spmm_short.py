@@ -322,6 +322,42 @@ def test_loss_with_six_values_a_lane(name, d):
     test_loss_in_the_epilogue(name, torch.bfloat16, d)
 
 
+# widths and strides of no multiple, and a class that a bias takes out of the sums: its share is 0, the rest as without it
+@pytest.mark.parametrize("x_dtype,d,ld", [(torch.float32, 67, 69), (torch.float32, 127, 127), (torch.bfloat16, 95, 97), (torch.bfloat16, 130, 131),
+                                          (torch.bfloat16, 255, 255), (torch.bfloat16, 47, 47)])
+@pytest.mark.parametrize("out", [-np.inf, -3.4e38])
+def test_loss_at_any_stride_and_without_a_class(x_dtype, d, ld, out):
+    lens = _few_pieces()
+    n = len(lens)
+    rp, ci, v = _csr(lens, n, d)
+    v = v * np.float32(0.1)
+    A = sg.Csr.from_arrays(n, n, rp, ci, v, DEV, with_plan=True)
+    ctx().reserve(n, len(ci), n, 256, len(ci))
+    sg.sgnn_csr_plan(ctx(), A)
+    X = _operand(n, d, x_dtype, ld, d)
+    b = torch.zeros(d, device=DEV)
+    b[d // 2] = out
+    y = np.random.default_rng(d).integers(0, d, n).astype(np.int32)
+    y[y == d // 2] = 0
+    O = oracle.spmm(rp, ci, v, _np(X))
+    O[:, d // 2] = -np.inf
+    m = O.max(1, keepdims=True)
+    e = np.exp(O - m)
+    s = e.sum(1, keepdims=True)
+    dO_ref = e / s
+    dO_ref[np.arange(n), y] -= 1
+    dO_ref /= n
+    loss_ref = ((m + np.log(s))[:, 0] - O[np.arange(n), y]).mean()
+    loss, db = torch.zeros(1, device=DEV), torch.empty(d, device=DEV)
+    dO = torch.full((n + 1, ld), 7.0, dtype=x_dtype, device=DEV)
+    sg.sgnn_spmm_xent(ctx(), A, X, b, dev(y), loss, dO[:n, :d], dO_colsum=db)
+    assert torch.all(dO[n] == 7.0) and torch.all(dO[:, d:] == 7.0) and torch.all(dO[:n, d // 2] == 0)
+    got = _np(dO[:n, :d])
+    assert rel_err(got, dO_ref) < (2.0 ** -8 if x_dtype == torch.bfloat16 else TOL_F32)
+    assert np.abs(_np(db) - got.sum(0)).max() < 1e-5 * np.abs(got).sum(0).max()
+    assert abs(loss.item() - loss_ref) < TOL_F32 * abs(loss_ref)
+
+
 # The integer sums of long rows (both kernels) begin at zero whatever the call before wanted, at another width, and on every replay of a graph
 @pytest.mark.parametrize("d", [47, 172, 300])
 def test_loss_after_other_calls(d):
