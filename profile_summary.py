@@ -50,8 +50,8 @@ def short(n: str) -> str:
     m = re.match(r"(spmm_main_kernel)<(\d+), (\d+), .*?(true|false)>", n)
     if m:      # the last template argument: the instantiation with the loss in its epilogue
         return "%s<%s,%s%s>" % (m.group(1), m.group(2), m.group(3), ",xent" if m.group(4) == "true" else "")
-    m = re.match(r"(spmm_short_kernel)<(\d+), .*, (\d+)>", n)
-    if m:      # the last template argument: what happens to a finished row, 4 the loss
+    m = re.match(r"(spmm_short_kernel)<(\d+), .*, (\d+), \d+>", n)
+    if m:      # the last but one template argument: what happens to a finished row, 4 the loss
         return "%s<%s%s>" % (m.group(1), m.group(2), ",xent" if m.group(3) == "4" else "")
     return re.sub(r"<.*>$", "", n)
 
