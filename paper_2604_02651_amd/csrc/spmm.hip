@@ -85,7 +85,7 @@ __device__ __forceinline__ void spmm_row_xent(const float (&v)[CH][VEC], const s
 {
     unsigned long long *fix = SHARED_ROW ? ep.fix + (uint64_t)(row % XENT_SLOTS) * (uint64_t)(d + 1) : nullptr;
     auto add_loss = [&](float t) {
-        if constexpr (SHARED_ROW) atomicAdd(fix + d, (unsigned long long)(long long)llrint((double)t * XENT_FIX_LOSS));
+        if constexpr (SHARED_ROW) xent_add_fixed(fix + d, t, XENT_FIX_LOSS, xs.loss);
         else xs.loss += t;
     };
     // d is a multiple of VEC (the launcher's condition for this instantiation): a lane's VEC columns of a chunk are
@@ -130,7 +130,7 @@ __device__ __forceinline__ void spmm_row_xent(const float (&v)[CH][VEC], const s
                 g[i] = (e[m][i] * inv - (hit ? 1.f : 0.f)) * ep.inv_rows;
                 if (ep.dO_bf16) g[i] = (float)(__bf16)g[i];       // the column sums add what is stored
                 if constexpr (SHARED_ROW) {
-                    if (ep.cs_partial) atomicAdd(fix + col + i, (unsigned long long)(long long)llrint((double)g[i] * XENT_FIX_CS));
+                    if (ep.cs_partial) xent_add_fixed(fix + col + i, g[i], XENT_FIX_CS, xs.cs[m][i]);
                 } else xs.cs[m][i] += g[i];
             }
             if (ep.dO) vstore_out<VEC>(static_cast<float *>(ep.dO), row * ep.lddo + col, g, ep.dO_bf16);

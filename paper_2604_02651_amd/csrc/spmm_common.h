@@ -242,6 +242,13 @@ struct spmm_epi {
 constexpr int XENT_SLOTS = 256;
 constexpr double XENT_FIX_CS = 1152921504606846976.0;      // 2^60: a gradient entry is at most 1 in magnitude, their sum too
 constexpr double XENT_FIX_LOSS = 1073741824.0;             // 2^30: loss terms are below 2^10, at most 2^20 long rows
+// One term of such a sum.  What is no finite number in that range (a NaN or an infinity among the row's logits, a label whose class its
+// logit takes out) has no integer: it goes into the wavefront's own sum, where a NaN or an infinity gives the same result in any order.
+__device__ __forceinline__ void xent_add_fixed(unsigned long long *p, float t, double unit, float &own)
+{
+    if (fabsf(t) < 1048576.f) atomicAdd(p, (unsigned long long)(long long)llrint((double)t * unit));
+    else own += t;
+}
 
 // per-wavefront running sums of the cross-entropy epilogue
 template <int VEC, int CH> struct spmm_xent_sums {

@@ -229,7 +229,7 @@ __global__ __launch_bounds__(SPMM_NT, 4) void spmm_short_kernel(spmm_panel_args 
     auto xent = [&](auto elem_of, int32_t y, auto shared_row) {
         constexpr bool SHARED = decltype(shared_row)::value;
         auto add_loss = [&](float t) {
-            if constexpr (SHARED) atomicAdd(&fixed[W], (unsigned long long)(long long)llrint((double)t * XENT_FIX_LOSS));
+            if constexpr (SHARED) xent_add_fixed(&fixed[W], t, XENT_FIX_LOSS, loss);
             else loss += t;
         };
         float mx = -INFINITY;
@@ -258,7 +258,7 @@ __global__ __launch_bounds__(SPMM_NT, 4) void spmm_short_kernel(spmm_panel_args 
         auto add_columns = [&]() {      // the column sums add what is stored
 #pragma unroll
             for (int i = 0; i < VEC; ++i) {
-                if constexpr (SHARED) atomicAdd(&fixed[i * G + k], (unsigned long long)(long long)llrint((double)acc[i] * XENT_FIX_CS));
+                if constexpr (SHARED) xent_add_fixed(&fixed[i * G + k], acc[i], XENT_FIX_CS, cs[i]);
                 else cs[i] += acc[i];
             }
         };

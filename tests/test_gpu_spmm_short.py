@@ -358,6 +358,40 @@ def test_loss_at_any_stride_and_without_a_class(x_dtype, d, ld, out):
     assert abs(loss.item() - loss_ref) < TOL_F32 * abs(loss_ref)
 
 
+# Long rows add to the sums as integers: what is no finite number comes through all the same (both kernels, every piece length)
+@pytest.mark.parametrize("name,row", [("few", 1500), ("many", 5), ("hubs", 20000)])
+@pytest.mark.parametrize("x_dtype,d,ld", [(torch.float32, 47, 48), (torch.float32, 67, 69), (torch.float32, 300, 300), (torch.bfloat16, 47, 48),
+                                          (torch.bfloat16, 95, 97), (torch.bfloat16, 172, 176)])
+def test_long_row_that_is_not_finite(name, row, x_dtype, d, ld):
+    lens = {**MATRICES, **HUBS}[name]()
+    n = len(lens)
+    rp, ci, v = _csr(lens, n, d)
+    ctx().reserve(n, len(ci), n, 512, len(ci))
+    X = _operand(n, d, x_dtype, ld, d)
+    y = np.random.default_rng(d).integers(0, d - 1, n).astype(np.int32)
+
+    def call(v, y, b):
+        A = sg.Csr.from_arrays(n, n, rp, ci, v, DEV, with_plan=True)
+        sg.sgnn_csr_plan(ctx(), A)
+        loss, db, dO = torch.zeros(1, device=DEV), torch.zeros(d, device=DEV), torch.zeros((n, ld), dtype=x_dtype, device=DEV)[:, :d]
+        sg.sgnn_spmm_xent(ctx(), A, X, b, dev(y), loss, dO, dO_colsum=db)
+        return loss.item(), db, dO
+
+    others = torch.arange(n, device=DEV) != row
+    for bad in (np.nan, np.inf):
+        w = v * np.float32(0.1)
+        w[rp[row] + 1] = bad
+        loss, db, dO = call(w, y, None)
+        assert np.isnan(loss) and torch.isnan(db).all()
+        assert torch.isnan(dO[row]).all() and torch.isfinite(dO[others]).all()
+    # the row's label is a class of logit minus infinity: an infinite loss, a gradient of -1 / n there
+    b, t = torch.zeros(d, device=DEV), y.copy()
+    b[d - 1], t[row] = -np.inf, d - 1
+    loss, db, dO = call(v * np.float32(0.1), t, b)
+    assert loss == np.inf and torch.isfinite(db).all() and torch.isfinite(dO).all()
+    assert abs(db[d - 1].item() * n + 1) < 2.0 ** -8
+
+
 # The integer sums of long rows (both kernels) begin at zero whatever the call before wanted, at another width, and on every replay of a graph
 @pytest.mark.parametrize("d", [47, 172, 300])
 def test_loss_after_other_calls(d):
