@@ -31,7 +31,7 @@ struct sgnn_ctx {
     uint32_t *status;   // device uint32[4]: [0] sticky error bits set by kernels
     uint64_t res_N, res_E;
     uint32_t res_B, res_d;
-    bool xent_dirty;    // a call failed between the kernel that adds to the loss slots and the one that makes them zero again
+    uint32_t not_zero;  // SGNN_ZERO_* areas that a failed call left as they were and could not clear
 };
 
 // The persistent area: the sampler's histogram and state, the status words at SGNN_PERSIST_STATUS_OFF, and from SGNN_PERSIST_XENT_OFF on the
@@ -40,6 +40,9 @@ struct sgnn_ctx {
 #define SGNN_PERSIST_XENT_OFF 32768
 #define SGNN_PERSIST_XENT_BYTES (256 * 513 * 8)
 #define SGNN_PERSIST_BYTES (SGNN_PERSIST_XENT_OFF + SGNN_PERSIST_XENT_BYTES)
+
+// Areas of the persistent memory that are zero between calls: a call adds to them in one kernel and a later one of its kernels leaves zeros.
+#define SGNN_ZERO_XENT 1u
 
 // status bits
 #define SGNN_ST_CAND_OVERFLOW 1u
@@ -187,6 +190,9 @@ int sgnn_launch_sgd(sgnn_ctx *ctx, float *w, const float *g, int64_t n, double l
 int sgnn_launch_adam(sgnn_ctx *ctx, float *w, const float *g, float *m, float *v, int64_t n, double lr, double b1, double b2,
                      double eps, int64_t t, hipStream_t st);
 int sgnn_launch_graph_normalize(sgnn_ctx *ctx, const sgnn_graph *g, int32_t *rowptr32, float *val, hipStream_t st);
+// Around the kernels of a call that use such an area (elementwise.hip); close: rc is theirs, and its result that of the call
+int sgnn_zero_open(sgnn_ctx *ctx, uint32_t area, void *p, size_t bytes, hipStream_t st);
+int sgnn_zero_close(sgnn_ctx *ctx, int rc, uint32_t area, void *p, size_t bytes, hipStream_t st);
 int sgnn_launch_copy(sgnn_ctx *ctx, const float *src, float *dst, int64_t n, hipStream_t st);
 // mean loss and column sums from the per-workgroup partial sums of a loss kernel (n rows of partial sums)
 // fix (may be null): fix_slots rows of cols + 1 fixed-point sums (64-bit integers; column `cols` holds loss terms) that are

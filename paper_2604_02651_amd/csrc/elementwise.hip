@@ -4,6 +4,7 @@
 
 #include "block_prims.h"
 #include <math.h>
+#include <string.h>
 
 #include "common.h"
 
@@ -341,7 +342,45 @@ __global__ __launch_bounds__(256) void adam_kernel(float *__restrict__ w, const 
     w[i] = w[i] - lr * (mi * c1) / (sqrtf(vi * c2) + eps);
 }
 
+__global__ __launch_bounds__(256) void clear_kernel(uint32_t *__restrict__ p, unsigned n)
+{
+    const unsigned i = blockIdx.x * 256 + threadIdx.x;
+    if (i < n) p[i] = 0;
+}
+
+int clear_area(sgnn_ctx *ctx, void *p, size_t bytes, hipStream_t st)
+{
+    const unsigned n = (unsigned)(bytes / 4);
+    SGNN_LAUNCH(ctx, st, "clear_kernel", SGNN_TAG, clear_kernel, dim3(cdiv(n, 256)), dim3(256), 0, st, static_cast<uint32_t *>(p), n);
+    return SGNN_OK;
+}
+
 } // namespace
+
+// A call that fails between its kernels (a launch that does, or one that ran and whose check reports an error that was left by somebody else)
+// clears the area itself: graphs that were captured before and are replayed after it find zeros, as calls do.  If not even
+// that can be launched, the area is marked, and every call clears it first; the mark goes when that was launched, not when it was recorded
+// into a graph, which may be replayed late or never.
+int sgnn_zero_open(sgnn_ctx *ctx, uint32_t area, void *p, size_t bytes, hipStream_t st)
+{
+    if (!(ctx->not_zero & area)) return SGNN_OK;
+    const int rc = clear_area(ctx, p, bytes, st);
+    if (rc) return rc;
+    hipStreamCaptureStatus capture = hipStreamCaptureStatusActive;
+    SGNN_HIP(ctx, hipStreamIsCapturing(st, &capture));
+    if (capture == hipStreamCaptureStatusNone) ctx->not_zero &= ~area;
+    return SGNN_OK;
+}
+
+int sgnn_zero_close(sgnn_ctx *ctx, int rc, uint32_t area, void *p, size_t bytes, hipStream_t st)
+{
+    if (rc == SGNN_OK) return rc;
+    char err[sizeof(ctx->err)];
+    memcpy(err, ctx->err, sizeof(err));          // of the call
+    if (clear_area(ctx, p, bytes, st) != SGNN_OK) ctx->not_zero |= area;
+    memcpy(ctx->err, err, sizeof(err));
+    return rc;
+}
 
 int sgnn_launch_copy(sgnn_ctx *ctx, const float *src, float *dst, int64_t n, hipStream_t st)
 {

@@ -552,29 +552,21 @@ __global__ __launch_bounds__(SPMM_NT) void spmm_main_kernel(uint32_t rows, const
     }
 }
 
-__global__ __launch_bounds__(256) void spmm_xent_clear_kernel(unsigned long long *__restrict__ p, unsigned n)
-{
-    const unsigned i = blockIdx.x * 256 + threadIdx.x;
-    if (i < n) p[i] = 0ull;
-}
-
 // The slots of the loss's integer sums: in the context's persistent area, zero between calls (xent_final_kernel sees to it)
 static_assert(SGNN_PERSIST_XENT_BYTES == XENT_SLOTS * 513 * sizeof(unsigned long long), "slots of up to 512 columns");
 int xent_slots(sgnn_ctx *ctx, unsigned long long **fix, hipStream_t st)
 {
     *fix = reinterpret_cast<unsigned long long *>(ctx->persist + SGNN_PERSIST_XENT_OFF);
-    constexpr unsigned n = SGNN_PERSIST_XENT_BYTES / sizeof(unsigned long long);
-    if (ctx->xent_dirty) SGNN_LAUNCH(ctx, st, "spmm_xent_clear_kernel", SGNN_TAG, spmm_xent_clear_kernel, dim3(cdiv(n, 256)), dim3(256), 0, st, *fix, n);
-    ctx->xent_dirty = true;
-    return SGNN_OK;
+    return sgnn_zero_open(ctx, SGNN_ZERO_XENT, *fix, SGNN_PERSIST_XENT_BYTES, st);
 }
 
-int xent_final(sgnn_ctx *ctx, const spmm_epi &ep, unsigned grid, int d, float *loss, float *colsum, hipStream_t st)
+// rc: of the launch of the product
+int xent_final(sgnn_ctx *ctx, int rc, const spmm_epi &ep, unsigned grid, int d, float *loss, float *colsum, hipStream_t st)
 {
-    const int rc = sgnn_launch_xent_final(ctx, ep.loss_partial, (int)grid, ep.inv_rows, loss, ep.cs_partial, d, colsum, ep.fix, XENT_SLOTS,
-                                          1.0 / XENT_FIX_CS, 1.0 / XENT_FIX_LOSS, st);
-    if (rc == SGNN_OK) ctx->xent_dirty = false;
-    return rc;
+    if (rc == SGNN_OK)
+        rc = sgnn_launch_xent_final(ctx, ep.loss_partial, (int)grid, ep.inv_rows, loss, ep.cs_partial, d, colsum, ep.fix, XENT_SLOTS,
+                                    1.0 / XENT_FIX_CS, 1.0 / XENT_FIX_LOSS, st);
+    return sgnn_zero_close(ctx, rc, SGNN_ZERO_XENT, ep.fix, SGNN_PERSIST_XENT_BYTES, st);
 }
 
 int build_plan(sgnn_ctx *ctx, const sgnn_csr *A, void *plan, bool cleared, hipStream_t st)
@@ -646,10 +638,14 @@ int launch_vc(sgnn_ctx *ctx, const sgnn_csr *A, const XT *X, int64_t ldx, const 
         const int rc = xent_slots(ctx, &ep.fix, st);
         if (rc) return rc;
     }
-    SGNN_LAUNCH(ctx, st, "spmm_main_kernel", tag, (spmm_main_kernel<VEC, CH, XT, XENT>), dim3(grid),
-                dim3(SPMM_NT), 0, st, A->rows, A->rowptr, A->rowptr_is_i64, A->colidx, A->val, A->capacity, X, ldx, row_index, d,
-                n_piece_waves, pv.n_chunks, max_chunks, pv.desc, pv.ticket, part, out, ldo, ep, rows_per_wave, mean_limit);
-    return XENT ? xent_final(ctx, ep, grid, d, loss_out, colsum_out, st) : SGNN_OK;
+    auto product = [&]() -> int {
+        SGNN_LAUNCH(ctx, st, "spmm_main_kernel", tag, (spmm_main_kernel<VEC, CH, XT, XENT>), dim3(grid),
+                    dim3(SPMM_NT), 0, st, A->rows, A->rowptr, A->rowptr_is_i64, A->colidx, A->val, A->capacity, X, ldx, row_index, d,
+                    n_piece_waves, pv.n_chunks, max_chunks, pv.desc, pv.ticket, part, out, ldo, ep, rows_per_wave, mean_limit);
+        return SGNN_OK;
+    };
+    const int rc = product();
+    return XENT ? xent_final(ctx, rc, ep, grid, d, loss_out, colsum_out, st) : rc;
 }
 
 template <int VEC, typename XT>
@@ -765,8 +761,9 @@ static int launch_short_xent(sgnn_ctx *ctx, const sgnn_csr *A_in, const XT *X, i
         if (rc) return rc;
     }
     int rc = xent_slots(ctx, &ep.fix, st);
-    if (!rc) rc = sgnn_launch_spmm_short_xent(ctx, &A, X, x16, ldx, (int)d, out, ldo, ep, &w2, st);
-    return rc ? rc : xent_final(ctx, ep, grid, (int)d, loss, colsum, st);
+    if (rc) return rc;
+    rc = sgnn_launch_spmm_short_xent(ctx, &A, X, x16, ldx, (int)d, out, ldo, ep, &w2, st);
+    return xent_final(ctx, rc, ep, grid, (int)d, loss, colsum, st);
 }
 
 // O = A X + bias with the softmax cross-entropy of O's rows in the epilogue (see spmm_row_xent).  Returns

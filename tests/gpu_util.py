@@ -1,5 +1,8 @@
 """Shared helpers of the GPU parity tests."""
+import ctypes
+
 import numpy as np
+import pytest
 import torch
 
 import oracle
@@ -41,6 +44,14 @@ def dev(a, dtype=None):
     if dtype is not None:
         t = t.to(dtype)
     return t.to(DEV)
+
+
+def fail_next_launch(call):
+    """`call` fails at the first kernel it launches, which runs all the same: the launch's check finds an error that an earlier call of this
+    thread (here one with a device number that no machine has) left behind."""
+    assert ctypes.CDLL("libamdhip64.so.7").hipSetDevice(9999) != 0
+    with pytest.raises(sg.SgnnError):
+        call()
 
 
 def gpu_sample(N, B, seed, step):

@@ -6,7 +6,7 @@ import torch
 
 import oracle
 import paper_2604_02651_amd as sg
-from gpu_util import DEV, TOL_F32, ctx, dev, rel_err
+from gpu_util import DEV, TOL_F32, ctx, dev, fail_next_launch, rel_err
 from test_gpu_spmm_panel import TOL_OUT, _np, _operand
 
 pytestmark = pytest.mark.gpu
@@ -435,6 +435,53 @@ def test_loss_after_other_calls(d):
         again = call(c, d, True, True, True)
         torch.cuda.synchronize()
         assert all(torch.equal(g, t) for g, t in zip(again, want))
+    c.close()
+
+
+# A call that fails behind its product leaves nothing for later ones: a graph captured before it, one captured after it and not replayed yet, a call
+@pytest.mark.parametrize("x_dtype,d", [(torch.float32, 47), (torch.bfloat16, 172), (torch.float32, 300)])
+def test_loss_after_a_call_that_failed(x_dtype, d):
+    lens = _hubs()
+    n = len(lens)
+    rp, ci, v = _csr(lens, n, 5)
+    A = sg.Csr.from_arrays(n, n, rp, ci, v * np.float32(0.1), DEV, with_plan=True)
+    c = sg.Context(0)
+    c.reserve(n, len(ci), n, 512, len(ci))
+    sg.sgnn_csr_plan(c, A)
+    y = dev(np.random.default_rng(d).integers(0, d, n).astype(np.int32))
+    X = _operand(n, d, x_dtype, d + 8 - d % 8, d)
+
+    def call(out=None):
+        out = out or [torch.full((1,), 3.0, device=DEV), torch.empty((n, d + 8 - d % 8), dtype=x_dtype, device=DEV)[:, :d], torch.full((d,), 3.0, device=DEV)]
+        sg.sgnn_spmm_xent(c, A, X, None, y, out[0], out[1], dO_colsum=out[2])
+        return out
+
+    def captured():
+        stream = torch.cuda.Stream()
+        stream.wait_stream(torch.cuda.current_stream())
+        graph = torch.cuda.CUDAGraph()
+        with torch.cuda.graph(graph, stream=stream):
+            out = call()
+        return graph, out
+
+    want = call()
+
+    def check(out):
+        torch.cuda.synchronize()
+        assert all(torch.equal(g, t) for g, t in zip(out, want))
+
+    before, out_before = captured()
+    spare = call()
+    fail_next_launch(lambda: call(spare))
+    before.replay()
+    check(out_before)
+    fail_next_launch(lambda: call(spare))
+    after, out_after = captured()
+    check(call())
+    for _ in range(3):
+        after.replay()
+        check(out_after)
+        check(call())
     c.close()
 
 
