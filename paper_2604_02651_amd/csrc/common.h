@@ -43,6 +43,7 @@ struct sgnn_ctx {
 
 // Areas of the persistent memory that are zero between calls: a call adds to them in one kernel and a later one of its kernels leaves zeros.
 #define SGNN_ZERO_XENT 1u
+#define SGNN_ZERO_SAMPLER 2u
 
 // status bits
 #define SGNN_ST_CAND_OVERFLOW 1u

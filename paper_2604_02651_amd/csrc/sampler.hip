@@ -965,8 +965,11 @@ int sgnn_launch_sampler(sgnn_ctx *ctx, uint64_t N, uint32_t B, uint64_t seed, ui
     if (!ws.ok)
         return sgnn_fail(ctx, SGNN_ERR_CAPACITY, "sgnn_sample_uniform: scratch too small (%zu bytes needed): call sgnn_ctx_reserve",
                          ws.off);
-    return sampler_launches(ctx, N, B, seed, step, S, bitmap, rank, hist, state, cand_key, cand_v, cap, wg_count, ctx->status, prefix, win,
-                            st);
+    // histogram and list are empty between calls, also behind one that failed half way
+    int rc = sgnn_zero_open(ctx, SGNN_ZERO_SAMPLER, ctx->persist, sgnn_sampler_persist_bytes(), st);
+    if (rc) return rc;
+    rc = sampler_launches(ctx, N, B, seed, step, S, bitmap, rank, hist, state, cand_key, cand_v, cap, wg_count, ctx->status, prefix, win, st);
+    return sgnn_zero_close(ctx, rc, SGNN_ZERO_SAMPLER, ctx->persist, sgnn_sampler_persist_bytes(), st);
 }
 
 // ---- the same sampler without any allocation: scratch in a file-scope device array ---------------------

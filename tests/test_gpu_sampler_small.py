@@ -4,7 +4,8 @@ import numpy as np
 import pytest
 
 import oracle
-from gpu_util import bitmap_rank_from_sample, gpu_sample
+import paper_2604_02651_amd as sg
+from gpu_util import bitmap_rank_from_sample, ctx, fail_next_launch, gpu_sample
 
 pytestmark = pytest.mark.gpu
 
@@ -42,6 +43,20 @@ def test_sparse_sample_in_one_pass_over_the_keys(N, B):
     for step in (3, 4):
         S, bitmap, rank = gpu_sample(N, B, 12, step)
         S_ref = oracle.sample_uniform(N, B, 12, step)
+        assert np.array_equal(S.cpu().numpy(), S_ref)
+        words, rk = bitmap_rank_from_sample(N, S_ref)
+        assert np.array_equal(bitmap.cpu().numpy(), words) and np.array_equal(rank.cpu().numpy(), rk)
+
+
+# a call that fails behind its first kernel leaves no keys in the histogram, nor candidates, for the next one: dense samples without and with stored
+# key prefixes, a launch of its own for the threshold, the sparse form
+@pytest.mark.parametrize("N,B", [(20001, 5000), (1048577, 500000), (4194305, 2097152), (1048576 + 63, 100)])
+def test_sample_after_a_call_that_failed(N, B):
+    S_ref = oracle.sample_uniform(N, B, 3, 2)
+    for _ in range(2):
+        S, bitmap, rank = gpu_sample(N, B, 3, 1)
+        fail_next_launch(lambda: sg.sgnn_sample_uniform(ctx(), N, B, 3, 7, S, bitmap, rank))
+        S, bitmap, rank = gpu_sample(N, B, 3, 2)
         assert np.array_equal(S.cpu().numpy(), S_ref)
         words, rk = bitmap_rank_from_sample(N, S_ref)
         assert np.array_equal(bitmap.cpu().numpy(), words) and np.array_equal(rank.cpu().numpy(), rk)
