@@ -9,7 +9,9 @@
 //  - C^T is computed, as in gemm_rows.hip and gemm_bwd.hip: the lane holds 4 columns of a row in 4 registers, two exchanges make that 16
 //    bytes a lane and 64 bytes of 16 rows a store;
 //  - stores outside the matrix are dropped by the bounds of the buffer, so that a wavefront has the same number of loads and stores a slice and the
-//    waits count exactly.
+//    waits count exactly.  Of a row's last chunk of eight columns the wavefront that has it stores four, two and one; where the columns
+//    are four more than a multiple of eight the four alone (with all three, dropped or not, a product with few steps waited for that wavefront:
+//    262144 x 172 x 57 41 us, 33 without; 131072 x 172 x 256 34 and 32).
 // Measured, us (the kernel in gemm.hip / here, TB/s of A and C here), K x N:
 //              256 x 256           256 x 172          256 x 128          128 x 256          256 x 47
 //   2^20       246 / 218 (4.9)     254 / 221 (4.1)    174 / 153 (5.2)    193 / 160 (5.0)    180 / 174 (3.6)
@@ -88,7 +90,8 @@ __global__ __launch_bounds__(64 * NT, 2) void gemm_skinny_bf16_kernel(tall_args 
     for (int st = 0; st < STEPS; ++st) b_load(st, x[st]);
     const float bias_n = (a.bias ? a.bias : a.B)[nc];
     asm volatile("" ::: "memory");          // B first: its loads would wait behind those of the slices
-    const bool ragged = a.N % 8 != 0 && wave == (a.N - 1) / 32;          // the wavefront with the chunk that is not whole: up to three more stores a row
+    // the wavefront with the chunk that is not whole: one more store a row where half of it exists, else three
+    const int more = a.N % 8 == 0 || wave != (a.N - 1) / 32 ? 0 : (a.N % 8 == 4 ? 1 : 3);
     auto nothing = [&](auto count) {
 #pragma unroll
         for (int t = 0; t < decltype(count)::value; ++t)
@@ -99,7 +102,8 @@ __global__ __launch_bounds__(64 * NT, 2) void gemm_skinny_bf16_kernel(tall_args 
         issue(s);
         asm volatile("" ::: "memory");
         // the loop's pattern, so that its first waits count the same (both counts known at compile time: else the compiler waits for everything)
-        if (ragged) nothing(std::integral_constant<int, 4 * STORES>{});
+        if (more == 3) nothing(std::integral_constant<int, 4 * STORES>{});
+        else if (more) nothing(std::integral_constant<int, 2 * STORES>{});
         else nothing(std::integral_constant<int, STORES>{});
         asm volatile("" ::: "memory");
     }
@@ -120,7 +124,8 @@ __global__ __launch_bounds__(64 * NT, 2) void gemm_skinny_bf16_kernel(tall_args 
     for (int s = 0; s < nslices; ++s) {
         asm volatile("" : "+v"(lane_a));                           // the chunks' addresses are put together in the loop: else a register each
         // slice s has landed (this wavefront's part)
-        if (ragged) STREAM_WAIT_VMCNT((STAGES - 2) * (LOADS + 4 * STORES) < 63 ? (STAGES - 2) * (LOADS + 4 * STORES) : 63);
+        if (more == 3) STREAM_WAIT_VMCNT((STAGES - 2) * (LOADS + 4 * STORES) < 63 ? (STAGES - 2) * (LOADS + 4 * STORES) : 63);
+        else if (more) STREAM_WAIT_VMCNT((STAGES - 2) * (LOADS + 2 * STORES));
         else STREAM_WAIT_VMCNT((STAGES - 2) * (LOADS + STORES));
         asm volatile("" ::: "memory");
         __builtin_amdgcn_s_barrier();                              // everybody's part has; and everybody is through slice s - 1
@@ -178,9 +183,9 @@ __global__ __launch_bounds__(64 * NT, 2) void gemm_skinny_bf16_kernel(tall_args 
             const uint32_t off = row < rows ? (uint32_t)row * (uint32_t)(a.ldc * 2) + 16u * (uint32_t)c_chunk : BEYOND;
             const auto rsrc = __builtin_amdgcn_make_buffer_rsrc(a.C + r0 * a.ldc, 0, 0x7fffffff, 0x00020000);
             __builtin_amdgcn_raw_buffer_store_b128(o[t], rsrc, c_left >= 8 ? off : BEYOND, 0, 0);
-            if (ragged) {
-                const bool part = c_left > 0 && c_left < 8;
-                __builtin_amdgcn_raw_buffer_store_b64(u32x2{o[t][0], o[t][1]}, rsrc, part && (c_left & 4) ? off : BEYOND, 0, 0);
+            const bool part = c_left > 0 && c_left < 8;
+            if (more) __builtin_amdgcn_raw_buffer_store_b64(u32x2{o[t][0], o[t][1]}, rsrc, part && (c_left & 4) ? off : BEYOND, 0, 0);
+            if (more == 3) {
                 __builtin_amdgcn_raw_buffer_store_b32((c_left & 4) ? o[t][2] : o[t][0], rsrc, part && (c_left & 2) ? off + 2 * (c_left & 4) : BEYOND, 0, 0);
                 const uint32_t w = c_left == 7 ? o[t][3] : (c_left == 5 ? o[t][2] : (c_left == 3 ? o[t][1] : o[t][0]));
                 __builtin_amdgcn_raw_buffer_store_b16((u16)w, rsrc, part && (c_left & 1) ? off + 2 * (c_left & 6) : BEYOND, 0, 0);
@@ -220,9 +225,20 @@ int sgnn_launch_gemm_tall(sgnn_ctx *ctx, int64_t M, int64_t N, int64_t K, const 
                          const float *bias, int relu, void *C, int64_t ldc, hipStream_t st)
 {
     constexpr int64_t LD_MAX = 1 << 20;          // offsets within a slice in 32 bits
-    // Up to 64 columns are two wavefronts a workgroup, three of those a compute unit: too little in flight where B and the first slices are half
-    // of the time (K x N, us there / here: 32768 x 256 x 47 12.0 / 13.1, 65536 15.9 / 16.8, 131072 26.1 / 24.4; 2^18 x 64 x 64 17.4 / 18.0, 2^20 47 / 44).
-    if (N <= 64 && (M < 100000 || K <= 64)) return SGNN_ERR_UNSUPPORTED;
+    // Where the kernel of gemm.hip keeps the call.  us there / here, rows x N x K; hot: A from the Infinity Cache, as behind the product that wrote it,
+    // cold: from memory.
+    // Up to 64 columns are two wavefronts a workgroup, three of those a compute unit, and each workgroup reads all of B: few rows, or little of A a row,
+    // and B and the first slices are half of the time.  131072 x 47 x 256 18.6 / 20.0 hot, 26.0 / 23.8 cold, x 64 x 256 17.3 / 19.9, 23.5 / 22.4;
+    // x 47 x 100 12.1 / 13.7, 17.9 / 17.3, 262144 x 47 x 100 20.1 / 19.5, 28.1 / 26.9; up to 32 columns 131072 x 20 x 256 15.6 / 19.2, 20.9 / 21.5,
+    // 262144 26.9 / 30.4, 35.1 / 35.7, 400000 x 20 x 172 4 % and 12 % less here.
+    if (N <= 64 && (K <= 64 || M < (K <= 128 ? 250000 : 100000) || (N <= 32 && K % 4 == 0 && M < 300000))) return SGNN_ERR_UNSUPPORTED;
+    // Whole tiles of 96 and 128 columns, three to five slices a workgroup: 49152 x 128 x 256 14.0 / 14.9, 16.7 / 16.6, 65536 15.0 / 16.2, 19.0 / 18.1,
+    // x 96 x 256 14.0 / 15.8, 18.3 / 17.3; 32768 x 128 x 256 13.5 / 12.3, 15.2 / 13.8, 90000 20.9 / 19.1, 27.7 / 20.6.
+    if (N > 64 && N <= 128 && N % 32 == 0 && K > 128 && M >= 40000 && M < 75000) return SGNN_ERR_UNSUPPORTED;
+    // Up to 64 steps a slice is 4 KB and has hardly anything to multiply between two barriers: 131072 x 172 x 57 17.7 / 20.4, 23.5 / 24.7, x 192 x 57
+    // 17.6 / 20.3, 18.5 / 21.1, 262144 x 96 x 57 18.5 / 21.1, 24.4 / 24.2, 400000 x 65 x 57 26.8 / 30.0, 41.5 / 40.7.  One tile for each wavefront (97 to 128
+    // columns) and more than 192 columns are even or better: 131072 x 100 x 57 13.6 / 13.3, 19.1 / 17.3, 400000 x 256 x 57 12 % and 7 % less here.
+    if (K <= 64 && M >= (N > 128 ? 60000 : 100000) && (N <= 96 || (N > 128 && N <= 192))) return SGNN_ERR_UNSUPPORTED;
     if (M < 4096 || N < 1 || N > 256 || K < 1 || K > 256 || lda % 8 || ldc % 8 || lda < K || ldc < N || lda >= LD_MAX || ldc >= LD_MAX || ldb >= LD_MAX ||
         (reinterpret_cast<uintptr_t>(A) & 15) || (reinterpret_cast<uintptr_t>(C) & 15))
         return SGNN_ERR_UNSUPPORTED;

@@ -14,8 +14,19 @@ SIZES = [(170001, 256, 256), (310017, 172, 100), (262177, 128, 192), (200003, 19
          (100033, 47, 256), (100001, 1, 129), (150007, 33, 193), (262145, 255, 57), (4096, 99, 256), (4127, 70, 1), (9999, 250, 130), (33000, 66, 65)]
 
 
-@pytest.mark.parametrize("M,N,K", SIZES)
-def test_against_float64(M, N, K):
+# rows that end four columns into a chunk of eight (one store there instead of three), in every number of tiles
+ENDS_IN_FOUR = [(33000, 68, 65), (33001, 132, 130), (12345, 100, 256), (40003, 164, 70), (250007, 36, 101), (100003, 20, 129), (33000, 252, 193)]
+# what the kernel of gemm.hip is the better one for: up to 64 columns with few rows or steps, whole tiles of few slices, few steps
+OTHERS = [(99999, 64, 256), (200001, 47, 128), (131072, 20, 172), (65537, 128, 192), (40001, 96, 250), (100001, 70, 57), (60001, 150, 64), (100003, 172, 57)]
+
+
+@pytest.mark.parametrize("M,N,K", OTHERS)
+def test_left_to_the_other_kernel(M, N, K):
+    test_against_float64(M, N, K, False)
+
+
+@pytest.mark.parametrize("M,N,K", SIZES + ENDS_IN_FOUR)
+def test_against_float64(M, N, K, tall=True):
     gen = torch.Generator(device=DEV).manual_seed(M + N + K)
     pad = -K % 8 + 8 * (N % 2)
     A = torch.full((M, K + pad), float("nan"), device=DEV, dtype=torch.bfloat16)
@@ -29,7 +40,7 @@ def test_against_float64(M, N, K):
         sg.sgnn_gemm(ctx(), False, False, A[:, :K], B, bias if use_bias else None, sg.SGNN_BF16_MFMA | (sg.SGNN_RELU if relu else 0), C[:M, :N])
         tags = [r[1] for r in ctx().profile_read()]
         ctx().profile(False)
-        assert any(t.startswith("NN tall") for t in tags)
+        assert any(t.startswith("NN tall") for t in tags) == tall
         for r0 in range(0, M, 1 << 16):
             a = A[r0:min(r0 + (1 << 16), M), :K].double()
             want, scale = a @ B.bfloat16().double(), a.abs() @ B.bfloat16().double().abs() + 8
