@@ -20,6 +20,8 @@
 //   200000      203 / 163  187 / 158   197 / 139  175 / 140   127 / 91  122 / 91     116 / 86  112 / 88     80 / 54  76 / 54
 //   65536       62 / 55  59 / 55       62 / 51  55 / 53       41 / 35  39 / 35       34 / 35  32 / 37       22 / 22  22 / 22
 //   32768       32 / 33  31 / 32       32 / 30  27 / 33       21 / 21  20 / 21       20 / 22  19 / 23       14 / 15  14 / 16
+// B given N x K with K no multiple of 64: 20000 x 256 x 96 19.5 / 17.7, 40000 x 128 x 96 19.6 / 18.2, x 128 x 200 29.4 / 25.7 (22.1, 23.2 and 31.8 with the
+// last steps of B's rows loaded value by value).
 // A slice of 32 rows takes 6.2 us where the matrix pipe is busy 3: the reads of A and of the third part of B from LDS, the splitting, a barrier for
 // every piece.  Results of a slice written one piece later by half of the wavefronts: slower (200000 x 128 x 256 91 -> 103 us).
 #include <algorithm>
@@ -104,17 +106,20 @@ __global__ __launch_bounds__(TALL_NT, 2) void gemm_split_kernel(split_tall_args 
 #pragma unroll
         for (int q = 0; q < 4; ++q) {
             const int k0 = 16 * (st0 + q) + 8 * kh;
-            if (TB && whole) {
-                const float *p = a.B + (int64_t)nc * a.ldb + k0;
-                const f32x4_any lo = *reinterpret_cast<const f32x4_any *>(p), hi = *reinterpret_cast<const f32x4_any *>(p + 4);
+            if (TB) {
+                // past the row's end the four that end with it, put right
+                const float *p = a.B + (int64_t)nc * a.ldb;
 #pragma unroll
-                for (int i = 0; i < 4; ++i) { x[q][i] = lo[i]; x[q][4 + i] = hi[i]; }
+                for (int h = 0; h < 2; ++h) {
+                    const int k = k0 + 4 * h, kc = whole ? k : min(k, K - 4);
+                    f32x4 v = *reinterpret_cast<const f32x4_any *>(p + kc);
+                    if (!whole) v = shifted(v, min(k - kc, 4));
+#pragma unroll
+                    for (int i = 0; i < 4; ++i) x[q][4 * h + i] = v[i];
+                }
             } else {
 #pragma unroll
-                for (int i = 0; i < 8; ++i) {
-                    const int k = whole ? k0 + i : min(k0 + i, K - 1);
-                    x[q][i] = TB ? a.B[(int64_t)nc * a.ldb + k] : a.B[(int64_t)k * a.ldb + nc];
-                }
+                for (int i = 0; i < 8; ++i) x[q][i] = a.B[(int64_t)(whole ? k0 + i : min(k0 + i, K - 1)) * a.ldb + nc];
             }
         }
         if (st0 == 0) {
