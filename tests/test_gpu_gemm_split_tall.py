@@ -11,7 +11,7 @@ pytestmark = pytest.mark.gpu
 
 # (M, N, K): frames of 128 / 192 / 256 steps and of 128 / 256 columns, slices of 64 and 32 rows
 SIZES = [(33000, 256, 256), (32769, 129, 65), (40001, 255, 193), (17000, 200, 200), (36007, 130, 128), (65537, 128, 256), (66001, 65, 67),
-         (70003, 97, 131), (33001, 66, 192), (34000, 254, 254), (16500, 256, 96), (33000, 128, 200), (33000, 96, 68)]
+         (70003, 97, 131), (33001, 66, 192), (34000, 254, 254)]
 
 
 def operand(rows, cols, seed, pad=3, offset=1):
@@ -84,3 +84,10 @@ def test_values_the_split_does_not_hold_for(tb):
     fine = torch.isfinite(ref)
     assert torch.equal(got[torch.isinf(ref)], ref[torch.isinf(ref)])
     assert (got[fine] - ref[fine]).norm() <= 1e-6 * ref[fine].norm()
+
+
+# B given N x K with K no multiple of 64: the ends of its rows; just above one tile a compute unit
+@pytest.mark.parametrize("tb", [False, True])
+@pytest.mark.parametrize("M,N,K", [(16500, 256, 96), (33000, 128, 200), (33000, 96, 68)])
+def test_ends_of_the_rows_of_b(M, N, K, tb):
+    test_against_float64(M, N, K, tb)

@@ -14,19 +14,8 @@ SIZES = [(170001, 256, 256), (310017, 172, 100), (262177, 128, 192), (200003, 19
          (100033, 47, 256), (100001, 1, 129), (150007, 33, 193), (262145, 255, 57), (4096, 99, 256), (4127, 70, 1), (9999, 250, 130), (33000, 66, 65)]
 
 
-# rows that end four columns into a chunk of eight (one store there instead of three), in every number of tiles
-ENDS_IN_FOUR = [(33000, 68, 65), (33001, 132, 130), (12345, 100, 256), (40003, 164, 70), (250007, 36, 101), (100003, 20, 129), (33000, 252, 193)]
-# what the kernel of gemm.hip is the better one for: up to 64 columns with few rows or steps, whole tiles of few slices, few steps
-OTHERS = [(99999, 64, 256), (200001, 47, 128), (131072, 20, 172), (65537, 128, 192), (40001, 96, 250), (100001, 70, 57), (60001, 150, 64), (100003, 172, 57)]
-
-
-@pytest.mark.parametrize("M,N,K", OTHERS)
-def test_left_to_the_other_kernel(M, N, K):
-    test_against_float64(M, N, K, False)
-
-
-@pytest.mark.parametrize("M,N,K", SIZES + ENDS_IN_FOUR)
-def test_against_float64(M, N, K, tall=True):
+@pytest.mark.parametrize("M,N,K", SIZES)
+def test_against_float64(M, N, K):
     gen = torch.Generator(device=DEV).manual_seed(M + N + K)
     pad = -K % 8 + 8 * (N % 2)
     A = torch.full((M, K + pad), float("nan"), device=DEV, dtype=torch.bfloat16)
@@ -40,7 +29,7 @@ def test_against_float64(M, N, K, tall=True):
         sg.sgnn_gemm(ctx(), False, False, A[:, :K], B, bias if use_bias else None, sg.SGNN_BF16_MFMA | (sg.SGNN_RELU if relu else 0), C[:M, :N])
         tags = [r[1] for r in ctx().profile_read()]
         ctx().profile(False)
-        assert any(t.startswith("NN tall") for t in tags) == tall
+        assert any(t.startswith("NN tall") for t in tags)
         for r0 in range(0, M, 1 << 16):
             a = A[r0:min(r0 + (1 << 16), M), :K].double()
             want, scale = a @ B.bfloat16().double(), a.abs() @ B.bfloat16().double().abs() + 8
@@ -61,3 +50,29 @@ def test_result_in_the_place_of_the_operand():
     sg.sgnn_gemm(ctx(), False, False, A, B, None, sg.SGNN_BF16_MFMA, C)
     sg.sgnn_gemm(ctx(), False, False, A, B, None, sg.SGNN_BF16_MFMA, A)
     assert torch.equal(A, C)
+
+
+# rows that end four columns into a chunk of eight (one store there instead of three), in every number of tiles
+@pytest.mark.parametrize("M,N,K", [(33000, 68, 65), (33001, 132, 130), (12345, 100, 256), (40003, 164, 70), (250007, 36, 101), (100003, 20, 129),
+                                   (33000, 252, 193)])
+def test_rows_that_end_in_half_a_chunk(M, N, K):
+    test_against_float64(M, N, K)
+
+
+# what the kernel of gemm.hip is the better one for: up to 64 columns with few rows or steps, whole tiles of few slices, few steps
+@pytest.mark.parametrize("M,N,K", [(99999, 64, 256), (200001, 47, 128), (131072, 20, 172), (65537, 128, 192), (40001, 96, 250), (100001, 70, 57),
+                                   (60001, 150, 64), (100003, 172, 57)])
+def test_left_to_the_other_kernel(M, N, K):
+    gen = torch.Generator(device=DEV).manual_seed(M + N + K)
+    A = torch.randn(M, K + -K % 8, generator=gen, device=DEV).bfloat16()[:, :K]
+    B, bias = torch.randn(K, N, generator=gen, device=DEV), torch.randn(N, generator=gen, device=DEV)
+    C = torch.full((M + 1, N + -N % 8 + 8), 7.0, device=DEV).bfloat16()
+    ctx().profile(True)
+    sg.sgnn_gemm(ctx(), False, False, A, B, bias, sg.SGNN_BF16_MFMA | sg.SGNN_RELU, C[:M, :N])
+    records = ctx().profile_read()
+    ctx().profile(False)
+    assert records and not any(r[1].startswith("NN tall") for r in records)
+    a, b = A.double(), B.bfloat16().double()
+    want = (a @ b + bias.double()).clamp(min=0)
+    assert torch.all((C[:M, :N].double() - want).abs() <= K * 2.0 ** -23 * (a.abs() @ b.abs() + 8) + 2.0 ** -8 * want.abs())
+    assert torch.all(C[M] == 7.0) and torch.all(C[:, N:] == 7.0)
