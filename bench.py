@@ -217,6 +217,10 @@ def measure(args, sg, si, torch, cfg, g, X, labels, weights, use_graph_req: str,
             key = "gemm_kernel<%s,%s,%s>" % (p[1], p[0], p[3])
         elif name == "gemm_split_kernel":
             key = "gemm_split_kernel<%s,%s>" % (tag.split()[1], tag.split()[0])
+        elif name == "gemm_split_tall_kernel":
+            key = "gemm_split_tall_kernel<%s>" % tag.split()[0]
+        elif name == "gemm_skinny_bf16_kernel" and tag.split()[1] == "tall":
+            key = "gemm_tall_kernel"
         elif name == "spmm_main_kernel":
             # the instantiation with the loss in its epilogue (tag: "... dO=<bytes>") is a kernel symbol of its own
             key = name + (tag.split()[2][:-1] + ",xent>" if " dO=" in tag else tag.split()[2])
@@ -225,11 +229,11 @@ def measure(args, sg, si, torch, cfg, g, X, labels, weights, use_graph_req: str,
         gq = groups.setdefault(key, {"calls": 0, "ms": 0.0, "flops": 0.0, "bytes": 0.0})
         gq["calls"] += calls
         gq["ms"] += ms
-        if name in ("gemm_kernel", "gemm_split_kernel"):
+        if name in ("gemm_kernel", "gemm_split_kernel", "gemm_split_tall_kernel"):
             gq["flops"] += gemm_flops(tag) * calls
         elif name in ("gemm_skinny_bf16_kernel", "gemm_rows_kernel"):
             # tall operand streamed once, small operand resident: bound by reading A and writing C.
-            # tag: "NN|NT skinny MxNxK bf16 [a=<bytes>] [c=<bytes>]" (element sizes of the tall operand and of the
+            # tag: "NN|NT skinny|tall MxNxK bf16 [a=<bytes>] [c=<bytes>]" (element sizes of the tall operand and of the
             # result as stored; 4 where not stated)
             p = tag.split()
             m_, n_, k_ = (float(x) for x in p[2].split("x"))

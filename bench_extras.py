@@ -243,7 +243,7 @@ def bench_gemm(cfg, args):
         mask = torch.randn((M, N), device=dev, generator=gen) if masked else None
         recs = _timed(ctx, lambda: sg.sgnn_gemm(ctx, ta, tb, A, Bm, None, flags, Cm, mask=mask), reps)
         us = sum(ms for _, _, _, ms in recs) * 1e3 / reps
-        main_us = sum(ms for n, _, _, ms in recs if n in ("gemm_kernel", "gemm_split_kernel")) * 1e3 / reps
+        main_us = sum(ms for n, _, _, ms in recs if n in ("gemm_kernel", "gemm_split_kernel", "gemm_split_tall_kernel")) * 1e3 / reps
         fl = 2.0 * M * N * K
         byt = 4.0 * (M * K + K * N + M * N * (2 if masked else 1))
         out.append({"product": name, "M": M, "N": N, "K": K, "us": us, "gemm_kernel_us": main_us,

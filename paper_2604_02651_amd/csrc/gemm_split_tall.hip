@@ -64,7 +64,7 @@ template <int FK, int CT> struct split_tall_shape {
 
 // FK: frame of K; CT: tiles of 32 columns, 8 / CT tiles of 32 rows a slice; TB: B is given N x K
 template <int FK, int CT, bool TB>
-__global__ __launch_bounds__(TALL_NT, 2) void gemm_split_kernel(split_tall_args a)
+__global__ __launch_bounds__(TALL_NT, 2) void gemm_split_tall_kernel(split_tall_args a)
 {
     using SH = split_tall_shape<FK, CT>;
     constexpr int BR = SH::BR, PLANE = SH::PLANE, BUF = SH::BUF, NP = FK / PIECE, STEPS = SH::STEPS, W2 = SH::W2, U = BR / 32;
@@ -307,11 +307,11 @@ __global__ __launch_bounds__(TALL_NT, 2) void gemm_split_kernel(split_tall_args 
 template <int FK, int CT, bool TB> int launch_split_tall(sgnn_ctx *ctx, const split_tall_args &a, hipStream_t st)
 {
     constexpr int LDS = split_tall_shape<FK, CT>::LDS;
-    SGNN_HIP(ctx, (sgnn_allow_lds<&gemm_split_kernel<FK, CT, TB>>(ctx, LDS)));
+    SGNN_HIP(ctx, (sgnn_allow_lds<&gemm_split_tall_kernel<FK, CT, TB>>(ctx, LDS)));
     char tag[56];
     snprintf(tag, sizeof(tag), "N%c tall %lldx%dx%d f32 split", TB ? 'T' : 'N', (long long)a.M, a.N, a.K);
     const dim3 grid((unsigned)std::min<int64_t>(cdiv(a.M, split_tall_shape<FK, CT>::BR), 256)), block(TALL_NT);
-    SGNN_LAUNCH(ctx, st, "gemm_split_kernel", tag, (gemm_split_kernel<FK, CT, TB>), grid, block, LDS, st, a);
+    SGNN_LAUNCH(ctx, st, "gemm_split_tall_kernel", tag, (gemm_split_tall_kernel<FK, CT, TB>), grid, block, LDS, st, a);
     return SGNN_OK;
 }
 

@@ -1,6 +1,6 @@
 // The tall-operand product C = act(A B + bias) of a layer's transform with A [M x K] and C [M x N] stored as bfloat16, hundreds of thousands of
-// rows; B [K x N] fp32, rounded to bfloat16, K and N up to 256.  (With a mask, a row gather, fp32 storage or B given N x K: the kernel
-// of the same name in gemm.hip.)
+// rows; B [K x N] fp32, rounded to bfloat16, K and N up to 256.  (With a mask, a row gather, fp32 storage or B given N x K:
+// gemm_skinny_bf16_kernel in gemm.hip.)
 //
 // 128 flop per byte of A and C: a copy with matrix instructions on the way.
 //  - Slices of 32 rows of A go into LDS by direct loads, whole rows at a time, up to seven slices ahead, one barrier a slice;
@@ -44,7 +44,7 @@ template <int FK, int NT> struct tall_shape {
 
 // FK: frame of K; NT: tiles of 32 columns of C, one a wavefront
 template <int FK, int NT>
-__global__ __launch_bounds__(64 * NT, 2) void gemm_skinny_bf16_kernel(tall_args a)
+__global__ __launch_bounds__(64 * NT, 2) void gemm_tall_kernel(tall_args a)
 {
     constexpr int STAGE = tall_shape<FK, NT>::STAGE, STAGES = tall_shape<FK, NT>::STAGES;
     constexpr int CH = FK / 8, WL = STAGE / 1024, LOADS = (WL + NT - 1) / NT, STEPS = FK / 16, STORES = 2;
@@ -198,13 +198,14 @@ __global__ __launch_bounds__(64 * NT, 2) void gemm_skinny_bf16_kernel(tall_args 
 template <int FK, int NT> int launch_tall(sgnn_ctx *ctx, const tall_args &a, hipStream_t st)
 {
     constexpr int lds = tall_shape<FK, NT>::LDS;
-    SGNN_HIP(ctx, (sgnn_allow_lds<&gemm_skinny_bf16_kernel<FK, NT>>(ctx, lds)));
+    SGNN_HIP(ctx, (sgnn_allow_lds<&gemm_tall_kernel<FK, NT>>(ctx, lds)));
     const int64_t slices = cdiv(a.M, 32);
     // a workgroup reads all of B: four slices each (two where a workgroup has two wavefronts only) before there is more than one a compute unit
     const unsigned grid = (unsigned)std::min<int64_t>(slices, std::min<int64_t>(std::max<int64_t>(slices / (NT > 2 ? 4 : 2), 256), 256 * tall_shape<FK, NT>::GROUPS));
     char tag[56];
     snprintf(tag, sizeof(tag), "NN tall %lldx%dx%d bf16 a=2 c=2", (long long)a.M, a.N, a.K);
-    SGNN_LAUNCH(ctx, st, "gemm_skinny_bf16_kernel", tag, (gemm_skinny_bf16_kernel<FK, NT>), dim3(grid), dim3(64 * NT), lds, st, a);
+    // recorded with the other kernel of such products; the tag tells them apart
+    SGNN_LAUNCH(ctx, st, "gemm_skinny_bf16_kernel", tag, (gemm_tall_kernel<FK, NT>), dim3(grid), dim3(64 * NT), lds, st, a);
     return SGNN_OK;
 }
 

@@ -40,9 +40,9 @@ def short(n: str) -> str:
     if m:      # template arguments: are the operands contiguous along the reduction
         return "gemm_split_kernel<%sx%s,%s%s>" % (m.group(1), m.group(2), "N" if m.group(3) == "true" else "T",
                                                   "T" if m.group(4) == "true" else "N")
-    m = re.match(r"gemm_split_kernel<\d+, \d+, (\w+)>", n)
-    if m:      # the form for a tall A: is B given N x K
-        return "gemm_split_kernel<tall,N%s>" % ("T" if m.group(1) == "true" else "N")
+    m = re.match(r"gemm_split_tall_kernel<\d+, \d+, (\w+)>", n)
+    if m:      # is B given N x K
+        return "gemm_split_tall_kernel<N%s>" % ("T" if m.group(1) == "true" else "N")
     if n.startswith("gemm_thin_tn_kernel"):
         return "gemm_kernel<thin32,TN,f32>"
     if n.startswith("gemm_smallk_nt_kernel"):
