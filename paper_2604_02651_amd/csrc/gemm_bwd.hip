@@ -8,7 +8,7 @@
 //  - a workgroup (one a compute unit, eight wavefronts) takes slices w, w + grid, ...: BK rows of X and of D go into LDS by direct
 //    loads, several slices ahead, one barrier a slice, as in gemm_tn.hip;
 //  - C: the whole result in registers, operands by transposing LDS reads, as in gemm_tn.hip; one partial result a workgroup,
-//    added up by the split reduction of gemm.hip;
+//    added up by gemm_reduce.hip;
 //  - G: a wavefront has 32 columns of it and keeps its part of W in registers for the whole kernel, as many of its 16-step pieces
 //    as fit beside C (RS), the others in LDS in operand order (with all of it there the slices would have 32 KB, one in flight).  G^T like gemm_rows.hip: the lane holds 4 columns of a
 //    row in 4 registers, two exchanges make that 16 bytes a lane and 64 bytes of 16 rows a store;

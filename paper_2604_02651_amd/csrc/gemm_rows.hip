@@ -21,17 +21,11 @@
 #include <algorithm>
 #include <type_traits>
 
-#include "common.h"
+#include "gemm_stream.h"
 
 namespace {
 
-typedef float f32x4 __attribute__((ext_vector_type(4)));
-typedef float f32x16 __attribute__((ext_vector_type(16)));
-typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
-typedef uint32_t u32x2 __attribute__((ext_vector_type(2)));
-typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
 typedef uint32_t u32x4_any __attribute__((ext_vector_type(4), aligned(2)));
-typedef unsigned short u16;
 
 constexpr int ROWS_WAVES = 8;
 
@@ -48,11 +42,6 @@ struct rows_args {
 };
 
 template <int NT8, int S> constexpr size_t rows_lds_bytes() { return (size_t)32 * NT8 * (64 * S + 8) * 2 + (size_t)32 * NT8 * 4; }
-
-__device__ __forceinline__ uint32_t pack_bf16(float lo, float hi)
-{
-    return (uint32_t)__builtin_bit_cast(u16, (__bf16)lo) | (uint32_t)__builtin_bit_cast(u16, (__bf16)hi) << 16;
-}
 
 // NT8 tiles of 32 columns of C, S pieces of 64 columns of A; TB: B is given N x K
 template <int NT8, int S, bool TB, bool MASK>

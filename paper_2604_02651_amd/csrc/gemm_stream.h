@@ -1,4 +1,4 @@
-// What the kernels that stream rows of bfloat16 matrices through LDS share.
+// What the kernels that stream rows of bfloat16 matrices share.
 #pragma once
 
 #include "common.h"
@@ -19,7 +19,8 @@ typedef unsigned short u16;
 
 // ds_read_b64_tr_b16: sixteen lanes read 4 rows x 16 columns and each gets the four values of one column.  __restrict__ says that the
 // read is of nothing that a direct load may still be writing (the kernels' own waits see to that); without it the compiler waits for all direct
-// loads, the ones just issued among them, in front of such a read, and nothing is in flight behind the slice being multiplied.
+// loads, the ones just issued among them, in front of such a read, and nothing is in flight behind the slice being multiplied (a layer of
+// 2^20 rows, 256 x 256, of which the product of gemm_tn.hip was a fifth: 1288 -> 1257 us; 2^18 rows 517 -> 509).
 __device__ __forceinline__ uint2 read_tr(const unsigned char *__restrict__ p)
 {
     return __builtin_bit_cast(uint2, __builtin_amdgcn_ds_read_tr16_b64_v4i16((__attribute__((address_space(3))) i16x4 *)(p)));

@@ -16,7 +16,7 @@
 //    LDS in lane order, so the swizzle is in the global address a lane loads from;
 //  - the column sums of B (the bias gradient that rides along) come from the matrix pipe too: one more MFMA per B
 //    tile with an A operand that is 1 in result row 0 and 0 elsewhere;
-//  - every workgroup writes one partial product; they are added in a fixed order by the split reduction of gemm.hip.
+//  - every workgroup writes one partial product; they are added in a fixed order by gemm_reduce.hip.
 // Rows behind the last one of a ragged K repeat it in LDS and are zeroed in registers.  Columns of the frame beyond M or N repeat
 // the row's last chunk: they only feed result rows and columns that are never stored.
 // Measured with the reduction of the partial products (us, ordinary reads and permutes / here): 256 x 256 x 2^20 313 / 289, of which
@@ -24,23 +24,13 @@
 // width was outside the earlier form: 200 x 193 x 56399 183 / 40, 30 x 256 x 300007 565 / 47.
 #include <algorithm>
 
-#include "common.h"
+#include "gemm_stream.h"
 
 namespace {
-
-typedef float f32x16 __attribute__((ext_vector_type(16)));
-typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
-typedef short i16x4 __attribute__((ext_vector_type(4)));
-typedef unsigned short u16;
 
 constexpr int TNS_BK = 32;          // rows of a slice
 constexpr int TNS_STAGES = 4;
 constexpr int TNS_WAVES = 8;
-
-#define TNS_GPTR(p) ((const __attribute__((address_space(1))) void *)(p))
-#define TNS_LPTR(p) ((__attribute__((address_space(3))) void *)(p))
-// s_waitcnt vmcnt(n) only (expcnt and lgkmcnt left at their maxima), gfx9 encoding
-#define TNS_WAIT_VMCNT(n) __builtin_amdgcn_s_waitcnt(((n) & 15) | (((n) >> 4) << 14) | 0x0F70)
 
 struct tns_args {
     const u16 *A; int64_t lda;      // [K x M] bfloat16, lda a multiple of 8
@@ -59,15 +49,6 @@ template <int F> struct frame {
 };
 
 template <int FA, int FB> constexpr int tns_stage_bytes() { return frame<FA>::BYTES + frame<FB>::BYTES; }
-
-// The four values along the reduction of the lane's column (see above); p: where the lane reads its 8 bytes.  __restrict__ says that the
-// read is of nothing that a direct load may still be writing (the waits of the loop see to that); without it the compiler waits for all direct loads,
-// the ones just issued among them, in front of the first such read of a slice, and nothing is in flight behind the slice being multiplied
-// (a layer of 2^20 rows, 256 x 256, of which this product is a fifth: 1288 -> 1257 us; 2^18 rows 517 -> 509).
-__device__ __forceinline__ uint2 read_tr(const unsigned char *__restrict__ p)
-{
-    return __builtin_bit_cast(uint2, __builtin_amdgcn_ds_read_tr16_b64_v4i16((__attribute__((address_space(3))) i16x4 *)(p)));
-}
 
 // WM x WN wavefronts share the frame's FA x FB result
 template <int FA, int FB, int WM, int WN>
@@ -106,7 +87,7 @@ __global__ __launch_bounds__(64 * TNS_WAVES) void gemm_tn_stream_kernel(tns_args
         for (int j = 0; j < LOADS; ++j) {
             const int64_t r = k0 + min(row[j], last);
             const unsigned char *g = (of_b[j] ? reinterpret_cast<const unsigned char *>(a.B + r * a.ldb) : reinterpret_cast<const unsigned char *>(a.A + r * a.lda)) + off[j];
-            __builtin_amdgcn_global_load_lds(TNS_GPTR(g), TNS_LPTR(stage + 1024 * min(wave + TNS_WAVES * j, STAGE / 1024 - 1)), 16, 0, 0);
+            __builtin_amdgcn_global_load_lds(STREAM_GPTR(g), STREAM_LPTR(stage + 1024 * min(wave + TNS_WAVES * j, STAGE / 1024 - 1)), 16, 0, 0);
         }
     };
 
@@ -141,7 +122,7 @@ __global__ __launch_bounds__(64 * TNS_WAVES) void gemm_tn_stream_kernel(tns_args
     issue(1);
     issue(2);
     for (int s = 0; s < nslices; ++s) {
-        TNS_WAIT_VMCNT(2 * LOADS);               // slice s has landed (this wavefront's part); s + 1 and s + 2 may be in flight
+        STREAM_WAIT_VMCNT(2 * LOADS);               // slice s has landed (this wavefront's part); s + 1 and s + 2 may be in flight
         asm volatile("" ::: "memory");
         __builtin_amdgcn_s_barrier();            // everybody's part has; and everybody is through slice s - 1
         asm volatile("" ::: "memory");
@@ -183,7 +164,7 @@ __global__ __launch_bounds__(64 * TNS_WAVES) void gemm_tn_stream_kernel(tns_args
             }
         }
     }
-    TNS_WAIT_VMCNT(0);       // the repeated loads past the end are still in flight: nothing may leave before they land
+    STREAM_WAIT_VMCNT(0);       // the repeated loads past the end are still in flight: nothing may leave before they land
 
     // register r of lane (li, kh) of tile (i, j) is row 32 i + 8 (r / 4) + 4 kh + r % 4, column 32 j + li of the wavefront's part
     if (live) {

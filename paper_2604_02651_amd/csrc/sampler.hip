@@ -430,7 +430,7 @@ __global__ __launch_bounds__(SCAN_NT) void sampler_threshold_kernel(sampler_stat
 
 // The threshold at the head of the emit pass: every workgroup selects it for itself, and the first zeroes the histogram for the next call
 // (the rank pass empties the list).  Instead of a launch for one workgroup, whose 2 to 5 us of work and gap the others waited for, every
-// workgroup reads the candidates, up to 2048 of them at this N: with the grids of sampler_launches 2.6 10^5 vertices 24.1 -> 18.2 us the whole sample, 10^6 46 -> 26,
+// workgroup reads the candidates (some 2048 at the largest such N, never more than the list holds): with the grids of sampler_launches 2.6 10^5 vertices 24.1 -> 18.2 us the whole sample, 10^6 46 -> 26,
 // 2.4 10^6 36.1 -> 32.3.
 constexpr uint64_t FUSED_THR_MAX_N = 1ull << 22;
 struct thr_src {
@@ -903,7 +903,7 @@ static int sampler_launches(sgnn_ctx *ctx, uint64_t N, uint32_t B, uint64_t seed
     const unsigned grid =
         (unsigned)std::min<uint64_t>(cdiv(J, SCAN_NT), std::min<uint64_t>(std::max<uint64_t>(256, N >> 19), 2048));
     const uint64_t W = (N + 63) / 64;
-        // a workgroup of the emit pass has a threshold to select before its 2048 vertices or more: 5.2 10^5 vertices by 256 workgroups 21.4 us the
+    // a workgroup of the emit pass has a threshold to select before its 2048 vertices or more: 5.2 10^5 vertices by 256 workgroups 21.4 us the
     // whole sample, by 1024 23.9; 4 10^6 45.1 and 39.6
     const unsigned egrid =
         (unsigned)std::min<uint64_t>(cdiv(W, 8), std::min<uint64_t>(std::max<uint64_t>(256, N >> 11), EMIT_MAX_WG));
