@@ -19,9 +19,10 @@
 //  - every workgroup writes one partial product; they are added in a fixed order by gemm_reduce.hip.
 // Rows behind the last one of a ragged K repeat it in LDS and are zeroed in registers.  Columns of the frame beyond M or N repeat
 // the row's last chunk: they only feed result rows and columns that are never stored.
-// Measured with the reduction of the partial products (us, ordinary reads and permutes / here): 256 x 256 x 2^20 313 / 289, of which
-// the stream is 272 = 3.95 TB/s, what a plain read of 1 GiB reaches on the card; 256 x 47 x 2^18 62 / 46; and where the K or the
-// width was outside the earlier form: 200 x 193 x 56399 183 / 40, 30 x 256 x 300007 565 / 47.
+// Measured with the reduction of the partial products, us: 256 x 256 x 2^20 202 (5.3 TB/s of A and B, the rate of a copy), 256 x 172 179, 128 x 256 149, 256 x 256 x 2^18
+// 69, 256 x 47 36; with three, five stages 203 and 204, 176 and 176, 147 and 149, 69 and 70, 35 and 36.  Before the slices ahead stayed in flight (gemm_stream.h) and the
+// partial products were shared by more wavefronts (gemm_reduce.hip): 242, 217, 179, 78, 45.  With ordinary reads and permutes the first was 313 of then 289.
+// Where the K or the width was outside the earlier form: 200 x 193 x 56399 183 -> 40, 30 x 256 x 300007 565 -> 47.
 #include <algorithm>
 
 #include "gemm_stream.h"

@@ -29,8 +29,9 @@
 //   2^20 x 1.27        407 / 325      274 / 211      228 / 132      309 / 270      233 / 152
 //   2^18 x 6.4         204 / 156      146 / 108      129 / 83       149 / 128      128 / 80
 //   32768 x 2.9        54 / 36        33 / 30        29 / 28        37 / 31        29 / 26
-// What bounds it then is the instructions of a row's end (counters: vector unit active 78 % of the time, 117 instructions a row of which the product is 39).
-// Six bfloat16 values a lane where they cover the row, two values rounded at once, a maximum without canonical operands, the correction of the
+// What bounded it then is the instructions of a row's end (counters, 2^20 x 1.27 with 172 bfloat16 columns: 167 vector instructions a row, of which the product
+// is 48; the vector units busy 89 % of the time).  With the following it has 121, of which the product is 39, and 81 %:
+// six bfloat16 values a lane where they cover the row, two values rounded at once, a maximum without canonical operands, the correction of the
 // exponential in two products: from one call to the next, the final sum included, before / after, us:
 //                      bf16 256   bf16 172   bf16 100   bf16 70    bf16 47    fp32 100   fp32 47
 //   2^20 x 1.27        338 / 299  330 / 270  211 / 194  203 / 163  134 / 110  283 / 275  158 / 151
