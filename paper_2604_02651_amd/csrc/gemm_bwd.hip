@@ -115,14 +115,20 @@ __global__ __launch_bounds__(64 * BWD_WAVES, 2) void gemm_bwd_kernel(bwd_args a)
     const float *w_row = a.W + (int64_t)min(32 * mt + li, a.M - 1) * a.ldw;
     auto w_pieces = [&](int st0, bf16x8 (&v)[4]) {
         float x[4][8];
-        if (st0 + 4 < STEPS || a.N == FB) {          // (a frame is at most 63 columns wider than N)
+        const bool whole = st0 + 4 < STEPS || a.N == FB;          // (a frame is at most 63 columns wider than N)
+        if (whole || a.N >= 4) {
 #pragma unroll
-            for (int q = 0; q < 4; ++q) {
-                const float *p = w_row + 16 * (st0 + q) + 8 * kh;
-                const f32x4_any lo = *reinterpret_cast<const f32x4_any *>(p), hi = *reinterpret_cast<const f32x4_any *>(p + 4);
+            for (int q = 0; q < 4; ++q)
 #pragma unroll
-                for (int i = 0; i < 4; ++i) { x[q][i] = lo[i]; x[q][4 + i] = hi[i]; }
-            }
+                for (int h = 0; h < 2; ++h) {
+                    // past the row's end the four that end with it, put right (32 loads of one value each, eight times the requests in front of everything
+                    // else: 10000 x 192 x 224 48 us, 9000 x 256 x 96 38)
+                    const int c = 16 * (st0 + q) + 8 * kh + 4 * h, cc = whole ? c : min(c, a.N - 4);
+                    f32x4 v = *reinterpret_cast<const f32x4_any *>(w_row + cc);
+                    if (!whole) v = shifted(v, min(c - cc, 4));
+#pragma unroll
+                    for (int i = 0; i < 4; ++i) x[q][4 * h + i] = v[i];
+                }
         } else {
 #pragma unroll
             for (int q = 0; q < 4; ++q)
@@ -375,6 +381,9 @@ int sgnn_launch_gemm_bwd(sgnn_ctx *ctx, int64_t M, int64_t N, int64_t K, const v
     // two products out of the Infinity Cache are faster: 16384 x 128 x 256 38 us there, 44 here, 50000 x 128 x 128 40 / 43, 100 x 200 54 / 62;
     // 100000 x 128 x 256 68 / 67, 131072 x 100 x 200 78 / 78, 128 x 256 76 / 73.
     if (fa == 128 && fb > 64 && K < 110000) return SGNN_ERR_UNSUPPORTED;
+    // Up to 192 columns of X beside more than 192 of D, the frame half empty, and no mask to save: 10000 x 192 x 224 43 us there, 45 here, x 160 x 224 41 / 43, x 192 x 256
+    // 43 / 44.5, 14000 x 192 x 224 44 / 45.6; 16384 x 192 x 224 43.5 / 43.4, 10000 x 224 x 224 45 / 45.5, with a mask 10000 x 192 x 224 45 / 42.
+    if (!mask && fa == 256 && fb == 256 && M <= 192 && K < 16000) return SGNN_ERR_UNSUPPORTED;
     // A workgroup costs its partial result, written and read, and W, and with few slices its pipeline is never full: one for every 256 rows,
     // but 128 of them while that leaves each 128 rows.  us with a workgroup for 128 / 192 / 256 / 384 / 512 rows, M = N = 256: 16384 rows 47 / 49 / 50 / 59 / 64,
     // 24000 56 / 53 / 57 / 63 / 70, 40000 64 / 63 / 63 / 67 / 73, 65536 73 / 72 / 72 / 73 / 76.

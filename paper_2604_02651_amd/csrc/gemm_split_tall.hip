@@ -26,7 +26,7 @@
 // every piece.  Results of a slice written one piece later by half of the wavefronts: slower (200000 x 128 x 256 91 -> 103 us).
 #include <algorithm>
 
-#include "common.h"
+#include "gemm_stream.h"
 
 namespace {
 
@@ -46,14 +46,6 @@ struct split_tall_args {
     int relu;
     float *C; int64_t ldc;
 };
-
-// v moved down by s places, zeros from above
-__device__ __forceinline__ f32x4 shifted(f32x4 v, int s)
-{
-    v = (s & 1) ? f32x4{v[1], v[2], v[3], 0.f} : v;
-    v = (s & 2) ? f32x4{v[2], v[3], 0.f, 0.f} : v;
-    return s >= 4 ? f32x4{0.f, 0.f, 0.f, 0.f} : v;
-}
 
 template <int FK, int CT> struct split_tall_shape {
     static constexpr int BR = 32 * (8 / CT), PLANE = BR * PIECE * 2, BUF = 3 * PLANE;

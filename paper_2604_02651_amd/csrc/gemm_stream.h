@@ -1,4 +1,4 @@
-// What the kernels that stream rows of bfloat16 matrices share.
+// What the kernels that stream the rows of tall matrices share.
 #pragma once
 
 #include "common.h"
@@ -24,6 +24,14 @@ typedef unsigned short u16;
 __device__ __forceinline__ uint2 read_tr(const unsigned char *__restrict__ p)
 {
     return __builtin_bit_cast(uint2, __builtin_amdgcn_ds_read_tr16_b64_v4i16((__attribute__((address_space(3))) i16x4 *)(p)));
+}
+
+// v moved down by s places, zeros from above: four values from within the last four of a row, loaded as the four that end with it
+__device__ __forceinline__ f32x4 shifted(f32x4 v, int s)
+{
+    v = (s & 1) ? f32x4{v[1], v[2], v[3], 0.f} : v;
+    v = (s & 2) ? f32x4{v[2], v[3], 0.f, 0.f} : v;
+    return s >= 4 ? f32x4{0.f, 0.f, 0.f, 0.f} : v;
 }
 
 __device__ __forceinline__ uint32_t pack_bf16(float lo, float hi)

@@ -99,14 +99,16 @@ def backward_kernels(call):
 @pytest.mark.parametrize("K,M,N,xform", [
     (8192, 256, 256, False), (8192, 256, 256, True), (8193, 256, 255, True), (10007, 256, 193, False), (16415, 248, 192, True), (9999, 136, 129, False),
     (12345, 129, 1, False), (8221, 200, 47, True), (9001, 128, 30, False), (8200, 72, 64, True), (8201, 65, 33, False), (110003, 65, 128, False),
-    (110011, 72, 200, False), (110011, 72, 200, True), (110005, 104, 65, False), (110005, 104, 65, True), (110001, 96, 190, True), (110016, 128, 256, False)])
+    (110011, 72, 200, False), (110011, 72, 200, True), (110005, 104, 65, False), (110005, 104, 65, True), (110001, 96, 190, True), (110016, 128, 256, False),
+    (16000, 192, 250, False), (9003, 160, 224, True), (9003, 136, 192, False), (8205, 256, 96, False), (8195, 256, 3, True), (8200, 256, 4, False)])
 def test_one_pass_for_both(K, M, N, xform):
     tags = backward_kernels(lambda: test_both_products(K, M, N, xform))
     assert len(tags) == 1 and tags[0].startswith("bwd %dx%dx%d " % (M, N, K)) and ("mask" in tags[0]) == xform
 
 
 @pytest.mark.parametrize("K,M,N,xform", [
-    (8191, 256, 256, False), (12345, 64, 64, False), (8192, 128, 256, False), (8255, 72, 200, True), (109999, 65, 128, False), (12345, 129, 1, True)])
+    (8191, 256, 256, False), (12345, 64, 64, False), (8192, 128, 256, False), (8255, 72, 200, True), (109999, 65, 128, False), (12345, 129, 1, True),
+    (15999, 192, 193, False)])
 def test_two_products_where_it_does_not_pay_or_fit(K, M, N, xform):
     assert not backward_kernels(lambda: test_both_products(K, M, N, xform))
 
