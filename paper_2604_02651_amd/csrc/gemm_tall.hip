@@ -231,15 +231,27 @@ int sgnn_launch_gemm_tall(sgnn_ctx *ctx, int64_t M, int64_t N, int64_t K, const 
     // Up to 64 columns are two wavefronts a workgroup, three of those a compute unit, and each workgroup reads all of B: few rows, or little of A a row,
     // and B and the first slices are half of the time.  131072 x 47 x 256 18.6 / 20.0 hot, 26.0 / 23.8 cold, x 64 x 256 17.3 / 19.9, 23.5 / 22.4;
     // x 47 x 100 12.1 / 13.7, 17.9 / 17.3, 262144 x 47 x 100 20.1 / 19.5, 28.1 / 26.9; up to 32 columns 131072 x 20 x 256 15.6 / 19.2, 20.9 / 21.5,
-    // 262144 26.9 / 30.4, 35.1 / 35.7, 400000 x 20 x 172 4 % and 12 % less here.
-    if (N <= 64 && (K <= 64 || M < (K <= 128 ? 250000 : 100000) || (N <= 32 && K % 4 == 0 && M < 300000))) return SGNN_ERR_UNSUPPORTED;
-    // Whole tiles of 96 and 128 columns, three to five slices a workgroup: 49152 x 128 x 256 14.0 / 14.9, 16.7 / 16.6, 65536 15.0 / 16.2, 19.0 / 18.1,
-    // x 96 x 256 14.0 / 15.8, 18.3 / 17.3; 32768 x 128 x 256 13.5 / 12.3, 15.2 / 13.8, 90000 20.9 / 19.1, 27.7 / 20.6.
-    if (N > 64 && N <= 128 && N % 32 == 0 && K > 128 && M >= 40000 && M < 75000) return SGNN_ERR_UNSUPPORTED;
+    // 262144 26.9 / 30.4, 35.1 / 35.7, 300000 x 32 x 256 30.5 / 34.1 hot, 131072 x 20 x 150 12.7 / 15.8,
+    // 18 / 18; 400000 x 20 x 172 4 % and 12 % less here, 100001 x 3 x 129 3 % more and 7 % less.
+    if (N <= 64 && (K <= 64 || M < (K <= 128 ? 250000 : 100000) || (N <= 32 && (N > 4 || K >= 160) && M < 350000))) return SGNN_ERR_UNSUPPORTED;
+    // Up to 90 columns and 65 to 128 steps: three tiles of which the last is nearly empty.  180000 x 70 x 96 20.8 / 24.1, 33.4 / 32.5, 262144 x 70 x 128 27.0 / 28.4, 50.4 / 48.4;
+    // 32768 x 70 x 96 even, 600000 x 70 x 128 64.8 / 55.6, 102 / 100.
+    if (N > 64 && N <= 90 && K > 64 && K <= 128 && M >= 40000 && M < 500000) return SGNN_ERR_UNSUPPORTED;
+    // 91 to 128 columns, three to five slices a workgroup: 49152 x 128 x 256 14.0 / 14.9, 16.7 / 16.6, 65536 15.0 / 16.2, 19.0 / 18.1,
+    // x 96 x 256 14.0 / 15.8, 18.3 / 17.3, 65536 x 100 x 256 16.0 / 17.3, 27.9 / 24.4; 32768 x 128 x 256 13.5 / 12.3, 15.2 / 13.8, 90000 20.9 / 19.1, 27.7 / 20.6.
+    if (N > 90 && N <= 128 && K > 128 && M >= 40000 && M < 75000) return SGNN_ERR_UNSUPPORTED;
     // Up to 64 steps a slice is 4 KB and has hardly anything to multiply between two barriers: 131072 x 172 x 57 17.7 / 20.4, 23.5 / 24.7, x 192 x 57
-    // 17.6 / 20.3, 18.5 / 21.1, 262144 x 96 x 57 18.5 / 21.1, 24.4 / 24.2, 400000 x 65 x 57 26.8 / 30.0, 41.5 / 40.7.  One tile for each wavefront (97 to 128
-    // columns) and more than 192 columns are even or better: 131072 x 100 x 57 13.6 / 13.3, 19.1 / 17.3, 400000 x 256 x 57 12 % and 7 % less here.
-    if (K <= 64 && M >= (N > 128 ? 60000 : 100000) && (N <= 96 || (N > 128 && N <= 192))) return SGNN_ERR_UNSUPPORTED;
+    // 17.6 / 20.3, 18.5 / 21.1, 262144 x 96 x 57 18.5 / 21.1, 24.4 / 24.2, 400000 x 65 x 57 26.8 / 30.0, 41.5 / 40.7, 50000 x 160 x 57 11.4 / 13.1, 15.0 / 16.4,
+    // 131072 x 224 x 57 20.8 / 22.3, 25.8 / 28.5.  Small ones, one tile for each wavefront (97 to 128 columns) of more rows, and more than 192 columns of many are even or better:
+    // 16384 x 70 x 57 11.4 / 11.0, 11.4 / 10.0, 131072 x 100 x 57 13.6 / 13.3, 19.1 / 17.3 (65536 11.0 / 11.4, 15.1 / 15.2), 400000 x 224 x 57 even, 256 x 57 12 % and 7 % less here;
+    // and 129 to 192 columns that are no multiple of four up to 60000 rows: 50000 x 130 x 57 9 % and 24 % less.
+    if (K <= 64) {
+        const int64_t from = N <= 96 ? 25000 : (N <= 128 || N > 192 || N % 4 == 0 ? 40000 : 60000);
+        const int64_t to = N <= 96 || (N > 128 && N <= 192) ? INT64_MAX : (N <= 128 ? 80000 : (N <= 224 ? 300000 : 0));
+        if (M >= from && M < to) return SGNN_ERR_UNSUPPORTED;
+        // three more stores a row for the end of it: 262144 x 255 x 17 33.7 / 41.1, 400000 52 / 60, x 256 x 17 9 % less here
+        if (N > 224 && N % 4 && K <= 32 && M >= 100000 && M < 500000) return SGNN_ERR_UNSUPPORTED;
+    }
     if (M < 4096 || N < 1 || N > 256 || K < 1 || K > 256 || lda % 8 || ldc % 8 || lda < K || ldc < N || lda >= LD_MAX || ldc >= LD_MAX || ldb >= LD_MAX ||
         (reinterpret_cast<uintptr_t>(A) & 15) || (reinterpret_cast<uintptr_t>(C) & 15))
         return SGNN_ERR_UNSUPPORTED;

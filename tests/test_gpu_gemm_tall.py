@@ -53,15 +53,23 @@ def test_result_in_the_place_of_the_operand():
 
 
 # rows that end four columns into a chunk of eight (one store there instead of three), in every number of tiles
-@pytest.mark.parametrize("M,N,K", [(33000, 68, 65), (33001, 132, 130), (12345, 100, 256), (40003, 164, 70), (250007, 36, 101), (100003, 20, 129),
+@pytest.mark.parametrize("M,N,K", [(33000, 68, 65), (33001, 132, 130), (12345, 100, 256), (40003, 164, 70), (250007, 36, 101), (350003, 20, 129),
                                    (33000, 252, 193)])
 def test_rows_that_end_in_half_a_chunk(M, N, K):
     test_against_float64(M, N, K)
 
 
+# just inside the ranges that this kernel has
+@pytest.mark.parametrize("M,N,K", [(39999, 70, 101), (500003, 90, 65), (75001, 99, 170), (24999, 69, 57), (80001, 99, 30), (59999, 134, 63), (300007, 196, 17), (250001, 62, 65), (350000, 32, 256), (100000, 3, 159),
+                                   (99999, 255, 17)])
+def test_edges_of_its_ranges(M, N, K):
+    test_against_float64(M, N, K)
+
+
 # what the kernel of gemm.hip is the better one for: up to 64 columns with few rows or steps, whole tiles of few slices, few steps
 @pytest.mark.parametrize("M,N,K", [(99999, 64, 256), (200001, 47, 128), (131072, 20, 172), (65537, 128, 192), (40001, 96, 250), (100001, 70, 57),
-                                   (60001, 150, 64), (100003, 172, 57)])
+                                   (60001, 150, 64), (100003, 172, 57),
+                                   (40001, 70, 65), (499999, 90, 128), (74999, 99, 129), (25000, 96, 64), (40000, 128, 1), (40003, 160, 40), (299999, 224, 64), (349999, 5, 130), (100000, 4, 160), (100000, 255, 32)])
 def test_left_to_the_other_kernel(M, N, K):
     gen = torch.Generator(device=DEV).manual_seed(M + N + K)
     A = torch.randn(M, K + -K % 8, generator=gen, device=DEV).bfloat16()[:, :K]
