@@ -115,17 +115,23 @@ __global__ __launch_bounds__(64 * BWD_WAVES, 2) void gemm_bwd_kernel(bwd_args a)
     const float *w_row = a.W + (int64_t)min(32 * mt + li, a.M - 1) * a.ldw;
     auto w_pieces = [&](int st0, bf16x8 (&v)[4]) {
         float x[4][8];
-        const bool whole = st0 + 4 < STEPS || a.N == FB;          // (a frame is at most 63 columns wider than N)
-        if (whole || a.N >= 4) {
+        if (st0 + 4 < STEPS || a.N == FB) {          // (a frame is at most 63 columns wider than N)
+#pragma unroll
+            for (int q = 0; q < 4; ++q) {
+                const float *p = w_row + 16 * (st0 + q) + 8 * kh;
+                const f32x4_any lo = *reinterpret_cast<const f32x4_any *>(p), hi = *reinterpret_cast<const f32x4_any *>(p + 4);
+#pragma unroll
+                for (int i = 0; i < 4; ++i) { x[q][i] = lo[i]; x[q][4 + i] = hi[i]; }
+            }
+        } else if (a.N >= 4) {
+            // past the row's end the four that end with it, put right (32 loads of one value each, eight times the requests in front of everything
+            // else: 10000 x 192 x 224 48 us, 9000 x 256 x 96 38)
 #pragma unroll
             for (int q = 0; q < 4; ++q)
 #pragma unroll
                 for (int h = 0; h < 2; ++h) {
-                    // past the row's end the four that end with it, put right (32 loads of one value each, eight times the requests in front of everything
-                    // else: 10000 x 192 x 224 48 us, 9000 x 256 x 96 38)
-                    const int c = 16 * (st0 + q) + 8 * kh + 4 * h, cc = whole ? c : min(c, a.N - 4);
-                    f32x4 v = *reinterpret_cast<const f32x4_any *>(w_row + cc);
-                    if (!whole) v = shifted(v, min(c - cc, 4));
+                    const int c = 16 * (st0 + q) + 8 * kh + 4 * h, cc = min(c, a.N - 4);
+                    const f32x4 v = shifted(*reinterpret_cast<const f32x4_any *>(w_row + cc), min(c - cc, 4));
 #pragma unroll
                     for (int i = 0; i < 4; ++i) x[q][4 * h + i] = v[i];
                 }
